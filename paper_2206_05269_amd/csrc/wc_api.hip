@@ -695,6 +695,20 @@ bool tables_ok(const wc_result* const* t, uint32_t k) {
   return true;
 }
 
+// Device arrays of the tables; input i is column i of a joint table.
+std::vector<MergeInput> merge_inputs(const wc_result* const* t, uint32_t k) {
+  std::vector<MergeInput> v(k);
+  for (uint32_t i = 0; i < k; ++i) {
+    v[i].word_offsets = t[i]->d_word_offsets;
+    v[i].words = t[i]->d_words;
+    v[i].counts = t[i]->d_counts;
+    v[i].n = t[i]->n_entries;
+    v[i].count_bytes = t[i]->count_bytes;
+    v[i].column = i;
+  }
+  return v;
+}
+
 void layout_merge(const wc_result* const* t, uint32_t k, const wc_opts* o, void* ws,
                   MergeLayout* L) {
   uint64_t n = 0, wb = 0;
@@ -751,16 +765,8 @@ wc_status wc_merge(const wc_result* const* tables, uint32_t k, const wc_opts* op
   HIPCHK(launch_fill_zero(L.table, L.S * sizeof(Slot), s));
   const uint64_t occ_limit = L.S - L.S / 8;
   if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
-  for (uint32_t i = 0; i < k; ++i) {
-    MergeInput in;
-    in.word_offsets = tables[i]->d_word_offsets;
-    in.words = tables[i]->d_words;
-    in.counts = tables[i]->d_counts;
-    in.n = tables[i]->n_entries;
-    in.count_bytes = tables[i]->count_bytes;
-    in.column = 0;
-    HIPCHK(launch_merge_insert(in, L.table, L.S - 1, occ_limit, km, L.hdr, nullptr, 1, s));
-  }
+  const std::vector<MergeInput> ins = merge_inputs(tables, k);
+  HIPCHK(launch_merge_insert(ins.data(), k, L.table, L.S - 1, occ_limit, km, L.hdr, nullptr, 1, s));
   if (tm.on) HIPCHK(hipEventRecord(tm.b, s));
   ExportParams E;
   memset(&E, 0, sizeof(E));
@@ -819,12 +825,11 @@ struct TopkLayout {
   uint64_t* entry_total;   // [S] int64 counts of the joint table
   uint8_t* words;
   uint64_t* slot_of_entry;
-  uint64_t* joint_dense;   // [S * C]
   uint64_t* totals;        // [64]
-  uint32_t* lists;
-  uint32_t* list_len;
-  uint64_t* out_entry;
-  uint64_t* n_rows;        // [64]
+  uint64_t n;              // vocabulary bound: entries of all inputs
+  uint32_t* lists[2];
+  uint32_t* list_len[2];
+  TopkSizes* sizes;
   uint64_t* row_woff;
   uint8_t* row_words;
   uint64_t* row_nc;
@@ -853,26 +858,19 @@ void layout_topk(const wc_result* const* t, uint32_t C, uint32_t k, void* ws, To
   L->entry_total = B.take<uint64_t>(L->S * 8);
   L->words = B.take<uint8_t>(L->word_cap);
   L->slot_of_entry = B.take<uint64_t>(L->S * 8);
-  L->joint_dense = B.take<uint64_t>(L->S * C * 8);
   L->totals = B.take<uint64_t>(64 * 8);
-  L->lists = B.take<uint32_t>((uint64_t)C * 2 * kTopkThreads * k * 4);
-  L->list_len = B.take<uint32_t>((uint64_t)C * 2 * kTopkThreads * 4);
-  L->out_entry = B.take<uint64_t>((uint64_t)C * k * 8);
-  L->n_rows = B.take<uint64_t>(64 * 8);
+  L->n = n;
+  for (int i = 0; i < 2; ++i) {
+    L->lists[i] = B.take<uint32_t>(C * topk_list_ids(n, k) * 4);
+    L->list_len[i] = B.take<uint32_t>(C * topk_list_runs(n) * 4);
+  }
+  L->sizes = B.take<TopkSizes>(sizeof(TopkSizes));
   L->row_woff = B.take<uint64_t>(((uint64_t)C * k + 1) * 8);
   L->row_words = B.take<uint8_t>(L->row_word_cap * C);
   L->row_nc = B.take<uint64_t>((uint64_t)C * k * 8);
   L->row_nr = B.take<uint64_t>((uint64_t)C * k * 8);
   L->row_score = B.take<double>((uint64_t)C * k * 8);
   L->total = B.off;
-}
-
-__global__ void gather_joint_kernel(const uint64_t* joint_slots, const uint64_t* slot_of_entry,
-                                    const Header* hdr, uint32_t C, uint64_t* dense) {
-  uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-  if (e >= hdr->n_entries) return;
-  uint64_t i = slot_of_entry[e];
-  for (uint32_t c = 0; c < C; ++c) dense[e * C + c] = joint_slots[i * C + c];
 }
 
 }  // namespace
@@ -904,16 +902,9 @@ wc_status wc_topk_ratio(const wc_result* const* corpora, uint32_t n_corpora, uin
   HIPCHK(launch_fill_zero(L.joint_slots, L.S * C * 8, s));
   HIPCHK(launch_fill_zero(L.totals, 64 * 8, s));
   const uint64_t occ_limit = L.S - L.S / 8;
-  for (uint32_t c = 0; c < C; ++c) {
-    MergeInput in;
-    in.word_offsets = corpora[c]->d_word_offsets;
-    in.words = corpora[c]->d_words;
-    in.counts = corpora[c]->d_counts;
-    in.n = corpora[c]->n_entries;
-    in.count_bytes = corpora[c]->count_bytes;
-    in.column = c;
-    HIPCHK(launch_merge_insert(in, L.table, L.S - 1, occ_limit, ~0ull, L.hdr, L.joint_slots, C, s));
-  }
+  const std::vector<MergeInput> ins = merge_inputs(corpora, C);
+  HIPCHK(launch_merge_insert(ins.data(), C, L.table, L.S - 1, occ_limit, ~0ull, L.hdr,
+                             L.joint_slots, C, s));
   ExportParams E;
   memset(&E, 0, sizeof(E));
   E.table = L.table;
@@ -928,41 +919,43 @@ wc_status wc_topk_ratio(const wc_result* const* corpora, uint32_t n_corpora, uin
   E.count_bytes = 8;
   E.slot_of_entry = L.slot_of_entry;
   HIPCHK(launch_export(E, s));
-  uint32_t grid = (uint32_t)((L.S + 255) / 256);
-  hipLaunchKernelGGL(gather_joint_kernel, dim3(grid), dim3(256), 0, s, L.joint_slots,
-                     L.slot_of_entry, L.hdr, C, L.joint_dense);
-  HIPCHK(hipGetLastError());
-  Header h;
-  HIPCHK(hipMemcpyAsync(&h, L.hdr, sizeof(Header), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
-  if (h.flags) return finish_flags(h);
   TopkParams P;
+  P.hdr = L.hdr;
   P.word_offsets = L.woff;
   P.words = L.words;
-  P.joint = L.joint_dense;
-  P.V = h.n_entries;
+  P.joint = L.joint_slots;
+  P.slot_of_entry = L.slot_of_entry;
+  P.entry_total = L.entry_total;
   P.C = C;
   P.k = k;
   P.min_count = min_count;
   P.totals = L.totals;
-  P.lists = L.lists;
-  P.list_len = L.list_len;
-  P.out_entry = L.out_entry;
-  P.n_rows = L.n_rows;
+  for (int i = 0; i < 2; ++i) {
+    P.lists[i] = L.lists[i];
+    P.list_len[i] = L.list_len[i];
+  }
+  P.sizes = L.sizes;
   P.out_word_offsets = L.row_woff;
   P.out_words = L.row_words;
   P.out_nc = L.row_nc;
   P.out_nr = L.row_nr;
   P.out_score = L.row_score;
-  P.entry_total = L.entry_total;
-  HIPCHK(launch_topk(P, s));
-  memset(out, 0, sizeof(*out));
-  HIPCHK(hipMemcpyAsync(out->n_rows, L.n_rows, 8 * C, hipMemcpyDeviceToHost, s));
-  HIPCHK(hipMemcpyAsync(&out->word_bytes, L.row_woff + (uint64_t)C * k, 8, hipMemcpyDeviceToHost, s));
+  HIPCHK(launch_topk(P, L.n, s));
+  TopkSizes z;
+  HIPCHK(hipMemcpyAsync(&z, L.sizes, sizeof(z), hipMemcpyDeviceToHost, s));
   HIPCHK(hipStreamSynchronize(s));
+  if (z.flags) {
+    Header h;
+    memset(&h, 0, sizeof(h));
+    h.flags = (uint32_t)z.flags;
+    return finish_flags(h);
+  }
+  memset(out, 0, sizeof(*out));
+  memcpy(out->n_rows, z.n_rows, 8 * C);
+  out->word_bytes = z.word_bytes;
   out->n_corpora = C;
   out->k = k;
-  out->vocab_size = h.n_entries;
+  out->vocab_size = z.vocab;
   out->d_word_offsets = L.row_woff;
   out->d_words = L.row_words;
   out->d_n_c = L.row_nc;

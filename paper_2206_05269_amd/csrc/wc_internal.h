@@ -210,7 +210,13 @@ struct MergeInput {
   uint32_t count_bytes;
   uint32_t column;           // joint tables: column of this input
 };
-hipError_t launch_merge_insert(const MergeInput& in, Slot* table, uint64_t mask,
+constexpr uint32_t kMergeInputs = 32;  // tables one launch adds (they are kernel arguments)
+struct MergeBatch {
+  MergeInput in[kMergeInputs];
+  uint32_t first_block[kMergeInputs];
+  uint32_t n;
+};
+hipError_t launch_merge_insert(const MergeInput* in, uint32_t k, Slot* table, uint64_t mask,
                                uint64_t occ_limit, uint64_t key_mask, Header* hdr,
                                uint64_t* joint_counts, uint32_t n_columns, hipStream_t s);
 
@@ -227,29 +233,36 @@ hipError_t launch_dense_rowsum(const uint32_t* matrix, uint64_t rows, uint64_t n
                                hipStream_t s);
 
 // ---- top-k ---------------------------------------------------------------------------------
+struct TopkSizes {               // what the host reads back
+  uint64_t n_rows[64];
+  uint64_t word_bytes, vocab, flags;
+};
 struct TopkParams {
+  const Header* hdr;             // of the joint table: vocabulary size, flags
   const uint64_t* word_offsets;  // joint vocabulary, V entries
   const uint8_t* words;
-  const uint64_t* joint;         // [V * C] counts, entry-major
-  uint64_t V;
+  const uint64_t* joint;         // [slots * C] counts per slot and corpus
+  const uint64_t* slot_of_entry; // [V]
+  const uint64_t* entry_total;   // [V] sum over corpora
   uint32_t C;
   uint32_t k;
   uint64_t min_count;
-  uint64_t* totals;              // [C] token totals per corpus (computed by a kernel)
-  uint32_t* lists;               // scratch: [C][2][T][k] entry indices
-  uint32_t* list_len;            // scratch: [C][2][T]
-  uint64_t* out_entry;           // [C * k] selected entries
-  uint64_t* n_rows;              // [C]
+  uint64_t* totals;              // [C] token totals per corpus (zero before launch_topk)
+  uint32_t* lists[2];            // scratch: [C * topk_list_ids] kept ids of a level
+  uint32_t* list_len[2];         // scratch: [C * topk_list_runs]
+  TopkSizes* sizes;
   // outputs
   uint64_t* out_word_offsets;    // [C*k + 1]
   uint8_t* out_words;
   uint64_t* out_nc;
   uint64_t* out_nr;
   double* out_score;
-  const uint64_t* entry_total;   // [V] sum over corpora
 };
-constexpr uint32_t kTopkThreads = 256;
-hipError_t launch_topk(const TopkParams& P, hipStream_t s);
+constexpr uint32_t kRankSpan = 2048;         // candidates one workgroup sorts
+constexpr uint32_t kNoRank = 0xffffffffu;
+uint64_t topk_list_ids(uint64_t n, uint32_t k);
+uint64_t topk_list_runs(uint64_t n);
+hipError_t launch_topk(const TopkParams& P, uint64_t n, hipStream_t s);
 
 // ---- hashing (debug entry point) ------------------------------------------------------------
 hipError_t launch_hash_words(const uint8_t* bytes, const uint64_t* offsets, uint64_t n,

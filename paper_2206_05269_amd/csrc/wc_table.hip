@@ -265,10 +265,51 @@ hipError_t launch_export(const ExportParams& E, hipStream_t s) {
 // ------------------------------------------------------------------------------------------
 // merge: insert the entries of one table
 // ------------------------------------------------------------------------------------------
-__global__ void merge_insert_kernel(MergeInput in, Slot* table, uint64_t mask,
-                                    uint64_t occ_limit, uint64_t key_mask, Header* hdr,
-                                    uint64_t* joint, uint32_t C) {
-  uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+// The folded bytes of a word of 1..16 bytes at w, packed, read as the aligned dwords that hold them
+// (never a dword without a byte of the word). `end`: the end of the table's word bytes; a last
+// dword that would reach past it is read byte by byte.
+WC_DEV void load_packed(const uint8_t* w, uint32_t len, const uint8_t* end, uint64_t* plo,
+                        uint64_t* phi) {
+  const uint32_t sh = (uint32_t)((uintptr_t)w & 3u);
+  const uint32_t* p = (const uint32_t*)(w - sh);
+  uint32_t d[5];
+#pragma unroll
+  for (uint32_t j = 0; j < 5; ++j) {
+    d[j] = 0;
+    if (4 * j < sh + len) {
+      if ((const uint8_t*)(p + j + 1) <= end) {
+        d[j] = p[j];
+      } else {
+        for (uint32_t q = 0; q < 4; ++q) {
+          const uint8_t* x = (const uint8_t*)(p + j) + q;
+          if (x >= w && x < w + len) d[j] |= (uint32_t)*x << (8 * q);
+        }
+      }
+    }
+  }
+  uint64_t v[2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    uint32_t f, lo = __builtin_amdgcn_alignbyte(d[2 * x + 1], d[2 * x], sh);
+    uint32_t hi = __builtin_amdgcn_alignbyte(d[2 * x + 2], d[2 * x + 1], sh);
+    v[x] = (uint64_t)fold_classify4(lo, &f) | ((uint64_t)fold_classify4(hi, &f) << 32);
+  }
+  const uint32_t ka = len < 8 ? 64 - 8 * len : 0u;
+  *plo = (v[0] << ka) >> ka;
+  *phi = len <= 8 ? 0ull : len < 16 ? (v[1] << (128 - 8 * len)) >> (128 - 8 * len) : v[1];
+}
+
+// Adds the entries of up to kMergeInputs tables to one table; block b belongs to the input
+// whose first_block is the last one at or before it. (One launch per table cost a merge of 96
+// small tables 96 launches of about 10 us each, most of them with a handful of workgroups.)
+__global__ __launch_bounds__(256) void merge_insert_kernel(MergeBatch M, Slot* table, uint64_t mask,
+                                                           uint64_t occ_limit, uint64_t key_mask,
+                                                           Header* hdr, uint64_t* joint,
+                                                           uint32_t C) {
+  uint32_t x = 0;
+  while (x + 1 < M.n && M.first_block[x + 1] <= blockIdx.x) ++x;
+  const MergeInput& in = M.in[x];
+  uint64_t e = (blockIdx.x - M.first_block[x]) * 256ull + threadIdx.x;
   if (e >= in.n) return;
   uint64_t a = in.word_offsets[e], b = in.word_offsets[e + 1];
   uint64_t len = b - a;
@@ -277,11 +318,11 @@ __global__ void merge_insert_kernel(MergeInput in, Slot* table, uint64_t mask,
   if (len == 0 || c == 0) return;
   const uint8_t* w = in.words + a;
   uint64_t h = kFnvOffset, lo = 0, hi = 0;
-  for (uint64_t q = 0; q < len; ++q) {
-    uint32_t f = fold_byte(w[q]);
-    h = fnv_step(h, f);
-    if (q < 8) lo |= (uint64_t)f << (8 * q);
-    else if (q < 16) hi |= (uint64_t)f << (8 * (q - 8));
+  if (len <= 16) {
+    load_packed(w, (uint32_t)len, in.words + in.word_offsets[in.n], &lo, &hi);
+    h = fnv_packed(lo, hi, (uint32_t)len);
+  } else {
+    for (uint64_t q = 0; q < len; ++q) h = fnv_step(h, fold_byte(w[q]));
   }
   uint64_t key = finish_key(h, key_mask);
   WordId id = len <= 16 && packable(lo, hi) ? short_id(lo, hi, 0) : long_id(w, len, 0);
@@ -289,13 +330,24 @@ __global__ void merge_insert_kernel(MergeInput in, Slot* table, uint64_t mask,
   if (joint && slot != ~0ull) add64(&joint[slot * C + in.column], c);
 }
 
-hipError_t launch_merge_insert(const MergeInput& in, Slot* table, uint64_t mask,
+hipError_t launch_merge_insert(const MergeInput* in, uint32_t k, Slot* table, uint64_t mask,
                                uint64_t occ_limit, uint64_t key_mask, Header* hdr,
                                uint64_t* joint_counts, uint32_t n_columns, hipStream_t s) {
-  if (in.n == 0) return hipSuccess;
-  uint32_t grid = (uint32_t)((in.n + 255) / 256);
-  hipLaunchKernelGGL(merge_insert_kernel, dim3(grid), dim3(256), 0, s, in, table, mask,
-                     occ_limit, key_mask, hdr, joint_counts, n_columns);
+  for (uint32_t i = 0; i < k;) {
+    MergeBatch M;
+    uint64_t blocks = 0;
+    for (M.n = 0; i < k && M.n < kMergeInputs; ++i) {
+      const uint64_t nb = (in[i].n + 255) / 256;
+      if (nb == 0) continue;
+      if (blocks + nb > 0x7fffffffull && M.n) break;
+      M.in[M.n] = in[i];
+      M.first_block[M.n++] = (uint32_t)blocks;
+      blocks += nb;
+    }
+    if (M.n == 0) continue;
+    hipLaunchKernelGGL(merge_insert_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, M, table,
+                       mask, occ_limit, key_mask, hdr, joint_counts, n_columns);
+  }
   return hipGetLastError();
 }
 
@@ -331,153 +383,287 @@ hipError_t launch_hash_words(const uint8_t* bytes, const uint64_t* offsets, uint
 // ------------------------------------------------------------------------------------------
 // top-k distinctive words
 // ------------------------------------------------------------------------------------------
-__global__ void column_totals_kernel(const uint64_t* joint, uint64_t V, uint32_t C,
-                                     uint64_t* totals) {
-  __shared__ uint64_t s_t[64];
-  if (threadIdx.x < 64) s_t[threadIdx.x] = 0;
-  __syncthreads();
-  uint64_t e = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
-  if (e < V)
-    for (uint32_t c = 0; c < C; ++c) atomicAdd((unsigned long long*)&s_t[c], (unsigned long long)joint[e * C + c]);
-  __syncthreads();
-  if (threadIdx.x < C && s_t[threadIdx.x]) add64(&totals[threadIdx.x], s_t[threadIdx.x]);
-}
-
-struct Ranker {
-  const uint64_t* word_offsets;
-  const uint8_t* words;
-  const uint64_t* joint;
-  const uint64_t* total;  // per entry: sum over corpora
-  uint32_t C, c;
-
-  WC_DEV uint64_t nc(uint32_t e) const { return joint[(uint64_t)e * C + c]; }
-  WC_DEV uint64_t nr(uint32_t e) const { return total[e] - nc(e); }
-  // true when entry a ranks before entry b
-  WC_DEV bool better(uint32_t a, uint32_t b) const {
-    uint64_t na = nc(a), nb = nc(b), ra = total[a] - na, rb = total[b] - nb;
-    uint64_t x = na + 1, y = rb + 1, u = nb + 1, v = ra + 1;
-    uint64_t lh = __umul64hi(x, y), ll = x * y, rh = __umul64hi(u, v), rl = u * v;
-    if (lh != rh) return lh > rh;
-    if (ll != rl) return ll > rl;
-    if (na != nb) return na > nb;
-    uint64_t pa = word_offsets[a], la = word_offsets[a + 1] - pa;
-    uint64_t pb = word_offsets[b], lb = word_offsets[b + 1] - pb;
-    uint64_t m = la < lb ? la : lb;
-    for (uint64_t q = 0; q < m; ++q) {
-      uint8_t ca = words[pa + q], cb = words[pb + q];
-      if (ca != cb) return ca < cb;
-    }
-    return la < lb;
-  }
+// The rank of an entry: by (n_c + 1) / (n_R + 1), then n_c, then word bytes. Sorting happens in
+// LDS on 16-bit indices of records held there; most comparisons read only the ratio in double
+// precision, which decides when two ratios differ by more than its rounding (each has at most five
+// roundings of 2^-53); closer ratios are compared exactly.
+struct RankLds {
+  double* q;      // (n_c + 1) / (n_R + 1); -1: no entry here (after every entry)
+  uint64_t* nc;
+  uint64_t* nr;
+  uint64_t* head; // the word's first 8 bytes, the first byte highest
+  uint32_t* e;    // entry
 };
+constexpr size_t kRankBytes = 8 + 8 + 8 + 8 + 4 + 2;  // a record and its 16-bit index
 
-// One workgroup per corpus: per-thread sorted lists of the best k, then a merge tree.
-__global__ __launch_bounds__(kTopkThreads) void topk_kernel(TopkParams P, const uint64_t* total) {
-  const uint32_t c = blockIdx.x;
-  const uint32_t t = threadIdx.x;
-  const uint32_t T = kTopkThreads;
-  const uint32_t k = P.k;
-  Ranker R{P.word_offsets, P.words, P.joint, total, P.C, c};
-  uint32_t* buf[2] = {P.lists + ((uint64_t)c * 2 + 0) * T * k, P.lists + ((uint64_t)c * 2 + 1) * T * k};
-  uint32_t* lens[2] = {P.list_len + ((uint64_t)c * 2 + 0) * T, P.list_len + ((uint64_t)c * 2 + 1) * T};
-  const uint64_t minc = P.min_count > 0 ? P.min_count : 1;
-  // phase 1: thread-local top-k
-  uint32_t* my = buf[0] + (uint64_t)t * k;
-  uint32_t n = 0;
-  for (uint64_t e = t; e < P.V; e += T) {
-    if (R.nc((uint32_t)e) < minc) continue;
-    uint32_t ee = (uint32_t)e;
-    if (n == k && !R.better(ee, my[k - 1])) continue;
-    uint32_t pos = n < k ? n : k - 1;
-    while (pos > 0 && R.better(ee, my[pos - 1])) {
-      my[pos] = my[pos - 1];
-      --pos;
-    }
-    my[pos] = ee;
-    if (n < k) ++n;
-  }
-  lens[0][t] = n;
-  __syncthreads();
-  // phase 2: merge tree
-  int src = 0;
-  for (uint32_t step = 1; step < T; step <<= 1) {
-    int dst = src ^ 1;
-    if ((t % (2 * step)) == 0) {
-      const uint32_t* a = buf[src] + (uint64_t)t * k;
-      const uint32_t* b = buf[src] + (uint64_t)(t + step) * k;
-      uint32_t na = lens[src][t], nb = lens[src][t + step];
-      uint32_t* o = buf[dst] + (uint64_t)t * k;
-      uint32_t i = 0, j = 0, m = 0;
-      while (m < k && (i < na || j < nb)) {
-        bool take_a = j >= nb || (i < na && R.better(a[i], b[j]));
-        o[m++] = take_a ? a[i++] : b[j++];
-      }
-      lens[dst][t] = m;
-    }
-    __syncthreads();
-    src = dst;
-  }
-  // phase 3: rows
-  const uint32_t rows = lens[src][0];
-  const uint32_t* best = buf[src];
-  const double Nc = (double)P.totals[c];
-  uint64_t all = 0;
-  for (uint32_t q = 0; q < P.C; ++q) all += P.totals[q];
-  const double Nr = (double)(all - P.totals[c]);
-  const double Vd = (double)P.V;
-  for (uint32_t r = t; r < rows; r += T) {
-    uint32_t e = best[r];
-    uint64_t nc = R.nc(e), nr = R.nr(e);
-    uint64_t row = (uint64_t)c * k + r;
-    P.out_entry[row] = e;
-    P.out_nc[row] = nc;
-    P.out_nr[row] = nr;
-    P.out_score[row] = (((double)nc + 1.0) / (Nc + Vd)) / (((double)nr + 1.0) / (Nr + Vd));
-  }
-  if (t == 0) P.n_rows[c] = rows;
+// First 8 bytes of entry e's word, the first byte highest, zero padded (words have no zeros).
+WC_DEV uint64_t word_head(const TopkParams& P, uint64_t e) {
+  const uint64_t a = P.word_offsets[e], n = P.word_offsets[e + 1] - a;
+  uint64_t h = 0;
+  for (uint32_t q = 0; q < 8; ++q) h = (h << 8) | (q < n ? (uint64_t)P.words[a + q] : 0ull);
+  return h;
 }
 
-// Row word offsets (one workgroup) and row word bytes.
-__global__ __launch_bounds__(1024) void topk_rows_kernel(TopkParams P) {
+// true when word a comes before word b (bytes, unsigned, a proper prefix first)
+WC_DEV bool word_before(const TopkParams& P, uint64_t a, uint64_t b) {
+  const uint64_t pa = P.word_offsets[a], la = P.word_offsets[a + 1] - pa;
+  const uint64_t pb = P.word_offsets[b], lb = P.word_offsets[b + 1] - pb;
+  const uint64_t m = la < lb ? la : lb;
+  for (uint64_t q = 0; q < m; ++q) {
+    const uint8_t x = P.words[pa + q], y = P.words[pb + q];
+    if (x != y) return x < y;
+  }
+  return la < lb;
+}
+
+// The exact order of (nc, nr) pairs; 0 when both are equal.
+WC_DEV int pair_order(uint64_t na, uint64_t ra, uint64_t nb, uint64_t rb) {
+  const uint64_t x = na + 1, y = rb + 1, u = nb + 1, v = ra + 1;
+  const uint64_t lh = __umul64hi(x, y), ll = x * y, rh = __umul64hi(u, v), rl = u * v;
+  if (lh != rh) return lh > rh ? 1 : -1;
+  if (ll != rl) return ll > rl ? 1 : -1;
+  if (na != nb) return na > nb ? 1 : -1;
+  return 0;
+}
+
+WC_DEV bool rank_before(const TopkParams& P, const RankLds& R, uint32_t a, uint32_t b) {
+  const double qa = R.q[a], qb = R.q[b], d = qa - qb, tol = fmax(qa, qb) * 0x1p-48;
+  if (d > tol) return true;
+  if (d < -tol) return false;
+  if (R.e[a] == kNoRank || R.e[b] == kNoRank) return false;
+  const int o = pair_order(R.nc[a], R.nr[a], R.nc[b], R.nr[b]);
+  if (o) return o > 0;
+  const uint64_t ha = R.head[a], hb = R.head[b];
+  if (ha != hb) return ha < hb;
+  return word_before(P, R.e[a], R.e[b]);
+}
+
+// Sorts kRankSpan candidates of one corpus in LDS and keeps the best min(k, kRankSpan) of them.
+// Level 0 takes the vocabulary (chunk blockIdx.x of it) and adds up the corpus's tokens; a later
+// level takes the kept runs of the level before (run r: in_len[r] ids at in[r * run]).
+//
+// One workgroup per corpus inserting every entry into per-thread lists of k in device memory
+// took 4.35 ms for four corpora of 43,000 words (top 50), four workgroups on 256 CUs and a
+// dependent device read per comparison; here each chunk is a workgroup, the records compared
+// are in LDS, and a bitonic stage with partners less than 128 apart stays inside a wave (no
+// barrier). The whole wc_topk_ratio call of that size, joint table included: 4.63 -> 0.41 ms.
+template <bool kLevel0>
+__global__ __launch_bounds__(1024) void topk_sort_kernel(TopkParams P, const uint32_t* in,
+                                                         const uint32_t* in_len, uint32_t in_runs,
+                                                         uint32_t run, uint32_t* out,
+                                                         uint32_t* out_len) {
+  extern __shared__ __align__(16) uint8_t s_dyn[];
+  __shared__ uint64_t s_sum[16];
+  __shared__ uint32_t s_n;
+  RankLds R;
+  R.q = (double*)s_dyn;
+  R.nc = (uint64_t*)(R.q + kRankSpan);
+  R.nr = R.nc + kRankSpan;
+  R.head = R.nr + kRankSpan;
+  R.e = (uint32_t*)(R.head + kRankSpan);
+  uint16_t* s_i = (uint16_t*)(R.e + kRankSpan);
+  const uint32_t t = threadIdx.x, c = blockIdx.y;
+  if (P.hdr->flags) return;
+  const uint64_t V = P.hdr->n_entries;
+  const uint64_t minc = P.min_count > 0 ? P.min_count : 1;
+  const uint64_t first = (uint64_t)blockIdx.x * kRankSpan;
+  if (t == 0) s_n = 0;
+  __syncthreads();
+  uint64_t sum = 0;
+  for (uint32_t i = t; i < kRankSpan; i += 1024) {
+    uint32_t e = kNoRank;
+    if (kLevel0) {
+      if (first + i < V) e = (uint32_t)(first + i);
+    } else {
+      const uint64_t at = first + i;
+      const uint32_t r = (uint32_t)(at / run), j = (uint32_t)(at - (uint64_t)r * run);
+      if (r < in_runs && j < in_len[(uint64_t)c * in_runs + r])
+        e = in[(uint64_t)c * in_runs * run + at];
+    }
+    uint64_t nc = 0, nr = 0;
+    if (e != kNoRank) {
+      nc = P.joint[P.slot_of_entry[e] * P.C + c];
+      nr = P.entry_total[e] - nc;
+      sum += nc;
+      if (nc < minc) e = kNoRank;
+    }
+    R.e[i] = e;
+    R.nc[i] = nc;
+    R.nr[i] = nr;
+    R.q[i] = e == kNoRank ? -1.0 : ((double)nc + 1.0) / ((double)nr + 1.0);
+    R.head[i] = e == kNoRank ? 0 : word_head(P, e);
+    s_i[i] = (uint16_t)i;
+    const uint64_t m = __ballot(e != kNoRank);
+    if ((t & 63) == 0 && m) atomicAdd(&s_n, (uint32_t)__popcll(m));
+  }
+  if (kLevel0) {
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if ((t & 63) == 0) s_sum[t >> 6] = sum;
+  }
+  __syncthreads();
+  if (kLevel0 && t == 0) {
+    uint64_t s = 0;
+    for (int w = 0; w < 16; ++w) s += s_sum[w];
+    if (s) add64(&P.totals[c], s);
+  }
+  for (uint32_t size = 2; size <= kRankSpan; size <<= 1) {
+    for (uint32_t j = size >> 1; j; j >>= 1) {
+      const uint32_t i = ((t & ~(j - 1)) << 1) | (t & (j - 1)), l = i + j;
+      const uint32_t a = s_i[i], b = s_i[l];
+      if (rank_before(P, R, b, a) == ((i & size) == 0)) {
+        s_i[i] = (uint16_t)b;
+        s_i[l] = (uint16_t)a;
+      }
+      // a wave's 64 pairs at distance j <= 64 lie in its own 128 elements, and so do those of
+      // the next stage unless it starts a size above 128
+      const bool local = j > 1 ? j <= 64 : size < 128;
+      if (local) {
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        __builtin_amdgcn_wave_barrier();
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      } else {
+        __syncthreads();
+      }
+    }
+  }
+  __syncthreads();
+  const uint32_t keep = P.k < kRankSpan ? P.k : kRankSpan, n = min(s_n, keep);
+  uint32_t* o = out + ((uint64_t)c * gridDim.x + blockIdx.x) * keep;
+  for (uint32_t i = t; i < n; i += 1024) o[i] = R.e[s_i[i]];
+  if (t == 0) out_len[(uint64_t)c * gridDim.x + blockIdx.x] = n;
+}
+
+// For k above half of kRankSpan: pairs of sorted runs merged, each id to the place that its own
+// position and the number of better ids of the other run give (a binary search); the best k stay.
+__global__ __launch_bounds__(256) void topk_merge_kernel(TopkParams P, const uint32_t* in,
+                                                         const uint32_t* in_len, uint32_t in_runs,
+                                                         uint32_t run, uint32_t* out,
+                                                         uint32_t* out_len, uint32_t out_run) {
+  const uint32_t c = blockIdx.z, pair = blockIdx.y, out_runs = gridDim.y;
+  if (P.hdr->flags) return;
+  const uint32_t at = blockIdx.x * 256 + threadIdx.x;  // position among both runs
+  const uint32_t side = at / run, i = at - side * run;
+  if (side > 1) return;
+  const uint64_t base = (uint64_t)c * in_runs;
+  const uint32_t mine = 2 * pair + side, other = 2 * pair + 1 - side;
+  const uint32_t nm = mine < in_runs ? in_len[base + mine] : 0u;
+  const uint32_t no = other < in_runs ? in_len[base + other] : 0u;
+  if (at == 0) out_len[(uint64_t)c * out_runs + pair] = min(nm + no, P.k);
+  if (i >= nm) return;
+  const uint32_t* A = in + (base + mine) * run;
+  const uint32_t* B = in + (base + other) * run;
+  const uint64_t e = A[i];
+  const uint64_t na = P.joint[P.slot_of_entry[e] * P.C + c], ra = P.entry_total[e] - na;
+  uint32_t lo = 0, hi = no;  // ids of the other run before this one
+  while (lo < hi) {
+    const uint32_t m = (lo + hi) >> 1;
+    const uint64_t f = B[m];
+    const uint64_t nb = P.joint[P.slot_of_entry[f] * P.C + c], rb = P.entry_total[f] - nb;
+    const int o = pair_order(na, ra, nb, rb);
+    if (o < 0 || (o == 0 && word_before(P, f, e))) lo = m + 1;
+    else hi = m;
+  }
+  const uint32_t rank = i + lo;
+  if (rank < P.k) out[((uint64_t)c * out_runs + pair) * out_run + rank] = (uint32_t)e;
+}
+
+// Rows of the answer, their word offsets and bytes (one workgroup), and the sizes the host reads.
+__global__ __launch_bounds__(1024) void topk_rows_kernel(TopkParams P, const uint32_t* best,
+                                                         const uint32_t* best_len, uint32_t run) {
   __shared__ uint64_t s_tmp[16];
   __shared__ uint64_t s_carry;
-  if (threadIdx.x == 0) s_carry = 0;
+  if (threadIdx.x == 0) {
+    s_carry = 0;
+    P.sizes->flags = P.hdr->flags;
+    P.sizes->vocab = P.hdr->n_entries;
+  }
+  if (P.hdr->flags) return;
+  const uint64_t V = P.hdr->n_entries;
+  uint64_t all = 0;
+  for (uint32_t q = 0; q < P.C; ++q) all += P.totals[q];
+  if (threadIdx.x < P.C) P.sizes->n_rows[threadIdx.x] = best_len[threadIdx.x];
   __syncthreads();
   const uint64_t total_rows = (uint64_t)P.C * P.k;
   for (uint64_t base = 0; base < total_rows; base += 1024) {
-    uint64_t r = base + threadIdx.x;
-    uint64_t len = 0;
+    const uint64_t r = base + threadIdx.x;
+    uint64_t len = 0, e = 0;
     if (r < total_rows) {
-      uint32_t c = (uint32_t)(r / P.k), j = (uint32_t)(r % P.k);
-      if (j < P.n_rows[c]) {
-        uint64_t e = P.out_entry[r];
+      const uint32_t c = (uint32_t)(r / P.k), j = (uint32_t)(r % P.k);
+      if (j < best_len[c]) {
+        e = best[(uint64_t)c * run + j];
         len = P.word_offsets[e + 1] - P.word_offsets[e];
+        const uint64_t nc = P.joint[P.slot_of_entry[e] * P.C + c], nr = P.entry_total[e] - nc;
+        const double Nc = (double)P.totals[c], Nr = (double)(all - P.totals[c]), Vd = (double)V;
+        P.out_nc[r] = nc;
+        P.out_nr[r] = nr;
+        P.out_score[r] = (((double)nc + 1.0) / (Nc + Vd)) / (((double)nr + 1.0) / (Nr + Vd));
       }
     }
     uint64_t tot;
-    uint64_t ex = block_excl_scan<1024>(len, s_tmp, &tot);
-    uint64_t pos = ex + s_carry;
+    const uint64_t ex = block_excl_scan<1024>(len, s_tmp, &tot);
+    const uint64_t pos = ex + s_carry;
     if (r < total_rows) {
       P.out_word_offsets[r] = pos;
-      if (len) {
-        uint64_t e = P.out_entry[r];
-        const uint8_t* src = P.words + P.word_offsets[e];
-        for (uint64_t q = 0; q < len; ++q) P.out_words[pos + q] = src[q];
-      }
+      const uint8_t* src = P.words + P.word_offsets[e];
+      for (uint64_t q = 0; q < len; ++q) P.out_words[pos + q] = src[q];
     }
     __syncthreads();
     if (threadIdx.x == 0) s_carry += tot;
     __syncthreads();
   }
-  if (threadIdx.x == 0) P.out_word_offsets[total_rows] = s_carry;
+  if (threadIdx.x == 0) {
+    P.out_word_offsets[total_rows] = s_carry;
+    P.sizes->word_bytes = s_carry;
+  }
 }
 
-hipError_t launch_topk(const TopkParams& P, hipStream_t s) {
-  // P.totals must be zeroed by the caller; per-entry totals are in P.totals + C
-  uint32_t grid = (uint32_t)((P.V + 255) / 256);
-  if (grid) hipLaunchKernelGGL(column_totals_kernel, dim3(grid), dim3(256), 0, s, P.joint, P.V, P.C, P.totals);
-  hipLaunchKernelGGL(topk_kernel, dim3(P.C), dim3(kTopkThreads), 0, s, P, P.entry_total);
-  hipLaunchKernelGGL(topk_rows_kernel, dim3(1), dim3(1024), 0, s, P);
+// ids (and run lengths) that one of the two list buffers holds at most for `n` vocabulary words
+uint64_t topk_list_ids(uint64_t n, uint32_t k) {
+  return ((n + kRankSpan - 1) / kRankSpan + 1) * (k < kRankSpan ? k : kRankSpan) + k;
+}
+uint64_t topk_list_runs(uint64_t n) { return (n + kRankSpan - 1) / kRankSpan + 1; }
+
+// The vocabulary's size is on the device; `n` bounds it, so that no host wait comes between the
+// joint table and the ranking (chunks past the vocabulary keep nothing).
+hipError_t launch_topk(const TopkParams& P, uint64_t n, hipStream_t s) {
+  static const hipError_t attr = [] {
+    hipError_t e = hipFuncSetAttribute((const void*)topk_sort_kernel<true>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)(kRankSpan * kRankBytes));
+    if (e == hipSuccess)
+      e = hipFuncSetAttribute((const void*)topk_sort_kernel<false>,
+                              hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)(kRankSpan * kRankBytes));
+    return e;
+  }();
+  if (attr != hipSuccess) return attr;
+  const size_t dyn = kRankSpan * kRankBytes;
+  uint32_t runs = (uint32_t)((n + kRankSpan - 1) / kRankSpan);
+  if (runs == 0) runs = 1;
+  uint32_t run = P.k < kRankSpan ? P.k : kRankSpan;
+  hipLaunchKernelGGL(topk_sort_kernel<true>, dim3(runs, P.C), dim3(1024), dyn, s, P, nullptr,
+                     nullptr, 0u, 1u, P.lists[0], P.list_len[0]);
+  int src = 0;
+  while (runs > 1) {
+    const int dst = src ^ 1;
+    if (P.k <= kRankSpan / 2) {  // a level keeps at most half of what it sorts
+      const uint32_t next = (uint32_t)(((uint64_t)runs * run + kRankSpan - 1) / kRankSpan);
+      hipLaunchKernelGGL(topk_sort_kernel<false>, dim3(next, P.C), dim3(1024), dyn, s, P,
+                         P.lists[src], P.list_len[src], runs, run, P.lists[dst], P.list_len[dst]);
+      runs = next;
+    } else {
+      const uint32_t next = (runs + 1) / 2;
+      const uint32_t longer = 2 * run < P.k ? 2 * run : P.k;
+      hipLaunchKernelGGL(topk_merge_kernel, dim3((2 * run + 255) / 256, next, P.C), dim3(256), 0,
+                         s, P, P.lists[src], P.list_len[src], runs, run, P.lists[dst],
+                         P.list_len[dst], longer);
+      runs = next;
+      run = longer;
+    }
+    src = dst;
+  }
+  hipLaunchKernelGGL(topk_rows_kernel, dim3(1), dim3(1024), 0, s, P, P.lists[src],
+                     P.list_len[src], run);
   return hipGetLastError();
 }
 

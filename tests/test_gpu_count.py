@@ -737,6 +737,26 @@ def test_topk_ties_and_small_tables():
         assert got.words == want.words
 
 
+@pytest.mark.parametrize("k", [1, 50, 1024, 1025, 3000, 4096])
+def test_topk_levels_and_ties(k):
+    """Vocabularies of less and of more than one 2,048-entry sort, counts so small that most
+    ranks are decided by ties (up to the word bytes, past their first eight), min_count rows
+    short of k, and k on both sides of where levels of sorts turn into merges."""
+    rng = np.random.default_rng(41)
+    for n in (3, 2047, 2049, 9000):
+        vocab = [b"w%d" % i if i % 3 else b"commonprefix%d" % i for i in range(n)]
+        docs = [b" ".join(vocab[i] for i in rng.integers(0, n, size=2 * n)) for _ in range(3)]
+        tabs = [gpu_count(d) for d in docs]
+        otabs = [oracle.count(d) for d in docs]
+        for mc in (1, 4):
+            got, want = wc.topk_ratio(tabs, k, mc), oracle.topk_ratio(otabs, k, mc)
+            assert got.vocab_size == want.vocab_size
+            assert got.words == want.words
+            for c in range(3):
+                assert list(got.n_c[c]) == list(map(int, want.n_c[c]))
+                assert list(got.n_rest[c]) == list(map(int, want.n_rest[c]))
+
+
 def test_fnv1a_published_vectors():
     # FNV-1a 64 test vectors from the FNV reference (Fowler, Noll, Vo)
     h = wc.hash_words([b"", b"a", b"foobar"])
