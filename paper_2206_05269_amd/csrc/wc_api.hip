@@ -129,6 +129,13 @@ struct CountLayout {
   Header* sample_hdr = nullptr;
   DictImage* dict = nullptr;
   uint32_t* dict_part = nullptr;
+  // partitioned global count
+  bool part = false;
+  uint32_t part_grid = 0, parts = 0, max_lists = 0;
+  uint64_t stripes_per_wg = 0, cap_recs = 0;
+  uint4* rec_key = nullptr;
+  uint32_t* rec_cnt = nullptr;
+  uint2* dir = nullptr;
   uint64_t total;
 };
 
@@ -139,6 +146,21 @@ bool use_spill(uint64_t len, const wc_opts* o) {
   if (o->debug_flags & (WC_DEBUG_DIRECT | WC_DEBUG_NO_LDS)) return false;
   return len >= kSpillMinBytes;
 }
+
+// Global counts of ASCII text below the two-pass size take the partitioned kernels; a tuning is
+// for the one-pass kernel's launch, and so are the debug flags that name it and forced key
+// collisions (they concern its table's keys).
+constexpr uint32_t kNoPart = 1u << 31;  // internal debug flag: count with the one-pass kernel
+bool use_part(uint64_t len, uint64_t n_docs, const wc_opts* o) {
+  if (o->mode != WC_GLOBAL || !len || !n_docs || use_spill(len, o)) return false;
+  if (o->tokenizer == WC_TOKENIZE_UTF8 || o->debug_hash_bits) return false;
+  if (o->debug_flags & (WC_DEBUG_DIRECT | WC_DEBUG_NO_LDS | kNoPart)) return false;
+  const wc_tuning* t = o->tuning;
+  if (t && (t->stage_bytes || t->lds_entries || t->flush_policy || t->grid_blocks || t->lds_load_pct))
+    return false;
+  return len < kSpillMinBytes;
+}
+constexpr uint64_t kSingleBytes = 48ull << 10;  // texts counted and written by one workgroup
 
 // The two-pass kernels scan kGlobalStage-byte stages; the stage size tunes only the one-pass
 // kernel.
@@ -272,7 +294,36 @@ bool layout_count(uint64_t len, uint64_t n_docs, const wc_opts* o, const Tune& t
   L->word_cap = std::max<uint64_t>(cap, 16);
   Bump B(ws);
   L->hdr = B.take<Header>(sizeof(Header));
-  L->table = B.take<Slot>(S * sizeof(Slot));
+  L->part = use_part(len, n_docs, o) && !outs;
+  uint64_t region = S * sizeof(Slot);
+  if (L->part) {
+    // One workgroup per CU, each with at least a stripe per wave; about 64 KiB of text per
+    // partition, so that its workgroup has a few thousand records. Records: natural text makes
+    // one per 14 to 25 bytes; with twice that, only text with hardly a repeated word runs out
+    // (and is then counted by the one-pass kernel). The arena shares its memory with the one-pass
+    // kernel's table: only one of them is in use.
+    const uint64_t ns = (len + 15 + kStripe - 1) / kStripe;
+    uint64_t grid = std::min<uint64_t>((uint64_t)device_cus(), (ns + 15) / 16);
+    L->stripes_per_wg = (ns + grid - 1) / grid;
+    L->part_grid = (uint32_t)((ns + L->stripes_per_wg - 1) / L->stripes_per_wg);
+    L->parts = 16;
+    while (L->parts < kParts && (uint64_t)L->parts << 16 < len) L->parts *= 2;
+    L->cap_recs = (len <= (16ull << 20) ? len / 8 : std::max<uint64_t>(2ull << 20, len / 12)) + 8192;
+    L->max_lists = (uint32_t)(L->part_grid + L->cap_recs / 1024 + 64);
+    Bump A(nullptr);
+    A.take<uint4>(L->cap_recs * 16);
+    A.take<uint32_t>(L->cap_recs * 4);
+    A.take<uint2>((uint64_t)L->parts * L->max_lists * 8);
+    region = std::max(region, A.off);
+  }
+  uint8_t* const mem = B.take<uint8_t>(region);
+  L->table = (Slot*)mem;
+  if (L->part) {
+    Bump A(mem);
+    L->rec_key = A.take<uint4>(L->cap_recs * 16);
+    L->rec_cnt = A.take<uint32_t>(L->cap_recs * 4);
+    L->dir = A.take<uint2>((uint64_t)L->parts * L->max_lists * 8);
+  }
   L->stage_doc = B.take<uint64_t>((L->n_stages + 2) * 8);
   L->bsum = B.take<uint64_t>(L->n_blocks * 16);
   if (outs) {
@@ -362,6 +413,7 @@ hipError_t ensure_smem_attr() {
     hipError_t e = set_count_smem(512, 160 * 1024 - 40 * 1024);
     if (e == hipSuccess) e = set_count_smem(256, 160 * 1024 - 24 * 1024);
     if (e == hipSuccess) e = set_global_smem(kDictMax, kReduceLds);
+    if (e == hipSuccess) e = set_part_smem();
     if (e == hipSuccess) e = set_doc_smem(doc_dyn(kDocLds));
     return e;
   }();
@@ -511,11 +563,75 @@ wc_status count_table(const uint8_t* d_corpus, uint64_t corpus_len, const uint64
   HIPCHK(tm.init((opts->debug_flags & WC_DEBUG_TIME) && phases == kPhaseAll));
   if (tm.on) HIPCHK(hipEventRecord(tm.c, s));
 
+  const uint64_t occ_limit = L.S - L.S / 8;
+  if (L.part && phases == kPhaseAll) {
+    PartParams P;
+    memset(&P, 0, sizeof(P));
+    P.corpus = d_corpus;
+    P.len = corpus_len;
+    P.offsets = d_offsets;
+    P.n_docs = n_docs;
+    P.hdr = L.hdr;
+    P.base_off = base_offset(d_corpus);
+    P.n_stripes = (uint64_t)(((int64_t)corpus_len - P.base_off + kStripe - 1) / kStripe);
+    P.stripes_per_wg = L.stripes_per_wg;
+    P.parts = L.parts;
+    P.max_lists = L.max_lists;
+    P.cap_recs = L.cap_recs;
+    P.rec_key = L.rec_key;
+    P.rec_cnt = L.rec_cnt;
+    P.dir = L.dir;
+    P.word_offsets = L.woff;
+    P.words = L.words;
+    P.counts = L.counts;
+    P.slots = L.S;
+    P.occ_limit = occ_limit;
+    P.word_cap = L.word_cap;
+    P.count_bias = opts->debug_count_bias;
+    P.count_bytes = opts->count_bytes;
+    const bool single = corpus_len <= kSingleBytes;
+    if (single) P.stripes_per_wg = P.n_stripes;
+    else HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));
+    if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
+    HIPCHK(single ? launch_part_single(P, s) : launch_part_map(P, L.part_grid, s));
+    if (tm.on) HIPCHK(hipEventRecord(tm.b, s));
+    if (!single) HIPCHK(launch_part_reduce(P, s));
+    Header h;
+    HIPCHK(hipMemcpyAsync(&h, L.hdr, sizeof(Header), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    if ((h.flags & kFlagArena) && !(h.flags & kFlagBadOffsets)) {
+      CountLayout again = L;
+      again.part = false;
+      return count_table(d_corpus, corpus_len, d_offsets, n_docs, opts, tu, again, out, s, phases);
+    }
+    if (h.flags & (kFlagBadOffsets | kFlagTableFull)) return finish_flags(h);
+    memset(out, 0, sizeof(*out));
+    out->n_entries = h.n_entries;
+    out->total_tokens = h.total_tokens;
+    out->n_docs = n_docs;
+    out->table_slots = L.S;
+    out->count_bytes = opts->count_bytes;
+    out->mode = opts->mode;
+    out->d_word_offsets = L.woff;
+    out->d_words = L.words;
+    out->d_counts = L.counts;
+    out->word_bytes = h.word_bytes;
+    if (tm.on) {
+      HIPCHK(hipEventRecord(tm.d, s));
+      HIPCHK(hipEventSynchronize(tm.d));
+      float ms = 0;
+      HIPCHK(hipEventElapsedTime(&ms, tm.a, tm.b));
+      out->kernel_ms = ms;
+      HIPCHK(hipEventElapsedTime(&ms, tm.c, tm.d));
+      out->total_ms = ms;
+    }
+    return finish_flags(h);
+  }
+
   if (phases & kPhaseClear) {
     HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));
     HIPCHK(launch_fill_zero(L.table, L.S * sizeof(Slot), s));
   }
-  const uint64_t occ_limit = L.S - L.S / 8;
   if ((phases & kPhaseCount) && corpus_len && n_docs) {
     HIPCHK(launch_validate(d_offsets, n_docs, corpus_len, L.hdr, s));
     const int64_t b0 = base_offset(d_corpus);
@@ -1453,7 +1569,7 @@ void plan_pieces(const uint8_t* h, const uint64_t* off, uint64_t n_docs, uint64_
 // size it from one piece), and so are the exported word bytes.
 wc_opts piece_opts(const wc_opts* o, uint64_t corpus_len) {
   wc_opts q = *o;
-  q.debug_flags &= ~WC_DEBUG_TIME;
+  q.debug_flags = (q.debug_flags & ~WC_DEBUG_TIME) | kNoPart;  // pieces share one table
   if (!q.table_slots) {
     wc_plan p;
     if (wc_count_plan(corpus_len, 1, o, &p) == WC_OK) q.table_slots = p.table_slots;

@@ -38,6 +38,7 @@ constexpr uint32_t kFlagTableFull = 1u;
 constexpr uint32_t kFlagBadOffsets = 2u;
 constexpr uint32_t kFlagWordCap = 4u;
 constexpr uint32_t kFlagCountOverflow = 8u;
+constexpr uint32_t kFlagArena = 32u;  // the partitioned count ran out of room: count again one-pass
 constexpr uint32_t kFlagStall = 16u;  // a bounded wait inside a kernel gave up (internal error)
 
 struct Slot {
@@ -59,7 +60,8 @@ struct Header {
   uint64_t max_count;
   uint64_t work_next;     // work-queue cursor (persistent launches)
   uint64_t out_cursor;    // per-document output: (entries << 32) | word bytes reserved
-  uint64_t arena_next;    // per-document output: private-table slots taken
+  uint64_t arena_next;    // per-document output: private-table slots taken; partitioned count:
+                          // (lists << 40) | records
   // two-pass global count statistics: records written to the partitions, records pass 1
   // counted straight in the global table, dictionary words, (unused), records pass 2 could
   // not sum in LDS

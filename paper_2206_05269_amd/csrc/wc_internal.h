@@ -102,6 +102,38 @@ hipError_t set_global_smem(uint32_t dict_cap, uint32_t reduce_entries);
 // table, its header, the dictionary image and the block fills must be zero.
 hipError_t launch_global(const GlobalParams& P, hipEvent_t a, hipEvent_t b, hipStream_t s);
 
+// partitioned global count (wc_part.hip)
+constexpr uint32_t kPartMapEntries = 5120;  // LDS entries of a map workgroup (20 bytes each)
+constexpr uint32_t kPartRedEntries = 5888;  // of a reduce workgroup
+struct PartParams {
+  const uint8_t* corpus;
+  uint64_t len;
+  const uint64_t* offsets;
+  uint64_t n_docs;
+  Header* hdr;               // zero before the map
+  int64_t base_off;          // logical position of stripe 0 (<= 0, > -16)
+  uint64_t n_stripes;
+  uint64_t stripes_per_wg;
+  uint32_t parts;            // partitions: a power of two, at most kParts
+  uint32_t max_lists;
+  uint64_t cap_recs;
+  uint4* rec_key;            // [cap_recs] a word of a list ...
+  uint32_t* rec_cnt;         // [cap_recs] ... and its count in it
+  uint2* dir;                // [parts][max_lists] first record and records of a list's partition
+  uint64_t* word_offsets;    // [slots + 1]
+  uint8_t* words;            // [word_cap]
+  void* counts;              // [slots]
+  uint64_t slots, occ_limit, word_cap;
+  uint64_t count_bias;
+  uint32_t count_bytes;
+  uint32_t pad0;
+};
+hipError_t set_part_smem();
+hipError_t launch_part_map(const PartParams& P, uint32_t grid, hipStream_t s);
+hipError_t launch_part_reduce(const PartParams& P, hipStream_t s);
+// a text that one workgroup counts and writes by itself (clears the header too)
+hipError_t launch_part_single(const PartParams& P, hipStream_t s);
+
 // per-document count (wc_docs.hip)
 constexpr uint64_t kWin = 32 * 1024;   // default bytes per work item window
 constexpr uint64_t kMinWin = 16 * 1024;

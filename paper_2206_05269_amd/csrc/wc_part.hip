@@ -1,0 +1,772 @@
+// Partitioned global count, for texts up to the size from which the two-pass count with a sampled
+// dictionary (wc_global.hip) pays: the map of Section 3 (tokenise, count) in LDS, and the reduce
+// (sum the counts of each word) over hash partitions, each of which leaves LDS straight into the
+// result arrays. There is no table in device memory: nothing to clear, no device atomic per
+// word and no compaction pass.
+//
+//   part_map_kernel: each workgroup scans a contiguous range of the text and counts its words in
+//     an LDS table. When the table is nearly full, and at the end of the range, its words leave
+//     as a list of (word, count) records ordered by partition, with the place of every partition
+//     in a directory.
+//   part_reduce_kernel: one workgroup per partition adds the partition's records of every list
+//     in an LDS table and writes each distinct word, its count and its bytes to the output.
+//
+// A text of at most kSingleBytes is counted and written by one workgroup in one launch.
+//
+// Why. The one-pass kernel (wc_count.hip) keeps 2,048 words per workgroup and adds them to one
+// device table at every flush: on a 20 MB text of 50,000 words that is about 2.6 million inserts,
+// many of them on the same few hot slots (381 us, 52 GB/s); clearing and compacting the table took
+// another 65 us. Here a word costs one 20-byte record per list it occurs in, written and read once,
+// and contention stays in LDS.
+//
+// Words longer than 16 bytes are kept as references to an occurrence and compared by content.
+// What does not fit (more records than the arena, more lists than the directory) sets kFlagArena,
+// and the caller counts the text again with the one-pass kernel.
+#include "wc_internal.h"
+#include "wc_stripe.h"
+
+namespace wc {
+
+namespace {
+
+constexpr int kBlk = 1024;
+constexpr uint32_t kWaves = kBlk / 64;
+constexpr uint32_t kText = kStripe + 32;     // per wave: stripe, the 16 bytes after it, padding
+constexpr uint32_t kRound = 128;             // tokens of a wave counted at a time
+constexpr uint32_t kEnds = kStripe / 32 + 2; // word-end bitmap of a stripe and the 16 bytes after
+constexpr uint32_t kListWords = kRound / 2 + kEnds;
+constexpr uint32_t kNone = 0xffffffffu;
+
+// Entries a map table hands out before its words leave: a wave looks at the number of entries
+// before every round, in which it takes at most kRound more, so the table never runs out.
+constexpr uint32_t kMapFull = kPartMapEntries - kWaves * kRound;
+constexpr uint32_t kPerThread = (kPartMapEntries + kBlk - 1) / kBlk;
+
+// A word of at most 16 bytes is its packed bytes; a longer one the address of an occurrence and
+// its length under a top byte of 0xff, which no word byte of either tokeniser is.
+WC_DEV uint4 long_key(const uint8_t* p, uint64_t n) {
+  return key4((uint64_t)(uintptr_t)p, n | 0xff00000000000000ull);
+}
+WC_DEV bool is_long_key(const uint4 k) { return (k.w >> 24) == 0xffu; }
+WC_DEV const uint8_t* long_ptr(const uint4 k) {
+  return (const uint8_t*)(uintptr_t)((uint64_t)k.x | ((uint64_t)k.y << 32));
+}
+WC_DEV uint64_t long_len(const uint4 k) { return (uint64_t)k.z | ((uint64_t)(k.w & 0xffffffu) << 32); }
+
+WC_DEV uint32_t mix32(uint32_t h) {  // the 32-bit finaliser of MurmurHash3 (Appleby)
+  h ^= h >> 16;
+  h *= 0x85EBCA6Bu;
+  h ^= h >> 13;
+  h *= 0xC2B2AE35u;
+  h ^= h >> 16;
+  return h;
+}
+WC_DEV uint32_t long_hash(const uint8_t* p, uint64_t n) {
+  uint64_t h = kFnvOffset;
+  for (uint64_t i = 0; i < n; ++i) h = fnv_step(h, fold_byte(p[i]));
+  return (uint32_t)(h ^ (h >> 32));
+}
+// Two hashes of a key: `place` for the LDS tables (group and tag), `part` for the partition and,
+// above its low 8 bits, for splitting a partition that does not fit LDS.
+WC_DEV uint32_t part_hash(const uint4 k) {
+  if (is_long_key(k)) return mix32(long_hash(long_ptr(k), long_len(k)));
+  return mix32((k.x ^ __builtin_amdgcn_alignbit(k.y, k.y, 21)) +
+               (k.z ^ __builtin_amdgcn_alignbit(k.w, k.w, 13)));
+}
+WC_DEV uint32_t long_place(uint32_t h) { return (h ^ (h >> 15)) * 0x9E3779B1u; }
+
+WC_DEV bool same_key(const uint4 a, const uint4 b) {
+  if (key_eq(a, b)) return true;
+  return is_long_key(a) && a.z == b.z && a.w == b.w && long_equal(long_ptr(a), long_ptr(b), long_len(a));
+}
+
+// Adds n occurrences of a key, with an entry made for it when it has none. `mine`: an entry
+// already taken for this key whose slot another key got (kNone: none). False: no entry or slot.
+// The table is the tag-slot table of wc_stripe.h; an entry's key and zero count are written
+// before its slot is claimed (a wave's LDS accesses are in order), so entries need no clearing.
+// Every iteration counts the key, loses a slot of the group to another key (at most four
+// times) or moves to the next of 16 groups.
+WC_DEV bool part_add(const RedTable& T, const uint4 want, uint32_t h, uint32_t n, uint32_t mine) {
+  constexpr uint32_t kGroups = kRedSlots / 4;
+  const uint32_t tag = red_tag(h), lane = threadIdx.x & 63;
+  uint32_t g = red_group(h), probe = 0;
+  bool active = true, ok = false;
+  while (__any(active)) {
+    bool claim = false;
+    int free_j = -1;
+    if (active) {
+      const uint4 s4 = ((const uint4*)T.slot)[g];
+      const uint32_t e[4] = {s4.x, s4.y, s4.z, s4.w};
+      bool found = false;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (found) continue;
+        if ((e[j] >> 13) == tag) {
+          const uint32_t idx = e[j] & 0x1fffu;
+          if (same_key(T.key[idx], want)) {
+            atomicAdd(&T.cnt[idx], n);
+            found = true;
+          }
+        } else if (e[j] == 0 && free_j < 0) {
+          free_j = j;
+        }
+      }
+      if (found) {
+        ok = true;
+        active = false;
+      } else if (free_j >= 0) {
+        claim = true;
+      } else {
+        g = (g + 1) & (kGroups - 1);
+        if (++probe >= 16) active = false;
+      }
+    }
+    const bool need = claim && mine == kNone;
+    const uint64_t nm = __ballot(need);
+    if (nm) {
+      const uint32_t leader = (uint32_t)__ffsll((unsigned long long)nm) - 1;
+      uint32_t base = 0;
+      if (lane == leader) base = atomicAdd(T.n, (uint32_t)__popcll(nm));
+      base = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)leader);
+      if (need) {
+        const uint32_t m = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32),
+                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u));
+        if (m < T.cap) {
+          mine = m;
+          T.key[m] = want;
+          T.cnt[m] = 0;
+        } else {
+          claim = false;
+          active = false;
+        }
+      }
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    if (claim) {
+      if (atomicCAS(&T.slot[g * 4 + free_j], 0u, (tag << 13) | mine) == 0) {
+        atomicAdd(&T.cnt[mine], n);
+        ok = true;
+        active = false;
+      }
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  }
+  return ok;
+}
+
+// Adds n occurrences of a key that was not found: s4 is its home group as it was read, `match`
+// the slot of another key with its tag there (0: none). The common case of a new word takes two
+// LDS round trips (an entry for every lane of the wave with one atomic, then its slot) instead
+// of part_add's loop; what it cannot settle goes there.
+WC_DEV bool part_add_new(const RedTable& T, const uint4 want, uint32_t h, uint32_t n, const uint4 s4,
+                         uint32_t match) {
+  const uint32_t tag = red_tag(h), lane = threadIdx.x & 63;
+  // claimed slots of a group are a prefix
+  const uint32_t used = (s4.x != 0) + (s4.y != 0) + (s4.z != 0) + (s4.w != 0);
+  const bool fresh = used < 4 && match == 0;
+  uint32_t mine = kNone;
+  bool done = false;
+  const uint64_t nm = __ballot(fresh);
+  if (nm) {
+    const uint32_t leader = (uint32_t)__ffsll((unsigned long long)nm) - 1;
+    uint32_t base = 0;
+    if (lane == leader) base = atomicAdd(T.n, (uint32_t)__popcll(nm));
+    base = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)leader);
+    const uint32_t m = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u));
+    if (fresh && m < T.cap) {
+      mine = m;
+      T.key[m] = want;
+      T.cnt[m] = 0;
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      const uint32_t prev = atomicCAS(&T.slot[red_group(h) * 4 + used], 0u, (tag << 13) | m);
+      __atomic_signal_fence(__ATOMIC_SEQ_CST);
+      if (prev == 0) {
+        atomicAdd(&T.cnt[m], n);
+        done = true;
+      } else if ((prev >> 13) == tag) {  // most often the same new word in another lane
+        const uint32_t idx = prev & 0x1fffu;
+        if (key_eq(T.key[idx], want)) {
+          atomicAdd(&T.cnt[idx], n);
+          done = true;
+        }
+      }
+    }
+  }
+  return done || part_add(T, want, h, n, mine);
+}
+
+// Exclusive sums over the workgroup of a pair packed in 64 bits (no field overflows).
+WC_DEV uint64_t block_scan64(uint64_t v, uint64_t* s_tmp, uint64_t* total) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  uint64_t incl = v;
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint64_t y = __shfl_up(incl, d, 64);
+    if (lane >= (uint32_t)d) incl += y;
+  }
+  if (lane == 63) s_tmp[wave] = incl;
+  __syncthreads();
+  uint64_t base = 0, tot = 0;
+  for (uint32_t w = 0; w < kWaves; ++w) {
+    const uint64_t x = s_tmp[w];
+    base += w < wave ? x : 0;
+    tot += x;
+  }
+  __syncthreads();
+  *total = tot;
+  return base + incl - v;
+}
+
+WC_DEV uint64_t key_len(const uint4 k) {
+  if (is_long_key(k)) return long_len(k);
+  return packed_len((uint64_t)k.x | ((uint64_t)k.y << 32), (uint64_t)k.z | ((uint64_t)k.w << 32));
+}
+
+// Every entry of the table with a count to the output arrays, in space reserved with one atomic
+// on the packed cursor (entries << 32 | bytes; the text is below 2^31 bytes). All threads.
+WC_DEV void export_table(const PartParams& P, const RedTable& T, uint64_t* s_tmp, uint64_t* s_base) {
+  const uint32_t tid = threadIdx.x, ne = min(*T.n, T.cap);
+  uint64_t part = 0;
+  for (uint32_t i = tid; i < ne; i += kBlk)
+    if (T.cnt[i]) part += (1ull << 32) + key_len(T.key[i]);
+  uint64_t tot;
+  const uint64_t at = block_scan64(part, s_tmp, &tot);
+  if (tid == 0) *s_base = tot ? atomicAdd((unsigned long long*)&P.hdr->out_cursor, (unsigned long long)tot) : 0ull;
+  __syncthreads();
+  const uint64_t base = *s_base + at;
+  uint64_t e = base >> 32, b = base & 0xffffffffull;
+  for (uint32_t i = tid; i < ne; i += kBlk) {
+    const uint32_t n = T.cnt[i];
+    if (!n) continue;
+    const uint4 k = T.key[i];
+    const uint64_t len = key_len(k);
+    if (e < P.slots) {  // beyond: the call fails as full
+      const uint64_t c = (uint64_t)n + P.count_bias;
+      P.word_offsets[e] = b;
+      if (P.count_bytes == 4) {
+        if (c > 0x7fffffffull) or32(&P.hdr->flags, kFlagCountOverflow);
+        ((int32_t*)P.counts)[e] = (int32_t)c;
+      } else {
+        ((int64_t*)P.counts)[e] = (int64_t)c;
+      }
+    }
+    if (b + len <= P.word_cap) {
+      if (is_long_key(k)) {
+        const uint8_t* src = long_ptr(k);
+        for (uint64_t q = 0; q < len; ++q) P.words[b + q] = (uint8_t)fold_byte(src[q]);
+      } else {
+        const uint64_t lo = (uint64_t)k.x | ((uint64_t)k.y << 32);
+        const uint64_t hi = (uint64_t)k.z | ((uint64_t)k.w << 32);
+        for (uint32_t q = 0; q < (uint32_t)len; ++q)
+          P.words[b + q] = (uint8_t)((q < 8 ? lo >> (8 * q) : hi >> (8 * (q - 8))) & 0xff);
+      }
+    }
+    ++e;
+    b += len;
+  }
+  __syncthreads();
+}
+
+// Totals and limits, once every entry has its place (one thread).
+WC_DEV void finish_output(const PartParams& P) {
+  const uint64_t c = ld_relaxed(&P.hdr->out_cursor), n = c >> 32, b = c & 0xffffffffull;
+  P.hdr->n_entries = n;
+  P.hdr->word_bytes = b;
+  if (n <= P.slots) P.word_offsets[n] = b;
+  if (n > P.occ_limit) or32(&P.hdr->flags, kFlagTableFull);
+  if (b > P.word_cap) or32(&P.hdr->flags, kFlagWordCap);
+}
+
+WC_DEV int64_t lane_value(int64_t v, uint32_t lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), (int)lane);
+  return (int64_t)((uint64_t)lo | ((uint64_t)hi << 32));
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------------------------------
+// map
+// ---------------------------------------------------------------------------------------
+// Each wave scans its own contiguous run of the workgroup's 1 KiB stripes. The 16 bytes after a
+// stripe are staged with it (the next stripe is classified one step early), so a word of at most
+// 16 bytes that runs over the stripe's end is read whole from LDS, at the run's end too; a
+// longer one is read from device memory. Waves meet only when the table is to be emptied.
+template <bool kSingle>
+__global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
+  extern __shared__ __align__(16) uint8_t s_dyn[];
+  __shared__ uint32_t s_list[kWaves][kListWords];  // starts (16 bits each), then the end bitmap
+  __shared__ uint32_t s_bnd[kWaves][kEnds];
+  __shared__ uint4 s_lenmask[17];
+  __shared__ uint32_t s_hist[kParts], s_start[kParts];
+  __shared__ uint32_t s_nent, s_done, s_scan[4];
+  __shared__ uint64_t s_tmp[kWaves], s_base;
+  RedTable T;
+  T.slot = (uint32_t*)s_dyn;
+  T.key = (uint4*)(T.slot + kRedSlots);
+  T.cnt = (uint32_t*)(T.key + kPartMapEntries);
+  T.n = &s_nent;
+  T.cap = kPartMapEntries;
+  T.stall = nullptr;
+  const uint32_t tid = threadIdx.x, lane = tid & 63;
+  const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
+  uint8_t* const my_txt = (uint8_t*)(T.cnt + kPartMapEntries) + wv * kText;
+  uint16_t* const my_starts = (uint16_t*)s_list[wv];
+  uint32_t* const my_ends = s_list[wv] + kRound / 2;
+  uint32_t* const my_bnd = s_bnd[wv];
+  Header* const hdr = P.hdr;
+
+  // this wave's stripes
+  const uint64_t first = (uint64_t)blockIdx.x * P.stripes_per_wg;
+  const uint64_t last = min(first + P.stripes_per_wg, P.n_stripes);
+  const uint64_t n_wg = last > first ? last - first : 0;
+  const uint64_t per = (n_wg + kWaves - 1) / kWaves;
+  const uint64_t sa = first + min(wv * per, n_wg);
+  const uint32_t nsw = (uint32_t)(min(first + (wv + 1) * per, first + n_wg) - sa);
+  auto stripe_pos = [&](uint64_t i) -> int64_t { return P.base_off + (int64_t)((sa + i) * kStripe); };
+  // stripe i of the run; of the stripe after it, the first 16 bytes (lane 0)
+  const uint4 blank = make_uint4(0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u);
+  auto load = [&](uint32_t i) -> uint4 {
+    if (i > nsw || nsw == 0) return blank;
+    const int64_t p = stripe_pos(i);
+    uint4 v = blank;
+    if (i < nsw && p >= 0 && p + (int64_t)kStripe <= (int64_t)P.len) {
+      v = load_stream16(P.corpus + p + lane * 16);
+    } else if (i < nsw || lane == 0) {
+      v = load_text16(P.corpus, P.len, p + lane * 16);
+    }
+    return v;
+  };
+  const uint4 raw0 = load(0);
+  uint4 r1 = load(1), r2 = load(2);
+
+  for (uint32_t i = tid; i < kRedSlots / 4; i += kBlk) ((uint4*)T.slot)[i] = make_uint4(0, 0, 0, 0);
+  for (uint32_t i = tid; i < kWaves * kListWords; i += kBlk) (&s_list[0][0])[i] = 0;
+  for (uint32_t i = tid; i < kWaves * kEnds; i += kBlk) (&s_bnd[0][0])[i] = 0;
+  if (tid < kParts) s_hist[tid] = 0;
+  init_len_masks(s_lenmask, tid, kBlk);
+  if (tid == 0) {
+    s_nent = 0;
+    s_done = 0;
+    if (kSingle) {
+      *hdr = Header{};
+      __threadfence();
+    }
+  }
+  __syncthreads();
+
+  // Offsets must be non-decreasing and end inside the text; a bad one fails the call. Until the
+  // host sees that, positions taken from them are only compared, and ranges are cut to the text.
+  for (uint64_t d = blockIdx.x * (uint64_t)kBlk + tid; d <= P.n_docs; d += (uint64_t)gridDim.x * kBlk) {
+    const uint64_t o = P.offsets[d];
+    if (d < P.n_docs ? o > P.offsets[d + 1] : o > P.len) or32(&hdr->flags, kFlagBadOffsets);
+  }
+  const int64_t R0 = (int64_t)min(P.offsets[0], P.len), R1 = (int64_t)min(P.offsets[P.n_docs], P.len);
+
+  // Document starts from the run's first byte on, 64 at a time in the lanes (lane l: document
+  // d0 + l); those before dn lie before the current stripe. The first one: 64 probes at a time.
+  uint64_t d0 = 0;
+  uint32_t dn = 0;
+  int64_t doff = INT64_MAX;
+  auto load_docs = [&]() {
+    const uint64_t d = d0 + lane;
+    doff = d <= P.n_docs ? (int64_t)P.offsets[d] : INT64_MAX;
+  };
+  if (nsw) {
+    uint64_t lo = 0, hi = P.n_docs + 1;  // offsets[lo - 1] < run start <= offsets[hi]
+    const int64_t p0 = stripe_pos(0);
+    while (hi - lo > 64) {
+      const uint64_t step = (hi - lo + 63) / 64, d = lo + lane * step;
+      const uint64_t m = __ballot(d < hi && (int64_t)P.offsets[d] < p0);
+      const uint64_t k = (uint64_t)__popcll(m);
+      if (k == 0) {
+        hi = lo;
+      } else {
+        hi = min(hi, lo + k * step);
+        lo += (k - 1) * step + 1;
+      }
+    }
+    d0 = lo;
+    load_docs();
+    dn = (uint32_t)__popcll(__ballot(doff < p0));  // of these at most 64, the ones before the run
+    if (dn >= 64) {
+      d0 += 64;
+      dn = 0;
+      load_docs();
+    }
+  }
+  auto doc_limit = [&](uint64_t pos) -> uint64_t {  // first document start after pos, or the end
+    uint64_t a = 1, b = P.n_docs;
+    while (a < b) {
+      const uint64_t m = (a + b) >> 1;
+      if (P.offsets[m] > pos) b = m;
+      else a = m + 1;
+    }
+    return min(P.offsets[a], P.len);
+  };
+
+  // the byte before the run
+  uint32_t carry = 0;
+  if (nsw) {
+    const int64_t q = stripe_pos(0) - 1;
+    uint32_t f;
+    fold_classify4(load_text4(P.corpus, P.len, q - 3), &f);
+    carry = (q >= R0 && q < R1) ? f >> 31 : 0u;
+  }
+  const bool inside = nsw && stripe_pos(0) >= R0 && stripe_pos(nsw) + 16 <= R1;
+  uint32_t w16;
+  uint4 g = classify16(raw0, &w16);
+  if (!inside) w16 = cut16(w16, stripe_pos(0) + lane * 16, R0, R1);
+
+  uint32_t i = 0, n = 0, w0 = 0, start16 = 0, rank = 0;
+  int64_t p0 = 0;
+  uint64_t tokens = 0;
+  bool over = false;  // a word found no room (this lane)
+
+  // one occurrence of a word that is not wholly staged, or longer than 16 bytes
+  auto long_token = [&](uint32_t s, uint32_t len) {
+    const uint64_t start = (uint64_t)(p0 + s);
+    const uint64_t limit = len ? start + len : doc_limit(start);
+    uint64_t lo, hi, h64;
+    const uint64_t m = scan_word(P.corpus, start, limit, &lo, &hi, &h64);
+    const uint4 k = m > 16 ? long_key(P.corpus + start, m) : key4(lo, hi);
+    const uint32_t h = m > 16 ? long_place((uint32_t)(h64 ^ (h64 >> 32))) : red_hash(k);
+    if (!part_add(T, k, h, 1, kNone)) over = true;
+  };
+
+  while (true) {
+    // ---- scan: until the run ends or the table is nearly full ------------------------------
+    while (true) {
+      if (w0 >= n) {
+        if (i >= nsw) break;
+        // -- next stripe: (g, w16) classified; the next one's bytes are in r1
+        p0 = stripe_pos(i);
+        uint32_t w1;
+        const uint4 g1 = classify16(r1, &w1);
+        if (!inside) w1 = cut16(w1, p0 + (int64_t)kStripe + lane * 16, R0, R1);
+        r1 = r2;
+        r2 = load(i + 3);
+        ((uint4*)my_txt)[lane] = g;
+        if (lane == 0) ((uint4*)my_txt)[64] = g1;
+        uint32_t bnd16 = 0, bnext = 0, bsfx = 0;
+        if (lane_value(doff, dn) < p0 + (int64_t)kStripe + 16) {
+          while (true) {
+            const bool mine = lane >= dn && doff >= p0 && doff < p0 + (int64_t)kStripe + 16;
+            if (mine) {
+              const uint32_t rel = (uint32_t)(doff - p0);
+              atomicOr(&my_bnd[rel >> 5], 1u << (rel & 31));
+            }
+            dn += (uint32_t)__popcll(__ballot(lane >= dn && doff < p0 + (int64_t)kStripe));
+            if (dn < 64) break;
+            d0 += 64;
+            dn = 0;
+            load_docs();
+          }
+          wave_sync();
+          bnd16 = (my_bnd[lane >> 1] >> ((lane & 1) * 16)) & 0xffffu;
+          bnext = (my_bnd[(lane + 1) >> 1] >> (((lane + 1) & 1) * 16)) & 1u;
+          bsfx = my_bnd[kStripe / 32] & 0xffffu;
+          wave_sync();
+          if (lane < kEnds) my_bnd[lane] = 0;
+        }
+        const uint32_t sfx = (uint32_t)__builtin_amdgcn_readlane((int)w1, 0);
+        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)carry, (int)(w16 >> 15), 0x138,
+                                                                    0xf, 0xf, false);
+        const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)(sfx & 1u), (int)(w16 & 1u),
+                                                                    0x130, 0xf, 0xf, false);
+        start16 = w16 & (~((w16 << 1) | prev) | bnd16) & 0xffffu;
+        const uint32_t last16 =
+            w16 & (~((w16 >> 1) | (next << 15)) | (bnd16 >> 1) | (bnext << 15)) & 0xffffu;
+        ((uint16_t*)my_ends)[lane] = (uint16_t)last16;
+        // (a word of the stripe that reaches the last of these 16 bytes is longer than 16 bytes)
+        if (lane == 0) ((uint16_t*)my_ends)[64] = (uint16_t)(sfx & (~(sfx >> 1) | (bsfx >> 1)) & 0x7fffu);
+        const uint32_t c = __popc(start16), incl = wave_incl_scan(c);
+        rank = incl - c;
+        n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        carry = (uint32_t)__builtin_amdgcn_readlane((int)(w16 >> 15), 63);
+        tokens += n;
+        g = g1;
+        w16 = w1;
+        w0 = 0;
+        ++i;
+        continue;
+      }
+      if (!kSingle &&
+          (uint32_t)__builtin_amdgcn_readfirstlane(
+              (int)__hip_atomic_load(&s_nent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > kMapFull)
+        break;
+      // -- a round: the starts of ranks [w0, w0 + kRound), two per lane
+      {
+        uint32_t m = start16, r = rank;
+        while (m) {
+          const uint32_t j = __ffs(m) - 1;
+          if (r - w0 < kRound) my_starts[r - w0] = (uint16_t)(lane * 16 + j);
+          ++r;
+          m &= m - 1;
+        }
+      }
+      wave_sync();
+      const uint32_t nw = min(n - w0, kRound);
+      w0 += kRound;
+      uint32_t s2[2], n2[2], e0[2], e1[2];
+      bool f2[2];
+      // (starts past nw are of earlier rounds: in range, not counted)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) s2[x] = my_starts[lane + 64 * x];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        e0[x] = my_ends[s2[x] >> 5];
+        e1[x] = my_ends[(s2[x] >> 5) + 1];
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        n2[x] = __ffs(__builtin_amdgcn_alignbit(e1[x], e0[x], s2[x] & 31));  // 0: no end in 32
+        f2[x] = lane + 64 * x < nw && n2[x] - 1 < 16u;
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+        if (lane + 64 * x < nw && !f2[x]) {
+          long_token(s2[x], n2[x]);
+          wait_vmem();
+        }
+      // each LDS step reads for both tokens before either waits (pin)
+      PackSrc ps[2];
+      uint4 lm[2], key2[2], g2[2], k2[2];
+      uint32_t h2[2], e2[2];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        ps[x] = pack_read(my_txt, s2[x]);
+        lm[x] = s_lenmask[f2[x] ? n2[x] : 1u];
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        pin(ps[x]);
+        pin(lm[x]);
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        uint64_t lo, hi;
+        pack_join(ps[x], lm[x], &lo, &hi);
+        key2[x] = key4(lo, hi);
+        h2[x] = red_hash(key2[x]);
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x) g2[x] = ((const uint4*)T.slot)[red_group(h2[x])];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) pin(g2[x]);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const uint32_t tag = red_tag(h2[x]);
+        uint32_t m = 0u;
+        m = (g2[x].w >> 13) == tag ? g2[x].w : m;
+        m = (g2[x].z >> 13) == tag ? g2[x].z : m;
+        m = (g2[x].y >> 13) == tag ? g2[x].y : m;
+        m = (g2[x].x >> 13) == tag ? g2[x].x : m;
+        e2[x] = m;
+      }
+#pragma unroll
+      for (int x = 0; x < 2; ++x) k2[x] = T.key[e2[x] & 0x1fffu];
+#pragma unroll
+      for (int x = 0; x < 2; ++x) pin(k2[x]);
+#pragma unroll
+      for (int x = 0; x < 2; ++x) {
+        const bool eq = key_eq(k2[x], key2[x]);
+        const bool hit = f2[x] & (e2[x] != 0) & eq;
+        if (hit) atomicAdd(&T.cnt[e2[x] & 0x1fffu], 1u);
+        f2[x] = f2[x] && !hit;
+      }
+      // the new words, one token of the lanes at a time: the lookup is repeated by part_add when
+      // the first token's insertions took the slot this one saw free
+#pragma unroll 1
+      for (int x = 0; x < 2; ++x)
+        if (f2[x] && !part_add_new(T, key2[x], h2[x], 1, g2[x], e2[x])) over = true;
+      wave_sync();
+    }
+    if (i >= nsw && w0 >= n && i != kNone) {  // the run is done
+      i = kNone;
+      if (lane == 0) {
+        atomicAdd(&s_done, 1u);
+        if (tokens) add64(&hdr->total_tokens, tokens);
+      }
+    }
+    // ---- the table's words leave -------------------------------------------------------------
+    __syncthreads();
+    const bool end = s_done == kWaves;
+    if (kSingle) {  // (a word that found no room sets kFlagArena below)
+      export_table(P, T, s_tmp, &s_base);
+      if (tid == 0) finish_output(P);
+      break;
+    }
+    const uint32_t ne = min(s_nent, T.cap);
+    uint32_t at[kPerThread];  // partition << 16 | place in it
+#pragma unroll
+    for (uint32_t x = 0; x < kPerThread; ++x) {
+      const uint32_t j = tid + x * kBlk;
+      at[x] = kNone;
+      if (j < ne && T.cnt[j]) {
+        const uint32_t p = part_hash(T.key[j]) & (P.parts - 1);
+        at[x] = (p << 16) | atomicAdd(&s_hist[p], 1u);
+      }
+    }
+    __syncthreads();
+    uint32_t cnt = 0, incl = 0;
+    if (tid < kParts) {
+      cnt = s_hist[tid];
+      incl = wave_incl_scan(cnt);
+      if (lane == 63) s_scan[wv] = incl;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      const uint32_t tot = s_scan[0] + s_scan[1] + s_scan[2] + s_scan[3];
+      // lists << 40 | records
+      s_base = atomicAdd((unsigned long long*)&hdr->arena_next, (1ull << 40) | tot);
+      if ((s_base & ((1ull << 40) - 1)) + tot > P.cap_recs || (s_base >> 40) >= P.max_lists) {
+        or32(&hdr->flags, kFlagArena);
+        s_base = ~0ull;
+      }
+    }
+    if (tid < kParts) {
+      uint32_t b = incl - cnt;
+      for (uint32_t w = 0; w < 4; ++w) b += w < wv ? s_scan[w] : 0u;
+      s_start[tid] = b;
+      s_hist[tid] = 0;
+    }
+    __syncthreads();
+    if (s_base != ~0ull) {
+      const uint64_t list = s_base >> 40;
+      const uint32_t rec = (uint32_t)(s_base & ((1ull << 40) - 1));
+      if (tid < P.parts) P.dir[(uint64_t)tid * P.max_lists + list] = make_uint2(rec + s_start[tid], cnt);
+#pragma unroll
+      for (uint32_t x = 0; x < kPerThread; ++x) {
+        const uint32_t j = tid + x * kBlk;
+        if (at[x] == kNone) continue;
+        const uint32_t r = rec + s_start[at[x] >> 16] + (at[x] & 0xffffu);
+        P.rec_key[r] = T.key[j];
+        P.rec_cnt[r] = T.cnt[j];
+      }
+    }
+    __syncthreads();
+    if (end) break;
+    for (uint32_t j = tid; j < kRedSlots / 4; j += kBlk) ((uint4*)T.slot)[j] = make_uint4(0, 0, 0, 0);
+    if (tid == 0) s_nent = 0;
+    __syncthreads();
+  }
+  if (over) or32(&hdr->flags, kFlagArena);
+}
+
+// ---------------------------------------------------------------------------------------
+// reduce
+// ---------------------------------------------------------------------------------------
+// One workgroup per partition. The directory rows of kRows lists at a time give the flat order
+// of their records; a thread finds its record's list by a binary search in LDS. A partition
+// whose words do not fit the LDS table is summed in classes of its hash (two, four, ... classes,
+// each reading the records again), so that any number of distinct words is counted in LDS.
+__global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
+  constexpr uint32_t kRows = 1024;
+  constexpr uint32_t kMaxBits = 16;
+  extern __shared__ __align__(16) uint8_t s_dyn[];
+  __shared__ uint32_t s_pre[kRows + 1], s_rec[kRows];
+  __shared__ uint32_t s_nent, s_full;
+  __shared__ uint64_t s_tmp[kWaves], s_base;
+  Header* const hdr = P.hdr;
+  if (ld_relaxed32(&hdr->flags) & (kFlagBadOffsets | kFlagArena)) return;
+  RedTable T;
+  T.slot = (uint32_t*)s_dyn;
+  T.key = (uint4*)(T.slot + kRedSlots);
+  T.cnt = (uint32_t*)(T.key + kPartRedEntries);
+  T.n = &s_nent;
+  T.cap = kPartRedEntries;
+  T.stall = nullptr;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t lists = (uint32_t)(hdr->arena_next >> 40);
+  const uint2* dir = P.dir + (uint64_t)blockIdx.x * P.max_lists;
+
+  // classes of the part hash still to sum: the low `bits` bits above the partition's are `value`
+  uint32_t bits = 0, value = 0;
+  while (true) {
+    for (uint32_t i = tid; i < kRedSlots / 4; i += kBlk) ((uint4*)T.slot)[i] = make_uint4(0, 0, 0, 0);
+    if (tid == 0) {
+      s_nent = 0;
+      s_full = 0;
+    }
+    for (uint32_t q0 = 0; q0 < lists; q0 += kRows) {
+      const uint32_t nq = min(kRows, lists - q0);
+      uint2 d = make_uint2(0, 0);
+      if (tid < nq) d = dir[q0 + tid];
+      uint64_t tot;
+      const uint64_t pre = block_scan64(d.y, s_tmp, &tot);  // (its barriers also end the last rows' use)
+      s_pre[tid] = (uint32_t)pre;
+      s_rec[tid] = d.x;
+      if (tid == 0) s_pre[kRows] = (uint32_t)tot;
+      __syncthreads();
+      const uint32_t m = (uint32_t)tot;
+      for (uint32_t f = tid; f < m; f += kBlk) {
+        uint32_t lo = 0;  // the last list that starts at or before f and is not empty
+#pragma unroll
+        for (uint32_t step = kRows / 2; step; step >>= 1)
+          if (s_pre[lo + step] <= f) lo += step;
+        const uint32_t r = s_rec[lo] + (f - s_pre[lo]);
+        const uint4 k = P.rec_key[r];
+        const uint32_t c = P.rec_cnt[r];
+        if (bits && ((part_hash(k) >> 8) & ((1u << bits) - 1)) != value) continue;
+        const uint32_t h = is_long_key(k) ? long_place(long_hash(long_ptr(k), long_len(k))) : red_hash(k);
+        if (!part_add(T, k, h, c, kNone)) s_full = 1;
+      }
+      __syncthreads();
+    }
+    __syncthreads();
+    if (s_full) {
+      if (bits == kMaxBits) {
+        if (tid == 0) or32(&hdr->flags, kFlagArena);
+        return;
+      }
+      ++bits;  // this class in two: first the half whose new bit is 0
+      __syncthreads();
+      continue;
+    }
+    export_table(P, T, s_tmp, &s_base);
+    // the next class: the other half of the smallest split whose first half this one ends
+    while (bits && (value >> (bits - 1))) {
+      --bits;
+      value &= (1u << bits) - 1;
+    }
+    if (bits == 0) break;
+    value |= 1u << (bits - 1);
+  }
+  if (tid == 0) {
+    __threadfence();
+    const uint64_t done = __hip_atomic_fetch_add(&hdr->work_next, 1ull, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+    if (done + 1 == gridDim.x) finish_output(P);
+  }
+}
+
+size_t part_map_dyn() { return (size_t)kRedSlots * 4 + (size_t)kPartMapEntries * 20 + kWaves * kText; }
+size_t part_reduce_dyn() { return (size_t)kRedSlots * 4 + (size_t)kPartRedEntries * 20; }
+
+hipError_t set_part_smem() {
+  hipError_t e = hipFuncSetAttribute((const void*)part_map_kernel<false>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)part_map_dyn());
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)part_map_kernel<true>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)part_map_dyn());
+  if (e == hipSuccess)
+    e = hipFuncSetAttribute((const void*)part_reduce_kernel,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)part_reduce_dyn());
+  return e;
+}
+
+hipError_t launch_part_map(const PartParams& P, uint32_t grid, hipStream_t s) {
+  hipLaunchKernelGGL(part_map_kernel<false>, dim3(grid), dim3(kBlk), part_map_dyn(), s, P);
+  return hipGetLastError();
+}
+hipError_t launch_part_single(const PartParams& P, hipStream_t s) {
+  hipLaunchKernelGGL(part_map_kernel<true>, dim3(1), dim3(kBlk), part_map_dyn(), s, P);
+  return hipGetLastError();
+}
+hipError_t launch_part_reduce(const PartParams& P, hipStream_t s) {
+  hipLaunchKernelGGL(part_reduce_kernel, dim3(P.parts), dim3(kBlk), part_reduce_dyn(), s, P);
+  return hipGetLastError();
+}
+
+}  // namespace wc

@@ -522,6 +522,50 @@ def test_two_pass_one_byte_documents():
 # synthetic workloads
 # ------------------------------------------------------------------------------------------
 
+def _partitioned_texts(n, seed):
+    """Texts of n bytes for the partitioned count: random bytes, few hot words, hardly a repeated
+    word (several lists per workgroup, partitions beyond one LDS table), four-letter words all
+    different (more records than the arena: counted again one-pass), and long words."""
+    rng = np.random.default_rng(seed)
+    alphabet = np.frombuffer(b"abZ'09 ,\n\x80", np.uint8)
+    yield "bytes", alphabet[rng.integers(0, len(alphabet), n)].tobytes()
+    yield "hot", (b"the of a to The OF " * (n // 19 + 1))[:n]
+    yield "distinct", b" ".join(b"%06x" % i for i in range(n // 7 + 2))[:n]
+    d = np.frombuffer(b"abcdefghijklmnopqrstuvwxyz012345", np.uint8)
+    i = np.arange(n // 5 + 1)
+    w = np.full((len(i), 5), 0x20, np.uint8)
+    for j in range(4):
+        w[:, j] = d[(i >> (5 * j)) & 31]
+    yield "overflow", w.tobytes()[:n].ljust(n)
+    long = [b"x%d" % k * 9 for k in range(7)] + [b"q" * 17, b"Q" * 16, b"q" * 300, b"q" * 2000, b"s"]
+    yield "long", b" ".join(long[k] for k in rng.integers(0, len(long), n // 200 + 9)).ljust(n)[:n]
+
+
+@pytest.mark.parametrize("n", [1, 16, 17, 1023, 1024, 1025, 1040, 16_385, 49_152, 49_153, 70_001,
+                               300_007, 1_000_003])
+def test_partitioned_count(n):
+    """Sizes around a lane, a stripe, a workgroup's first range and the one-workgroup limit, at
+    odd addresses, whole and cut into documents (tiny, empty, and at stripe edges)."""
+    rng = np.random.default_rng(n)
+    for name, text in _partitioned_texts(n, n + 1):
+        for shift, docs in ((0, 1), (11, 1), (5, n // 3 + 4)):
+            if docs > 1 and n > 100_000:
+                docs = 5000
+            edge = min(1024 - shift, n)
+            off = np.array([0, n]) if docs == 1 else \
+                np.sort(np.append(rng.integers(0, n + 1, size=docs), [edge, edge]))
+            print(name, n, shift, docs, flush=True)
+            want = oracle.count(text, off)
+            buf = torch.empty(n + 16, dtype=torch.uint8, device=DEV)
+            t = buf[shift:shift + n]
+            t.copy_(torch.from_numpy(np.frombuffer(text, np.uint8).copy()))
+            got = wc.count(t, torch.from_numpy(off.astype(np.int64)).to(DEV))
+            assert got.total_tokens == want.total
+            assert got.as_dict() == want.as_dict(), (name, n, shift, docs)
+            wo = got.word_offsets().cpu().numpy()
+            assert (np.diff(wo) > 0).all() and wo[-1] == got.res.word_bytes
+
+
 @pytest.mark.parametrize("path", ["direct", "spill"])
 def test_plain_1mb_int32(path):
     c = synth.generate("plain-1MB")
