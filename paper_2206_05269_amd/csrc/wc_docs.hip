@@ -379,13 +379,20 @@ __global__ __launch_bounds__(BLOCK) void doc_kernel(DocParams P) {
         }
 #pragma unroll 1
         for (int x = 0; x < 2; ++x) {
-          if (sh2[x]) {
-            const uint64_t hr = recount ? hi2[x] : hi_with_doc(hi2[x], r2[x]);
-            if (!red_add(T, lo2[x], hr, h2[x])) {
-              overflow(lo2[x], hi2[x], r2[x]);
+          // (the second token's values move to the first's: an index into the pairs would put
+          // them in scratch memory)
+          if (sh2[0]) {
+            const uint64_t hr = recount ? hi2[0] : hi_with_doc(hi2[0], r2[0]);
+            if (!red_add(T, lo2[0], hr, h2[0])) {
+              overflow(lo2[0], hi2[0], r2[0]);
               if (recount) wait_vmem();
             }
           }
+          sh2[0] = sh2[1];
+          lo2[0] = lo2[1];
+          hi2[0] = hi2[1];
+          h2[0] = h2[1];
+          r2[0] = r2[1];
         }
         wave_sync();
       }
