@@ -42,16 +42,18 @@ constexpr uint32_t kNone = 0xffffffffu;
 constexpr uint32_t kMapFull = kPartMapEntries - kWaves * kRound;
 constexpr uint32_t kPerThread = (kPartMapEntries + kBlk - 1) / kBlk;
 
-// A word of at most 16 bytes is its packed bytes; a longer one the address of an occurrence and
-// its length under a top byte of 0xff, which no word byte of either tokeniser is.
-WC_DEV uint4 long_key(const uint8_t* p, uint64_t n) {
-  return key4((uint64_t)(uintptr_t)p, n | 0xff00000000000000ull);
+// A word of at most 16 bytes is its packed bytes; a longer one the address of an occurrence, its
+// length (below 2^32) and 24 bits of its hash under a top byte of 0xff, which no word byte of
+// either tokeniser is. (With the hash in the key a long word is read again only to be compared
+// with one of the same length and hash.)
+WC_DEV uint4 long_key(const uint8_t* p, uint64_t n, uint64_t fnv) {
+  const uint32_t h = (uint32_t)(fnv ^ (fnv >> 32));
+  return key4((uint64_t)(uintptr_t)p, (n & 0xffffffffull) | ((uint64_t)(h ^ (h >> 24)) << 32) | (0xffull << 56));
 }
 WC_DEV bool is_long_key(const uint4 k) { return (k.w >> 24) == 0xffu; }
 WC_DEV const uint8_t* long_ptr(const uint4 k) {
   return (const uint8_t*)(uintptr_t)((uint64_t)k.x | ((uint64_t)k.y << 32));
 }
-WC_DEV uint64_t long_len(const uint4 k) { return (uint64_t)k.z | ((uint64_t)(k.w & 0xffffffu) << 32); }
 
 WC_DEV uint32_t mix32(uint32_t h) {  // the 32-bit finaliser of MurmurHash3 (Appleby)
   h ^= h >> 16;
@@ -61,23 +63,37 @@ WC_DEV uint32_t mix32(uint32_t h) {  // the 32-bit finaliser of MurmurHash3 (App
   h ^= h >> 16;
   return h;
 }
-WC_DEV uint32_t long_hash(const uint8_t* p, uint64_t n) {
-  uint64_t h = kFnvOffset;
-  for (uint64_t i = 0; i < n; ++i) h = fnv_step(h, fold_byte(p[i]));
-  return (uint32_t)(h ^ (h >> 32));
+// Two hashes of a key: one for its place in the LDS tables, one for its partition (the low 8
+// bits) and, above those, for splitting a partition that does not fit LDS.
+WC_DEV uint32_t place_hash(const uint4 k) {
+  const uint4 l = make_uint4(k.z, k.w, 0u, 0u);
+  return red_hash(is_long_key(k) ? l : k);
 }
-// Two hashes of a key: `place` for the LDS tables (group and tag), `part` for the partition and,
-// above its low 8 bits, for splitting a partition that does not fit LDS.
 WC_DEV uint32_t part_hash(const uint4 k) {
-  if (is_long_key(k)) return mix32(long_hash(long_ptr(k), long_len(k)));
-  return mix32((k.x ^ __builtin_amdgcn_alignbit(k.y, k.y, 21)) +
-               (k.z ^ __builtin_amdgcn_alignbit(k.w, k.w, 13)));
+  const uint32_t s = (k.x ^ __builtin_amdgcn_alignbit(k.y, k.y, 21)) +
+                     (k.z ^ __builtin_amdgcn_alignbit(k.w, k.w, 13));
+  return mix32(is_long_key(k) ? k.z ^ __builtin_amdgcn_alignbit(k.w, k.w, 13) : s);
 }
-WC_DEV uint32_t long_place(uint32_t h) { return (h ^ (h >> 15)) * 0x9E3779B1u; }
 
+// Folded bytes of two words of n > 16 bytes, eight at a time (the last eight overlap the ones
+// before, so nothing past a word is read).
+WC_DEV bool long_same(const uint8_t* a, const uint8_t* b, uint64_t n) {
+  if (a == b) return true;
+  uint64_t i = 0;
+  while (true) {
+    uint32_t x[2], y[2], f;
+    __builtin_memcpy(x, a + i, 8);
+    __builtin_memcpy(y, b + i, 8);
+    if (fold_classify4(x[0], &f) != fold_classify4(y[0], &f) ||
+        fold_classify4(x[1], &f) != fold_classify4(y[1], &f))
+      return false;
+    if (i + 8 >= n) return true;
+    i = min(i + 8, n - 8);
+  }
+}
 WC_DEV bool same_key(const uint4 a, const uint4 b) {
   if (key_eq(a, b)) return true;
-  return is_long_key(a) && a.z == b.z && a.w == b.w && long_equal(long_ptr(a), long_ptr(b), long_len(a));
+  return is_long_key(a) && a.z == b.z && a.w == b.w && long_same(long_ptr(a), long_ptr(b), a.z);
 }
 
 // Adds n occurrences of a key, with an entry made for it when it has none. `mine`: an entry
@@ -218,7 +234,7 @@ WC_DEV uint64_t block_scan64(uint64_t v, uint64_t* s_tmp, uint64_t* total) {
 }
 
 WC_DEV uint64_t key_len(const uint4 k) {
-  if (is_long_key(k)) return long_len(k);
+  if (is_long_key(k)) return k.z;
   return packed_len((uint64_t)k.x | ((uint64_t)k.y << 32), (uint64_t)k.z | ((uint64_t)k.w << 32));
 }
 
@@ -429,9 +445,8 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     const uint64_t limit = len ? start + len : doc_limit(start);
     uint64_t lo, hi, h64;
     const uint64_t m = scan_word(P.corpus, start, limit, &lo, &hi, &h64);
-    const uint4 k = m > 16 ? long_key(P.corpus + start, m) : key4(lo, hi);
-    const uint32_t h = m > 16 ? long_place((uint32_t)(h64 ^ (h64 >> 32))) : red_hash(k);
-    if (!part_add(T, k, h, 1, kNone)) over = true;
+    const uint4 k = m > 16 ? long_key(P.corpus + start, m, h64) : key4(lo, hi);
+    if (!part_add(T, k, place_hash(k), 1, kNone)) over = true;
   };
 
   while (true) {
@@ -575,11 +590,17 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         if (hit) atomicAdd(&T.cnt[e2[x] & 0x1fffu], 1u);
         f2[x] = f2[x] && !hit;
       }
-      // the new words, one token of the lanes at a time: the lookup is repeated by part_add when
-      // the first token's insertions took the slot this one saw free
+      // the new words, one token of the lanes at a time (the second token's values move to the
+      // first's: an index into the pairs would put them in scratch memory)
 #pragma unroll 1
-      for (int x = 0; x < 2; ++x)
-        if (f2[x] && !part_add_new(T, key2[x], h2[x], 1, g2[x], e2[x])) over = true;
+      for (int x = 0; x < 2; ++x) {
+        if (f2[0] && !part_add_new(T, key2[0], h2[0], 1, g2[0], e2[0])) over = true;
+        f2[0] = f2[1];
+        key2[0] = key2[1];
+        h2[0] = h2[1];
+        g2[0] = g2[1];
+        e2[0] = e2[1];
+      }
       wave_sync();
     }
     if (i >= nsw && w0 >= n && i != kNone) {  // the run is done
@@ -709,8 +730,7 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
         const uint4 k = P.rec_key[r];
         const uint32_t c = P.rec_cnt[r];
         if (bits && ((part_hash(k) >> 8) & ((1u << bits) - 1)) != value) continue;
-        const uint32_t h = is_long_key(k) ? long_place(long_hash(long_ptr(k), long_len(k))) : red_hash(k);
-        if (!part_add(T, k, h, c, kNone)) s_full = 1;
+        if (!part_add(T, k, place_hash(k), c, kNone)) s_full = 1;
       }
       __syncthreads();
     }
