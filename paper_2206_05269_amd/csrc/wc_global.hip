@@ -618,6 +618,7 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
   __shared__ uint4 s_lenmask[17];       // byte masks of word lengths 0..16
   __shared__ uint32_t s_bnd[NW][kBndWords];
   __shared__ uint32_t s_stat[4];
+  __shared__ unsigned long long s_tokens;
 
   const uint32_t D = P.dict_cap;
   uint8_t* s_txt = s_dyn;                                       // [NW][kStripeText]
@@ -653,6 +654,7 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
   for (uint32_t i = tid; i < NW * kBndWords; i += BLOCK) (&s_bnd[0][0])[i] = 0;
   for (uint32_t i = tid; i < NW * kWaveStarts; i += BLOCK) s_pairs[i] = 0;
   if (tid < 4) s_stat[tid] = 0;
+  if (tid == 0) s_tokens = 0;
   __syncthreads();
 
   // This workgroup's j-th block of partition p is block k = w * J + j (J = S / G blocks each).
@@ -944,9 +946,10 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
   for (uint32_t i = tid; i < nd; i += BLOCK) P.dict_part[(uint64_t)blockIdx.x * D + i] = s_cnt[i];
   if (spilled) atomicAdd(&s_stat[0], spilled);
   if (direct) atomicAdd(&s_stat[1], direct);
-  if (lane == 0 && tokens) add64(&hdr->total_tokens, tokens);
+  if (lane == 0 && tokens) atomicAdd(&s_tokens, (unsigned long long)tokens);
   __syncthreads();
   if (tid == 0) {
+    add64(&hdr->total_tokens, s_tokens);
     if (s_stat[0]) add64(&hdr->stat[0], s_stat[0]);
     if (s_stat[1]) add64(&hdr->stat[1], s_stat[1]);
   }

@@ -37,18 +37,14 @@ constexpr uint32_t kEnds = kStripe / 32 + 2; // word-end bitmap of a stripe and 
 constexpr uint32_t kListWords = kRound / 2 + kEnds;
 constexpr uint32_t kNone = 0xffffffffu;
 
-// Entries a map table hands out before its words leave: a wave looks at the number of entries
-// before every round, in which it takes at most kRound more, so the table never runs out.
-constexpr uint32_t kMapFull = kPartMapEntries - kWaves * kRound;
 constexpr uint32_t kPerThread = (kPartMapEntries + kBlk - 1) / kBlk;
 
 // A word of at most 16 bytes is its packed bytes; a longer one the address of an occurrence, its
 // length (below 2^32) and 24 bits of its hash under a top byte of 0xff, which no word byte of
 // either tokeniser is. (With the hash in the key a long word is read again only to be compared
 // with one of the same length and hash.)
-WC_DEV uint4 long_key(const uint8_t* p, uint64_t n, uint64_t fnv) {
-  const uint32_t h = (uint32_t)(fnv ^ (fnv >> 32));
-  return key4((uint64_t)(uintptr_t)p, (n & 0xffffffffull) | ((uint64_t)(h ^ (h >> 24)) << 32) | (0xffull << 56));
+WC_DEV uint4 long_key(const uint8_t* p, uint32_t n, uint32_t h) {
+  return key4((uint64_t)(uintptr_t)p, n | ((uint64_t)((h ^ (h >> 24)) & 0xffffffu) << 32) | (0xffull << 56));
 }
 WC_DEV bool is_long_key(const uint4 k) { return (k.w >> 24) == 0xffu; }
 WC_DEV const uint8_t* long_ptr(const uint4 k) {
@@ -75,20 +71,64 @@ WC_DEV uint32_t part_hash(const uint4 k) {
   return mix32(is_long_key(k) ? k.z ^ __builtin_amdgcn_alignbit(k.w, k.w, 13) : s);
 }
 
-// Folded bytes of two words of n > 16 bytes, eight at a time (the last eight overlap the ones
-// before, so nothing past a word is read).
-WC_DEV bool long_same(const uint8_t* a, const uint8_t* b, uint64_t n) {
+// Hash of a long word: its folded bytes four at a time, the last ones zero padded.
+WC_DEV uint32_t long_step(uint32_t h, uint32_t d) {
+  h = (h ^ d) * 0x9E3779B1u;
+  return h ^ (h >> 15);
+}
+// the same of a word in device memory
+WC_DEV uint32_t long_hash(const uint8_t* p, uint32_t n) {
+  uint32_t h = n, i = 0, f;
+  for (; i + 16 <= n; i += 16) {
+    uint32_t d[4];
+    __builtin_memcpy(d, p + i, 16);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) h = long_step(h, fold_classify4(d[j], &f));
+  }
+  for (; i < n; i += 4) {
+    uint32_t d = 0;
+    for (uint32_t q = 0; q < 4 && i + q < n; ++q) d |= (uint32_t)p[i + q] << (8 * q);
+    h = long_step(h, fold_classify4(d, &f));
+  }
+  return h;
+}
+// Length of the word at position s of the text that ends at `end` at the latest.
+WC_DEV uint64_t long_len(const uint8_t* corpus, uint64_t len, uint64_t s, uint64_t end) {
+  uint64_t p = s;
+  while (p < end) {
+    // up to 64 bytes at once, from the 16-byte block holding p on
+    const int64_t a = (int64_t)p - (int64_t)((uintptr_t)(corpus + p) & 15);
+    uint32_t m[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) classify16(load_text16(corpus, len, a + 16 * j), &m[j]);
+    uint64_t w = (uint64_t)(m[0] | (m[1] << 16)) | ((uint64_t)(m[2] | (m[3] << 16)) << 32);
+    const uint32_t k = (uint32_t)((int64_t)p - a);
+    w = ~w >> k;  // first delimiter from p on
+    if (w) return min(p + (uint64_t)__ffsll((unsigned long long)w) - 1, end) - s;
+    p += 64 - k;
+  }
+  return end - s;
+}
+
+// Two words of n > 16 bytes: compared 32 bytes at a time, from both ends of what is left so that
+// nothing past a word is read and all loads of a step are in flight together.
+WC_DEV bool long_same(const uint8_t* a, const uint8_t* b, uint32_t n) {
   if (a == b) return true;
-  uint64_t i = 0;
   while (true) {
-    uint32_t x[2], y[2], f;
-    __builtin_memcpy(x, a + i, 8);
-    __builtin_memcpy(y, b + i, 8);
-    if (fold_classify4(x[0], &f) != fold_classify4(y[0], &f) ||
-        fold_classify4(x[1], &f) != fold_classify4(y[1], &f))
-      return false;
-    if (i + 8 >= n) return true;
-    i = min(i + 8, n - 8);
+    uint32_t x[8], y[8], f, d = 0;
+    const uint32_t tail = n < 32 ? n - 16 : 16;
+    __builtin_memcpy(x, a, 16);
+    __builtin_memcpy(y, b, 16);
+    __builtin_memcpy(x + 4, a + tail, 16);
+    __builtin_memcpy(y + 4, b + tail, 16);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) d |= fold_classify4(x[j], &f) ^ fold_classify4(y[j], &f);
+    if (d) return false;
+    if (n <= 32) return true;
+    const uint32_t step = min(32u, n - 16);  // (the next 16 bytes at least are the word's)
+    a += step;
+    b += step;
+    n -= step;
   }
 }
 WC_DEV bool same_key(const uint4 a, const uint4 b) {
@@ -96,15 +136,18 @@ WC_DEV bool same_key(const uint4 a, const uint4 b) {
   return is_long_key(a) && a.z == b.z && a.w == b.w && long_same(long_ptr(a), long_ptr(b), a.z);
 }
 
-// Adds n occurrences of a key, with an entry made for it when it has none. `mine`: an entry
-// already taken for this key whose slot another key got (kNone: none). False: no entry or slot.
-// The table is the tag-slot table of wc_stripe.h; an entry's key and zero count are written
-// before its slot is claimed (a wave's LDS accesses are in order), so entries need no clearing.
-// Every iteration counts the key, loses a slot of the group to another key (at most four
-// times) or moves to the next of 16 groups.
+// ---- the LDS table -----------------------------------------------------------------------
+// The tag-slot table of wc_stripe.h. An entry's key and count are written before its slot is
+// claimed (a wave's LDS accesses are in order), so a claimed slot shows its key and entries need
+// no clearing; an entry whose key turned out to have another keeps count 0.
+
+// A key that table_add could not place in its first two groups, with an entry already taken for
+// it. Every iteration finds the key, claims a slot, loses a slot of the group to another key (at
+// most four times) or moves to the next group. (At 5,120 entries in 8,192 slots a run of 16 full
+// groups is met about once in a million groups, which is several times in a text of 64 MB.)
 WC_DEV bool part_add(const RedTable& T, const uint4 want, uint32_t h, uint32_t n, uint32_t mine) {
   constexpr uint32_t kGroups = kRedSlots / 4;
-  const uint32_t tag = red_tag(h), lane = threadIdx.x & 63;
+  const uint32_t tag = red_tag(h);
   uint32_t g = red_group(h), probe = 0;
   bool active = true, ok = false;
   while (__any(active)) {
@@ -128,88 +171,188 @@ WC_DEV bool part_add(const RedTable& T, const uint4 want, uint32_t h, uint32_t n
         }
       }
       if (found) {
+        T.cnt[mine] = 0;
         ok = true;
         active = false;
       } else if (free_j >= 0) {
         claim = true;
       } else {
         g = (g + 1) & (kGroups - 1);
-        if (++probe >= 16) active = false;
-      }
-    }
-    const bool need = claim && mine == kNone;
-    const uint64_t nm = __ballot(need);
-    if (nm) {
-      const uint32_t leader = (uint32_t)__ffsll((unsigned long long)nm) - 1;
-      uint32_t base = 0;
-      if (lane == leader) base = atomicAdd(T.n, (uint32_t)__popcll(nm));
-      base = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)leader);
-      if (need) {
-        const uint32_t m = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32),
-                                                            __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u));
-        if (m < T.cap) {
-          mine = m;
-          T.key[m] = want;
-          T.cnt[m] = 0;
-        } else {
-          claim = false;
-          active = false;
-        }
+        if (++probe >= kGroups) active = false;  // (never: there are more slots than entries)
       }
     }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    if (claim) {
-      if (atomicCAS(&T.slot[g * 4 + free_j], 0u, (tag << 13) | mine) == 0) {
-        atomicAdd(&T.cnt[mine], n);
-        ok = true;
-        active = false;
-      }
+    if (claim && atomicCAS(&T.slot[g * 4 + free_j], 0u, (tag << 13) | mine) == 0) {
+      ok = true;
+      active = false;
     }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
   }
+  if (!ok) T.cnt[mine] = 0;
   return ok;
 }
 
-// Adds n occurrences of a key that was not found: s4 is its home group as it was read, `match`
-// the slot of another key with its tag there (0: none). The common case of a new word takes two
-// LDS round trips (an entry for every lane of the wave with one atomic, then its slot) instead
-// of part_add's loop; what it cannot settle goes there.
-WC_DEV bool part_add_new(const RedTable& T, const uint4 want, uint32_t h, uint32_t n, const uint4 s4,
-                         uint32_t match) {
-  const uint32_t tag = red_tag(h), lane = threadIdx.x & 63;
-  // claimed slots of a group are a prefix
-  const uint32_t used = (s4.x != 0) + (s4.y != 0) + (s4.z != 0) + (s4.w != 0);
-  const bool fresh = used < 4 && match == 0;
-  uint32_t mine = kNone;
-  bool done = false;
-  const uint64_t nm = __ballot(fresh);
-  if (nm) {
-    const uint32_t leader = (uint32_t)__ffsll((unsigned long long)nm) - 1;
-    uint32_t base = 0;
-    if (lane == leader) base = atomicAdd(T.n, (uint32_t)__popcll(nm));
-    base = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)leader);
-    const uint32_t m = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(nm >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)nm, 0u));
-    if (fresh && m < T.cap) {
-      mine = m;
-      T.key[m] = want;
-      T.cnt[m] = 0;
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      const uint32_t prev = atomicCAS(&T.slot[red_group(h) * 4 + used], 0u, (tag << 13) | m);
-      __atomic_signal_fence(__ATOMIC_SEQ_CST);
-      if (prev == 0) {
-        atomicAdd(&T.cnt[m], n);
-        done = true;
-      } else if ((prev >> 13) == tag) {  // most often the same new word in another lane
-        const uint32_t idx = prev & 0x1fffu;
-        if (key_eq(T.key[idx], want)) {
-          atomicAdd(&T.cnt[idx], n);
-          done = true;
-        }
+WC_DEV uint32_t pick4(const uint4 g, uint32_t tag) {  // the first slot with the tag, or 0
+  uint32_t m = 0u;
+  m = (g.w >> 13) == tag ? g.w : m;
+  m = (g.z >> 13) == tag ? g.z : m;
+  m = (g.y >> 13) == tag ? g.y : m;
+  m = (g.x >> 13) == tag ? g.x : m;
+  return m;
+}
+
+// Adds n[x] occurrences of key[x] (hash h[x]) for the lanes and x with f[x]; called by whole
+// waves. kNoRoom: the entries ran out and nothing was counted; kNoSlot: some key found no slot.
+//
+// Each LDS step is taken for all N keys of a lane before any is waited for: the home group, the
+// key of its first tag match, and, for the lanes whose home group is full without the key, the
+// same of the next group. Then the new keys of the whole wave take entries with one atomic and
+// claim slots from the first free one of their group on, where a lost claim's answer is the
+// slot's occupant: compared when its tag matches, passed by otherwise, without reading the
+// group again. (Before, each key of the lanes went through an entry, a claim and, for what was
+// left, the loop of part_add by itself: map of a 20 MB text 62 -> 55 us, of a 64 MB text 271 -> 181.)
+constexpr int kAdded = 0, kNoRoom = 1, kNoSlot = 2;
+template <int N>
+WC_DEV int table_add(const RedTable& T, const uint4 (&key)[N], const uint32_t (&h)[N],
+                     const uint32_t (&n)[N], const bool (&f)[N]) {
+  constexpr uint32_t kGroups = kRedSlots / 4;
+  const uint32_t lane = threadIdx.x & 63;
+  uint4 g[N], k[N];
+  uint32_t e[N], gi[N], tag[N];
+  bool hit[N], next[N];
+#pragma unroll
+  for (int x = 0; x < N; ++x) {
+    gi[x] = red_group(h[x]);
+    g[x] = ((const uint4*)T.slot)[gi[x]];
+  }
+#pragma unroll
+  for (int x = 0; x < N; ++x) pin(g[x]);
+#pragma unroll
+  for (int x = 0; x < N; ++x) {
+    tag[x] = red_tag(h[x]);
+    e[x] = pick4(g[x], tag[x]);
+    k[x] = T.key[e[x] & 0x1fffu];
+  }
+#pragma unroll
+  for (int x = 0; x < N; ++x) pin(k[x]);
+  bool more = false;
+#pragma unroll
+  for (int x = 0; x < N; ++x) {
+    const bool eq = key_eq(k[x], key[x]);
+    hit[x] = f[x] & (e[x] != 0) & eq;
+    next[x] = f[x] & (e[x] == 0) & (g[x].w != 0);  // (claimed slots of a group are a prefix)
+    more |= next[x];
+  }
+  if (__any(more)) {
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+      if (next[x]) {
+        gi[x] = (gi[x] + 1) & (kGroups - 1);
+        g[x] = ((const uint4*)T.slot)[gi[x]];
+        e[x] = pick4(g[x], tag[x]);
+        if (e[x] != 0) hit[x] = key_eq(T.key[e[x] & 0x1fffu], key[x]);
       }
     }
   }
-  return done || part_add(T, want, h, n, mine);
+  uint64_t mm[N];
+  uint32_t tot = 0;
+  bool miss[N];
+#pragma unroll
+  for (int x = 0; x < N; ++x) {
+    miss[x] = f[x] && !hit[x];
+    mm[x] = __ballot(miss[x]);
+    tot += (uint32_t)__popcll(mm[x]);
+  }
+  uint32_t base = 0;
+  if (tot) {
+    if (lane == 0) base = atomicAdd(T.n, tot);
+    base = (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+    if (base + tot > T.cap) {
+      // the entries taken stay unused (giving them back could take a later wave's from the end)
+      for (uint32_t i = base + lane; i < min(base + tot, T.cap); i += 64) T.cnt[i] = 0;
+      return kNoRoom;
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < N; ++x)
+    if (hit[x]) atomicAdd(&T.cnt[e[x] & 0x1fffu], n[x]);
+  if (tot == 0) return kAdded;
+  uint32_t mine[N], at[N];
+  bool act[N], any = false, slow = false;
+#pragma unroll
+  for (int x = 0; x < N; ++x) {
+    mine[x] = base + __builtin_amdgcn_mbcnt_hi((uint32_t)(mm[x] >> 32),
+                                               __builtin_amdgcn_mbcnt_lo((uint32_t)mm[x], 0u));
+    base += (uint32_t)__popcll(mm[x]);
+    const uint32_t used = (g[x].x != 0) + (g[x].y != 0) + (g[x].z != 0) + (g[x].w != 0);
+    at[x] = gi[x] * 4 + used;
+    if (miss[x]) {
+      T.key[mine[x]] = key[x];
+      T.cnt[mine[x]] = n[x];
+    }
+    act[x] = miss[x] && e[x] == 0 && used < 4;
+    any |= act[x];
+  }
+  __atomic_signal_fence(__ATOMIC_SEQ_CST);
+  while (__any(any)) {
+    any = false;
+    uint32_t prev[N];
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+      prev[x] = 0;
+      if (act[x]) prev[x] = atomicCAS(&T.slot[at[x]], 0u, (tag[x] << 13) | mine[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+      if (!act[x]) continue;
+      if (prev[x] == 0) {
+        act[x] = miss[x] = false;
+      } else {
+        const uint32_t idx = prev[x] & 0x1fffu;
+        if ((prev[x] >> 13) == tag[x]) {  // most often the same new word in another lane
+          if (key_eq(T.key[idx], key[x])) {
+            atomicAdd(&T.cnt[idx], n[x]);
+            T.cnt[mine[x]] = 0;
+            miss[x] = false;
+          }
+          act[x] = false;
+        } else if ((++at[x] & 3u) == 0) {
+          act[x] = false;
+        }
+      }
+      any |= act[x];
+    }
+  }
+#pragma unroll
+  for (int x = 0; x < N; ++x) slow |= miss[x];
+  bool ok = true;
+  if (__any(slow)) {
+    // (one copy of the loop: the values of the next x move to the first's place)
+    uint4 kk[N];
+    uint32_t hh[N], nn[N], mi[N];
+    bool ss[N];
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+      kk[x] = key[x];
+      hh[x] = h[x];
+      nn[x] = n[x];
+      mi[x] = mine[x];
+      ss[x] = miss[x];
+    }
+#pragma unroll 1
+    for (int x = 0; x < N; ++x) {
+      if (ss[0]) ok &= part_add(T, kk[0], hh[0], nn[0], mi[0]);
+#pragma unroll
+      for (int y = 0; y + 1 < N; ++y) {
+        kk[y] = kk[y + 1];
+        hh[y] = hh[y + 1];
+        nn[y] = nn[y + 1];
+        mi[y] = mi[y + 1];
+        ss[y] = ss[y + 1];
+      }
+    }
+  }
+  return __all(ok) ? kAdded : kNoSlot;
 }
 
 // Exclusive sums over the workgroup of a pair packed in 64 bits (no field overflows).
@@ -238,19 +381,42 @@ WC_DEV uint64_t key_len(const uint4 k) {
   return packed_len((uint64_t)k.x | ((uint64_t)k.y << 32), (uint64_t)k.z | ((uint64_t)k.w << 32));
 }
 
-// Every entry of the table with a count to the output arrays, in space reserved with one atomic
-// on the packed cursor (entries << 32 | bytes; the text is below 2^31 bytes). All threads.
-WC_DEV void export_table(const PartParams& P, const RedTable& T, uint64_t* s_tmp, uint64_t* s_base) {
+// The packed output cursor: partitions done << 55 | entries << 28 | word bytes (the text is below
+// 2^28 bytes, so both fit), so that one atomic reserves a partition's space and tells the last one
+// that it is the last.
+constexpr uint32_t kCurEntry = 28, kCurPart = 55;
+WC_DEV uint64_t cur_entries(uint64_t c) { return (c >> kCurEntry) & ((1ull << (kCurPart - kCurEntry)) - 1); }
+WC_DEV uint64_t cur_bytes(uint64_t c) { return c & ((1ull << kCurEntry) - 1); }
+
+// Totals and limits, once every entry has its place (one thread): cursor c with all partitions in.
+WC_DEV void finish_output(const PartParams& P, uint64_t c) {
+  const uint64_t n = cur_entries(c), b = cur_bytes(c);
+  P.hdr->n_entries = n;
+  P.hdr->word_bytes = b;
+  if (n <= P.slots) P.word_offsets[n] = b;
+  if (n > P.occ_limit) or32(&P.hdr->flags, kFlagTableFull);
+  if (b > P.word_cap) or32(&P.hdr->flags, kFlagWordCap);
+}
+
+// Every entry of the table with a count to the output arrays; `last`: nothing of this partition
+// comes after. All threads.
+WC_DEV void export_table(const PartParams& P, const RedTable& T, bool last, uint32_t parts,
+                         uint64_t* s_tmp, uint64_t* s_base) {
   const uint32_t tid = threadIdx.x, ne = min(*T.n, T.cap);
   uint64_t part = 0;
   for (uint32_t i = tid; i < ne; i += kBlk)
-    if (T.cnt[i]) part += (1ull << 32) + key_len(T.key[i]);
+    if (T.cnt[i]) part += (1ull << kCurEntry) + key_len(T.key[i]);
   uint64_t tot;
   const uint64_t at = block_scan64(part, s_tmp, &tot);
-  if (tid == 0) *s_base = tot ? atomicAdd((unsigned long long*)&P.hdr->out_cursor, (unsigned long long)tot) : 0ull;
+  if (tid == 0) {
+    if (last) tot += 1ull << kCurPart;
+    *s_base = atomicAdd((unsigned long long*)&P.hdr->out_cursor, (unsigned long long)tot);
+    const uint64_t now = *s_base + tot;
+    if (last && now >> kCurPart == parts) finish_output(P, now);
+  }
   __syncthreads();
   const uint64_t base = *s_base + at;
-  uint64_t e = base >> 32, b = base & 0xffffffffull;
+  uint64_t e = cur_entries(base), b = cur_bytes(base);
   for (uint32_t i = tid; i < ne; i += kBlk) {
     const uint32_t n = T.cnt[i];
     if (!n) continue;
@@ -283,16 +449,6 @@ WC_DEV void export_table(const PartParams& P, const RedTable& T, uint64_t* s_tmp
   __syncthreads();
 }
 
-// Totals and limits, once every entry has its place (one thread).
-WC_DEV void finish_output(const PartParams& P) {
-  const uint64_t c = ld_relaxed(&P.hdr->out_cursor), n = c >> 32, b = c & 0xffffffffull;
-  P.hdr->n_entries = n;
-  P.hdr->word_bytes = b;
-  if (n <= P.slots) P.word_offsets[n] = b;
-  if (n > P.occ_limit) or32(&P.hdr->flags, kFlagTableFull);
-  if (b > P.word_cap) or32(&P.hdr->flags, kFlagWordCap);
-}
-
 WC_DEV int64_t lane_value(int64_t v, uint32_t lane) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)lane);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), (int)lane);
@@ -315,7 +471,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   __shared__ uint32_t s_bnd[kWaves][kEnds];
   __shared__ uint4 s_lenmask[17];
   __shared__ uint32_t s_hist[kParts], s_start[kParts];
-  __shared__ uint32_t s_nent, s_done, s_scan[4];
+  __shared__ uint32_t s_nent, s_done, s_tokens, s_scan[4];
   __shared__ uint64_t s_tmp[kWaves], s_base;
   RedTable T;
   T.slot = (uint32_t*)s_dyn;
@@ -364,6 +520,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   if (tid == 0) {
     s_nent = 0;
     s_done = 0;
+    s_tokens = 0;
     if (kSingle) {
       *hdr = Header{};
       __threadfence();
@@ -436,17 +593,32 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
 
   uint32_t i = 0, n = 0, w0 = 0, start16 = 0, rank = 0;
   int64_t p0 = 0;
-  uint64_t tokens = 0;
+  uint32_t tokens = 0;
   bool over = false;  // a word found no room (this lane)
 
-  // one occurrence of a word that is not wholly staged, or longer than 16 bytes
-  auto long_token = [&](uint32_t s, uint32_t len) {
+  // Key of the word at staged byte s, longer than 16 bytes; len: its length, or 0 when its end is
+  // not within 32 bytes. Its bytes come from the staged text when its end is staged.
+  auto long_word = [&](uint32_t s, uint32_t len) -> uint4 {
+    const uint8_t* const p = P.corpus + (p0 + s);
+    for (uint32_t w = (s + 32) >> 5; !len && w < kEnds; ++w) {
+      uint32_t m = my_ends[w];
+      if (w == (s + 32) >> 5) m &= 0xffffffffu << (s & 31);
+      if (m) len = w * 32 + __ffs(m) - s;
+    }
+    if (len) {
+      const uint32_t* tw = (const uint32_t*)my_txt;
+      uint32_t h = len;
+      for (uint32_t i = 0; i < len; i += 4) {
+        const uint32_t at = s + i;
+        uint32_t d = __builtin_amdgcn_alignbyte(tw[(at >> 2) + 1], tw[at >> 2], at & 3);
+        if (len - i < 4) d &= (1u << (8 * (len - i))) - 1u;
+        h = long_step(h, d);
+      }
+      return long_key(p, len, h);
+    }
     const uint64_t start = (uint64_t)(p0 + s);
-    const uint64_t limit = len ? start + len : doc_limit(start);
-    uint64_t lo, hi, h64;
-    const uint64_t m = scan_word(P.corpus, start, limit, &lo, &hi, &h64);
-    const uint4 k = m > 16 ? long_key(P.corpus + start, m, h64) : key4(lo, hi);
-    if (!part_add(T, k, place_hash(k), 1, kNone)) over = true;
+    len = (uint32_t)long_len(P.corpus, P.len, start, max(doc_limit(start), start));
+    return long_key(p, len, long_hash(p, len));
   };
 
   while (true) {
@@ -506,10 +678,6 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         ++i;
         continue;
       }
-      if (!kSingle &&
-          (uint32_t)__builtin_amdgcn_readfirstlane(
-              (int)__hip_atomic_load(&s_nent, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) > kMapFull)
-        break;
       // -- a round: the starts of ranks [w0, w0 + kRound), two per lane
       {
         uint32_t m = start16, r = rank;
@@ -522,7 +690,6 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
       }
       wave_sync();
       const uint32_t nw = min(n - w0, kRound);
-      w0 += kRound;
       uint32_t s2[2], n2[2], e0[2], e1[2];
       bool f2[2];
       // (starts past nw are of earlier rounds: in range, not counted)
@@ -536,22 +703,17 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         n2[x] = __ffs(__builtin_amdgcn_alignbit(e1[x], e0[x], s2[x] & 31));  // 0: no end in 32
-        f2[x] = lane + 64 * x < nw && n2[x] - 1 < 16u;
+        f2[x] = lane + 64 * x < nw;
       }
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-        if (lane + 64 * x < nw && !f2[x]) {
-          long_token(s2[x], n2[x]);
-          wait_vmem();
-        }
       // each LDS step reads for both tokens before either waits (pin)
       PackSrc ps[2];
-      uint4 lm[2], key2[2], g2[2], k2[2];
-      uint32_t h2[2], e2[2];
+      uint4 lm[2], key2[2];
+      uint32_t h2[2];
+      const uint32_t one2[2] = {1u, 1u};
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
         ps[x] = pack_read(my_txt, s2[x]);
-        lm[x] = s_lenmask[f2[x] ? n2[x] : 1u];
+        lm[x] = s_lenmask[n2[x] - 1 < 16u ? n2[x] : 1u];
       }
 #pragma unroll
       for (int x = 0; x < 2; ++x) {
@@ -566,59 +728,39 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         h2[x] = red_hash(key2[x]);
       }
 #pragma unroll
-      for (int x = 0; x < 2; ++x) g2[x] = ((const uint4*)T.slot)[red_group(h2[x])];
-#pragma unroll
-      for (int x = 0; x < 2; ++x) pin(g2[x]);
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        const uint32_t tag = red_tag(h2[x]);
-        uint32_t m = 0u;
-        m = (g2[x].w >> 13) == tag ? g2[x].w : m;
-        m = (g2[x].z >> 13) == tag ? g2[x].z : m;
-        m = (g2[x].y >> 13) == tag ? g2[x].y : m;
-        m = (g2[x].x >> 13) == tag ? g2[x].x : m;
-        e2[x] = m;
-      }
-#pragma unroll
-      for (int x = 0; x < 2; ++x) k2[x] = T.key[e2[x] & 0x1fffu];
-#pragma unroll
-      for (int x = 0; x < 2; ++x) pin(k2[x]);
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        const bool eq = key_eq(k2[x], key2[x]);
-        const bool hit = f2[x] & (e2[x] != 0) & eq;
-        if (hit) atomicAdd(&T.cnt[e2[x] & 0x1fffu], 1u);
-        f2[x] = f2[x] && !hit;
-      }
-      // the new words, one token of the lanes at a time (the second token's values move to the
-      // first's: an index into the pairs would put them in scratch memory)
-#pragma unroll 1
-      for (int x = 0; x < 2; ++x) {
-        if (f2[0] && !part_add_new(T, key2[0], h2[0], 1, g2[0], e2[0])) over = true;
-        f2[0] = f2[1];
-        key2[0] = key2[1];
-        h2[0] = h2[1];
-        g2[0] = g2[1];
-        e2[0] = e2[1];
-      }
+      for (int x = 0; x < 2; ++x)
+        if (f2[x] && n2[x] - 1 >= 16u) {
+          key2[x] = long_word(s2[x], n2[x]);
+          h2[x] = place_hash(key2[x]);
+          wait_vmem();
+        }
+      const int r = table_add<2>(T, key2, h2, one2, f2);
+      if (r == kNoRoom && !kSingle) break;  // this round again when the table is empty
+      if (r != kAdded) over = true;
+      w0 += kRound;
       wave_sync();
     }
     if (i >= nsw && w0 >= n && i != kNone) {  // the run is done
       i = kNone;
       if (lane == 0) {
         atomicAdd(&s_done, 1u);
-        if (tokens) add64(&hdr->total_tokens, tokens);
+        atomicAdd(&s_tokens, (uint32_t)tokens);
       }
     }
     // ---- the table's words leave -------------------------------------------------------------
     __syncthreads();
     const bool end = s_done == kWaves;
+    // (one addition per workgroup: one per wave, 4,096 on one address, took about 40 us)
+    if (end && tid == 0) add64(&hdr->total_tokens, s_tokens);
     if (kSingle) {  // (a word that found no room sets kFlagArena below)
-      export_table(P, T, s_tmp, &s_base);
-      if (tid == 0) finish_output(P);
+      export_table(P, T, true, 1u, s_tmp, &s_base);
       break;
     }
     const uint32_t ne = min(s_nent, T.cap);
+    // room for all entries, those without a count too: the answer arrives while they are looked at
+    // (lists << 40 | records)
+    uint64_t got = 0;
+    if (tid == 0) got = atomicAdd((unsigned long long*)&hdr->arena_next, (1ull << 40) | ne);
     uint32_t at[kPerThread];  // partition << 16 | place in it
 #pragma unroll
     for (uint32_t x = 0; x < kPerThread; ++x) {
@@ -638,10 +780,8 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     }
     __syncthreads();
     if (tid == 0) {
-      const uint32_t tot = s_scan[0] + s_scan[1] + s_scan[2] + s_scan[3];
-      // lists << 40 | records
-      s_base = atomicAdd((unsigned long long*)&hdr->arena_next, (1ull << 40) | tot);
-      if ((s_base & ((1ull << 40) - 1)) + tot > P.cap_recs || (s_base >> 40) >= P.max_lists) {
+      s_base = got;
+      if ((got & ((1ull << 40) - 1)) + ne > P.cap_recs || (got >> 40) >= P.max_lists) {
         or32(&hdr->flags, kFlagArena);
         s_base = ~0ull;
       }
@@ -685,6 +825,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
 __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
   constexpr uint32_t kRows = 1024;
   constexpr uint32_t kMaxBits = 16;
+  constexpr int kRecs = 4;  // records of a thread read and added together
   extern __shared__ __align__(16) uint8_t s_dyn[];
   __shared__ uint32_t s_pre[kRows + 1], s_rec[kRows];
   __shared__ uint32_t s_nent, s_full;
@@ -721,16 +862,31 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
       if (tid == 0) s_pre[kRows] = (uint32_t)tot;
       __syncthreads();
       const uint32_t m = (uint32_t)tot;
-      for (uint32_t f = tid; f < m; f += kBlk) {
-        uint32_t lo = 0;  // the last list that starts at or before f and is not empty
+      for (uint32_t f0 = 0; f0 < m; f0 += kRecs * kBlk) {
+        uint4 k[kRecs];
+        uint32_t c[kRecs], h[kRecs], lo[kRecs];
+        bool use[kRecs];
+#pragma unroll
+        for (int x = 0; x < kRecs; ++x) lo[x] = 0;
 #pragma unroll
         for (uint32_t step = kRows / 2; step; step >>= 1)
-          if (s_pre[lo + step] <= f) lo += step;
-        const uint32_t r = s_rec[lo] + (f - s_pre[lo]);
-        const uint4 k = P.rec_key[r];
-        const uint32_t c = P.rec_cnt[r];
-        if (bits && ((part_hash(k) >> 8) & ((1u << bits) - 1)) != value) continue;
-        if (!part_add(T, k, place_hash(k), c, kNone)) s_full = 1;
+#pragma unroll
+          for (int x = 0; x < kRecs; ++x)  // the last list that starts at or before the record
+            if (s_pre[lo[x] + step] <= f0 + x * kBlk + tid) lo[x] += step;
+#pragma unroll
+        for (int x = 0; x < kRecs; ++x) {
+          const uint32_t f = f0 + x * kBlk + tid;
+          use[x] = f < m;
+          const uint32_t r = use[x] ? s_rec[lo[x]] + (f - s_pre[lo[x]]) : 0u;
+          k[x] = P.rec_key[r];
+          c[x] = P.rec_cnt[r];
+        }
+#pragma unroll
+        for (int x = 0; x < kRecs; ++x) {
+          h[x] = place_hash(k[x]);
+          if (bits) use[x] &= ((part_hash(k[x]) >> 8) & ((1u << bits) - 1)) == value;
+        }
+        if (f0 + (tid & ~63u) < m && table_add<kRecs>(T, k, h, c, use) != kAdded) s_full = 1;
       }
       __syncthreads();
     }
@@ -744,20 +900,14 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
       __syncthreads();
       continue;
     }
-    export_table(P, T, s_tmp, &s_base);
     // the next class: the other half of the smallest split whose first half this one ends
     while (bits && (value >> (bits - 1))) {
       --bits;
       value &= (1u << bits) - 1;
     }
+    export_table(P, T, bits == 0, gridDim.x, s_tmp, &s_base);
     if (bits == 0) break;
     value |= 1u << (bits - 1);
-  }
-  if (tid == 0) {
-    __threadfence();
-    const uint64_t done = __hip_atomic_fetch_add(&hdr->work_next, 1ull, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-    if (done + 1 == gridDim.x) finish_output(P);
   }
 }
 

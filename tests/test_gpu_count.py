@@ -537,18 +537,20 @@ def _partitioned_texts(n, seed):
     for j in range(4):
         w[:, j] = d[(i >> (5 * j)) & 31]
     yield "overflow", w.tobytes()[:n].ljust(n)
-    long = [b"x%d" % k * 9 for k in range(7)] + [b"q" * 17, b"Q" * 16, b"q" * 300, b"q" * 2000, b"s"]
+    long = [b"x%d" % k * 9 for k in range(7)] + [b"q" * 17, b"Q" * 16, b"q" * 300, b"q" * 2000, b"s",
+            b"Mixed'Case09" * 3, b"mixed'CASE09" * 3]
     yield "long", b" ".join(long[k] for k in rng.integers(0, len(long), n // 200 + 9)).ljust(n)[:n]
 
 
 @pytest.mark.parametrize("n", [1, 16, 17, 1023, 1024, 1025, 1040, 16_385, 49_152, 49_153, 70_001,
-                               300_007, 1_000_003])
+                               300_007, 1_000_003, 20_000_003])
 def test_partitioned_count(n):
     """Sizes around a lane, a stripe, a workgroup's first range and the one-workgroup limit, at
-    odd addresses, whole and cut into documents (tiny, empty, and at stripe edges)."""
+    odd addresses, whole and cut into documents (tiny, empty, and at stripe edges). The largest
+    gives every workgroup more distinct words than its table holds."""
     rng = np.random.default_rng(n)
     for name, text in _partitioned_texts(n, n + 1):
-        for shift, docs in ((0, 1), (11, 1), (5, n // 3 + 4)):
+        for shift, docs in ((0, 1), (11, 1), (5, n // 3 + 4))[2 if n > 2_000_000 else 0:]:
             if docs > 1 and n > 100_000:
                 docs = 5000
             edge = min(1024 - shift, n)
