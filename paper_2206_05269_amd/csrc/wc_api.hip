@@ -798,6 +798,13 @@ struct MergeLayout {
   uint64_t* woff;
   void* counts;
   uint8_t* words;
+  // through hash partitions (the arena shares the table's memory)
+  bool part;
+  uint32_t parts, max_lists;
+  uint64_t n;
+  uint4* rec_key;
+  uint64_t* rec_cnt;
+  uint2* dir;
 };
 
 bool tables_ok(const wc_result* const* t, uint32_t k) {
@@ -827,19 +834,38 @@ std::vector<MergeInput> merge_inputs(const wc_result* const* t, uint32_t k) {
 
 void layout_merge(const wc_result* const* t, uint32_t k, const wc_opts* o, void* ws,
                   MergeLayout* L) {
-  uint64_t n = 0, wb = 0;
+  uint64_t n = 0, wb = 0, lists = 0;
   for (uint32_t i = 0; i < k; ++i) {
     n += t[i]->n_entries;
     wb += t[i]->word_bytes;
+    lists += (t[i]->n_entries + kMergeSpan - 1) / kMergeSpan;
   }
   uint64_t S = o && o->table_slots ? o->table_slots : next_pow2(std::max<uint64_t>(4096, 2 * n));
   L->S = S;
   L->n_blocks = (S + kExportSpan - 1) / kExportSpan;
   L->word_cap = std::max<uint64_t>(o && o->word_bytes_cap ? o->word_bytes_cap : wb, 16);
   uint32_t cb = o ? o->count_bytes : 8;
+  // The packed output cursor and the record numbers have 32 bits; forced key collisions concern
+  // the device table.
+  L->part = n && n < (1ull << 32) && wb < (1ull << 32) && !(o && o->debug_hash_bits);
+  L->n = n;
+  L->parts = 16;  // a few thousand records per partition
+  while (L->parts < kParts && (uint64_t)L->parts * 4096 < n) L->parts *= 2;
+  L->max_lists = (uint32_t)std::max<uint64_t>(lists, 1);
+  auto arena = [&](void* at) {
+    Bump A(at);
+    L->rec_key = A.take<uint4>(n * 16);
+    L->rec_cnt = A.take<uint64_t>(n * 8);
+    L->dir = A.take<uint2>((uint64_t)L->parts * L->max_lists * 8);
+    return A.off;
+  };
+  uint64_t region = S * sizeof(Slot);
+  if (L->part) region = std::max(region, arena(nullptr));
   Bump B(ws);
   L->hdr = B.take<Header>(sizeof(Header));
-  L->table = B.take<Slot>(S * sizeof(Slot));
+  uint8_t* const mem = B.take<uint8_t>(region);
+  L->table = (Slot*)mem;
+  if (L->part && mem) arena(mem);
   L->bsum = B.take<uint64_t>(L->n_blocks * 16);
   L->woff = B.take<uint64_t>((S + 1) * 8);
   L->counts = B.take<uint8_t>(S * cb);
@@ -877,30 +903,58 @@ wc_status wc_merge(const wc_result* const* tables, uint32_t k, const wc_opts* op
   Timer tm;
   HIPCHK(tm.init(opts && (opts->debug_flags & WC_DEBUG_TIME)));
   if (tm.on) HIPCHK(hipEventRecord(tm.c, s));
-  HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));
-  HIPCHK(launch_fill_zero(L.table, L.S * sizeof(Slot), s));
   const uint64_t occ_limit = L.S - L.S / 8;
-  if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
   const std::vector<MergeInput> ins = merge_inputs(tables, k);
-  HIPCHK(launch_merge_insert(ins.data(), k, L.table, L.S - 1, occ_limit, km, L.hdr, nullptr, 1, s));
-  if (tm.on) HIPCHK(hipEventRecord(tm.b, s));
-  ExportParams E;
-  memset(&E, 0, sizeof(E));
-  E.table = L.table;
-  E.slots = L.S;
-  E.hdr = L.hdr;
-  E.block_sums = L.bsum;
-  E.n_blocks = L.n_blocks;
-  E.word_offsets = L.woff;
-  E.words = L.words;
-  E.word_cap = L.word_cap;
-  E.counts = L.counts;
-  E.count_bytes = cb;
-  E.count_bias = opts ? opts->debug_count_bias : 0;
-  HIPCHK(launch_export(E, s));
   Header h;
-  HIPCHK(hipMemcpyAsync(&h, L.hdr, sizeof(Header), hipMemcpyDeviceToHost, s));
-  HIPCHK(hipStreamSynchronize(s));
+  h.flags = kFlagArena;
+  if (L.part) {
+    PartParams P;
+    memset(&P, 0, sizeof(P));
+    P.hdr = L.hdr;
+    P.parts = L.parts;
+    P.max_lists = L.max_lists;
+    P.cap_recs = L.n;
+    P.rec_key = L.rec_key;
+    P.rec_cnt = L.rec_cnt;
+    P.dir = L.dir;
+    P.word_offsets = L.woff;
+    P.words = L.words;
+    P.counts = L.counts;
+    P.slots = L.S;
+    P.occ_limit = occ_limit;
+    P.word_cap = L.word_cap;
+    P.count_bias = opts ? opts->debug_count_bias : 0;
+    P.count_bytes = cb;
+    HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));
+    if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
+    HIPCHK(launch_part_merge(ins.data(), k, P, s));
+    if (tm.on) HIPCHK(hipEventRecord(tm.b, s));
+    HIPCHK(hipMemcpyAsync(&h, L.hdr, sizeof(Header), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+  }
+  if (h.flags & kFlagArena) {
+    HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));
+    HIPCHK(launch_fill_zero(L.table, L.S * sizeof(Slot), s));
+    if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
+    HIPCHK(launch_merge_insert(ins.data(), k, L.table, L.S - 1, occ_limit, km, L.hdr, nullptr, 1, s));
+    if (tm.on) HIPCHK(hipEventRecord(tm.b, s));
+    ExportParams E;
+    memset(&E, 0, sizeof(E));
+    E.table = L.table;
+    E.slots = L.S;
+    E.hdr = L.hdr;
+    E.block_sums = L.bsum;
+    E.n_blocks = L.n_blocks;
+    E.word_offsets = L.woff;
+    E.words = L.words;
+    E.word_cap = L.word_cap;
+    E.counts = L.counts;
+    E.count_bytes = cb;
+    E.count_bias = opts ? opts->debug_count_bias : 0;
+    HIPCHK(launch_export(E, s));
+    HIPCHK(hipMemcpyAsync(&h, L.hdr, sizeof(Header), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+  }
   memset(out, 0, sizeof(*out));
   out->n_entries = h.n_entries;
   uint64_t total = 0;

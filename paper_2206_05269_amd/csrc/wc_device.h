@@ -249,6 +249,40 @@ WC_DEV uint64_t scan_word(const uint8_t* corpus, uint64_t s, uint64_t limit, uin
   return n;
 }
 
+// The folded bytes of a word of 1..16 bytes at w, packed, read as the aligned dwords that hold them
+// (never a dword without a byte of the word). `end`: the end of the table's word bytes; a last
+// dword that would reach past it is read byte by byte.
+WC_DEV void load_packed(const uint8_t* w, uint32_t len, const uint8_t* end, uint64_t* plo,
+                        uint64_t* phi) {
+  const uint32_t sh = (uint32_t)((uintptr_t)w & 3u);
+  const uint32_t* p = (const uint32_t*)(w - sh);
+  uint32_t d[5];
+#pragma unroll
+  for (uint32_t j = 0; j < 5; ++j) {
+    d[j] = 0;
+    if (4 * j < sh + len) {
+      if ((const uint8_t*)(p + j + 1) <= end) {
+        d[j] = p[j];
+      } else {
+        for (uint32_t q = 0; q < 4; ++q) {
+          const uint8_t* x = (const uint8_t*)(p + j) + q;
+          if (x >= w && x < w + len) d[j] |= (uint32_t)*x << (8 * q);
+        }
+      }
+    }
+  }
+  uint64_t v[2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    uint32_t f, lo = __builtin_amdgcn_alignbyte(d[2 * x + 1], d[2 * x], sh);
+    uint32_t hi = __builtin_amdgcn_alignbyte(d[2 * x + 2], d[2 * x + 1], sh);
+    v[x] = (uint64_t)fold_classify4(lo, &f) | ((uint64_t)fold_classify4(hi, &f) << 32);
+  }
+  const uint32_t ka = len < 8 ? 64 - 8 * len : 0u;
+  *plo = (v[0] << ka) >> ka;
+  *phi = len <= 8 ? 0ull : len < 16 ? (v[1] << (128 - 8 * len)) >> (128 - 8 * len) : v[1];
+}
+
 // ---------------------------------------------------------------------------------------
 // global table insert
 // ---------------------------------------------------------------------------------------

@@ -105,6 +105,7 @@ hipError_t launch_global(const GlobalParams& P, hipEvent_t a, hipEvent_t b, hipS
 // partitioned global count (wc_part.hip)
 constexpr uint32_t kPartMapEntries = 5120;  // LDS entries of a map workgroup (20 bytes each)
 constexpr uint32_t kPartRedEntries = 5888;  // of a reduce workgroup
+constexpr uint32_t kPartMergeEntries = 5056;  // of a merge's reduce workgroup (24 bytes each)
 struct PartParams {
   const uint8_t* corpus;
   uint64_t len;
@@ -118,7 +119,7 @@ struct PartParams {
   uint32_t max_lists;
   uint64_t cap_recs;
   uint4* rec_key;            // [cap_recs] a word of a list ...
-  uint32_t* rec_cnt;         // [cap_recs] ... and its count in it
+  void* rec_cnt;             // [cap_recs] ... and its count in it (uint32_t; merge: uint64_t)
   uint2* dir;                // [parts][max_lists] first record and records of a list's partition
   uint64_t* word_offsets;    // [slots + 1]
   uint8_t* words;            // [word_cap]
@@ -248,9 +249,34 @@ struct MergeBatch {
   uint32_t first_block[kMergeInputs];
   uint32_t n;
 };
+// launch(batch, workgroups) for the inputs, kMergeInputs at a time, `span` entries per workgroup
+template <class Launch>
+hipError_t for_merge_batches(const MergeInput* in, uint32_t k, uint32_t span, Launch launch) {
+  for (uint32_t i = 0; i < k;) {
+    MergeBatch M;
+    uint64_t blocks = 0;
+    for (M.n = 0; i < k && M.n < kMergeInputs; ++i) {
+      const uint64_t nb = (in[i].n + span - 1) / span;
+      if (nb == 0) continue;
+      if (blocks + nb > 0x7fffffffull && M.n) break;
+      M.in[M.n] = in[i];
+      M.first_block[M.n++] = (uint32_t)blocks;
+      blocks += nb;
+    }
+    if (M.n == 0) continue;
+    const hipError_t e = launch(M, (uint32_t)blocks);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 hipError_t launch_merge_insert(const MergeInput* in, uint32_t k, Slot* table, uint64_t mask,
                                uint64_t occ_limit, uint64_t key_mask, Header* hdr,
                                uint64_t* joint_counts, uint32_t n_columns, hipStream_t s);
+
+// merge through hash partitions (wc_part.hip): the inputs' entries as records, then the reduce.
+// The header must be zero; arena for all entries (64-bit counts), a list per kMergeSpan of an input.
+constexpr uint32_t kMergeSpan = 4096;
+hipError_t launch_part_merge(const MergeInput* in, uint32_t k, const PartParams& P, hipStream_t s);
 
 // ---- dense reduce (the zero-padded keys x documents matrix) --------------------------------
 hipError_t launch_dense_keys(const MergeInput& in, Slot* table, uint64_t mask,

@@ -137,7 +137,20 @@ WC_DEV bool same_key(const uint4 a, const uint4 b) {
 }
 
 // ---- the LDS table -----------------------------------------------------------------------
-// The tag-slot table of wc_stripe.h. An entry's key and count are written before its slot is
+template <class C>
+struct PartTable {
+  uint32_t* slot;  // [kRedSlots], 0 = empty
+  uint4* key;      // [cap]
+  C* cnt;          // [cap]
+  uint32_t* n;     // entries handed out (may pass cap)
+  uint32_t cap;
+};
+WC_DEV void lds_add(uint32_t* p, uint32_t v) { atomicAdd(p, v); }
+WC_DEV void lds_add(uint64_t* p, uint64_t v) {
+  atomicAdd((unsigned long long*)p, (unsigned long long)v);
+}
+
+// The tag-slot table of wc_stripe.h (counts of type C). An entry's key and count are written before its slot is
 // claimed (a wave's LDS accesses are in order), so a claimed slot shows its key and entries need
 // no clearing; an entry whose key turned out to have another keeps count 0.
 
@@ -145,7 +158,8 @@ WC_DEV bool same_key(const uint4 a, const uint4 b) {
 // it. Every iteration finds the key, claims a slot, loses a slot of the group to another key (at
 // most four times) or moves to the next group. (At 5,120 entries in 8,192 slots a run of 16 full
 // groups is met about once in a million groups, which is several times in a text of 64 MB.)
-WC_DEV bool part_add(const RedTable& T, const uint4 want, uint32_t h, uint32_t n, uint32_t mine) {
+template <class C>
+WC_DEV bool part_add(const PartTable<C>& T, const uint4 want, uint32_t h, C n, uint32_t mine) {
   constexpr uint32_t kGroups = kRedSlots / 4;
   const uint32_t tag = red_tag(h);
   uint32_t g = red_group(h), probe = 0;
@@ -163,7 +177,7 @@ WC_DEV bool part_add(const RedTable& T, const uint4 want, uint32_t h, uint32_t n
         if ((e[j] >> 13) == tag) {
           const uint32_t idx = e[j] & 0x1fffu;
           if (same_key(T.key[idx], want)) {
-            atomicAdd(&T.cnt[idx], n);
+            lds_add(&T.cnt[idx], n);
             found = true;
           }
         } else if (e[j] == 0 && free_j < 0) {
@@ -212,9 +226,9 @@ WC_DEV uint32_t pick4(const uint4 g, uint32_t tag) {  // the first slot with the
 // group again. (Before, each key of the lanes went through an entry, a claim and, for what was
 // left, the loop of part_add by itself: map of a 20 MB text 62 -> 55 us, of a 64 MB text 271 -> 181.)
 constexpr int kAdded = 0, kNoRoom = 1, kNoSlot = 2;
-template <int N>
-WC_DEV int table_add(const RedTable& T, const uint4 (&key)[N], const uint32_t (&h)[N],
-                     const uint32_t (&n)[N], const bool (&f)[N]) {
+template <int N, class C>
+WC_DEV int table_add(const PartTable<C>& T, const uint4 (&key)[N], const uint32_t (&h)[N],
+                     const C (&n)[N], const bool (&f)[N]) {
   constexpr uint32_t kGroups = kRedSlots / 4;
   const uint32_t lane = threadIdx.x & 63;
   uint4 g[N], k[N];
@@ -275,7 +289,7 @@ WC_DEV int table_add(const RedTable& T, const uint4 (&key)[N], const uint32_t (&
   }
 #pragma unroll
   for (int x = 0; x < N; ++x)
-    if (hit[x]) atomicAdd(&T.cnt[e[x] & 0x1fffu], n[x]);
+    if (hit[x]) lds_add(&T.cnt[e[x] & 0x1fffu], n[x]);
   if (tot == 0) return kAdded;
   uint32_t mine[N], at[N];
   bool act[N], any = false, slow = false;
@@ -311,7 +325,7 @@ WC_DEV int table_add(const RedTable& T, const uint4 (&key)[N], const uint32_t (&
         const uint32_t idx = prev[x] & 0x1fffu;
         if ((prev[x] >> 13) == tag[x]) {  // most often the same new word in another lane
           if (key_eq(T.key[idx], key[x])) {
-            atomicAdd(&T.cnt[idx], n[x]);
+            lds_add(&T.cnt[idx], n[x]);
             T.cnt[mine[x]] = 0;
             miss[x] = false;
           }
@@ -329,7 +343,8 @@ WC_DEV int table_add(const RedTable& T, const uint4 (&key)[N], const uint32_t (&
   if (__any(slow)) {
     // (one copy of the loop: the values of the next x move to the first's place)
     uint4 kk[N];
-    uint32_t hh[N], nn[N], mi[N];
+    uint32_t hh[N], mi[N];
+    C nn[N];
     bool ss[N];
 #pragma unroll
     for (int x = 0; x < N; ++x) {
@@ -381,16 +396,18 @@ WC_DEV uint64_t key_len(const uint4 k) {
   return packed_len((uint64_t)k.x | ((uint64_t)k.y << 32), (uint64_t)k.z | ((uint64_t)k.w << 32));
 }
 
-// The packed output cursor: partitions done << 55 | entries << 28 | word bytes (the text is below
-// 2^28 bytes, so both fit), so that one atomic reserves a partition's space and tells the last one
-// that it is the last.
-constexpr uint32_t kCurEntry = 28, kCurPart = 55;
-WC_DEV uint64_t cur_entries(uint64_t c) { return (c >> kCurEntry) & ((1ull << (kCurPart - kCurEntry)) - 1); }
-WC_DEV uint64_t cur_bytes(uint64_t c) { return c & ((1ull << kCurEntry) - 1); }
+// The output cursor. Counting a text (below 2^28 bytes): partitions done << 55 | entries << 28 |
+// word bytes, so that one atomic reserves a partition's space and tells the last one that it is
+// the last. Merging tables (wide, below 2^32 entries and word bytes): entries << 32 | bytes, and the
+// partitions done are counted beside it.
+constexpr uint32_t kCurPart = 55;
+WC_DEV uint64_t cur_entries(uint64_t c, bool wide) {
+  return wide ? c >> 32 : (c >> 28) & ((1ull << (kCurPart - 28)) - 1);
+}
+WC_DEV uint64_t cur_bytes(uint64_t c, bool wide) { return c & (wide ? 0xffffffffull : 0xfffffffull); }
 
-// Totals and limits, once every entry has its place (one thread): cursor c with all partitions in.
-WC_DEV void finish_output(const PartParams& P, uint64_t c) {
-  const uint64_t n = cur_entries(c), b = cur_bytes(c);
+// Totals and limits, once every entry has its place (one thread).
+WC_DEV void finish_output(const PartParams& P, uint64_t n, uint64_t b) {
   P.hdr->n_entries = n;
   P.hdr->word_bytes = b;
   if (n <= P.slots) P.word_offsets[n] = b;
@@ -400,25 +417,32 @@ WC_DEV void finish_output(const PartParams& P, uint64_t c) {
 
 // Every entry of the table with a count to the output arrays; `last`: nothing of this partition
 // comes after. All threads.
-WC_DEV void export_table(const PartParams& P, const RedTable& T, bool last, uint32_t parts,
+template <bool kWide, class C>
+WC_DEV void export_table(const PartParams& P, const PartTable<C>& T, bool last, uint32_t parts,
                          uint64_t* s_tmp, uint64_t* s_base) {
   const uint32_t tid = threadIdx.x, ne = min(*T.n, T.cap);
-  uint64_t part = 0;
+  uint64_t part = 0;  // entries << 32 | bytes
   for (uint32_t i = tid; i < ne; i += kBlk)
-    if (T.cnt[i]) part += (1ull << kCurEntry) + key_len(T.key[i]);
+    if (T.cnt[i]) part += (1ull << 32) + key_len(T.key[i]);
   uint64_t tot;
   const uint64_t at = block_scan64(part, s_tmp, &tot);
   if (tid == 0) {
-    if (last) tot += 1ull << kCurPart;
-    *s_base = atomicAdd((unsigned long long*)&P.hdr->out_cursor, (unsigned long long)tot);
-    const uint64_t now = *s_base + tot;
-    if (last && now >> kCurPart == parts) finish_output(P, now);
+    const uint64_t tn = tot >> 32, tb = tot & 0xffffffffull;
+    unsigned long long* const cur = (unsigned long long*)&P.hdr->out_cursor;
+    if (kWide) {
+      *s_base = atomicAdd(cur, (unsigned long long)tot);
+    } else {
+      const uint64_t add = (last ? 1ull << kCurPart : 0ull) | (tn << 28) | tb;
+      *s_base = atomicAdd(cur, (unsigned long long)add);
+      const uint64_t now = *s_base + add;
+      if (last && now >> kCurPart == parts) finish_output(P, cur_entries(now, false), cur_bytes(now, false));
+    }
   }
   __syncthreads();
-  const uint64_t base = *s_base + at;
-  uint64_t e = cur_entries(base), b = cur_bytes(base);
+  uint64_t e = cur_entries(*s_base, kWide) + (at >> 32);
+  uint64_t b = cur_bytes(*s_base, kWide) + (at & 0xffffffffull);
   for (uint32_t i = tid; i < ne; i += kBlk) {
-    const uint32_t n = T.cnt[i];
+    const C n = T.cnt[i];
     if (!n) continue;
     const uint4 k = T.key[i];
     const uint64_t len = key_len(k);
@@ -447,6 +471,15 @@ WC_DEV void export_table(const PartParams& P, const RedTable& T, bool last, uint
     b += len;
   }
   __syncthreads();
+  if (kWide && last && tid == 0) {
+    __threadfence();
+    const uint64_t done = __hip_atomic_fetch_add(&P.hdr->work_next, 1ull, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT);
+    if (done + 1 == parts) {
+      const uint64_t c = ld_relaxed(&P.hdr->out_cursor);
+      finish_output(P, cur_entries(c, true), cur_bytes(c, true));
+    }
+  }
 }
 
 WC_DEV int64_t lane_value(int64_t v, uint32_t lane) {
@@ -473,13 +506,12 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   __shared__ uint32_t s_hist[kParts], s_start[kParts];
   __shared__ uint32_t s_nent, s_done, s_tokens, s_scan[4];
   __shared__ uint64_t s_tmp[kWaves], s_base;
-  RedTable T;
+  PartTable<uint32_t> T;
   T.slot = (uint32_t*)s_dyn;
   T.key = (uint4*)(T.slot + kRedSlots);
   T.cnt = (uint32_t*)(T.key + kPartMapEntries);
   T.n = &s_nent;
   T.cap = kPartMapEntries;
-  T.stall = nullptr;
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   uint8_t* const my_txt = (uint8_t*)(T.cnt + kPartMapEntries) + wv * kText;
@@ -753,7 +785,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     // (one addition per workgroup: one per wave, 4,096 on one address, took about 40 us)
     if (end && tid == 0) add64(&hdr->total_tokens, s_tokens);
     if (kSingle) {  // (a word that found no room sets kFlagArena below)
-      export_table(P, T, true, 1u, s_tmp, &s_base);
+      export_table<false>(P, T, true, 1u, s_tmp, &s_base);
       break;
     }
     const uint32_t ne = min(s_nent, T.cap);
@@ -803,7 +835,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         if (at[x] == kNone) continue;
         const uint32_t r = rec + s_start[at[x] >> 16] + (at[x] & 0xffffu);
         P.rec_key[r] = T.key[j];
-        P.rec_cnt[r] = T.cnt[j];
+        ((uint32_t*)P.rec_cnt)[r] = T.cnt[j];
       }
     }
     __syncthreads();
@@ -822,7 +854,11 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
 // of their records; a thread finds its record's list by a binary search in LDS. A partition
 // whose words do not fit the LDS table is summed in classes of its hash (two, four, ... classes,
 // each reading the records again), so that any number of distinct words is counted in LDS.
+template <class C>
+constexpr uint32_t kRedEntries = sizeof(C) == 4 ? kPartRedEntries : kPartMergeEntries;
+template <class C>
 __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
+  constexpr bool kWide = sizeof(C) == 8;
   constexpr uint32_t kRows = 1024;
   constexpr uint32_t kMaxBits = 16;
   constexpr int kRecs = 4;  // records of a thread read and added together
@@ -832,13 +868,12 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
   __shared__ uint64_t s_tmp[kWaves], s_base;
   Header* const hdr = P.hdr;
   if (ld_relaxed32(&hdr->flags) & (kFlagBadOffsets | kFlagArena)) return;
-  RedTable T;
+  PartTable<C> T;
   T.slot = (uint32_t*)s_dyn;
   T.key = (uint4*)(T.slot + kRedSlots);
-  T.cnt = (uint32_t*)(T.key + kPartRedEntries);
+  T.cnt = (C*)(T.key + kRedEntries<C>);
   T.n = &s_nent;
-  T.cap = kPartRedEntries;
-  T.stall = nullptr;
+  T.cap = kRedEntries<C>;
   const uint32_t tid = threadIdx.x;
   const uint32_t lists = (uint32_t)(hdr->arena_next >> 40);
   const uint2* dir = P.dir + (uint64_t)blockIdx.x * P.max_lists;
@@ -864,7 +899,8 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
       const uint32_t m = (uint32_t)tot;
       for (uint32_t f0 = 0; f0 < m; f0 += kRecs * kBlk) {
         uint4 k[kRecs];
-        uint32_t c[kRecs], h[kRecs], lo[kRecs];
+        uint32_t h[kRecs], lo[kRecs];
+        C c[kRecs];
         bool use[kRecs];
 #pragma unroll
         for (int x = 0; x < kRecs; ++x) lo[x] = 0;
@@ -879,7 +915,7 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
           use[x] = f < m;
           const uint32_t r = use[x] ? s_rec[lo[x]] + (f - s_pre[lo[x]]) : 0u;
           k[x] = P.rec_key[r];
-          c[x] = P.rec_cnt[r];
+          c[x] = ((const C*)P.rec_cnt)[r];
         }
 #pragma unroll
         for (int x = 0; x < kRecs; ++x) {
@@ -905,25 +941,120 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
       --bits;
       value &= (1u << bits) - 1;
     }
-    export_table(P, T, bits == 0, gridDim.x, s_tmp, &s_base);
+    export_table<kWide>(P, T, bits == 0, gridDim.x, s_tmp, &s_base);
     if (bits == 0) break;
     value |= 1u << (bits - 1);
   }
 }
 
+// ---------------------------------------------------------------------------------------
+// merge: entries of tables as records
+// ---------------------------------------------------------------------------------------
+// A workgroup makes one list of kMergeSpan entries of one input: their words are packed, ranked
+// inside their partition with one LDS atomic each and written as records (64-bit counts: those of
+// the inputs may be wide). Words are not summed here: a (document, word) table holds a word once
+// per document, so a few documents' entries hardly repeat.
+//
+// Adding every entry to one device table instead took 374 us for the tables of 2,000 documents
+// (1.4 million entries of 50,000 words): the frequent words are in every document, and their
+// slots were hit 2,000 times each. The whole merge of them: 491 -> 86 us (map 30, reduce 29).
+__global__ __launch_bounds__(kBlk) void part_merge_kernel(MergeBatch M, PartParams P) {
+  constexpr uint32_t kMine = kMergeSpan / kBlk;
+  __shared__ uint32_t s_hist[kParts], s_start[kParts], s_scan[4];
+  __shared__ uint64_t s_base;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  uint32_t x = 0;
+  while (x + 1 < M.n && M.first_block[x + 1] <= blockIdx.x) ++x;
+  const MergeInput& in = M.in[x];
+  const uint64_t first = (uint64_t)(blockIdx.x - M.first_block[x]) * kMergeSpan;
+  if (tid < kParts) s_hist[tid] = 0;
+  uint64_t got = 0;
+  if (tid == 0) {
+    const uint64_t n = min((uint64_t)kMergeSpan, in.n - first);
+    got = atomicAdd((unsigned long long*)&P.hdr->arena_next, (1ull << 40) | n);
+    s_base = got;
+    if ((got & ((1ull << 40) - 1)) + n > P.cap_recs || (got >> 40) >= P.max_lists) {
+      or32(&P.hdr->flags, kFlagArena);
+      s_base = ~0ull;
+    }
+  }
+  uint4 k[kMine];
+  uint64_t c[kMine];
+  uint32_t at[kMine];
+  const uint8_t* const end = in.words + in.word_offsets[in.n];
+#pragma unroll
+  for (uint32_t j = 0; j < kMine; ++j) {
+    const uint64_t e = first + j * kBlk + tid;
+    c[j] = 0;
+    k[j] = make_uint4(0, 0, 0, 0);
+    if (e < in.n) {
+      const uint64_t a = in.word_offsets[e], len = in.word_offsets[e + 1] - a;
+      c[j] = in.count_bytes == 4 ? (uint64_t)(int64_t)((const int32_t*)in.counts)[e]
+                                 : (uint64_t)((const int64_t*)in.counts)[e];
+      const uint8_t* w = in.words + a;
+      if (len == 0) {
+        c[j] = 0;
+      } else {
+        uint64_t lo = 0, hi = 0xffull << 56;
+        if (len <= 16) load_packed(w, (uint32_t)len, end, &lo, &hi);
+        k[j] = key4(lo, hi);
+        if (is_long_key(k[j])) k[j] = long_key(w, (uint32_t)len, long_hash(w, (uint32_t)len));
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t j = 0; j < kMine; ++j) {
+    at[j] = kNone;
+    if (c[j]) {
+      const uint32_t p = part_hash(k[j]) & (P.parts - 1);
+      at[j] = (p << 16) | atomicAdd(&s_hist[p], 1u);
+    }
+  }
+  __syncthreads();
+  uint32_t cnt = 0, incl = 0;
+  if (tid < kParts) {
+    cnt = s_hist[tid];
+    incl = wave_incl_scan(cnt);
+    if (lane == 63) s_scan[wv] = incl;
+  }
+  __syncthreads();
+  if (tid < kParts) {
+    uint32_t b = incl - cnt;
+    for (uint32_t w = 0; w < 4; ++w) b += w < wv ? s_scan[w] : 0u;
+    s_start[tid] = b;
+  }
+  __syncthreads();
+  if (s_base == ~0ull) return;
+  const uint64_t list = s_base >> 40;
+  const uint32_t rec = (uint32_t)(s_base & ((1ull << 40) - 1));
+  if (tid < P.parts) P.dir[(uint64_t)tid * P.max_lists + list] = make_uint2(rec + s_start[tid], cnt);
+#pragma unroll
+  for (uint32_t j = 0; j < kMine; ++j) {
+    if (at[j] == kNone) continue;
+    const uint32_t r = rec + s_start[at[j] >> 16] + (at[j] & 0xffffu);
+    P.rec_key[r] = k[j];
+    ((uint64_t*)P.rec_cnt)[r] = c[j];
+  }
+}
+
 size_t part_map_dyn() { return (size_t)kRedSlots * 4 + (size_t)kPartMapEntries * 20 + kWaves * kText; }
-size_t part_reduce_dyn() { return (size_t)kRedSlots * 4 + (size_t)kPartRedEntries * 20; }
+template <class C>
+size_t part_reduce_dyn() { return (size_t)kRedSlots * 4 + (size_t)kRedEntries<C> * (16 + sizeof(C)); }
 
 hipError_t set_part_smem() {
-  hipError_t e = hipFuncSetAttribute((const void*)part_map_kernel<false>,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)part_map_dyn());
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)part_map_kernel<true>,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)part_map_dyn());
-  if (e == hipSuccess)
-    e = hipFuncSetAttribute((const void*)part_reduce_kernel,
-                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)part_reduce_dyn());
-  return e;
+  static const hipError_t once = [] {
+    const struct { const void* f; size_t dyn; } k[4] = {
+        {(const void*)part_map_kernel<false>, part_map_dyn()},
+        {(const void*)part_map_kernel<true>, part_map_dyn()},
+        {(const void*)part_reduce_kernel<uint32_t>, part_reduce_dyn<uint32_t>()},
+        {(const void*)part_reduce_kernel<uint64_t>, part_reduce_dyn<uint64_t>()}};
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < 4 && e == hipSuccess; ++i)
+      e = hipFuncSetAttribute(k[i].f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k[i].dyn);
+    return e;
+  }();
+  return once;
 }
 
 hipError_t launch_part_map(const PartParams& P, uint32_t grid, hipStream_t s) {
@@ -935,7 +1066,21 @@ hipError_t launch_part_single(const PartParams& P, hipStream_t s) {
   return hipGetLastError();
 }
 hipError_t launch_part_reduce(const PartParams& P, hipStream_t s) {
-  hipLaunchKernelGGL(part_reduce_kernel, dim3(P.parts), dim3(kBlk), part_reduce_dyn(), s, P);
+  hipLaunchKernelGGL(part_reduce_kernel<uint32_t>, dim3(P.parts), dim3(kBlk),
+                     part_reduce_dyn<uint32_t>(), s, P);
+  return hipGetLastError();
+}
+
+hipError_t launch_part_merge(const MergeInput* in, uint32_t k, const PartParams& P, hipStream_t s) {
+  hipError_t e = set_part_smem();
+  if (e != hipSuccess) return e;
+  e = for_merge_batches(in, k, kMergeSpan, [&](const MergeBatch& M, uint32_t blocks) {
+    hipLaunchKernelGGL(part_merge_kernel, dim3(blocks), dim3(kBlk), 0, s, M, P);
+    return hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(part_reduce_kernel<uint64_t>, dim3(P.parts), dim3(kBlk),
+                     part_reduce_dyn<uint64_t>(), s, P);
   return hipGetLastError();
 }
 

@@ -265,40 +265,6 @@ hipError_t launch_export(const ExportParams& E, hipStream_t s) {
 // ------------------------------------------------------------------------------------------
 // merge: insert the entries of one table
 // ------------------------------------------------------------------------------------------
-// The folded bytes of a word of 1..16 bytes at w, packed, read as the aligned dwords that hold them
-// (never a dword without a byte of the word). `end`: the end of the table's word bytes; a last
-// dword that would reach past it is read byte by byte.
-WC_DEV void load_packed(const uint8_t* w, uint32_t len, const uint8_t* end, uint64_t* plo,
-                        uint64_t* phi) {
-  const uint32_t sh = (uint32_t)((uintptr_t)w & 3u);
-  const uint32_t* p = (const uint32_t*)(w - sh);
-  uint32_t d[5];
-#pragma unroll
-  for (uint32_t j = 0; j < 5; ++j) {
-    d[j] = 0;
-    if (4 * j < sh + len) {
-      if ((const uint8_t*)(p + j + 1) <= end) {
-        d[j] = p[j];
-      } else {
-        for (uint32_t q = 0; q < 4; ++q) {
-          const uint8_t* x = (const uint8_t*)(p + j) + q;
-          if (x >= w && x < w + len) d[j] |= (uint32_t)*x << (8 * q);
-        }
-      }
-    }
-  }
-  uint64_t v[2];
-#pragma unroll
-  for (int x = 0; x < 2; ++x) {
-    uint32_t f, lo = __builtin_amdgcn_alignbyte(d[2 * x + 1], d[2 * x], sh);
-    uint32_t hi = __builtin_amdgcn_alignbyte(d[2 * x + 2], d[2 * x + 1], sh);
-    v[x] = (uint64_t)fold_classify4(lo, &f) | ((uint64_t)fold_classify4(hi, &f) << 32);
-  }
-  const uint32_t ka = len < 8 ? 64 - 8 * len : 0u;
-  *plo = (v[0] << ka) >> ka;
-  *phi = len <= 8 ? 0ull : len < 16 ? (v[1] << (128 - 8 * len)) >> (128 - 8 * len) : v[1];
-}
-
 // Adds the entries of up to kMergeInputs tables to one table; block b belongs to the input
 // whose first_block is the last one at or before it. (One launch per table cost a merge of 96
 // small tables 96 launches of about 10 us each, most of them with a handful of workgroups.)
@@ -333,22 +299,11 @@ __global__ __launch_bounds__(256) void merge_insert_kernel(MergeBatch M, Slot* t
 hipError_t launch_merge_insert(const MergeInput* in, uint32_t k, Slot* table, uint64_t mask,
                                uint64_t occ_limit, uint64_t key_mask, Header* hdr,
                                uint64_t* joint_counts, uint32_t n_columns, hipStream_t s) {
-  for (uint32_t i = 0; i < k;) {
-    MergeBatch M;
-    uint64_t blocks = 0;
-    for (M.n = 0; i < k && M.n < kMergeInputs; ++i) {
-      const uint64_t nb = (in[i].n + 255) / 256;
-      if (nb == 0) continue;
-      if (blocks + nb > 0x7fffffffull && M.n) break;
-      M.in[M.n] = in[i];
-      M.first_block[M.n++] = (uint32_t)blocks;
-      blocks += nb;
-    }
-    if (M.n == 0) continue;
-    hipLaunchKernelGGL(merge_insert_kernel, dim3((uint32_t)blocks), dim3(256), 0, s, M, table,
-                       mask, occ_limit, key_mask, hdr, joint_counts, n_columns);
-  }
-  return hipGetLastError();
+  return for_merge_batches(in, k, 256, [&](const MergeBatch& M, uint32_t blocks) {
+    hipLaunchKernelGGL(merge_insert_kernel, dim3(blocks), dim3(256), 0, s, M, table, mask,
+                       occ_limit, key_mask, hdr, joint_counts, n_columns);
+    return hipGetLastError();
+  });
 }
 
 // ------------------------------------------------------------------------------------------

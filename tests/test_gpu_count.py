@@ -752,6 +752,31 @@ def test_dense_reduce_matches_merge_and_oracle():
     assert e.value.status == wc.WC_EOVERFLOW
 
 
+def test_merge_partitions():
+    """The merge's hash partitions: 70 tables (more than one launch holds) of 0, 1 and thousands of
+    entries, long words under different foldings, 32- and 64-bit counts that add up past 2^32,
+    and 2.1 million distinct words (more than the partitions' LDS tables hold at once)."""
+    rng = np.random.default_rng(5)
+    big = 3 << 30
+    tabs, want = [], collections.Counter()
+    for i in range(70):
+        n = (0, 1, 40, 4097, 9000)[i % 5]
+        words = [b"W%x" % x if x % 7 else b"Very'Long" * 3 + b"%x" % x for x in rng.integers(0, 6000, n)]
+        text = b" ".join(words)
+        wide = i % 3 == 0
+        tabs.append(gpu_count(text, count_bytes=8 if wide else 4, debug_count_bias=big if wide else 0))
+        for w, c in collections.Counter(x.lower() for x in words).items():
+            want[w] += c + (big if wide else 0)
+    assert wc.merge(tabs).as_dict() == dict(want)
+    m = 2_100_000
+    text = b" ".join(b"%07x" % (x * 127) for x in range(m))
+    t = gpu_count(text)
+    got = wc.merge([t, t, t])
+    assert got.n_entries == m and (got.counts() == 3).all()
+    w = np.sort(got.words().cpu().numpy().reshape(m, 7).view("S7").ravel())
+    assert (w == np.array(text.split(), dtype="S7")).all()
+
+
 def test_merge_long_words_and_collisions():
     w = b"Q" * 40
     t1 = gpu_count(b" ".join([w, w.lower(), b"a" * 17, b"b"]))
