@@ -147,13 +147,13 @@ bool use_spill(uint64_t len, const wc_opts* o) {
   return len >= kSpillMinBytes;
 }
 
-// Global counts of ASCII text below the two-pass size take the partitioned kernels; a tuning is
+// Global counts of text below the two-pass size take the partitioned kernels; a tuning is
 // for the one-pass kernel's launch, and so are the debug flags that name it and forced key
 // collisions (they concern its table's keys).
 constexpr uint32_t kNoPart = 1u << 31;  // internal debug flag: count with the one-pass kernel
 bool use_part(uint64_t len, uint64_t n_docs, const wc_opts* o) {
   if (o->mode != WC_GLOBAL || !len || !n_docs || use_spill(len, o)) return false;
-  if (o->tokenizer == WC_TOKENIZE_UTF8 || o->debug_hash_bits) return false;
+  if (o->debug_hash_bits) return false;
   if (o->debug_flags & (WC_DEBUG_DIRECT | WC_DEBUG_NO_LDS | kNoPart)) return false;
   const wc_tuning* t = o->tuning;
   if (t && (t->stage_bytes || t->lds_entries || t->flush_policy || t->grid_blocks || t->lds_load_pct))
@@ -589,6 +589,7 @@ wc_status count_table(const uint8_t* d_corpus, uint64_t corpus_len, const uint64
     P.word_cap = L.word_cap;
     P.count_bias = opts->debug_count_bias;
     P.count_bytes = opts->count_bytes;
+    P.utf8 = opts->tokenizer == WC_TOKENIZE_UTF8 ? 1u : 0u;
     const bool single = corpus_len <= kSingleBytes;
     if (single) P.stripes_per_wg = P.n_stripes;
     else HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));

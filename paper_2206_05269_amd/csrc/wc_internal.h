@@ -127,7 +127,7 @@ struct PartParams {
   uint64_t slots, occ_limit, word_cap;
   uint64_t count_bias;
   uint32_t count_bytes;
-  uint32_t pad0;
+  uint32_t utf8;             // WC_TOKENIZE_UTF8: the UTF-8 reading of word bytes
 };
 hipError_t set_part_smem();
 hipError_t launch_part_map(const PartParams& P, uint32_t grid, hipStream_t s);

@@ -24,6 +24,7 @@
 // and the caller counts the text again with the one-pass kernel.
 #include "wc_internal.h"
 #include "wc_stripe.h"
+#include "wc_utf8.h"
 
 namespace wc {
 
@@ -92,7 +93,7 @@ WC_DEV uint32_t long_hash(const uint8_t* p, uint32_t n) {
   }
   return h;
 }
-// Length of the word at position s of the text that ends at `end` at the latest.
+// Length of the word at position s that ends at `end` (its document's end) at the latest.
 WC_DEV uint64_t long_len(const uint8_t* corpus, uint64_t len, uint64_t s, uint64_t end) {
   uint64_t p = s;
   while (p < end) {
@@ -131,6 +132,28 @@ WC_DEV bool long_same(const uint8_t* a, const uint8_t* b, uint32_t n) {
     n -= step;
   }
 }
+// The same under the UTF-8 reading.
+WC_DEV uint64_t long_len_utf8(const uint8_t* corpus, uint64_t len, uint64_t s, uint64_t end) {
+  uint64_t p = s;
+  uint32_t over = 0;  // bytes of the next block that end a sequence of this one
+  while (p < end) {
+    const int64_t a = (int64_t)p - (int64_t)((uintptr_t)(corpus + p) & 15);
+    uint32_t m;
+    const uint4 g = classify16(load_text16(corpus, len, a), &m);
+    const uint32_t next = load_text4(corpus, len, a + 16);
+    const int64_t left = (int64_t)end - a;
+    const uint32_t stop = left < 19 ? 1u << left : 0u;  // the document's end
+    const uint32_t res = utf8_mask(g, next, stop);
+    m |= (res & 0xffffu) | over;
+    over = res >> 16;
+    const uint32_t k = (uint32_t)((int64_t)p - a);
+    const uint32_t w = (~m & 0xffffu) >> k;
+    if (w) return min(p + (uint64_t)__ffs(w) - 1, end) - s;
+    p += 16 - k;
+  }
+  return end - s;
+}
+
 WC_DEV bool same_key(const uint4 a, const uint4 b) {
   if (key_eq(a, b)) return true;
   return is_long_key(a) && a.z == b.z && a.w == b.w && long_same(long_ptr(a), long_ptr(b), a.z);
@@ -497,7 +520,13 @@ WC_DEV int64_t lane_value(int64_t v, uint32_t lane) {
 // stripe are staged with it (the next stripe is classified one step early), so a word of at most
 // 16 bytes that runs over the stripe's end is read whole from LDS, at the run's end too; a
 // longer one is read from device memory. Waves meet only when the table is to be emptied.
-template <bool kSingle>
+//
+// UTF-8. A stripe's multi-byte sequences are read when it is classified, as if no document
+// started in it; a sequence's bytes in the next lane, or the next stripe, are passed on. When a
+// document does start in the stripe or just after it, the stripe and the 16 bytes after it
+// are read again with the starts in hand. ASCII text takes the same steps as without UTF-8, and
+// one test per stripe.
+template <bool kSingle, bool kUtf8>
 __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   extern __shared__ __align__(16) uint8_t s_dyn[];
   __shared__ uint32_t s_list[kWaves][kListWords];  // starts (16 bits each), then the end bitmap
@@ -528,7 +557,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   const uint64_t sa = first + min(wv * per, n_wg);
   const uint32_t nsw = (uint32_t)(min(first + (wv + 1) * per, first + n_wg) - sa);
   auto stripe_pos = [&](uint64_t i) -> int64_t { return P.base_off + (int64_t)((sa + i) * kStripe); };
-  // stripe i of the run; of the stripe after it, the first 16 bytes (lane 0)
+  // stripe i of the run; of the stripe after it, the first 16 bytes (lane 0; UTF-8: 32)
   const uint4 blank = make_uint4(0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u);
   auto load = [&](uint32_t i) -> uint4 {
     if (i > nsw || nsw == 0) return blank;
@@ -536,13 +565,14 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     uint4 v = blank;
     if (i < nsw && p >= 0 && p + (int64_t)kStripe <= (int64_t)P.len) {
       v = load_stream16(P.corpus + p + lane * 16);
-    } else if (i < nsw || lane == 0) {
+    } else if (i < nsw || lane <= (kUtf8 ? 1u : 0u)) {
       v = load_text16(P.corpus, P.len, p + lane * 16);
     }
     return v;
   };
   const uint4 raw0 = load(0);
-  uint4 r1 = load(1), r2 = load(2);
+  uint4 r1 = load(1), r2 = load(2), r3 = blank;
+  if (kUtf8) r3 = load(3);
 
   for (uint32_t i = tid; i < kRedSlots / 4; i += kBlk) ((uint4*)T.slot)[i] = make_uint4(0, 0, 0, 0);
   for (uint32_t i = tid; i < kWaves * kListWords; i += kBlk) (&s_list[0][0])[i] = 0;
@@ -612,15 +642,49 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
 
   // the byte before the run
   uint32_t carry = 0;
+  // UTF-8: bytes of the next stripe to classify that end a sequence of the one before (its first
+  // three bytes at most), and of the stripe at hand, corrected for document starts
+  uint32_t uc = 0, uc0 = 0;
   if (nsw) {
     const int64_t q = stripe_pos(0) - 1;
-    uint32_t f;
-    fold_classify4(load_text4(P.corpus, P.len, q - 3), &f);
-    carry = (q >= R0 && q < R1) ? f >> 31 : 0u;
+    if (kUtf8) {
+      // lane l: the word flag of byte q + l, for l < 4 (for all but the first, if it is not ASCII)
+      uint32_t f = 0;
+      if (lane < 4) {
+        auto byte_at = [&](int64_t x) -> uint32_t { return P.corpus[x]; };
+        auto starts_at = [&](int64_t x) -> bool { return doc_starts_at(P.offsets, P.n_docs, x); };
+        const int64_t x = q + lane;
+        if (x >= R0 && x < R1 && (lane == 0 || (P.corpus[x] & 0xc0u) == 0x80u))
+          f = utf8_word_byte(x, R0, R1, byte_at, starts_at);
+      }
+      const uint32_t m = (uint32_t)__ballot(f != 0);
+      carry = m & 1u;
+      uc = (m >> 1) & 7u;
+    } else {
+      uint32_t f;
+      fold_classify4(load_text4(P.corpus, P.len, q - 3), &f);
+      carry = (q >= R0 && q < R1) ? f >> 31 : 0u;
+    }
   }
   const bool inside = nsw && stripe_pos(0) >= R0 && stripe_pos(nsw) + 16 <= R1;
+  // Folded bytes and word bytes of a stripe; after: the stripe after it.
+  auto classify = [&](const uint4 v, const uint4 after, uint32_t* w) -> uint4 {
+    const uint4 c = classify16(v, w);
+    if (kUtf8 && __any(((c.x | c.y | c.z | c.w) & 0x80808080u) != 0)) {
+      const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)after.x, 0);
+      const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)c.x, 0x130, 0xf, 0xf, false);
+      const uint32_t res = utf8_mask(c, next, 0u);
+      *w |= (res & 0xffffu) |
+            (uint32_t)__builtin_amdgcn_update_dpp((int)uc, (int)(res >> 16), 0x138, 0xf, 0xf, false);
+      uc = (uint32_t)__builtin_amdgcn_readlane((int)(res >> 16), 63);
+    } else {
+      uc = 0;
+    }
+    return c;
+  };
   uint32_t w16;
-  uint4 g = classify16(raw0, &w16);
+  uc0 = uc;
+  uint4 g = classify(raw0, r1, &w16);
   if (!inside) w16 = cut16(w16, stripe_pos(0) + lane * 16, R0, R1);
 
   uint32_t i = 0, n = 0, w0 = 0, start16 = 0, rank = 0;
@@ -649,7 +713,8 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
       return long_key(p, len, h);
     }
     const uint64_t start = (uint64_t)(p0 + s);
-    len = (uint32_t)long_len(P.corpus, P.len, start, max(doc_limit(start), start));
+    const uint64_t end = max(doc_limit(start), start);
+    len = (uint32_t)(kUtf8 ? long_len_utf8(P.corpus, P.len, start, end) : long_len(P.corpus, P.len, start, end));
     return long_key(p, len, long_hash(p, len));
   };
 
@@ -661,16 +726,22 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         // -- next stripe: (g, w16) classified; the next one's bytes are in r1
         p0 = stripe_pos(i);
         uint32_t w1;
-        const uint4 g1 = classify16(r1, &w1);
-        if (!inside) w1 = cut16(w1, p0 + (int64_t)kStripe + lane * 16, R0, R1);
+        uint32_t uc1 = uc;  // of the next stripe's first bytes
+        const uint4 g1 = classify(r1, r2, &w1);
         r1 = r2;
-        r2 = load(i + 3);
+        if (kUtf8) {
+          r2 = r3;
+          r3 = load(i + 4);
+        } else {
+          r2 = load(i + 3);
+        }
+        constexpr int64_t kReach = kStripe + (kUtf8 ? 20 : 16);  // document starts that matter here
         ((uint4*)my_txt)[lane] = g;
         if (lane == 0) ((uint4*)my_txt)[64] = g1;
-        uint32_t bnd16 = 0, bnext = 0, bsfx = 0;
-        if (lane_value(doff, dn) < p0 + (int64_t)kStripe + 16) {
+        uint32_t bnd16 = 0, bnext = 0, bsfx = 0, wsfx = w1;
+        if (lane_value(doff, dn) < p0 + kReach) {
           while (true) {
-            const bool mine = lane >= dn && doff >= p0 && doff < p0 + (int64_t)kStripe + 16;
+            const bool mine = lane >= dn && doff >= p0 && doff < p0 + kReach;
             if (mine) {
               const uint32_t rel = (uint32_t)(doff - p0);
               atomicOr(&my_bnd[rel >> 5], 1u << (rel & 31));
@@ -685,10 +756,32 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
           bnd16 = (my_bnd[lane >> 1] >> ((lane & 1) * 16)) & 0xffffu;
           bnext = (my_bnd[(lane + 1) >> 1] >> (((lane + 1) & 1) * 16)) & 1u;
           bsfx = my_bnd[kStripe / 32] & 0xffffu;
+          if (kUtf8) {
+            const uint32_t b0 = bnd16 | (((my_bnd[(lane + 1) >> 1] >> (((lane + 1) & 1) * 16)) & 0xffffu) << 16);
+            uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)g1.x, 0);
+            uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)g.x, 0x130, 0xf, 0xf, false);
+            uint32_t res = utf8_mask(g, next, b0);
+            classify16(g, &w16);
+            w16 |= (res & 0xffffu) |
+                   (uint32_t)__builtin_amdgcn_update_dpp((int)uc0, (int)(res >> 16), 0x138, 0xf, 0xf, false);
+            const uint32_t now = (uint32_t)__builtin_amdgcn_readlane((int)(res >> 16), 63);
+            if (lane == 0) w1 = (w1 & ~uc1) | now;
+            uc1 = now;
+            // the first 16 bytes of the next stripe (lane 0), for the words that run into them
+            next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)g1.x, 0x130, 0xf, 0xf, false);
+            res = utf8_mask(g1, next, my_bnd[kStripe / 32]);
+            classify16(g1, &wsfx);
+            wsfx |= (res & 0xffffu) | now;
+          }
           wave_sync();
           if (lane < kEnds) my_bnd[lane] = 0;
         }
-        const uint32_t sfx = (uint32_t)__builtin_amdgcn_readlane((int)w1, 0);
+        if (!inside) {
+          if (kUtf8) w16 = cut16(w16, p0 + lane * 16, R0, R1);
+          w1 = cut16(w1, p0 + (int64_t)kStripe + lane * 16, R0, R1);
+          wsfx = cut16(wsfx, p0 + (int64_t)kStripe + lane * 16, R0, R1);
+        }
+        uint32_t sfx = (uint32_t)__builtin_amdgcn_readlane((int)wsfx, 0);
         const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)carry, (int)(w16 >> 15), 0x138,
                                                                     0xf, 0xf, false);
         const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)(sfx & 1u), (int)(w16 & 1u),
@@ -704,6 +797,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
         carry = (uint32_t)__builtin_amdgcn_readlane((int)(w16 >> 15), 63);
         tokens += n;
+        uc0 = uc1;
         g = g1;
         w16 = w1;
         w0 = 0;
@@ -1044,27 +1138,33 @@ size_t part_reduce_dyn() { return (size_t)kRedSlots * 4 + (size_t)kRedEntries<C>
 
 hipError_t set_part_smem() {
   static const hipError_t once = [] {
-    const struct { const void* f; size_t dyn; } k[4] = {
-        {(const void*)part_map_kernel<false>, part_map_dyn()},
-        {(const void*)part_map_kernel<true>, part_map_dyn()},
+    const struct { const void* f; size_t dyn; } k[6] = {
+        {(const void*)part_map_kernel<false, false>, part_map_dyn()},
+        {(const void*)part_map_kernel<true, false>, part_map_dyn()},
+        {(const void*)part_map_kernel<false, true>, part_map_dyn()},
+        {(const void*)part_map_kernel<true, true>, part_map_dyn()},
         {(const void*)part_reduce_kernel<uint32_t>, part_reduce_dyn<uint32_t>()},
         {(const void*)part_reduce_kernel<uint64_t>, part_reduce_dyn<uint64_t>()}};
     hipError_t e = hipSuccess;
-    for (int i = 0; i < 4 && e == hipSuccess; ++i)
+    for (int i = 0; i < 6 && e == hipSuccess; ++i)
       e = hipFuncSetAttribute(k[i].f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)k[i].dyn);
     return e;
   }();
   return once;
 }
 
+template <bool kSingle>
+static hipError_t launch_map(const PartParams& P, uint32_t grid, hipStream_t s) {
+  if (P.utf8)
+    hipLaunchKernelGGL((part_map_kernel<kSingle, true>), dim3(grid), dim3(kBlk), part_map_dyn(), s, P);
+  else
+    hipLaunchKernelGGL((part_map_kernel<kSingle, false>), dim3(grid), dim3(kBlk), part_map_dyn(), s, P);
+  return hipGetLastError();
+}
 hipError_t launch_part_map(const PartParams& P, uint32_t grid, hipStream_t s) {
-  hipLaunchKernelGGL(part_map_kernel<false>, dim3(grid), dim3(kBlk), part_map_dyn(), s, P);
-  return hipGetLastError();
+  return launch_map<false>(P, grid, s);
 }
-hipError_t launch_part_single(const PartParams& P, hipStream_t s) {
-  hipLaunchKernelGGL(part_map_kernel<true>, dim3(1), dim3(kBlk), part_map_dyn(), s, P);
-  return hipGetLastError();
-}
+hipError_t launch_part_single(const PartParams& P, hipStream_t s) { return launch_map<true>(P, 1, s); }
 hipError_t launch_part_reduce(const PartParams& P, hipStream_t s) {
   hipLaunchKernelGGL(part_reduce_kernel<uint32_t>, dim3(P.parts), dim3(kBlk),
                      part_reduce_dyn<uint32_t>(), s, P);

@@ -1132,6 +1132,29 @@ def test_utf8_random_bytes_stage_edges_and_cuts(stage):
         check_utf8(t, off, per_doc=True, tuning=tu)
 
 
+@pytest.mark.parametrize("n", [1, 3, 17, 1023, 1024, 1025, 1041, 16_387, 49_152, 49_153, 300_007])
+def test_utf8_partitioned(n):
+    """The partitioned count under the UTF-8 reading: valid, cut and malformed sequences at lane and
+    stripe edges, words of multi-byte letters below and above 16 bytes, ASCII stripes between
+    others, one document and many (starts inside sequences, empty documents)."""
+    rng = np.random.default_rng(n)
+    pieces = np.frombuffer(b"ab \xc3\xa9\xe2\x80\x94\xe6\x97\xa5\xf0\x9f\x98\x80\xce\xa9.", np.uint8)
+    words = ["Grüße", "日本語のテキストテスト日本語", "и", "Ωμέγα", "naïve", "plain", "a" * 15 + "é", "é" * 40,
+             "x" * 30 + "é", "5×3÷2", "“q”", "z\ufeffz", "\U0001f600\U0001f600", " ", "、", "ASCII only text "]
+    texts = {"bytes": rng.choice(pieces, n).tobytes(),
+             "words": b" ".join(words[i].encode() for i in rng.integers(0, len(words), n // 4 + 8))[:n],
+             "runs": (b"ascii words only, " * 90 + "слова и слова ".encode() * 60) * (n // 2500 + 1)}
+    for name, text in texts.items():
+        text = text[:n]
+        for shift in (0, 13):
+            t = b"q" * shift + text
+            for docs in (1, 3, len(t) // 2 + 1):
+                off = [0, len(t)] if docs == 1 else \
+                    synth.random_splits(len(t), min(docs, 20_000), shift + docs)
+                say(name, n, shift, docs)
+                check_utf8(t, off)
+
+
 def test_utf8_multilingual_and_ascii_agreement():
     text = ("Grüße aus Köln — naïve CAFÉ; Ωμέγα και άλφα… 日本語のテキスト、テスト。"
             "Привет, мир! ‘quoted’ “double” 5×3÷2 Zebra zebra\ufeffword ").encode() * 3000
