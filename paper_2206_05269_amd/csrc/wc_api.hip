@@ -270,7 +270,7 @@ struct OutBufs {
 
 bool layout_count(uint64_t len, uint64_t n_docs, const wc_opts* o, const Tune& tu,
                   const uint8_t* corpus, void* ws, CountLayout* L,
-                  const OutBufs* outs = nullptr) {
+                  const OutBufs* outs = nullptr, uint64_t pieces = 1) {
   const bool per_doc = o->mode == WC_PER_DOC;
   uint64_t S = o->table_slots;
   if (!S) {
@@ -309,7 +309,7 @@ bool layout_count(uint64_t len, uint64_t n_docs, const wc_opts* o, const Tune& t
     L->parts = 16;
     while (L->parts < kParts && (uint64_t)L->parts << 16 < len) L->parts *= 2;
     L->cap_recs = (len <= (16ull << 20) ? len / 8 : std::max<uint64_t>(2ull << 20, len / 12)) + 8192;
-    L->max_lists = (uint32_t)(L->part_grid + L->cap_recs / 1024 + 64);
+    L->max_lists = (uint32_t)(pieces * L->part_grid + L->cap_recs / 1024 + 64);
     Bump A(nullptr);
     A.take<uint4>(L->cap_recs * 16);
     A.take<uint32_t>(L->cap_recs * 4);
@@ -552,6 +552,55 @@ wc_status wc_count(const uint8_t* d_corpus, uint64_t corpus_len, const uint64_t*
 
 namespace {
 
+// The partitioned count of a text: the whole corpus of L's layout, or a piece of it.
+PartParams part_params(const uint8_t* d_corpus, uint64_t corpus_len, const uint64_t* d_offsets,
+                       uint64_t n_docs, const wc_opts* opts, const CountLayout& L) {
+  PartParams P;
+  memset(&P, 0, sizeof(P));
+  P.corpus = d_corpus;
+  P.len = corpus_len;
+  P.offsets = d_offsets;
+  P.n_docs = n_docs;
+  P.hdr = L.hdr;
+  P.base_off = base_offset(d_corpus);
+  P.n_stripes = (uint64_t)(((int64_t)corpus_len - P.base_off + kStripe - 1) / kStripe);
+  P.stripes_per_wg = L.stripes_per_wg;
+  P.parts = L.parts;
+  P.max_lists = L.max_lists;
+  P.cap_recs = L.cap_recs;
+  P.rec_key = L.rec_key;
+  P.rec_cnt = L.rec_cnt;
+  P.dir = L.dir;
+  P.word_offsets = L.woff;
+  P.words = L.words;
+  P.counts = L.counts;
+  P.slots = L.S;
+  P.occ_limit = L.S - L.S / 8;
+  P.word_cap = L.word_cap;
+  P.count_bias = opts->debug_count_bias;
+  P.count_bytes = opts->count_bytes;
+  P.utf8 = opts->tokenizer == WC_TOKENIZE_UTF8 ? 1u : 0u;
+  return P;
+}
+
+// The result of a partitioned count whose header has been read.
+wc_status part_result(const Header& h, uint64_t n_docs, const wc_opts* opts, const CountLayout& L,
+                      wc_result* out) {
+  if (h.flags & (kFlagBadOffsets | kFlagTableFull)) return finish_flags(h);
+  memset(out, 0, sizeof(*out));
+  out->n_entries = h.n_entries;
+  out->total_tokens = h.total_tokens;
+  out->n_docs = n_docs;
+  out->table_slots = L.S;
+  out->count_bytes = opts->count_bytes;
+  out->mode = opts->mode;
+  out->d_word_offsets = L.woff;
+  out->d_words = L.words;
+  out->d_counts = L.counts;
+  out->word_bytes = h.word_bytes;
+  return finish_flags(h);
+}
+
 // The table path of wc_count (one global table, or one (document, word) table sorted into a
 // CSR) over a laid-out workspace: clear, count (one- or two-pass), export. `phases` selects
 // the steps (a global count in pieces: clear with the first piece, export after the last).
@@ -565,31 +614,7 @@ wc_status count_table(const uint8_t* d_corpus, uint64_t corpus_len, const uint64
 
   const uint64_t occ_limit = L.S - L.S / 8;
   if (L.part && phases == kPhaseAll) {
-    PartParams P;
-    memset(&P, 0, sizeof(P));
-    P.corpus = d_corpus;
-    P.len = corpus_len;
-    P.offsets = d_offsets;
-    P.n_docs = n_docs;
-    P.hdr = L.hdr;
-    P.base_off = base_offset(d_corpus);
-    P.n_stripes = (uint64_t)(((int64_t)corpus_len - P.base_off + kStripe - 1) / kStripe);
-    P.stripes_per_wg = L.stripes_per_wg;
-    P.parts = L.parts;
-    P.max_lists = L.max_lists;
-    P.cap_recs = L.cap_recs;
-    P.rec_key = L.rec_key;
-    P.rec_cnt = L.rec_cnt;
-    P.dir = L.dir;
-    P.word_offsets = L.woff;
-    P.words = L.words;
-    P.counts = L.counts;
-    P.slots = L.S;
-    P.occ_limit = occ_limit;
-    P.word_cap = L.word_cap;
-    P.count_bias = opts->debug_count_bias;
-    P.count_bytes = opts->count_bytes;
-    P.utf8 = opts->tokenizer == WC_TOKENIZE_UTF8 ? 1u : 0u;
+    PartParams P = part_params(d_corpus, corpus_len, d_offsets, n_docs, opts, L);
     const bool single = corpus_len <= kSingleBytes;
     if (single) P.stripes_per_wg = P.n_stripes;
     else HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));
@@ -605,19 +630,8 @@ wc_status count_table(const uint8_t* d_corpus, uint64_t corpus_len, const uint64
       again.part = false;
       return count_table(d_corpus, corpus_len, d_offsets, n_docs, opts, tu, again, out, s, phases);
     }
-    if (h.flags & (kFlagBadOffsets | kFlagTableFull)) return finish_flags(h);
-    memset(out, 0, sizeof(*out));
-    out->n_entries = h.n_entries;
-    out->total_tokens = h.total_tokens;
-    out->n_docs = n_docs;
-    out->table_slots = L.S;
-    out->count_bytes = opts->count_bytes;
-    out->mode = opts->mode;
-    out->d_word_offsets = L.woff;
-    out->d_words = L.words;
-    out->d_counts = L.counts;
-    out->word_bytes = h.word_bytes;
-    if (tm.on) {
+    const wc_status st = part_result(h, n_docs, opts, L, out);
+    if (tm.on && !(h.flags & (kFlagBadOffsets | kFlagTableFull))) {
       HIPCHK(hipEventRecord(tm.d, s));
       HIPCHK(hipEventSynchronize(tm.d));
       float ms = 0;
@@ -626,7 +640,7 @@ wc_status count_table(const uint8_t* d_corpus, uint64_t corpus_len, const uint64
       HIPCHK(hipEventElapsedTime(&ms, tm.c, tm.d));
       out->total_ms = ms;
     }
-    return finish_flags(h);
+    return st;
   }
 
   if (phases & kPhaseClear) {
@@ -1566,6 +1580,15 @@ namespace {
 
 constexpr uint64_t kMinPiece = 1ull << 20;
 
+// Piece size of a host count. The partitioned kernels count pieces of any size into one set of
+// lists, so the text is cut finer than asked: what is counted after the last byte has arrived is
+// one piece (192 MB from pinned memory in one piece: 3.5 ms of copy, then the count; in eight, the
+// copy and the count of an eighth).
+uint64_t host_piece(uint64_t len, uint64_t asked, bool part) {
+  const uint64_t p = std::max<uint64_t>(asked, kMinPiece);
+  return part ? std::min<uint64_t>(p, std::max<uint64_t>(len / 8, 8ull << 20)) : p;
+}
+
 inline bool ascii_delimiter(uint8_t x) {
   if (x >= 0x80) return false;  // may belong to a UTF-8 sequence: not taken as a cut
   const uint8_t f = (x >= 'A' && x <= 'Z') ? (uint8_t)(x + 32) : x;
@@ -1624,7 +1647,7 @@ void plan_pieces(const uint8_t* h, const uint64_t* off, uint64_t n_docs, uint64_
 // size it from one piece), and so are the exported word bytes.
 wc_opts piece_opts(const wc_opts* o, uint64_t corpus_len) {
   wc_opts q = *o;
-  q.debug_flags = (q.debug_flags & ~WC_DEBUG_TIME) | kNoPart;  // pieces share one table
+  q.debug_flags &= ~WC_DEBUG_TIME;
   if (!q.table_slots) {
     wc_plan p;
     if (wc_count_plan(corpus_len, 1, o, &p) == WC_OK) q.table_slots = p.table_slots;
@@ -1648,7 +1671,15 @@ wc_status wc_count_host_plan(uint64_t corpus_len, uint64_t n_docs, const wc_opts
   // whole corpus covers every piece's
   wc_status st = wc_count_plan(corpus_len, n_docs, &q, out);
   if (st != WC_OK) return st;
-  const uint64_t n_pieces = corpus_len / std::max<uint64_t>(piece_bytes, kMinPiece) + 2;
+  const bool part = use_part(corpus_len, n_docs, &q);
+  const uint64_t n_pieces = corpus_len / host_piece(corpus_len, piece_bytes, part) + 2;
+  if (part) {
+    Tune tu;
+    resolve_tuning(q.tuning, &tu);
+    CountLayout L;
+    layout_count(corpus_len, n_docs, &q, tu, nullptr, nullptr, &L, nullptr, n_pieces);
+    out->workspace_bytes = L.total + kAlign;
+  }
   out->workspace_bytes += align_up((n_docs + 1 + 2 * n_pieces) * 8) + kAlign;
   return WC_OK;
 }
@@ -1665,15 +1696,19 @@ wc_status wc_count_host(const uint8_t* h_corpus, uint64_t corpus_len, const uint
   if (n_docs && h_offsets[n_docs] > corpus_len) return WC_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   HIPCHK(ensure_smem_attr());
-  const wc_opts q = piece_opts(opts, corpus_len);
+  wc_opts q = piece_opts(opts, corpus_len);
+  const bool part = use_part(corpus_len, n_docs, &q);
+  if (!part) q.debug_flags |= kNoPart;  // pieces share one table
   Tune tu;
   if (!resolve_tuning(q.tuning, &tu)) return WC_EINVAL;
   HostPieces H;
-  if (n_docs) plan_pieces(h_corpus, h_offsets, n_docs, std::max<uint64_t>(piece_bytes, kMinPiece), &H);
+  const uint64_t piece = host_piece(corpus_len, piece_bytes, part);
+  if (n_docs) plan_pieces(h_corpus, h_offsets, n_docs, piece, &H);
   // piece offset arrays at the end of the workspace, after the largest piece's layout
   CountLayout L0;
   global_stage(corpus_len, &q, &tu);
-  if (!layout_count(corpus_len, std::max<uint64_t>(n_docs, 1), &q, tu, nullptr, nullptr, &L0))
+  if (!layout_count(corpus_len, std::max<uint64_t>(n_docs, 1), &q, tu, nullptr, nullptr, &L0, nullptr,
+                    corpus_len / piece + 2))
     return WC_EDEVICE;
   const uint64_t off_at = align_up(L0.total + kAlign);
   if (off_at + H.offs.size() * 8 > workspace_bytes) return WC_ENOMEM;
@@ -1685,36 +1720,72 @@ wc_status wc_count_host(const uint8_t* h_corpus, uint64_t corpus_len, const uint
   std::vector<hipEvent_t> ev(H.count.size(), nullptr);
   wc_status st = WC_OK;
   hipError_t e = hipSuccess;
-  CountLayout L;
-  // the table is cleared before the first piece (also for an empty corpus)
-  Tune t0 = tu;
-  global_stage(H.max_len, &q, &t0);
-  if (!layout_count(std::max<uint64_t>(H.max_len, 1), 1, &q, t0, d_text, d_workspace, &L))
-    st = WC_EDEVICE;
-  if (st == WC_OK) st = count_table(nullptr, 0, nullptr, 0, &q, t0, L, out, s, kPhaseClear);
-  for (size_t p = 0; st == WC_OK && e == hipSuccess && p < H.count.size(); ++p) {
+  // piece p on its way, and stream s behind it
+  auto copy_piece = [&](size_t p) -> hipError_t {
     const uint64_t a = H.cuts[p], n = H.cuts[p + 1] - a;
-    e = hipEventCreateWithFlags(&ev[p], hipEventDisableTiming);
-    if (e == hipSuccess && n) e = hipMemcpyAsync(d_text + a, h_corpus + a, n, hipMemcpyHostToDevice, cs);
-    if (e == hipSuccess) e = hipEventRecord(ev[p], cs);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s, ev[p], 0);
-    if (e != hipSuccess) break;
-    Tune tp = tu;
-    global_stage(n, &q, &tp);
-    CountLayout Lp;
-    if (!layout_count(n, H.count[p], &q, tp, d_text + a, d_workspace, &Lp)) {
+    hipError_t r = hipEventCreateWithFlags(&ev[p], hipEventDisableTiming);
+    if (r == hipSuccess && n) r = hipMemcpyAsync(d_text + a, h_corpus + a, n, hipMemcpyHostToDevice, cs);
+    if (r == hipSuccess) r = hipEventRecord(ev[p], cs);
+    if (r == hipSuccess) r = hipStreamWaitEvent(s, ev[p], 0);
+    return r;
+  };
+  bool copied = false;
+  if (part) {
+    // every piece's lists in one arena, reduced once
+    CountLayout L;
+    if (!layout_count(corpus_len, std::max<uint64_t>(n_docs, 1), &q, tu, d_text, d_workspace, &L, nullptr,
+                      corpus_len / piece + 2))
       st = WC_EDEVICE;
-      break;
+    if (st == WC_OK) e = launch_fill_zero(L.hdr, sizeof(Header), s);
+    PartParams P = part_params(d_text, corpus_len, nullptr, 0, &q, L);
+    for (size_t p = 0; st == WC_OK && e == hipSuccess && p < H.count.size(); ++p) {
+      const uint64_t a = H.cuts[p], n = H.cuts[p + 1] - a;
+      e = copy_piece(p);
+      if (e != hipSuccess || !n) continue;
+      P = part_params(d_text + a, n, d_offs + H.first[p], H.count[p], &q, L);
+      const uint64_t grid = std::min<uint64_t>(L.part_grid, (P.n_stripes + 15) / 16);
+      P.stripes_per_wg = (P.n_stripes + grid - 1) / grid;
+      e = launch_part_map(P, (uint32_t)((P.n_stripes + P.stripes_per_wg - 1) / P.stripes_per_wg), s);
     }
-    if (Lp.total > off_at || Lp.table != L.table || Lp.hdr != L.hdr) {
-      st = WC_ENOMEM;
-      break;
-    }
-    st = count_table(d_text + a, n, d_offs + H.first[p], H.count[p], &q, tp, Lp, out, s,
-                     kPhaseCount);
+    copied = true;
+    Header h;
+    memset(&h, 0, sizeof(h));
+    if (st == WC_OK && e == hipSuccess) e = launch_part_reduce(P, s);
+    if (st == WC_OK && e == hipSuccess)
+      e = hipMemcpyAsync(&h, L.hdr, sizeof(Header), hipMemcpyDeviceToHost, s);
+    if (st == WC_OK && e == hipSuccess) e = hipStreamSynchronize(s);
+    if (st == WC_OK && e == hipSuccess && !(h.flags & kFlagArena)) st = part_result(h, n_docs, &q, L, out);
+    if (h.flags & kFlagArena) q.debug_flags |= kNoPart;  // the pieces again, into one table
   }
-  if (e == hipSuccess && st == WC_OK)
-    st = count_table(nullptr, 0, nullptr, 0, &q, t0, L, out, s, kPhaseExport);
+  if (st == WC_OK && e == hipSuccess && (q.debug_flags & kNoPart)) {
+    CountLayout L;
+    // the table is cleared before the first piece (also for an empty corpus)
+    Tune t0 = tu;
+    global_stage(H.max_len, &q, &t0);
+    if (!layout_count(std::max<uint64_t>(H.max_len, 1), 1, &q, t0, d_text, d_workspace, &L))
+      st = WC_EDEVICE;
+    if (st == WC_OK) st = count_table(nullptr, 0, nullptr, 0, &q, t0, L, out, s, kPhaseClear);
+    for (size_t p = 0; st == WC_OK && e == hipSuccess && p < H.count.size(); ++p) {
+      const uint64_t a = H.cuts[p], n = H.cuts[p + 1] - a;
+      if (!copied) e = copy_piece(p);
+      if (e != hipSuccess) break;
+      Tune tp = tu;
+      global_stage(n, &q, &tp);
+      CountLayout Lp;
+      if (!layout_count(n, H.count[p], &q, tp, d_text + a, d_workspace, &Lp)) {
+        st = WC_EDEVICE;
+        break;
+      }
+      if (Lp.total > off_at || Lp.table != L.table || Lp.hdr != L.hdr) {
+        st = WC_ENOMEM;
+        break;
+      }
+      st = count_table(d_text + a, n, d_offs + H.first[p], H.count[p], &q, tp, Lp, out, s,
+                       kPhaseCount);
+    }
+    if (e == hipSuccess && st == WC_OK)
+      st = count_table(nullptr, 0, nullptr, 0, &q, t0, L, out, s, kPhaseExport);
+  }
   hipError_t e2 = hipStreamSynchronize(cs);
   for (hipEvent_t x : ev)
     if (x) (void)hipEventDestroy(x);
