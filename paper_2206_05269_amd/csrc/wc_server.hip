@@ -11,8 +11,14 @@
 // Continuous batching. `max_streams` worker threads each own a HIP stream (default priority),
 // so admitted requests run concurrently on the device. A worker that takes a small
 // single-document request also takes the small single-document requests queued right behind
-// it (up to kPackDocs requests / kPackBytes bytes) and counts them in one per-document launch,
-// then splits the per-document tables into one resident table per request.
+// it (up to kPackDocs requests) and counts them in one per-document launch, then splits the
+// per-document tables into one resident table per request: one kernel gathers the group's texts,
+// one finds every request's entries, bytes and tokens, and one copies all their tables, with a
+// host wait after the second and the third. Requests above kSmallBytes are counted alone: the
+// partitioned count takes 42 us and up, text in device memory is read where it is, and the table
+// goes to its resident block with one launch. (Requests of up to 1 MiB used to be packed and
+// split one at a time, with two host waits and three copies each: 96 requests of 1 KiB to 4 MiB and
+// a merge of their tables took 5.8 ms.)
 //
 // Uploads. Each worker owns two pinned host buffers: it copies a request's text into one while
 // the other is on its way to the device, so host copies of several workers and their DMA
@@ -41,8 +47,7 @@ namespace {
 using Clock = std::chrono::steady_clock;
 
 constexpr uint32_t kPackDocs = 64;
-constexpr uint64_t kPackBytes = 4ull << 20;
-constexpr uint64_t kSmallBytes = 1ull << 20;
+constexpr uint64_t kSmallBytes = 32ull << 10;
 constexpr uint64_t kStageBytes = 8ull << 20;  // per pinned upload buffer (two per worker)
 
 struct Request {
@@ -83,13 +88,14 @@ struct wc_server {
   std::unordered_map<uint64_t, std::shared_ptr<Request>> reqs;
   std::vector<std::thread> workers;
   std::vector<hipStream_t> streams;
+  static constexpr uint32_t kSmallWords = 512;  // a group's spans and the offsets of its texts
   struct Staging {
     uint8_t* buf[2] = {nullptr, nullptr};
     hipEvent_t ev[2] = {nullptr, nullptr};
     bool used[2] = {false, false};
     uint32_t next = 0;
-    uint64_t* small = nullptr;  // pinned: a few values read back from the device
-    unsigned long long* d_small = nullptr;  // device: per-request token totals of a group
+    uint64_t* small = nullptr;  // pinned: kSmallWords values on their way to or from the device
+    uint64_t* d_small = nullptr;  // device: the spans of a group
   };
   std::vector<Staging> staging;  // one per worker
   uint64_t next_id = 1;
@@ -99,45 +105,108 @@ struct wc_server {
 
 namespace {
 
-// compact a table (device arrays) into one resident block: [word_offsets | counts | words]
-// d[i] = s[i] - s[0] for i < n1: a table's word offsets rebased to its first word
-__global__ void rebase_offsets_kernel(const uint64_t* src, uint64_t n1, uint64_t* dst) {
-  const uint64_t b0 = src[0];
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n1;
-       i += (uint64_t)gridDim.x * blockDim.x)
-    dst[i] = src[i] - b0;
+// ---- copies of many pieces by one launch ----------------------------------------------------
+// A table's entries [0, n) on the way to a resident block: offsets rebased to the first word,
+// counts, word bytes; or (off null) just bytes. Pieces are kernel arguments, kKeep at a time; a
+// piece has a workgroup per kKeepSpan bytes.
+constexpr uint32_t kKeep = 32;
+constexpr uint64_t kKeepSpan = 32768;
+struct KeepItem {
+  const uint64_t* off;
+  const uint8_t* counts;
+  const uint8_t* words;
+  uint64_t n, count_bytes, word_bytes;  // count_bytes: of all entries
+  uint64_t* d_off;
+  uint8_t* d_counts;
+  uint8_t* d_words;
+};
+struct KeepBatch {
+  KeepItem item[kKeep];
+  uint32_t first_block[kKeep];
+  uint32_t n;
+};
+
+// bytes [a, b) of a copy of n bytes, eight at a time at any address
+__device__ void copy_part(uint8_t* dst, const uint8_t* src, uint64_t n, uint64_t a, uint64_t b) {
+  b = min(b, n);
+  for (uint64_t i = a + threadIdx.x * 8; i < b; i += blockDim.x * 8) {
+    if (i + 8 <= n) {
+      uint64_t v;
+      __builtin_memcpy(&v, src + i, 8);
+      __builtin_memcpy(dst + i, &v, 8);
+    } else {
+      for (uint64_t q = i; q < n; ++q) dst[q] = src[q];
+    }
+  }
 }
 
-// *out += sum of n counts (4 or 8 bytes each); integer, so the order of additions is free
-__global__ void sum_counts_kernel(const void* counts, uint32_t cb, uint64_t n,
-                                  unsigned long long* out) {
+__global__ __launch_bounds__(256) void keep_kernel(KeepBatch K) {
+  uint32_t x = 0;
+  while (x + 1 < K.n && K.first_block[x + 1] <= blockIdx.x) ++x;
+  const KeepItem& it = K.item[x];
+  // the block's span of offsets | counts | words laid end to end (each rounded up to 8)
+  const uint64_t a = (blockIdx.x - K.first_block[x]) * kKeepSpan, b = a + kKeepSpan;
+  const uint64_t o = it.off ? (it.n + 1) * 8 : 0, c = (it.count_bytes + 7) & ~7ull;
+  if (a < o) {
+    const uint64_t base = it.off[0];
+    for (uint64_t i = a / 8 + threadIdx.x; i < min(b, o) / 8; i += blockDim.x)
+      it.d_off[i] = it.off[i] - base;
+  }
+  if (a < o + c && b > o)
+    copy_part(it.d_counts, it.counts, it.count_bytes, a > o ? a - o : 0, b - o);
+  if (b > o + c)
+    copy_part(it.d_words, it.words + (it.off ? it.off[0] : 0), it.word_bytes,
+              a > o + c ? a - o - c : 0, b - o - c);
+}
+
+hipError_t launch_keep(const std::vector<KeepItem>& items, hipStream_t s) {
+  for (size_t i = 0; i < items.size();) {
+    KeepBatch K;
+    uint32_t blocks = 0;
+    for (K.n = 0; i < items.size() && K.n < kKeep; ++i) {
+      const KeepItem& it = items[i];
+      const uint64_t bytes =
+          (it.off ? (it.n + 1) * 8 : 0) + ((it.count_bytes + 7) & ~7ull) + it.word_bytes;
+      if (!bytes) continue;
+      K.item[K.n] = it;
+      K.first_block[K.n++] = blocks;
+      blocks += (uint32_t)((bytes + kKeepSpan - 1) / kKeepSpan);
+    }
+    if (!K.n) continue;
+    hipLaunchKernelGGL(keep_kernel, dim3(blocks), dim3(256), 0, s, K);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// Document d of a packed group (one workgroup each): its first entry, entries, word bytes and
+// tokens (the sum of its counts), at out[4 d].
+__global__ __launch_bounds__(256) void doc_span_kernel(wc_result t, uint64_t* out) {
+  __shared__ unsigned long long s_sum;
+  const uint64_t d = blockIdx.x, p = t.d_doc_ptr[d], n = t.d_doc_len[d];
+  if (threadIdx.x == 0) s_sum = 0;
+  __syncthreads();
   unsigned long long v = 0;
-  for (uint64_t i = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * blockDim.x)
-    v += cb == 4 ? (unsigned long long)((const int32_t*)counts)[i]
-                 : (unsigned long long)((const int64_t*)counts)[i];
-  for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-  if ((threadIdx.x & 63) == 0 && v) atomicAdd(out, v);
+  for (uint64_t i = p + threadIdx.x; i < p + n; i += blockDim.x)
+    v += t.count_bytes == 4 ? (unsigned long long)((const int32_t*)t.d_counts)[i]
+                            : (unsigned long long)((const int64_t*)t.d_counts)[i];
+  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+  if ((threadIdx.x & 63) == 0 && v) atomicAdd(&s_sum, v);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    out[4 * d] = p;
+    out[4 * d + 1] = n;
+    out[4 * d + 2] = n ? t.d_word_offsets[p + n] - t.d_word_offsets[p] : 0;
+    out[4 * d + 3] = s_sum;
+  }
 }
 
-uint32_t small_grid(uint64_t n) {
-  const uint64_t g = (n + 255) / 256;
-  return (uint32_t)std::min<uint64_t>(std::max<uint64_t>(g, 1), 1024);
-}
-
-// Copy entries [e_begin, e_begin + n) of table t into an exact-size resident block. Only the
-// byte range of their words crosses to the host (two values); offsets are rebased and counts
-// and words copied on the device.
-wc_status keep_resident(wc_server* S, wc_server::Staging& W, hipStream_t s, const wc_result& t,
-                        uint64_t e_begin, uint64_t n, Request* R) {
+// A resident block for entries [e_begin, e_begin + n) of table t with nb word bytes: R's result
+// points into it, and *item is the copy that fills it.
+wc_status take_resident(wc_server* S, const wc_result& t, uint64_t e_begin, uint64_t n, uint64_t nb,
+                        uint64_t tokens, Request* R, KeepItem* item) {
   const uint32_t cb = t.count_bytes;
-  if (hipMemcpyAsync(&W.small[0], t.d_word_offsets + e_begin, 8, hipMemcpyDeviceToHost, s) !=
-          hipSuccess ||
-      hipMemcpyAsync(&W.small[1], t.d_word_offsets + e_begin + n, 8, hipMemcpyDeviceToHost, s) !=
-          hipSuccess ||
-      hipStreamSynchronize(s) != hipSuccess)
-    return WC_EDEVICE;
-  const uint64_t b0 = W.small[0], nb = W.small[1] - W.small[0];
   const uint64_t bytes = (n + 1) * 8 + n * cb + nb + 64;
   uint8_t* mem = nullptr;
   {
@@ -157,21 +226,8 @@ wc_status keep_resident(wc_server* S, wc_server::Staging& W, hipStream_t s, cons
   uint64_t* d_off = (uint64_t*)mem;
   uint8_t* d_cnt = mem + (((n + 1) * 8 + 15) & ~15ull);
   uint8_t* d_words = d_cnt + ((n * cb + 15) & ~15ull);
-  hipLaunchKernelGGL(rebase_offsets_kernel, dim3(small_grid(n + 1)), dim3(256), 0, s,
-                     (const uint64_t*)(t.d_word_offsets + e_begin), n + 1, d_off);
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess && n)
-    e = hipMemcpyAsync(d_cnt, (const uint8_t*)t.d_counts + e_begin * cb, n * cb,
-                       hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess && nb)
-    e = hipMemcpyAsync(d_words, t.d_words + b0, nb, hipMemcpyDeviceToDevice, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) {
-    std::lock_guard<std::mutex> lk(S->mu);
-    S->adm.free_resident((uint64_t)(mem - S->pool_mem));
-    S->cv_mem.notify_all();
-    return WC_EDEVICE;
-  }
+  *item = KeepItem{t.d_word_offsets + e_begin, (const uint8_t*)t.d_counts + e_begin * cb, t.d_words,
+                   n, n * cb, nb, d_off, d_cnt, d_words};
   R->resident = mem;
   memset(&R->res, 0, sizeof(R->res));
   R->res.n_entries = n;
@@ -179,10 +235,33 @@ wc_status keep_resident(wc_server* S, wc_server::Staging& W, hipStream_t s, cons
   R->res.count_bytes = cb;
   R->res.mode = WC_GLOBAL;
   R->res.n_docs = 1;
+  R->res.total_tokens = tokens;
   R->res.d_word_offsets = d_off;
   R->res.d_words = d_words;
   R->res.d_counts = d_cnt;
   return WC_OK;
+}
+
+// The blocks taken are filled, and the requests of a failed copy give theirs back.
+wc_status fill_residents(wc_server* S, const std::vector<KeepItem>& items, const std::vector<Request*>& rs,
+                         hipStream_t s) {
+  hipError_t e = launch_keep(items, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e == hipSuccess) return WC_OK;
+  std::lock_guard<std::mutex> lk(S->mu);
+  for (Request* R : rs) {
+    S->adm.free_resident((uint64_t)(R->resident - S->pool_mem));
+    R->resident = nullptr;
+  }
+  S->cv_mem.notify_all();
+  return WC_EDEVICE;
+}
+
+// The whole table t into a resident block of R.
+wc_status keep_table(wc_server* S, hipStream_t s, const wc_result& t, Request* R) {
+  std::vector<KeepItem> item(1);
+  const wc_status st = take_resident(S, t, 0, t.n_entries, t.word_bytes, t.total_tokens, R, &item[0]);
+  return st == WC_OK ? fill_residents(S, item, {R}, s) : st;
 }
 
 // Take count memory for a request (wc::Admission::try_count): wait while other requests
@@ -279,40 +358,41 @@ void run_group(wc_server* S, int idx, std::vector<std::shared_ptr<Request>>& G) 
       wc_result t;
       st = wc_merge(ins.data(), (uint32_t)ins.size(), &o, ws, p.workspace_bytes, &t, s);
       S->launches++;
-      if (st == WC_OK) st = keep_resident(S, S->staging[idx], s, t, 0, t.n_entries, R);
-      if (st == WC_OK) R->res.total_tokens = t.total_tokens;
+      if (st == WC_OK) st = keep_table(S, s, t, R);
     }
     if (ws) pool_free(S, ws);
     unpin_inputs(S, R);  // the merge's stream is synchronised: nothing reads the inputs now
     return finish(S, R, st);
   }
-  // stage the texts on the device (one buffer for the group)
+  // the texts on the device: one buffer for the group (a device text counted alone stays where it is)
   uint64_t total = 0;
   for (auto& r : G) total += r->len;
   const bool packed = G.size() > 1;
+  const bool in_place = !packed && G[0]->dev_text;
   uint64_t n_docs_all = 0;
   for (auto& r : G) n_docs_all += packed ? 1 : r->offsets.size() - 1;
   wc_opts o = G[0]->opts;
+  wc_server::Staging& W = S->staging[idx];
   if (packed) {
     o.mode = WC_PER_DOC;
     o.tuning = nullptr;
     o.table_slots = 0;
-    o.word_bytes_cap = 0;
+    o.word_bytes_cap = total;  // room for any texts (the group is small): counted once
+    o.debug_flags = (o.debug_flags & ~WC_DEBUG_DIRECT) | WC_DEBUG_DOCS;
   }
   wc_status st = WC_OK;
   for (int attempt = 0; attempt < 8; ++attempt) {
     wc_plan p;
     st = wc_count_plan(total, n_docs_all, &o, &p);
     if (st != WC_OK) break;
-    if (packed && !(o.debug_flags & WC_DEBUG_DOCS) && p.workspace_bytes > S->budget / 4) {
-      // the one-pass (document, word) table needs about 12 bytes per text byte; under a
-      // tight budget the document-centric kernel (a fraction of that) is counted instead
-      o.debug_flags |= WC_DEBUG_DOCS;
+    if (packed && p.workspace_bytes > S->budget / 4 && o.word_bytes_cap == total) {
+      o.word_bytes_cap = 0;  // a tight budget: the default room
       st = wc_count_plan(total, n_docs_all, &o, &p);
       if (st != WC_OK) break;
     }
     const uint64_t off_bytes = (n_docs_all + 1) * 8;
-    const uint64_t need = p.workspace_bytes + ((total + 255) & ~255ull) + off_bytes + 512;
+    const uint64_t text_bytes = in_place ? 0 : (total + 255) & ~255ull;
+    const uint64_t need = p.workspace_bytes + text_bytes + off_bytes + 512;
     if (need > S->budget) {
       st = WC_ENOMEM;
       break;
@@ -322,29 +402,45 @@ void run_group(wc_server* S, int idx, std::vector<std::shared_ptr<Request>>& G) 
       st = WC_ENOMEM;
       break;
     }
-    uint8_t* d_text = mem;
-    uint64_t* d_off = (uint64_t*)(mem + ((total + 255) & ~255ull));
+    uint8_t* buf = mem;
+    const uint8_t* d_text = in_place ? G[0]->dev_text : buf;
+    uint64_t* d_off = (uint64_t*)(mem + text_bytes);
     uint8_t* ws = (uint8_t*)d_off + ((off_bytes + 255) & ~255ull);
     std::vector<uint64_t> off;
     off.reserve(n_docs_all + 1);
     uint64_t pos = 0;
     hipError_t e = hipSuccess;
+    std::vector<KeepItem> gather;  // device texts of a group
     for (auto& r : G) {
-      if (r->dev_text) e = hipMemcpyAsync(d_text + pos, r->dev_text, r->len, hipMemcpyDeviceToDevice, s);
-      else if (r->host_text && r->len)  // in place: pinned memory goes straight to the DMA engine
-        e = hipMemcpyAsync(d_text + pos, r->host_text, r->len, hipMemcpyHostToDevice, s);
-      else if (r->len) e = upload(S->staging[idx], d_text + pos, r->text.data(), r->len, s);
+      if (in_place) {
+      } else if (r->dev_text) {
+        if (packed) gather.push_back(KeepItem{nullptr, nullptr, r->dev_text, 0, 0, r->len, nullptr, nullptr, buf + pos});
+        else e = hipMemcpyAsync(buf + pos, r->dev_text, r->len, hipMemcpyDeviceToDevice, s);
+      } else if (r->host_text && r->len) {  // in place: pinned memory goes straight to the DMA engine
+        e = hipMemcpyAsync(buf + pos, r->host_text, r->len, hipMemcpyHostToDevice, s);
+      } else if (r->len) {
+        e = upload(W, buf + pos, r->text.data(), r->len, s);
+      }
       if (e != hipSuccess) break;
       if (packed) {
         off.push_back(pos);
       } else {
-        for (size_t i = 0; i + 1 < r->offsets.size(); ++i) off.push_back(pos + r->offsets[i]);
+        for (size_t i = 0; i + 1 < r->offsets.size(); ++i) off.push_back(r->offsets[i]);
       }
       pos += r->len;
     }
     if (packed) off.push_back(pos);
-    else off.push_back(pos - G[0]->len + G[0]->offsets.back());
-    if (e == hipSuccess) e = hipMemcpyAsync(d_off, off.data(), off_bytes, hipMemcpyHostToDevice, s);
+    else off.push_back(G[0]->offsets.back());
+    if (e == hipSuccess) e = launch_keep(gather, s);
+    if (e == hipSuccess) {
+      // (few offsets go through the worker's pinned words; the call waits before their next use)
+      const uint64_t* from = off.data();
+      if (off.size() <= wc_server::kSmallWords) {
+        memcpy(W.small, off.data(), off_bytes);
+        from = W.small;
+      }
+      e = hipMemcpyAsync(d_off, from, off_bytes, hipMemcpyHostToDevice, s);
+    }
     if (e != hipSuccess) {
       pool_free(S, mem);
       st = WC_EDEVICE;
@@ -370,37 +466,27 @@ void run_group(wc_server* S, int idx, std::vector<std::shared_ptr<Request>>& G) 
     }
     if (st == WC_OK) {
       if (!packed) {
-        st = keep_resident(S, S->staging[idx], s, t, 0, t.n_entries, G[0].get());
-        if (st == WC_OK) G[0]->res.total_tokens = t.total_tokens;
+        st = keep_table(S, s, t, G[0].get());
       } else {
-        std::vector<uint64_t> dptr(n_docs_all), dlen(n_docs_all);
-        e = hipMemcpyAsync(dptr.data(), t.d_doc_ptr, n_docs_all * 8, hipMemcpyDeviceToHost, s);
+        hipLaunchKernelGGL(doc_span_kernel, dim3((uint32_t)G.size()), dim3(256), 0, s, t, W.d_small);
+        e = hipGetLastError();
         if (e == hipSuccess)
-          e = hipMemcpyAsync(dlen.data(), t.d_doc_len, n_docs_all * 8, hipMemcpyDeviceToHost, s);
+          e = hipMemcpyAsync(W.small, W.d_small, G.size() * 32, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) st = WC_EDEVICE;
+        std::vector<KeepItem> items;
+        std::vector<Request*> taken;
         for (size_t i = 0; st == WC_OK && i < G.size(); ++i) {
-          wc_status si = keep_resident(S, S->staging[idx], s, t, dptr[i], dlen[i], G[i].get());
-          if (si != WC_OK) st = si;
-        }
-        // token totals per request: sum of its counts, on the device, read back together
-        wc_server::Staging& W = S->staging[idx];
-        if (st == WC_OK) {
-          e = hipMemsetAsync(W.d_small, 0, G.size() * 8, s);
-          for (size_t i = 0; e == hipSuccess && i < G.size(); ++i) {
-            const Request* R = G[i].get();
-            if (!R->res.n_entries) continue;
-            hipLaunchKernelGGL(sum_counts_kernel, dim3(small_grid(R->res.n_entries)), dim3(256), 0,
-                               s, R->res.d_counts, R->res.count_bytes, R->res.n_entries,
-                               W.d_small + i);
-            e = hipGetLastError();
+          const uint64_t* v = W.small + 4 * i;
+          KeepItem item;
+          st = take_resident(S, t, v[0], v[1], v[2], v[3], G[i].get(), &item);
+          if (st == WC_OK) {
+            items.push_back(item);
+            taken.push_back(G[i].get());
           }
-          if (e == hipSuccess)
-            e = hipMemcpyAsync(W.small, W.d_small, G.size() * 8, hipMemcpyDeviceToHost, s);
-          if (e == hipSuccess) e = hipStreamSynchronize(s);
-          if (e != hipSuccess) st = WC_EDEVICE;
-          for (size_t i = 0; st == WC_OK && i < G.size(); ++i) G[i]->res.total_tokens = W.small[i];
         }
+        const wc_status filled = fill_residents(S, items, taken, s);
+        if (st == WC_OK) st = filled;
       }
     }
     pool_free(S, mem);
@@ -442,14 +528,12 @@ void worker(wc_server* S, int idx) {
                r.len <= kSmallBytes;
       };
       if (small(*first)) {
-        uint64_t bytes = first->len;
         while (!S->queue.empty() && G.size() < kPackDocs) {
           auto& nx = S->queue.front();
-          if (!small(*nx) || bytes + nx->len > kPackBytes ||
-              nx->opts.count_bytes != first->opts.count_bytes ||
+          if (!small(*nx) || nx->opts.count_bytes != first->opts.count_bytes ||
+              nx->opts.tokenizer != first->opts.tokenizer ||
               nx->opts.debug_hash_bits != first->opts.debug_hash_bits)
             break;
-          bytes += nx->len;
           nx->state = 1;
           G.push_back(nx);
           S->queue.pop_front();
@@ -491,9 +575,9 @@ wc_status wc_server_create(int device, uint64_t mem_budget, uint32_t max_streams
     for (int k = 0; k < 2; ++k) {
       if (hipHostMalloc((void**)&W.buf[k], kStageBytes, hipHostMallocDefault) != hipSuccess ||
           hipEventCreateWithFlags(&W.ev[k], hipEventDisableTiming) != hipSuccess ||
-          (k == 0 && (hipHostMalloc((void**)&W.small, kPackDocs * 8, hipHostMallocDefault) !=
+          (k == 0 && (hipHostMalloc((void**)&W.small, wc_server::kSmallWords * 8, hipHostMallocDefault) !=
                           hipSuccess ||
-                      hipMalloc((void**)&W.d_small, kPackDocs * 8) != hipSuccess))) {
+                      hipMalloc((void**)&W.d_small, kPackDocs * 32) != hipSuccess))) {
         release_staging(S);
         for (auto x : S->streams) hipStreamDestroy(x);
         hipFree(S->pool_mem);
@@ -525,7 +609,13 @@ wc_status wc_server_submit(wc_server* S, const uint8_t* text, uint64_t len,
   o.tuning = nullptr;
   wc_status st = wc_count_plan(len, n_docs, &o, &p);
   if (st != WC_OK) return st;
-  if (p.workspace_bytes + len + (n_docs + 1) * 8 + 1024 > S->budget) return WC_ENOMEM;
+  auto fits = [&] { return p.workspace_bytes + len + (n_docs + 1) * 8 + 1024 <= S->budget; };
+  if (!fits() && len < (256ull << 20)) {
+    // below the two-pass size the one-pass kernel needs less memory than the partitioned ones
+    o.debug_flags |= WC_DEBUG_DIRECT;
+    if ((st = wc_count_plan(len, n_docs, &o, &p)) != WC_OK) return st;
+  }
+  if (!fits()) return WC_ENOMEM;
   auto R = std::make_shared<Request>();
   R->len = len;
   if (text_on_device == WC_TEXT_DEVICE) R->dev_text = text;

@@ -994,6 +994,31 @@ def test_server_release_during_merge():
     srv.close()
 
 
+@pytest.mark.parametrize("where", ["host", "device", "mixed"])
+def test_server_packed_group_edges(where):
+    """A burst of requests around the packing limit of 32 KiB (0, 1 and 7 bytes among them, more
+    than one group's worth) from host and device memory, at odd addresses: each resident table is
+    the oracle's, and so is the merge of all."""
+    base = synth.generate("plain-1MB").text.numpy()
+    sizes = ([0, 1, 7, 8, 9, 4095, 32_767, 32_768, 32_769, 49_153] + [333 * i % 3001 for i in range(90)])
+    texts = [base[1000 * i + 3:1000 * i + 3 + n].tobytes() for i, n in enumerate(sizes)]
+    srv = wc.Server(mem_budget=256 << 20, max_streams=2)
+    keep = to_dev(b"".join([b"q" * 5] + texts))[0]
+    pos = 5 + np.concatenate([[0], np.cumsum(sizes)])
+    ids = []
+    for i, t in enumerate(texts):
+        dev = where == "device" or (where == "mixed" and i % 2)
+        ids.append(srv.submit(keep[pos[i]:pos[i + 1]] if dev and t else t))
+    m = srv.merge(ids)
+    total = collections.Counter()
+    for t, i in zip(texts, ids):
+        r, want = srv.wait(i), oracle.count(t)
+        assert wc.result_to_dict(r) == want.as_dict() and r.total_tokens == want.total
+        total.update(want.as_dict())
+    assert wc.result_to_dict(srv.wait(m)) == dict(total)
+    srv.close()
+
+
 def test_server_budget_errors():
     srv = wc.Server(mem_budget=4 << 20, max_streams=1)
     with pytest.raises(wc.WcError) as e:
