@@ -1101,7 +1101,7 @@ void layout_topk(const wc_result* const* t, uint32_t C, uint32_t k, void* ws, To
   L->k = k;
   L->S = next_pow2(std::max<uint64_t>(4096, 2 * n));
   L->n_blocks = (L->S + kExportSpan - 1) / kExportSpan;
-  L->word_cap = std::max<uint64_t>(wb, 16);
+  L->word_cap = std::max<uint64_t>(wb, 16) + 8;  // (eight bytes are read from any word's first)
   L->row_word_cap = std::max<uint64_t>(std::min<uint64_t>(wb, (uint64_t)C * wb), 16);
   Bump B(ws);
   L->hdr = B.take<Header>(sizeof(Header));
@@ -1119,11 +1119,12 @@ void layout_topk(const wc_result* const* t, uint32_t C, uint32_t k, void* ws, To
     L->list_len[i] = B.take<uint32_t>(C * topk_list_runs(n) * 4);
   }
   L->sizes = B.take<TopkSizes>(sizeof(TopkSizes));
-  L->row_woff = B.take<uint64_t>(((uint64_t)C * k + 1) * 8);
-  L->row_words = B.take<uint8_t>(L->row_word_cap * C);
+  // the rows side by side, their words last: one copy takes them to the host
   L->row_nc = B.take<uint64_t>((uint64_t)C * k * 8);
   L->row_nr = B.take<uint64_t>((uint64_t)C * k * 8);
   L->row_score = B.take<double>((uint64_t)C * k * 8);
+  L->row_woff = B.take<uint64_t>(((uint64_t)C * k + 1) * 8);
+  L->row_words = B.take<uint8_t>(L->row_word_cap * C);
   L->total = B.off;
 }
 

@@ -545,18 +545,21 @@ def topk_ratio(tables: Sequence[Table], k: int, min_count: int = 1, stream=None)
                              ctypes.byref(out), _stream_handle(stream))
     if st != WC_OK:
         raise WcError(st, "wc_topk_ratio")
-    base = ws.data_ptr()
+    rows = C * k
+    # the rows lie side by side in the workspace, their words last: one copy to the host
+    first = min(int(p) for p in (out.d_word_offsets, out.d_n_c, out.d_n_rest, out.d_score))
+    begin = first - ws.data_ptr()
+    end = max(int(out.d_words) + int(out.word_bytes), int(out.d_word_offsets) + 8 * (rows + 1))
+    host = ws[begin:begin + end - first].cpu().numpy()
 
     def view(ptr, nbytes, dtype):
-        off = int(ptr) - base
-        return ws[off:off + nbytes].view(dtype) if nbytes else torch.empty(0, dtype=dtype)
+        return host[int(ptr) - first:int(ptr) - first + nbytes].view(dtype)
 
-    rows = C * k
-    woff = view(out.d_word_offsets, 8 * (rows + 1), torch.int64).cpu().numpy()
-    wbytes = view(out.d_words, int(out.word_bytes), torch.uint8).cpu().numpy().tobytes()
-    nc = view(out.d_n_c, 8 * rows, torch.int64).cpu().numpy()
-    nr = view(out.d_n_rest, 8 * rows, torch.int64).cpu().numpy()
-    sc = view(out.d_score, 8 * rows, torch.float64).cpu().numpy()
+    woff = view(out.d_word_offsets, 8 * (rows + 1), np.int64)
+    wbytes = view(out.d_words, int(out.word_bytes), np.uint8).tobytes()
+    nc = view(out.d_n_c, 8 * rows, np.int64)
+    nr = view(out.d_n_rest, 8 * rows, np.int64)
+    sc = view(out.d_score, 8 * rows, np.float64)
     words, ncs, nrs, scs = [], [], [], []
     for c in range(C):
         r = int(out.n_rows[c])
