@@ -152,7 +152,8 @@ bool resolve_tuning(const wc_tuning* t, Tune* out) {
   u.pct = t && t->lds_load_pct ? t->lds_load_pct : 0;
   u.flush_at = (uint32_t)((uint64_t)u.lds * pct / 100);
   u.chunk = t && t->chunk_bytes ? t->chunk_bytes : (uint32_t)kWin;
-  if (!is_pow2(u.chunk) || u.chunk < kMinWin || u.chunk > (1u << 20)) return false;
+  if (t && t->chunk_bytes && !is_pow2(u.chunk)) return false;
+  if (u.chunk < kMinWin || u.chunk > (1u << 20)) return false;
   const uint32_t dk = t ? t->direct_kib : 0u;
   u.direct_kib = dk == WC_DIRECT_NEVER ? 0u : dk ? dk : (u.chunk >> 10) * 9 / 4;
   *out = u;
@@ -297,9 +298,8 @@ void layout_docs(uint64_t len, uint64_t n_docs, const wc_opts* o, void* ws, DocL
 DocParams doc_params(const DocLayout& L, const wc_opts* o, uint32_t lds, uint32_t pct,
                      uint32_t chunk, uint32_t direct_kib) {
   DocParams P;
-  P.lds_cap = (uint32_t)((uint64_t)lds * (pct ? pct : 85) / 100);
-  if (P.lds_cap < 1) P.lds_cap = 1;
-  if (P.lds_cap > lds - lds / 8) P.lds_cap = lds - lds / 8;
+  // (a round's keys at least: an empty table takes them whatever was asked for)
+  P.lds_cap = std::max<uint32_t>((uint32_t)((uint64_t)lds * (pct ? pct : 100) / 100), 128);
   P.direct_kib = direct_kib;
   P.win_bytes = chunk;
   P.task = L.task;
@@ -310,9 +310,6 @@ DocParams doc_params(const DocLayout& L, const wc_opts* o, uint32_t lds, uint32_
   P.words = L.words;
   P.counts = L.counts;
   P.count_bytes = o->count_bytes;
-  P.lds_entries = lds;
-  P.rc_entries = recount_entries();
-  P.pad1 = 0;
   P.docs = L.docs;
   P.doc_ptr = L.doc_ptr;
   P.doc_len = L.doc_len;
@@ -322,7 +319,6 @@ DocParams doc_params(const DocLayout& L, const wc_opts* o, uint32_t lds, uint32_
   P.over_docs = L.over_docs;
   P.over_sorted = L.over_sorted;
   P.arena_slots = L.arena_slots;
-  P.key_mask = key_mask_of(o);
   P.count_bias = o->debug_count_bias;
   return P;
 }
@@ -483,7 +479,7 @@ hipError_t ensure_smem_attr() {
     if (e == hipSuccess) e = set_count_smem(256, 160 * 1024 - 24 * 1024);
     if (e == hipSuccess) e = set_global_smem(kDictMax, kReduceLds);
     if (e == hipSuccess) e = set_part_smem();
-    if (e == hipSuccess) e = set_doc_smem(doc_dyn(kDocLds));
+    if (e == hipSuccess) e = set_doc_smem();
     return e;
   }();
   return once;
@@ -580,7 +576,7 @@ wc_status wc_count(const uint8_t* d_corpus, uint64_t corpus_len, const uint64_t*
     uint32_t grid = tu.grid ? tu.grid : (uint32_t)device_cus();
     DocParams P = doc_params(D, opts, lds, tu.pct, tu.chunk, tu.direct_kib);
     if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
-    HIPCHK(launch_docs(P, grid, doc_dyn(lds), s));
+    HIPCHK(launch_docs(P, grid, s));
     if (tm.on) HIPCHK(hipEventRecord(tm.b, s));
     HostBox box;
     HIPCHK(box.read(D.hdr, s));
@@ -591,7 +587,7 @@ wc_status wc_count(const uint8_t* d_corpus, uint64_t corpus_len, const uint64_t*
     out->total_tokens = h.total_tokens;
     out->n_docs = n_docs;
     out->table_slots = std::max<uint64_t>(h.arena_next, D.arena_slots);
-    out->stats[3] = h.over_n;
+    out->stats[3] = h.over_n + h.stat[3];
     out->count_bytes = opts->count_bytes;
     out->mode = WC_PER_DOC;
     out->d_word_offsets = D.woff;
@@ -1328,7 +1324,7 @@ wc_status wc_batch_run(wc_batch* b, const uint8_t* d_corpus, uint64_t corpus_len
     hipError_t e = hipMemcpyAsync(b->D.task, b->h_task, sizeof(DocTask), hipMemcpyHostToDevice,
                                   b->bs);
     if (e == hipSuccess) e = launch_fill_zero(b->D.hdr, sizeof(Header), b->bs);
-    if (e == hipSuccess) e = launch_docs(P, b->grid, doc_dyn(b->lds), b->bs);
+    if (e == hipSuccess) e = launch_docs(P, b->grid, b->bs);
     if (e == hipSuccess)
       e = hipMemcpyAsync(b->h_hdr, b->D.hdr, sizeof(Header), hipMemcpyDeviceToHost, b->bs);
     hipGraph_t g = nullptr;
@@ -1352,7 +1348,7 @@ wc_status wc_batch_run(wc_batch* b, const uint8_t* d_corpus, uint64_t corpus_len
   out->total_tokens = h.total_tokens;
   out->n_docs = n_docs;
   out->table_slots = std::max<uint64_t>(h.arena_next, b->D.arena_slots);
-  out->stats[3] = h.over_n;
+  out->stats[3] = h.over_n + h.stat[3];
   out->count_bytes = b->opts.count_bytes;
   out->mode = WC_PER_DOC;
   out->d_word_offsets = b->D.woff;

@@ -139,7 +139,7 @@ hipError_t launch_part_single(const PartParams& P, hipStream_t s);
 constexpr uint64_t kWin = 32 * 1024;   // default bytes per work item window
 constexpr uint64_t kMinWin = 16 * 1024;
 constexpr uint32_t kDocW = 256;        // documents per sub-window
-constexpr uint32_t kDocLds = 4096;     // LDS table entries (20 bytes each, beside 8192 slots)
+constexpr uint32_t kDocLds = 4608;     // LDS table entries (20 bytes each, beside 8192 slots)
 
 struct DocTask {           // device-resident: every size the per-document kernels read
   const uint8_t* corpus;
@@ -158,30 +158,23 @@ struct DocParams {
   void* counts;
   uint32_t count_bytes;
   uint32_t lds_entries;
-  uint32_t lds_cap;        // live LDS entries before relief
-  uint32_t direct_kib;     // documents above this many KiB (0: none) skip the first pass
+  uint32_t lds_cap;        // entries used before keys are spilled
+  uint32_t direct_kib;     // documents above this many KiB, and a window, are queued first (0: none)
   uint64_t win_bytes;      // work item window
   uint64_t* docs;          // [cap_e]
   uint64_t* doc_ptr;       // [n_docs]
   uint64_t* doc_len;       // [n_docs]
   uint64_t cap_e, cap_b;
-  Slot* arena;             // private tables of large documents
-  uint64_t* over_docs;     // [n_docs] documents for the second pass, as queued
+  Slot* arena;             // spilled keys and tables set aside
+  uint64_t* over_docs;     // [n_docs] documents counted from the queue, as found
   uint64_t* over_sorted;   // [n_docs] the same, largest first
   uint64_t arena_slots;
-  uint64_t key_mask;
   uint64_t count_bias;     // added to every exported count (debug; 0 normally)
-  uint32_t rc_entries;     // second pass: LDS table entries (all of them usable)
-  uint32_t pad1;
 };
-// second-pass queue entries: document index (bits 0-55), size class while the queue is sorted
-// (bits 56-62), queued without a first count (bit 63)
-constexpr uint64_t kDirectDoc = 1ull << 63;
+// queue entries: document index (bits 0-55), size class while the queue is sorted (bits 56-62)
 constexpr uint64_t kDocIdMask = (1ull << 56) - 1;
-size_t doc_dyn(uint32_t entries);  // dynamic LDS of the document kernel
-uint32_t recount_entries();         // LDS entries of its second pass (the most that fit)
-hipError_t set_doc_smem(size_t dyn);
-hipError_t launch_docs(const DocParams& P, uint32_t grid, size_t dyn, hipStream_t s);
+hipError_t set_doc_smem();
+hipError_t launch_docs(const DocParams& P, uint32_t grid, hipStream_t s);
 
 hipError_t launch_count(const CountParams& P, bool per_doc, uint32_t grid, uint32_t block,
                         size_t dyn, hipStream_t s);

@@ -1100,6 +1100,39 @@ def test_per_doc_direct_second_pass(direct_kib):
     b.close()
 
 
+def _group_texts(kind, rng):
+    """Documents at the edges of the per-document kernel's groups, tables and spilled parts."""
+    words = [bytes(rng.choice(list(b"abcdefgh"), rng.integers(1, 24))) for _ in range(3000)]
+
+    def doc(n):  # n bytes; words of neighbouring documents touch
+        out, size = [], 0
+        while size < n:
+            out.append(words[rng.integers(len(words))])
+            size += len(out[-1]) + 1
+        return b" ".join(out)[:n]
+
+    if kind == "many":  # groups hold 256 documents; empty ones share their start
+        return [doc(int(n)) for n in rng.integers(0, 40, 255 + 256 + 257 + 600)]
+    if kind == "edges":  # lengths around the windows and the size that is counted on its own
+        sizes = [k * 1024 + d for k in (16, 32, 48, 64, 72, 96) for d in (-1, 0, 1)]
+        return [doc(int(n)) for s in sizes for n in (s, rng.integers(0, 300), 1, 0)]
+    # "vocabulary": more distinct words than a table, and than 256 parts of a 256-entry one, holds
+    many = [b"%x" % (i * 2654435761 % (1 << 34)) + b"q" * (i % 5) * 6 for i in range(90_000)]
+    order = rng.permutation(np.concatenate([np.arange(90_000), rng.integers(0, 500, 60_000)]))
+    return [doc(3000), b" ".join(many[i] for i in order), doc(1), b"", doc(200_000), doc(5000)]
+
+
+@pytest.mark.parametrize("lds", [0, 256])
+@pytest.mark.parametrize("kind", ["many", "edges", "vocabulary"])
+def test_per_doc_groups_and_spilled_words(kind, lds):
+    docs = _group_texts(kind, np.random.default_rng(7))
+    text, off = join_docs(docs)
+    kw = {"tuning": wc.make_tuning(lds_entries=lds)} if lds else {}
+    check(text, off, per_doc=True, debug_flags=wc.WC_DEBUG_DOCS, **kw)
+    if kind == "vocabulary":  # too little room for the spilled words at first
+        check(text, off, per_doc=True, debug_flags=wc.WC_DEBUG_DOCS, table_slots=1 << 12, **kw)
+
+
 @pytest.mark.parametrize("chunk", [16 << 10, 32 << 10, 256 << 10, 1 << 20])
 def test_per_doc_chunk_sizes(chunk):
     c = synth.generate("batched-100k", scale=0.002)
