@@ -89,16 +89,15 @@ typedef struct wc_tuning {
   uint32_t flush_policy;  /* WC_FLUSH_ALL or WC_FLUSH_BYPASS */
   uint32_t grid_blocks;   /* workgroups in the count launch (0 = 2 per CU) */
   uint32_t lds_load_pct;  /* LDS table load at which it is flushed (one-pass kernel) or at
-                             which a document counts as overflowed (document-centric kernel:
-                             it is then counted again with a private table); 0 = default
-                             (50 % for the one-pass kernel, 85 % for the document-centric) */
+                             which further words are spilled to device memory (document-
+                             centric kernel); 0 = default (50 % for the one-pass kernel, all
+                             of it for the document-centric) */
   uint32_t chunk_bytes;   /* per-document mode: bytes per work item, power of two in
-                             16 KiB..1 MiB (0 = 32 KiB) */
-  uint32_t direct_kib;    /* per-document mode, document-centric kernel: a document longer
-                             than chunk_bytes and than this many KiB skips the first,
-                             optimistic count (in which it would likely overflow the LDS
-                             table) and is counted once, by the second pass (0 = 9/4 of
-                             chunk_bytes; WC_DIRECT_NEVER = no document skips it) */
+                             16 KiB..1 MiB (0 = by the size of the text, 16 to 48 KiB) */
+  uint32_t direct_kib;    /* per-document mode, document-centric kernel: documents longer
+                             than chunk_bytes and than this many KiB are counted before all
+                             others, largest first (0 = 9/4 of chunk_bytes, 72 KiB without
+                             it; WC_DIRECT_NEVER = none) */
 } wc_tuning;
 
 #define WC_DIRECT_NEVER 0xffffffffu

@@ -151,11 +151,10 @@ bool resolve_tuning(const wc_tuning* t, Tune* out) {
   if (pct > 100) return false;
   u.pct = t && t->lds_load_pct ? t->lds_load_pct : 0;
   u.flush_at = (uint32_t)((uint64_t)u.lds * pct / 100);
-  u.chunk = t && t->chunk_bytes ? t->chunk_bytes : (uint32_t)kWin;
-  if (t && t->chunk_bytes && !is_pow2(u.chunk)) return false;
-  if (u.chunk < kMinWin || u.chunk > (1u << 20)) return false;
+  u.chunk = t ? t->chunk_bytes : 0;  // 0: by the size of the text (window_bytes)
+  if (u.chunk && (!is_pow2(u.chunk) || u.chunk < kMinWin || u.chunk > (1u << 20))) return false;
   const uint32_t dk = t ? t->direct_kib : 0u;
-  u.direct_kib = dk == WC_DIRECT_NEVER ? 0u : dk ? dk : (u.chunk >> 10) * 9 / 4;
+  u.direct_kib = dk == WC_DIRECT_NEVER ? 0u : dk ? dk : u.chunk ? (u.chunk >> 10) * 9 / 4 : kDirectKib;
   *out = u;
   return true;
 }
@@ -246,10 +245,10 @@ int64_t base_offset(const uint8_t* corpus) {
 
 // Per-document count (document-centric kernel): outputs and private tables of large documents.
 struct DocLayout {
-  uint64_t n_win, cap_e, cap_b, arena_slots;
+  uint64_t cap_e, cap_b, arena_slots;
   Header* hdr;
   DocTask* task;
-  uint64_t* win_doc;
+  uint64_t* items;
   uint64_t* woff;
   uint8_t* words;
   void* counts;
@@ -274,7 +273,6 @@ bool use_doc_kernel(const wc_opts* o, uint64_t len, uint64_t n_docs) {
 }
 
 void layout_docs(uint64_t len, uint64_t n_docs, const wc_opts* o, void* ws, DocLayout* L) {
-  L->n_win = len / kMinWin + 1;  // room for any work-item size
   L->cap_b = o->word_bytes_cap ? o->word_bytes_cap : std::max<uint64_t>(len / 4, 4096);
   L->cap_e = L->cap_b / 3 + n_docs + 64;
   L->arena_slots = o->table_slots ? o->table_slots
@@ -282,7 +280,7 @@ void layout_docs(uint64_t len, uint64_t n_docs, const wc_opts* o, void* ws, DocL
   Bump B(ws);
   L->hdr = B.take<Header>(sizeof(Header));
   L->task = B.take<DocTask>(sizeof(DocTask));
-  L->win_doc = B.take<uint64_t>((L->n_win + 1) * 8);
+  L->items = B.take<uint64_t>(std::max<uint64_t>(n_docs, 1) * 8);
   L->woff = B.take<uint64_t>((L->cap_e + 1) * 8);
   L->words = B.take<uint8_t>(L->cap_b);
   L->counts = B.take<uint8_t>(L->cap_e * o->count_bytes);
@@ -296,16 +294,16 @@ void layout_docs(uint64_t len, uint64_t n_docs, const wc_opts* o, void* ws, DocL
 }
 
 DocParams doc_params(const DocLayout& L, const wc_opts* o, uint32_t lds, uint32_t pct,
-                     uint32_t chunk, uint32_t direct_kib) {
+                     uint32_t chunk, uint32_t direct_kib, uint32_t grid) {
   DocParams P;
   // (a round's keys at least: an empty table takes them whatever was asked for)
   P.lds_cap = std::max<uint32_t>((uint32_t)((uint64_t)lds * (pct ? pct : 100) / 100), 128);
   P.direct_kib = direct_kib;
   P.win_bytes = chunk;
+  P.grid = grid;
   P.task = L.task;
   P.hdr = L.hdr;
-  P.win_doc = L.win_doc;
-  P.max_win = L.n_win;
+  P.items = L.items;
   P.word_offsets = L.woff;
   P.words = L.words;
   P.counts = L.counts;
@@ -574,9 +572,9 @@ wc_status wc_count(const uint8_t* d_corpus, uint64_t corpus_len, const uint64_t*
     HIPCHK(hipMemcpyAsync(D.task, &task, sizeof(task), hipMemcpyHostToDevice, s));
     HIPCHK(launch_fill_zero(D.hdr, sizeof(Header), s));
     uint32_t grid = tu.grid ? tu.grid : (uint32_t)device_cus();
-    DocParams P = doc_params(D, opts, lds, tu.pct, tu.chunk, tu.direct_kib);
+    DocParams P = doc_params(D, opts, lds, tu.pct, tu.chunk, tu.direct_kib, grid);
     if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
-    HIPCHK(launch_docs(P, grid, s));
+    HIPCHK(launch_docs(P, s));
     if (tm.on) HIPCHK(hipEventRecord(tm.b, s));
     HostBox box;
     HIPCHK(box.read(D.hdr, s));
@@ -1320,11 +1318,11 @@ wc_status wc_batch_run(wc_batch* b, const uint8_t* d_corpus, uint64_t corpus_len
     HIPCHK(hipStreamBeginCapture(b->bs, hipStreamCaptureModeThreadLocal));
     Tune tu;
     resolve_tuning(b->opts.tuning, &tu);
-    DocParams P = doc_params(b->D, &b->opts, b->lds, tu.pct, tu.chunk, tu.direct_kib);
+    DocParams P = doc_params(b->D, &b->opts, b->lds, tu.pct, tu.chunk, tu.direct_kib, b->grid);
     hipError_t e = hipMemcpyAsync(b->D.task, b->h_task, sizeof(DocTask), hipMemcpyHostToDevice,
                                   b->bs);
     if (e == hipSuccess) e = launch_fill_zero(b->D.hdr, sizeof(Header), b->bs);
-    if (e == hipSuccess) e = launch_docs(P, b->grid, b->bs);
+    if (e == hipSuccess) e = launch_docs(P, b->bs);
     if (e == hipSuccess)
       e = hipMemcpyAsync(b->h_hdr, b->D.hdr, sizeof(Header), hipMemcpyDeviceToHost, b->bs);
     hipGraph_t g = nullptr;

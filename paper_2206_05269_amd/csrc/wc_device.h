@@ -71,6 +71,29 @@ struct Header {
 };
 static_assert(sizeof(Header) == 128, "header layout");
 
+// a value that is the same in all lanes, in scalar registers
+WC_DEV uint64_t uniform64(uint64_t v) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(v >> 32)) << 32) |
+         (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
+}
+
+// A pointer into device memory that was itself read from memory. Without the cast its accesses
+// are flat ones, which count as LDS accesses too: every wait for an LDS read then also waits for
+// the text loads in flight.
+// (The empty asm keeps the two casts from being taken as none.)
+template <class T>
+WC_DEV T* as_global(T* p) {  // p: the same in all lanes
+  __attribute__((address_space(1))) T* g = (__attribute__((address_space(1))) T*)uniform64((uint64_t)p);
+  __asm__("" : "+s"(g));
+  return (T*)g;
+}
+template <class T>
+WC_DEV T* as_global_lane(T* p) {
+  __attribute__((address_space(1))) T* g = (__attribute__((address_space(1))) T*)p;
+  __asm__("" : "+v"(g));
+  return (T*)g;
+}
+
 // ---------------------------------------------------------------------------------------
 // atomics (device scope, relaxed)
 // ---------------------------------------------------------------------------------------

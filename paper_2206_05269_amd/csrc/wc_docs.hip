@@ -1,11 +1,11 @@
 // Per-document count (one table per document; the paper's per-document dictionaries of
 // Section 3.1, before the grouping of Section 3.3).
 //
-// Work. The corpus is cut into windows of `win_bytes`; a window owns the documents whose first
-// byte lies in it. A document longer than the window is always its last one; such documents are
-// counted alone, and those longer than the size limit (direct_kib) are queued before all windows,
-// largest first. Persistent workgroups (1024 threads, one per CU) take queue positions: first the
-// queued documents, then the windows, up to kDocW documents of a window at a time ("group").
+// Work. The corpus is cut into windows; a window owns the documents whose first byte lies in it. A
+// document longer than the window is always its last one; such documents are counted alone, and
+// those longer than the size limit (direct_kib) too, largest first and before all others. The rest
+// of a window is counted up to kDocW documents at a time ("group"). doc_plan_kernel lists the
+// groups; persistent workgroups (1024 threads, one per CU) take them from a queue.
 //
 // Counting. A group's text is scanned by the workgroup's waves, each on a contiguous run of 1 KiB
 // stripes and on its own (no workgroup barrier inside the scan). A token's document is its index r
@@ -29,14 +29,17 @@
 // then the entries in LDS, and those set aside, are written, so every document's entries and word
 // bytes are contiguous and the word offsets stay a valid CSR over the whole output.
 //
-// What a group waits for is taken early: thread 0 takes the next queue position when a group
-// begins, its documents and their offsets are read while the current group's entries are placed
-// and written, so that a group begins with its text loads.
+// What a group waits for is taken early: the queue position after the next group's is asked for by
+// the first wave that ends its scan, its offsets are read while this group's entries find their
+// places, and the next group's first text is loaded before this group's entries are written.
 //
-// The scan is bound by instructions: about 1,000 vector and 500 scalar ones per 1 KiB
-// stripe and wave, vector units 60 % busy over the kernel. 100,000 documents (lognormal, median
-// 16 KiB, 2.7 GB, 119 million entries), before as two passes with tables of 4,096 entries in LDS
-// and in device memory: 12.7 -> 7.5 ms; 2,000 documents of 2 to 20 KiB: 181 -> 100 us.
+// Bound by instructions: of 16.3 million cycles per CU for the text below vector units are busy for
+// 58 %; a third is the table (and what spills), a fifth taking the words apart, a tenth writing the
+// output, a sixth finding words, and the rest the waits between groups, about 5 us each. Two
+// workgroups per CU with half the table each were slower (more and smaller groups, more spills).
+// 100,000 documents (lognormal, median 16 KiB, 2.7 GB, 119 million entries), before as two passes
+// with tables of 4,096 entries in LDS and in device memory: 12.7 -> 6.6 ms; 2,000 documents of 2 to
+// 20 KiB: 181 -> 96 us.
 //
 // Every size the kernels need is read from a device-side task description, so a whole call
 // can be captured once in a HIP graph and replayed for other corpora.
@@ -51,6 +54,7 @@ namespace wc {
 namespace {
 
 constexpr int kBlk = 1024;
+constexpr uint32_t kDocSlots = 8192;
 constexpr uint32_t kWaves = kBlk / 64;
 constexpr uint32_t kText = kStripe + 32;      // per wave: stripe, the 16 bytes after it, padding
 constexpr uint32_t kList = 256;               // starts of a stripe listed at a time
@@ -98,42 +102,50 @@ WC_DEV uint4 without_doc(uint4 k) {
 
 }  // namespace
 
-constexpr size_t kDyn = (size_t)kRedSlots * 4 + (size_t)kDocLds * 20 + (size_t)kWaves * kText;
+constexpr size_t kDyn = (size_t)kDocSlots * 4 + (size_t)kDocLds * 20 + (size_t)kWaves * kText;
 
-__global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
+// (the parameters are read with args(): as an argument by name they would be loaded once, at the
+// start, and held or spilled over the scan: 50 of its instructions per stripe read such values back)
+__global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
+  typedef const __attribute__((address_space(4))) DocParams* Args;
+  auto args = []() -> Args {
+    Args a = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(a));
+    return a;
+  };
+
   extern __shared__ __align__(16) uint8_t s_dyn[];
   __shared__ uint32_t s_list[kWaves][kListWords];  // starts (16 bits each), then the end bitmap
   __shared__ uint32_t s_bnd[kWaves][kEnds];        // document starts of a stripe
   __shared__ uint4 s_lenmask[17];
-  __shared__ uint64_t s_doff[2][kDocW + 1];        // the group's document offsets, and the next group's
+  __shared__ uint64_t s_doff[3][kDocW + 1];        // document offsets of the group and the next two
   __shared__ unsigned long long s_dcur[kDocW];     // places taken: (entries << 32 | bytes)
-  __shared__ uint64_t s_sum[4];
-  __shared__ uint64_t s_out, s_next;
+  __shared__ uint32_t s_sum[4];
+  __shared__ uint64_t s_out;
   __shared__ unsigned long long s_tokens;
-  __shared__ uint32_t s_nent, s_spill;
+  __shared__ uint32_t s_nent, s_spill, s_next, s_done;
   __shared__ uint32_t s_region[16 * kClassesMax];  // first unit + 1 (0: not taken yet)
   __shared__ uint32_t s_part[kDocParts];
   __shared__ uint32_t s_used, s_lost, s_at;         // virtual slots used; some region was refused
 
   const uint32_t tid = threadIdx.x, lane = tid & 63;
   const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
-  Header* const hdr = P.hdr;
+  auto hdr_of = [&]() -> Header* { return as_global(args()->hdr); };
 
-  const uint8_t* const corpus = P.task->corpus;
-  const uint64_t len = P.task->len;
-  const uint64_t* const offsets = P.task->offsets;
-  const uint64_t n_docs = P.task->n_docs;
+  const uint8_t* const corpus = as_global(as_global(args()->task)->corpus);
+  const uint64_t len = uniform64(as_global(args()->task)->len);
+  auto offset_at = [&](uint32_t d) -> uint64_t { return as_global(as_global(args()->task)->offsets)[d]; };
   const int64_t base_off = -(int64_t)((uintptr_t)corpus & 15);
-  const uint64_t win = P.win_bytes, direct = (uint64_t)P.direct_kib << 10;
-  const uint64_t n_win = len / win + 1, n_big = hdr->over_n;
-  if ((ld_relaxed32(&hdr->flags) & kFlagBadOffsets) || n_win > P.max_win) return;
+  const uint32_t n_big = (uint32_t)uniform64(hdr_of()->over_n);
+  const uint32_t n_items = n_big + (uint32_t)uniform64(hdr_of()->over_next);
+  if (ld_relaxed32(&hdr_of()->flags) & kFlagBadOffsets) return;
 
-  PartTable<uint32_t> T;
+  PartTable<uint32_t, kDocSlots> T;
   T.slot = (uint32_t*)s_dyn;
-  T.key = (uint4*)(T.slot + kRedSlots);
+  T.key = (uint4*)(T.slot + kDocSlots);
   T.cnt = (uint32_t*)(T.key + kDocLds);
   T.n = &s_nent;
-  T.cap = min(P.lds_cap, kDocLds);
+  T.cap = (uint32_t)uniform64(min(args()->lds_cap, kDocLds));
   uint8_t* const my_txt = (uint8_t*)(T.cnt + kDocLds) + wv * kText;
   uint16_t* const my_starts = (uint16_t*)s_list[wv];
   uint32_t* const my_ends = s_list[wv] + kList / 2;
@@ -144,25 +156,11 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
   for (uint32_t i = tid; i < 16 * kClassesMax; i += kBlk) s_region[i] = 0;
   if (tid == 0) s_lost = 0;
   init_len_masks(s_lenmask, tid, kBlk);
+  for (uint32_t r = tid; r < kDocW; r += kBlk) s_dcur[r] = 0;
   auto clear_slots = [&]() {
-    for (uint32_t i = tid; i < kRedSlots / 4; i += kBlk) ((uint4*)T.slot)[i] = make_uint4(0, 0, 0, 0);
-    if (tid == 0) {
-      s_nent = 0;
-      s_spill = 0;
-    }
+    for (uint32_t i = tid; i < kDocSlots / 4; i += kBlk) ((uint4*)T.slot)[i] = make_uint4(0, 0, 0, 0);
   };
-
-  // the documents of queue position q
-  uint64_t da = 0, db = 0;
-  auto find_item = [&](uint64_t q) {
-    if (q < n_big) {
-      da = P.over_sorted[q] & kDocIdMask;
-      db = da + 1;
-    } else {
-      da = P.win_doc[q - n_big];
-      db = min(P.win_doc[q - n_big + 1], n_docs);
-    }
-  };
+  clear_slots();
 
   // ---- device memory of the group ----------------------------------------------------------
   auto region_of = [&](uint32_t v, uint32_t* start) -> uint32_t {
@@ -174,7 +172,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
   auto slot_at = [&](uint32_t v) -> Slot* {
     uint32_t start;
     const uint32_t i = region_of(v, &start);
-    return P.arena + (uint64_t)(s_region[i] - 1) * kUnit + (v - start);
+    return as_global(args()->arena) + (uint64_t)(s_region[i] - 1) * kUnit + (v - start);
   };
   // the region of virtual slot v is taken by one lane; the others wait for it. False: refused
   auto ensure = [&](uint32_t v) -> bool {
@@ -183,8 +181,8 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
     uint32_t r = atomicCAS(&s_region[i], 0u, kTaking);
     if (r == 0) {
       const uint64_t size = (uint64_t)kUnit << (i / 16);
-      const uint64_t at = atomicAdd((unsigned long long*)&hdr->arena_next, (unsigned long long)size);
-      r = at + size <= P.arena_slots ? (uint32_t)(at / kUnit) + 1 : kNoRegion;
+      const uint64_t at = atomicAdd((unsigned long long*)&hdr_of()->arena_next, (unsigned long long)size);
+      r = at + size <= args()->arena_slots ? (uint32_t)(at / kUnit) + 1 : kNoRegion;
       atomicExch(&s_region[i], r);
     }
     while (r == kTaking) {
@@ -192,7 +190,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
       r = atomicOr(&s_region[i], 0u);
     }
     if (r == kNoRegion) {
-      or32(&hdr->flags, kFlagWordCap);
+      or32(&hdr_of()->flags, kFlagWordCap);
       atomicOr(&s_lost, 1u);
     }
     return r != kNoRegion;
@@ -245,47 +243,60 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
 
   // ---- the scan of documents [0, nd) of the group at doff ----------------------------------
   uint32_t tokens = 0;
-  auto scan = [&](const uint64_t* doff, uint32_t nd) {
-    const int64_t A = (int64_t)doff[0], B = (int64_t)doff[nd];
+  // this wave's stripes of the text [A, B) (equal parts in bytes, with a part of a stripe at the end
+  // of each, were no faster: the waves with a stripe less leave their issue slots to the others)
+  struct Run {
+    int64_t first;  // position of the first
+    uint32_t n;
+  };
+  auto run_of = [&](int64_t A, int64_t B) -> Run {
     const int64_t k0 = (A - base_off) / (int64_t)kStripe;
     const int64_t k1 = B > A ? (B - base_off + (int64_t)kStripe - 1) / (int64_t)kStripe : k0;
     const int64_t per = (k1 - k0 + kWaves - 1) / kWaves;
     const int64_t ka = min(k0 + (int64_t)wv * per, k1);
-    const uint32_t nsw = (uint32_t)(min(ka + per, k1) - ka);
-    auto stripe_pos = [&](uint32_t i) -> int64_t { return base_off + (ka + i) * (int64_t)kStripe; };
-    const uint4 blank = make_uint4(0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u);
-    auto load = [&](uint32_t i) -> uint4 {
-      uint4 v = blank;
-      if (i > nsw || nsw == 0) return v;
-      const int64_t p = stripe_pos(i);
-      if (i < nsw && p >= 0 && p + (int64_t)kStripe <= (int64_t)len) v = load_stream16(corpus + p + lane * 16);
-      else if (i < nsw || lane == 0) v = load_text16(corpus, len, p + lane * 16);
-      return v;
-    };
-    const uint4 raw0 = load(0);
-    uint4 r1 = load(1), r2 = load(2);
-    uint32_t before = 0;
-    if (nsw) before = load_text4(corpus, len, stripe_pos(0) - 4);
-    clear_slots();
-    if (tid == 0) s_used = 0;
-    for (uint32_t r = tid; r < nd; r += kBlk) s_dcur[r] = 0;
-    __syncthreads();
+    return Run{base_off + ka * (int64_t)kStripe, (uint32_t)(min(ka + per, k1) - ka)};
+  };
+  // stripe i of a run; of the one after it only the first 16 bytes
+  auto load = [&](const Run& R, uint32_t i) -> uint4 {
+    uint4 v = make_uint4(0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u);
+    if (i > R.n || R.n == 0) return v;
+    const int64_t p = R.first + i * (int64_t)kStripe;
+    uint32_t at = lane * 16;
+    pin(at);  // (an offset to a scalar address: as a sum of its own it was kept, and spilled)
+    if (i < R.n && p >= 0 && p + (int64_t)kStripe <= (int64_t)len) v = load_stream16(corpus + p + at);
+    else if (i < R.n || lane == 0) v = load_text16(corpus, len, p + at);
+    return v;
+  };
+  // the next group's first stripes, loaded before the current group's entries are written
+  uint4 t0 = make_uint4(0, 0, 0, 0), t1 = t0;
+  uint32_t t_before = 0;
+  auto load_first = [&](const Run& R) {
+    t0 = load(R, 0);
+    t1 = load(R, 1);
+    t_before = R.n ? load_text4(corpus, len, R.first - 4) : 0u;
+  };
+  auto scan = [&](const uint64_t* doff, uint32_t nd) {
+    const int64_t A = (int64_t)uniform64(doff[0]), B = (int64_t)uniform64(doff[nd]);
+    const Run R = run_of(A, B);
+    const uint32_t nsw = R.n;
     if (nsw == 0) return;
+    auto stripe_pos = [&](uint32_t i) -> int64_t { return R.first + i * (int64_t)kStripe; };
+    uint4 r1 = t1;
     // rb: the last document that starts before the stripe (-1: none), upcoming: the next start
     int32_t rb = -1;
     for (uint32_t j = 0; j < nd; j += 64)
       rb += (int32_t)__popcll(__ballot(j + lane < nd && (int64_t)doff[min(j + lane, nd)] < stripe_pos(0)));
-    int64_t upcoming = (int64_t)doff[rb + 1];
+    int64_t upcoming = (int64_t)uniform64(doff[rb + 1]);
     uint32_t carry;
     {
       const int64_t q = stripe_pos(0) - 1;
       uint32_t f;
-      fold_classify4(before, &f);
+      fold_classify4(t_before, &f);
       carry = (q >= A && q < B) ? f >> 31 : 0u;
     }
     const bool inside = stripe_pos(0) >= A && stripe_pos(nsw) + 16 <= B;
     uint32_t w16;
-    uint4 g = classify16(raw0, &w16);
+    uint4 g = classify16(t0, &w16);
     if (!inside) w16 = cut16(w16, stripe_pos(0) + lane * 16, A, B);
 
     for (uint32_t i = 0; i < nsw; ++i) {
@@ -293,8 +304,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
       uint32_t w1;
       const uint4 g1 = classify16(r1, &w1);
       if (!inside) w1 = cut16(w1, p0 + (int64_t)kStripe + lane * 16, A, B);
-      r1 = r2;
-      r2 = load(i + 3);
+      r1 = load(R, i + 2);
       ((uint4*)my_txt)[lane] = g;
       if (lane == 0) ((uint4*)my_txt)[64] = g1;
       // document starts in the stripe and the 16 bytes after it
@@ -416,7 +426,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
           }
         const int res = table_add<NX, true>(T, key, h, one, in, left);
         if (res == kNoRoom) spill(key, left, nx);
-        else if (res == kNoSlot && lane == 0) or32(&hdr->flags, kFlagStall);
+        else if (res == kNoSlot && lane == 0) or32(&hdr_of()->flags, kFlagStall);
       };
       for (uint32_t w0 = 0; w0 < n; w0 += kList) {
         {
@@ -437,7 +447,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
         wave_sync();
       }
       rb += (int32_t)nb;
-      if (nb) upcoming = (int64_t)doff[rb + 1];
+      if (nb) upcoming = (int64_t)uniform64(doff[rb + 1]);
     }
   };
 
@@ -484,7 +494,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
     }
     if (ok) dump = d + 1;
     __syncthreads();
-    for (uint32_t i = tid; i < kRedSlots / 4; i += kBlk) ((uint4*)T.slot)[i] = make_uint4(0, 0, 0, 0);
+    for (uint32_t i = tid; i < kDocSlots / 4; i += kBlk) ((uint4*)T.slot)[i] = make_uint4(0, 0, 0, 0);
     if (tid == 0) s_nent = 0;
     __syncthreads();
   };
@@ -530,7 +540,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
       }
       const int res = table_add<2, true>(T, k, h, one, use, left);
       if (res == kNoRoom) spill(k, left, std::integral_constant<int, 2>());
-      else if (res == kNoSlot && lane == 0) or32(&hdr->flags, kFlagStall);
+      else if (res == kNoSlot && lane == 0) or32(&hdr_of()->flags, kFlagStall);
     }
   };
   // One level of the spilled keys (all threads, after a barrier; ends with one).
@@ -606,202 +616,184 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams P) {
     __syncthreads();
   };
 
-  auto put = [&](uint64_t e, uint64_t b, const uint4 k, uint64_t cnt, uint64_t d) {
-    P.word_offsets[e] = b;
+  struct Out {
+    uint64_t *woff, *docs, bias;
+    uint8_t* words;
+    void* counts;
+    uint32_t count_bytes;
+  };
+  auto put = [&](const Out& o, uint64_t e, uint64_t b, const uint4 k, uint64_t cnt, uint64_t d) {
+    o.woff[e] = b;
     // a document has fewer than 2^31 tokens (the corpus is below 4 GiB), so only a debug bias can
     // take a count past the 32-bit width
-    const uint64_t c = cnt + P.count_bias;
-    if (P.count_bytes == 4) {
-      if (c > 0x7fffffffull) or32(&hdr->flags, kFlagCountOverflow);
-      ((int32_t*)P.counts)[e] = (int32_t)c;
+    const uint64_t c = cnt + o.bias;
+    if (o.count_bytes == 4) {
+      if (c > 0x7fffffffull) or32(&hdr_of()->flags, kFlagCountOverflow);
+      ((int32_t*)o.counts)[e] = (int32_t)c;
     } else {
-      ((int64_t*)P.counts)[e] = (int64_t)c;
+      ((int64_t*)o.counts)[e] = (int64_t)c;
     }
-    P.docs[e] = d;
+    o.docs[e] = d;
     if (is_long_key(k)) {
       const uint8_t* src = long_ptr(k);
-      for (uint32_t q = 0; q < k.z; ++q) P.words[b + q] = (uint8_t)fold_byte(src[q]);
+      for (uint32_t q = 0; q < k.z; ++q) o.words[b + q] = (uint8_t)fold_byte(src[q]);
     } else {
-      store_word(P.words + b, (uint64_t)k.x | ((uint64_t)k.y << 32), (uint64_t)k.z | ((uint64_t)k.w << 32),
+      store_word(o.words + b, (uint64_t)k.x | ((uint64_t)k.y << 32), (uint64_t)k.z | ((uint64_t)k.w << 32),
                  (uint32_t)key_len(k));
     }
   };
 
   // ---- the queue ------------------------------------------------------------------------------
-  uint64_t nxt = 0;
+  // An item is a run of documents: (documents << 32 | first one), 0 when there is none left.
+  auto item_at = [&](uint32_t q) -> uint64_t {
+    if (q >= n_items) return 0;
+    return uniform64(q < n_big ? (1ull << 32) | as_global(args()->over_sorted)[q] : as_global(args()->items)[q - n_big]);
+  };
+  auto next_pos = [&]() -> uint32_t {  // (one lane's)
+    return gridDim.x + (uint32_t)atomicAdd((unsigned long long*)&hdr_of()->work_next, 1ull);
+  };
   uint32_t lost_most = 0;
   if (tid == 0) {
     s_tokens = 0;
-    s_next = atomicAdd((unsigned long long*)&hdr->work_next, 1ull);
+    s_nent = s_spill = s_used = s_done = 0;
+    s_next = next_pos();
   }
+  uint64_t it = item_at(blockIdx.x);
+  uint32_t cur = 0;  // s_doff buffer of the group
+  if (it && tid <= (uint32_t)(it >> 32)) s_doff[0][tid] = offset_at((uint32_t)it + tid);
   __syncthreads();
-  uint64_t q = s_next;
+  uint64_t ahead = item_at(s_next);
+  if (ahead && tid <= (uint32_t)(ahead >> 32)) s_doff[1][tid] = offset_at((uint32_t)ahead + tid);
   __syncthreads();
-  if (q < n_big + n_win) find_item(q);
-  uint32_t cur = 0;      // s_doff buffer of the group
-  bool have = false;     // its offsets are there
-  while (q < n_big + n_win) {
-    if (tid == 0) nxt = atomicAdd((unsigned long long*)&hdr->work_next, 1ull);
-    bool ahead = false;  // the next position's first group has been looked up
-    for (uint64_t d0 = da; d0 < db;) {
-      uint32_t nd = (uint32_t)min((uint64_t)kDocW, db - d0);
-      if (!have) {
-        for (uint32_t i = tid; i <= nd; i += kBlk) s_doff[cur][i] = offsets[d0 + i];
-        __syncthreads();
+  if (it) load_first(run_of((int64_t)uniform64(s_doff[0][0]), (int64_t)uniform64(s_doff[0][it >> 32])));
+  while (it) {
+    const uint32_t nd = (uint32_t)(it >> 32);
+    const uint64_t d0 = (uint32_t)it;
+    const uint64_t* const doff = s_doff[cur];
+    chunk = 0;
+    chunk_n = 0;
+    dump = 0;
+    scan(doff, nd);
+    // the first wave that is done takes the position after the next (asked for by wave 0 before
+    // the scan, its answer was waited for on the spot, with the acknowledgements of the stores of
+    // the group before: 20 % of the time)
+    if (lane == 0 && atomicAdd(&s_done, 1u) == 0) s_next = next_pos();
+    __syncthreads();
+    const uint64_t after = ahead ? item_at(s_next) : 0;
+    const uint32_t nxt = cur == 2 ? 0 : cur + 1, nxt2 = cur == 0 ? 2 : cur - 1;
+    if (ahead) load_first(run_of((int64_t)uniform64(s_doff[nxt][0]), (int64_t)uniform64(s_doff[nxt][ahead >> 32])));
+    if (s_spill) {
+      if (tid == 0) add64(&hdr_of()->stat[3], nd);
+      for (uint32_t level = 0; s_spill && !s_lost; ++level) count_spilled(level);
+      if (s_lost && tid == 0 && s_used > lost_most) {  // what the rest would have taken, roughly
+        add64(&hdr_of()->arena_next, 3ull * (s_used - lost_most));
+        lost_most = s_used;
       }
-      have = false;
-      const uint64_t* const doff = s_doff[cur];
-      // a window's last document, when it is longer than the window: already counted from the
-      // queue, or alone after the others
-      const bool big = q >= n_big && doff[nd] - doff[nd - 1] > win;
-      const bool queued = big && direct && doff[nd] - doff[nd - 1] > direct;
-      const uint32_t all = nd;
-      if (big && (queued || nd > 1)) --nd;
-      const uint64_t d_end = d0 + (queued ? all : nd);
-      const bool last = d_end >= db;
-      if (nd == 0) {  // a queued document by itself
-        __syncthreads();
-        d0 = d_end;
-        continue;
+    }
+    // places of the entries in their documents; the slots are not needed any more
+    clear_slots();
+    const uint32_t ne = min(s_nent, T.cap);
+    uint64_t at[kPerThread];
+#pragma unroll
+    for (uint32_t x = 0; x < kPerThread; ++x) {
+      const uint32_t i = tid + x * kBlk;
+      at[x] = 0;
+      if (x * kBlk < ne) {
+        const uint32_t cnt = i < ne ? T.cnt[i] : 0u;
+        const uint4 k = i < ne ? T.key[i] : make_uint4(0, 0, 0, 0);
+        at[x] = place(cnt != 0, key_doc(k), (uint32_t)key_len(without_doc(k)));
       }
-      chunk = 0;
-      chunk_n = 0;
-      dump = 0;
-      scan(doff, nd);
-      if (tid == 0) s_next = nxt;
-      __syncthreads();
-      const bool spilled = s_spill != 0;
-      if (spilled) {
-        if (tid == 0) add64(&hdr->stat[3], nd);
-        for (uint32_t level = 0; s_spill && !s_lost; ++level) count_spilled(level);
-        if (s_lost && tid == 0 && s_used > lost_most) {  // what the rest would have taken, roughly
-          add64(&hdr->arena_next, 3ull * (s_used - lost_most));
-          lost_most = s_used;
+    }
+    uint64_t off = 0;
+    if (after && tid <= (uint32_t)(after >> 32)) off = offset_at((uint32_t)after + tid);
+    __syncthreads();
+    // documents' places in the group, and its place in the output, by wave 0; the other waves
+    // go on to their text of the next group
+    if (wv == 0) {
+      uint64_t v[kDocW / 64], incl = 0;
+#pragma unroll
+      for (uint32_t j = 0; j < kDocW / 64; ++j) {
+        const uint32_t r = lane * (kDocW / 64) + j;
+        v[j] = r < nd ? s_dcur[r] : 0ull;
+        incl += v[j];
+      }
+      const uint64_t sum = incl;
+      const uint32_t ie = wave_incl_scan((uint32_t)(sum >> 32)), ib = wave_incl_scan((uint32_t)sum);
+      incl = ((uint64_t)ie << 32) | ib;
+      uint64_t o = 0;
+      if (lane == 63) o = atomicAdd((unsigned long long*)&hdr_of()->out_cursor, (unsigned long long)incl);
+      o = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(o >> 32), 63) << 32) |
+          (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)o, 63);
+      uint64_t first = o + incl - sum;
+#pragma unroll
+      for (uint32_t j = 0; j < kDocW / 64; ++j) {
+        const uint32_t r = lane * (kDocW / 64) + j;
+        if (r < nd) {
+          s_dcur[r] = first;
+          as_global(args()->doc_ptr)[d0 + r] = first >> 32;
+          as_global(args()->doc_len)[d0 + r] = v[j] >> 32;
         }
+        first += v[j];
       }
-      // the next group's documents, while this one's entries find their places
-      uint64_t nda = 0, ndb = 0;
-      const uint64_t nq = s_next;
-      const bool look = last && nq < n_big + n_win;
-      if (look) {
-        const uint64_t a = da, b = db;
-        find_item(nq);
-        nda = da;
-        ndb = db;
-        da = a;
-        db = b;
+      if (lane == 63) {
+        s_out = first;  // the end of the group's output
+        s_nent = s_spill = s_used = s_done = 0;
+        if ((first >> 32) > args()->cap_e || (first & 0xffffffffull) > args()->cap_b) or32(&hdr_of()->flags, kFlagWordCap);
       }
-      const uint32_t ne = min(s_nent, T.cap);
-      uint64_t at[kPerThread];
+    }
+    // what was asked for before the entries' stores is taken before them (loads and stores are
+    // waited for in their order)
+    if (after && tid <= (uint32_t)(after >> 32)) s_doff[nxt2][tid] = off;
+    pin(t0);
+    pin(t1);
+    pin(t_before);
+    __syncthreads();
+    const bool room = (s_out >> 32) <= args()->cap_e && (s_out & 0xffffffffull) <= args()->cap_b;
+    if (room) {
+      const Args A = args();
+      const Out o{as_global(A->word_offsets), as_global(A->docs), A->count_bias, as_global(A->words),
+                  (void*)as_global((uint8_t*)A->counts), A->count_bytes};
 #pragma unroll
       for (uint32_t x = 0; x < kPerThread; ++x) {
         const uint32_t i = tid + x * kBlk;
-        at[x] = 0;
-        if (x * kBlk < ne) {
-          const uint32_t cnt = i < ne ? T.cnt[i] : 0u;
-          const uint4 k = i < ne ? T.key[i] : make_uint4(0, 0, 0, 0);
-          at[x] = place(cnt != 0, key_doc(k), (uint32_t)key_len(without_doc(k)));
-        }
+        if (i >= ne) continue;
+        const uint32_t cnt = T.cnt[i];
+        if (!cnt) continue;
+        const uint4 k = T.key[i];
+        const uint32_t r = key_doc(k);
+        const uint64_t pos = s_dcur[r] + at[x];
+        put(o, pos >> 32, pos & 0xffffffffull, without_doc(k), cnt, d0 + r);
       }
-      uint64_t noff = 0;
-      const uint32_t nnd = (uint32_t)min((uint64_t)kDocW, ndb - nda);
-      if (look && nda < ndb && tid <= nnd) noff = offsets[nda + tid];
-      __syncthreads();
-      // documents' places in the group: a scan over the first 256 threads
-      uint64_t v = 0, incl = 0;
-      if (tid < kDocW) {
-        v = tid < nd ? s_dcur[tid] : 0ull;
-        const uint32_t ie = wave_incl_scan((uint32_t)(v >> 32)), ib = wave_incl_scan((uint32_t)v);
-        incl = ((uint64_t)ie << 32) | ib;
-        if (lane == 63) s_sum[wv] = incl;
-      }
-      __syncthreads();
-      const uint64_t tot = s_sum[0] + s_sum[1] + s_sum[2] + s_sum[3];
-      const uint64_t tn = tot >> 32, tb = tot & 0xffffffffull;
-      if (tid == 0) {
-        const uint64_t o = atomicAdd((unsigned long long*)&hdr->out_cursor, (unsigned long long)tot);
-        s_out = o;
-        if ((o >> 32) + tn > P.cap_e || (o & 0xffffffffull) + tb > P.cap_b) or32(&hdr->flags, kFlagWordCap);
-      }
-      uint64_t first = incl - v;
-      if (tid < kDocW) {
-        for (uint32_t w = 0; w < wv; ++w) first += s_sum[w];
-        if (tid < nd) s_dcur[tid] = first;
-      }
-      __syncthreads();
-      const uint64_t e0 = s_out >> 32, b0 = s_out & 0xffffffffull;
-      const bool room = e0 + tn <= P.cap_e && b0 + tb <= P.cap_b;
-      if (tid < nd) {
-        P.doc_ptr[d0 + tid] = e0 + (first >> 32);
-        P.doc_len[d0 + tid] = v >> 32;
-      }
-      if (look && tid <= nnd) s_doff[cur ^ 1][tid] = noff;
-      if (room) {
-#pragma unroll
-        for (uint32_t x = 0; x < kPerThread; ++x) {
-          const uint32_t i = tid + x * kBlk;
-          if (i >= ne) continue;
-          const uint32_t cnt = T.cnt[i];
-          if (!cnt) continue;
-          const uint4 k = T.key[i];
+      for (uint32_t du = s_lost ? 0u : dump; du;) {
+        const Slot h = *slot_at(du - 1);
+        for (uint32_t i = tid; i < (uint32_t)h.cnt; i += kBlk) {
+          const Slot sl = *slot_at(du + i);
+          if (!sl.cnt) continue;
+          const uint4 k = key4(sl.key, sl.w0);
           const uint32_t r = key_doc(k);
-          const uint64_t pos = s_dcur[r] + at[x];
-          put(e0 + (pos >> 32), b0 + (pos & 0xffffffffull), without_doc(k), cnt, d0 + r);
+          const uint64_t pos = s_dcur[r] + sl.w1;
+          put(o, pos >> 32, pos & 0xffffffffull, without_doc(k), sl.cnt, d0 + r);
         }
-        for (uint32_t du = s_lost ? 0u : dump; du;) {
-          const Slot h = *slot_at(du - 1);
-          for (uint32_t i = tid; i < (uint32_t)h.cnt; i += kBlk) {
-            const Slot sl = *slot_at(du + i);
-            if (!sl.cnt) continue;
-            const uint4 k = key4(sl.key, sl.w0);
-            const uint32_t r = key_doc(k);
-            const uint64_t pos = s_dcur[r] + sl.w1;
-            put(e0 + (pos >> 32), b0 + (pos & 0xffffffffull), without_doc(k), sl.cnt, d0 + r);
-          }
-          du = (uint32_t)h.key;
-        }
-      }
-      __syncthreads();  // the table and the places are free again
-      d0 = d_end;
-      if (last) {
-        ahead = true;
-        if (look) {
-          da = nda;
-          db = ndb;
-          cur ^= 1;
-          have = true;
-        }
-        q = nq;
-        break;
-      }
-      if (big && !queued && all > 1) {
-        // the long document alone: its offsets are the group's last two
-        if (tid < 2) s_doff[cur ^ 1][tid] = doff[all - 1 + tid];
-        __syncthreads();
-        cur ^= 1;
-        have = true;
+        du = (uint32_t)h.key;
       }
     }
-    if (!ahead) {  // nothing was counted at this position's end
-      if (tid == 0) s_next = nxt;
-      __syncthreads();
-      q = s_next;
-      __syncthreads();
-      if (q < n_big + n_win) find_item(q);
-      have = false;
-    }
+    __syncthreads();  // the table and the places are free again
+    for (uint32_t r = tid; r < nd; r += kBlk) s_dcur[r] = 0;
+    it = ahead;
+    ahead = after;
+    cur = nxt;
   }
   if (lane == 0 && tokens) atomicAdd(&s_tokens, (unsigned long long)tokens);
   __syncthreads();
   if (tid == 0) {
-    if (s_tokens) add64(&hdr->total_tokens, s_tokens);
+    if (s_tokens) add64(&hdr_of()->total_tokens, s_tokens);
     __threadfence();
-    const uint64_t done = __hip_atomic_fetch_add(&hdr->over_next, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t done = __hip_atomic_fetch_add(&hdr_of()->occupied, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (done + 1 == gridDim.x) {  // the last workgroup closes the output
-      const uint64_t c = ld_relaxed(&hdr->out_cursor);
-      hdr->n_entries = c >> 32;
-      hdr->word_bytes = c & 0xffffffffull;
-      if ((c >> 32) <= P.cap_e) P.word_offsets[c >> 32] = c & 0xffffffffull;
+      const uint64_t c = ld_relaxed(&hdr_of()->out_cursor);
+      hdr_of()->n_entries = c >> 32;
+      hdr_of()->word_bytes = c & 0xffffffffull;
+      if ((c >> 32) <= args()->cap_e) as_global(args()->word_offsets)[c >> 32] = c & 0xffffffffull;
     }
   }
 }
@@ -813,7 +805,7 @@ __global__ __launch_bounds__(1024) void doc_order_kernel(DocParams P) {
   constexpr uint32_t kClasses = 48;  // floor(log2(bytes)), largest first
   __shared__ uint32_t s_cnt[kClasses], s_at[kClasses];
   const uint64_t n = P.hdr->over_n;
-  const uint64_t* offsets = P.task->offsets;
+  const uint64_t* offsets = as_global(P.task->offsets);
   if (threadIdx.x < kClasses) s_cnt[threadIdx.x] = 0;
   __syncthreads();
   for (uint64_t q = threadIdx.x; q < n; q += blockDim.x) {
@@ -839,45 +831,62 @@ __global__ __launch_bounds__(1024) void doc_order_kernel(DocParams P) {
   }
 }
 
-// Checks the offsets, finds the first document that starts at or after each window, and lists the
-// documents that are counted from the queue.
-__global__ void doc_plan_kernel(DocParams P) {
+// Bytes per work item where the caller has not said: two items per workgroup, in steps of 16 KiB.
+// Fewer and larger ones have less to wait for between them (the output's place, the first text;
+// about 5 us an item), until many do not fit the table: kernel time of 100,000 documents (2.7 GB)
+// with 16 / 24 / 32 / 48 / 64 KiB 8.4 / 8.3 / 7.5 / 7.1 / 7.6 ms, of 2,000 (18 MB, 256 workgroups)
+// 122 / 105 / 100 / 133 / 195 us.
+WC_DEV uint64_t window_bytes(uint64_t len, uint32_t grid) {
+  const uint64_t w = len / (2 * (uint64_t)grid) & ~(kMinWin - 1);
+  return min(max(w, kMinWin), kMaxWin);
+}
+
+// Checks the offsets and lists the work: documents longer than a window and the size limit in
+// the queue, other documents longer than a window as an item each, and the rest of each window's
+// documents, the window's first document's lane by kDocW at a time.
+__global__ __launch_bounds__(256) void doc_plan_kernel(DocParams P) {
   const uint64_t len = P.task->len, n_docs = P.task->n_docs;
-  const uint64_t* offsets = P.task->offsets;
-  const uint64_t n_win = len / P.win_bytes + 1;
-  const uint64_t first = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
+  const uint64_t* offsets = as_global(P.task->offsets);
+  const uint32_t lane = threadIdx.x & 63;
   const uint64_t step = (uint64_t)gridDim.x * blockDim.x;
-  if (n_win + 1 > P.max_win + 1) {
-    if (first == 0) or32(&P.hdr->flags, kFlagWordCap);
-    return;
-  }
-  const uint64_t limit = max(P.win_bytes, (uint64_t)P.direct_kib << 10);
-  for (uint64_t i0 = first & ~63ull; i0 <= n_docs; i0 += step) {
-    const uint64_t i = i0 + (threadIdx.x & 63);
+  const uint64_t win = P.win_bytes ? P.win_bytes : window_bytes(len, P.grid), limit = P.direct_kib ? max(win, (uint64_t)P.direct_kib << 10) : ~0ull;
+  for (uint64_t i0 = blockIdx.x * (uint64_t)blockDim.x + (threadIdx.x & ~63u); i0 <= n_docs; i0 += step) {
+    const uint64_t i = i0 + lane;
     const uint64_t a = i <= n_docs ? offsets[i] : 0, b = i < n_docs ? offsets[i + 1] : a;
     const bool bad = i <= n_docs && (a > b || (i == n_docs && a > len));
     if (bad) or32(&P.hdr->flags, kFlagBadOffsets);
-    const bool big = !bad && P.direct_kib && i < n_docs && b - a > limit;
-    const uint64_t m = __ballot(big);
-    if (m) {
-      uint64_t at = 0;
-      const uint32_t leader = (uint32_t)__ffsll((unsigned long long)m) - 1;
-      if ((threadIdx.x & 63) == leader)
-        at = atomicAdd((unsigned long long*)&P.hdr->over_n, (unsigned long long)__popcll(m));
-      at = __shfl(at, (int)leader, 64);
-      if (big)
-        P.over_docs[at + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = i;
+    const bool doc = i < n_docs && !bad;
+    const bool queued = doc && b - a > limit, alone = doc && !queued && b - a > win;
+    uint64_t end = i;  // documents [i, end) of this lane's window
+    if (doc && b - a <= win && (i == 0 || offsets[i - 1] / win != a / win)) {
+      const uint64_t x = (a / win + 1) * win;
+      uint64_t lo = i + 1, hi = lo, s = 1;  // offsets[lo - 1] < x
+      while (hi < n_docs && offsets[hi] < x) {
+        lo = hi + 1;
+        hi = min(hi + s, n_docs);
+        s *= 2;
+      }
+      while (lo < hi) {
+        const uint64_t mid = (lo + hi) >> 1;
+        if (offsets[mid] < x) lo = mid + 1; else hi = mid;
+      }
+      end = lo;
+      const uint64_t z = offsets[end] - offsets[end - 1];
+      if (end - 1 > i && z > win && z <= len) --end;  // the window's last, listed by its own lane
     }
-  }
-  for (uint64_t w = first; w <= n_win; w += step) {
-    const uint64_t x = w * P.win_bytes;
-    uint64_t lo = 0, hi = n_docs + 1;
-    while (lo < hi) {
-      const uint64_t mid = (lo + hi) >> 1;
-      if (offsets[mid] < x) lo = mid + 1; else hi = mid;
+    const uint32_t n = alone ? 1u : (uint32_t)((end - i + kDocW - 1) / kDocW);
+    const uint32_t ni = wave_incl_scan(n), nq = wave_incl_scan(queued ? 1u : 0u);
+    uint64_t at = 0, aq = 0;
+    if (lane == 63) {
+      if (ni) at = atomicAdd((unsigned long long*)&P.hdr->over_next, (unsigned long long)ni);
+      if (nq) aq = atomicAdd((unsigned long long*)&P.hdr->over_n, (unsigned long long)nq);
     }
-    P.win_doc[w] = lo;
+    at = __shfl(at, 63, 64) + ni - n;
+    aq = __shfl(aq, 63, 64) + nq - 1;
+    if (queued) P.over_docs[aq] = i;
+    // (runs of offsets in order are apart, so that there are at most n_docs)
+    for (uint64_t d = i; d < (alone ? i + 1 : end) && at < n_docs; d += kDocW)
+      P.items[at++] = ((alone ? 1ull : min((uint64_t)kDocW, end - d)) << 32) | d;
   }
 }
 
@@ -885,10 +894,10 @@ hipError_t set_doc_smem() {
   return hipFuncSetAttribute((const void*)doc_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDyn);
 }
 
-hipError_t launch_docs(const DocParams& P, uint32_t grid, hipStream_t s) {
+hipError_t launch_docs(const DocParams& P, hipStream_t s) {
   hipLaunchKernelGGL(doc_plan_kernel, dim3(256), dim3(256), 0, s, P);
   if (P.direct_kib) hipLaunchKernelGGL(doc_order_kernel, dim3(1), dim3(1024), 0, s, P);
-  hipLaunchKernelGGL(doc_kernel, dim3(grid), dim3(kBlk), kDyn, s, P);
+  hipLaunchKernelGGL(doc_kernel, dim3(P.grid), dim3(kBlk), kDyn, s, P);
   return hipGetLastError();
 }
 

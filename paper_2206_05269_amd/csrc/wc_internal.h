@@ -136,10 +136,10 @@ hipError_t launch_part_reduce(const PartParams& P, hipStream_t s);
 hipError_t launch_part_single(const PartParams& P, hipStream_t s);
 
 // per-document count (wc_docs.hip)
-constexpr uint64_t kWin = 32 * 1024;   // default bytes per work item window
-constexpr uint64_t kMinWin = 16 * 1024;
+constexpr uint64_t kMinWin = 16 * 1024, kMaxWin = 48 * 1024;  // bytes per work item
+constexpr uint32_t kDirectKib = 72;
 constexpr uint32_t kDocW = 256;        // documents per sub-window
-constexpr uint32_t kDocLds = 4608;     // LDS table entries (20 bytes each, beside 8192 slots)
+constexpr uint32_t kDocLds = 4528;     // LDS table entries (20 bytes each, beside 8192 slots)
 
 struct DocTask {           // device-resident: every size the per-document kernels read
   const uint8_t* corpus;
@@ -151,16 +151,15 @@ struct DocTask {           // device-resident: every size the per-document kerne
 struct DocParams {
   const DocTask* task;
   Header* hdr;
-  uint64_t* win_doc;       // [max_win + 1]
-  uint64_t max_win;
+  uint64_t* items;         // [n_docs] runs of documents (documents << 32 | the first)
   uint64_t* word_offsets;  // [cap_e + 1]
   uint8_t* words;          // [cap_b]
   void* counts;
   uint32_t count_bytes;
-  uint32_t lds_entries;
+  uint32_t grid;           // workgroups
   uint32_t lds_cap;        // entries used before keys are spilled
   uint32_t direct_kib;     // documents above this many KiB, and a window, are queued first (0: none)
-  uint64_t win_bytes;      // work item window
+  uint64_t win_bytes;      // work item window; 0: by the size of the text
   uint64_t* docs;          // [cap_e]
   uint64_t* doc_ptr;       // [n_docs]
   uint64_t* doc_len;       // [n_docs]
@@ -174,7 +173,7 @@ struct DocParams {
 // queue entries: document index (bits 0-55), size class while the queue is sorted (bits 56-62)
 constexpr uint64_t kDocIdMask = (1ull << 56) - 1;
 hipError_t set_doc_smem();
-hipError_t launch_docs(const DocParams& P, uint32_t grid, hipStream_t s);
+hipError_t launch_docs(const DocParams& P, hipStream_t s);
 
 hipError_t launch_count(const CountParams& P, bool per_doc, uint32_t grid, uint32_t block,
                         size_t dyn, hipStream_t s);

@@ -20,7 +20,7 @@ WC_DEV uint4 long_key(const uint8_t* p, uint32_t n, uint32_t h) {
 }
 WC_DEV bool is_long_key(const uint4 k) { return (k.w >> 24) == 0xffu; }
 WC_DEV const uint8_t* long_ptr(const uint4 k) {
-  return (const uint8_t*)(uintptr_t)((uint64_t)k.x | ((uint64_t)(k.y & 0xffffu) << 32));
+  return as_global_lane((const uint8_t*)(uintptr_t)((uint64_t)k.x | ((uint64_t)(k.y & 0xffffu) << 32)));
 }
 
 WC_DEV uint32_t mix32(uint32_t h) {  // the 32-bit finaliser of MurmurHash3 (Appleby)
@@ -132,9 +132,13 @@ WC_DEV bool same_key(const uint4 a, const uint4 b) {
 }
 
 // ---- the LDS table -----------------------------------------------------------------------
-template <class C>
+template <class Count, uint32_t kTableSlots = kRedSlots>
 struct PartTable {
-  uint32_t* slot;  // [kRedSlots], 0 = empty
+  using C = Count;
+  static constexpr uint32_t kSlots = kTableSlots, kGroups = kSlots / 4;
+  // the home group of a hash: its top bits
+  static WC_DEV uint32_t group(uint32_t h) { return h >> (32 - __builtin_ctz(kGroups)); }
+  uint32_t* slot;  // [kSlots], 0 = empty
   uint4* key;      // [cap]
   C* cnt;          // [cap]
   uint32_t* n;     // entries handed out (may pass cap)
@@ -153,11 +157,11 @@ WC_DEV void lds_add(uint64_t* p, uint64_t v) {
 // it. Every iteration finds the key, claims a slot, loses a slot of the group to another key (at
 // most four times) or moves to the next group. (At 5,120 entries in 8,192 slots a run of 16 full
 // groups is met about once in a million groups, which is several times in a text of 64 MB.)
-template <class C>
-WC_DEV bool part_add(const PartTable<C>& T, const uint4 want, uint32_t h, C n, uint32_t mine) {
-  constexpr uint32_t kGroups = kRedSlots / 4;
+template <class Table>
+WC_DEV bool part_add(const Table& T, const uint4 want, uint32_t h, typename Table::C n, uint32_t mine) {
+  constexpr uint32_t kGroups = Table::kGroups;
   const uint32_t tag = red_tag(h);
-  uint32_t g = red_group(h), probe = 0;
+  uint32_t g = Table::group(h), probe = 0;
   bool active = true, ok = false;
   while (__any(active)) {
     bool claim = false;
@@ -222,17 +226,18 @@ WC_DEV uint32_t pick4(const uint4 g, uint32_t tag) {  // the first slot with the
 // group again. (Before, each key of the lanes went through an entry, a claim and, for what was
 // left, the loop of part_add by itself: map of a 20 MB text 62 -> 55 us, of a 64 MB text 271 -> 181.)
 constexpr int kAdded = 0, kNoRoom = 1, kNoSlot = 2;
-template <int N, bool kPartial = false, class C>
-WC_DEV int table_add(const PartTable<C>& T, const uint4 (&key)[N], const uint32_t (&h)[N],
-                     const C (&n)[N], const bool (&f)[N], bool* left = nullptr) {
-  constexpr uint32_t kGroups = kRedSlots / 4;
+template <int N, bool kPartial = false, class Table>
+WC_DEV int table_add(const Table& T, const uint4 (&key)[N], const uint32_t (&h)[N],
+                     const typename Table::C (&n)[N], const bool (&f)[N], bool* left = nullptr) {
+  using C = typename Table::C;
+  constexpr uint32_t kGroups = Table::kGroups;
   const uint32_t lane = threadIdx.x & 63;
   uint4 g[N], k[N];
   uint32_t e[N], gi[N], tag[N];
   bool hit[N], next[N];
 #pragma unroll
   for (int x = 0; x < N; ++x) {
-    gi[x] = red_group(h[x]);
+    gi[x] = Table::group(h[x]);
     g[x] = ((const uint4*)T.slot)[gi[x]];
   }
 #pragma unroll
@@ -307,13 +312,13 @@ WC_DEV int table_add(const PartTable<C>& T, const uint4 (&key)[N], const uint32_
       T.key[mine[x]] = key[x];
       T.cnt[mine[x]] = n[x];
     }
-    act[x] = miss[x] && e[x] == 0 && used < 4;
+    act[x] = miss[x] & (e[x] == 0) & (used < 4);
     any |= act[x];
   }
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   while (__any(any)) {
-    any = false;
     uint32_t prev[N];
+    bool lost = false;
 #pragma unroll
     for (int x = 0; x < N; ++x) {
       prev[x] = 0;
@@ -321,22 +326,29 @@ WC_DEV int table_add(const PartTable<C>& T, const uint4 (&key)[N], const uint32_
     }
 #pragma unroll
     for (int x = 0; x < N; ++x) {
-      if (!act[x]) continue;
-      if (prev[x] == 0) {
-        act[x] = miss[x] = false;
-      } else {
-        const uint32_t idx = prev[x] & 0x1fffu;
-        if ((prev[x] >> 13) == tag[x]) {  // most often the same new word in another lane
-          if (key_eq(T.key[idx], key[x])) {
-            lds_add(&T.cnt[idx], n[x]);
-            T.cnt[mine[x]] = 0;
-            miss[x] = false;
-          }
-          act[x] = false;
-        } else if ((++at[x] & 3u) == 0) {
-          act[x] = false;
-        }
+      miss[x] &= !(act[x] & (prev[x] == 0));
+      act[x] &= prev[x] != 0;
+      lost |= act[x];
+    }
+    if (!__any(lost)) break;
+    // most often the same new word in another lane
+    uint4 k2[N];
+#pragma unroll
+    for (int x = 0; x < N; ++x) k2[x] = T.key[prev[x] & 0x1fffu];
+#pragma unroll
+    for (int x = 0; x < N; ++x) pin(k2[x]);
+    any = false;
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+      const bool same = act[x] & ((prev[x] >> 13) == tag[x]);
+      const bool eq = same & key_eq(k2[x], key[x]);
+      if (eq) {
+        lds_add(&T.cnt[prev[x] & 0x1fffu], n[x]);
+        T.cnt[mine[x]] = 0;
       }
+      miss[x] &= !eq;
+      at[x] += act[x] ? 1 : 0;
+      act[x] = act[x] & !same & ((at[x] & 3u) != 0);
       any |= act[x];
     }
   }
@@ -374,11 +386,11 @@ WC_DEV int table_add(const PartTable<C>& T, const uint4 (&key)[N], const uint32_
 }
 
 // Entry of a key in a table that nobody is changing, or -1 (claimed slots of a group are a prefix).
-template <class C>
-WC_DEV int table_find(const PartTable<C>& T, const uint4 want, uint32_t h) {
-  constexpr uint32_t kGroups = kRedSlots / 4;
+template <class Table>
+WC_DEV int table_find(const Table& T, const uint4 want, uint32_t h) {
+  constexpr uint32_t kGroups = Table::kGroups;
   const uint32_t tag = red_tag(h);
-  uint32_t g = red_group(h);
+  uint32_t g = Table::group(h);
   for (uint32_t probe = 0; probe < kGroups; ++probe) {
     const uint4 s4 = ((const uint4*)T.slot)[g];
     const uint32_t e[4] = {s4.x, s4.y, s4.z, s4.w};

@@ -1122,12 +1122,13 @@ def _group_texts(kind, rng):
     return [doc(3000), b" ".join(many[i] for i in order), doc(1), b"", doc(200_000), doc(5000)]
 
 
-@pytest.mark.parametrize("lds", [0, 256])
+# (one workgroup: the largest work items)
+@pytest.mark.parametrize("tuning", [{}, {"lds_entries": 256}, {"grid_blocks": 1}])
 @pytest.mark.parametrize("kind", ["many", "edges", "vocabulary"])
-def test_per_doc_groups_and_spilled_words(kind, lds):
+def test_per_doc_groups_and_spilled_words(kind, tuning):
     docs = _group_texts(kind, np.random.default_rng(7))
     text, off = join_docs(docs)
-    kw = {"tuning": wc.make_tuning(lds_entries=lds)} if lds else {}
+    kw = {"tuning": wc.make_tuning(**tuning)} if tuning else {}
     check(text, off, per_doc=True, debug_flags=wc.WC_DEBUG_DOCS, **kw)
     if kind == "vocabulary":  # too little room for the spilled words at first
         check(text, off, per_doc=True, debug_flags=wc.WC_DEBUG_DOCS, table_slots=1 << 12, **kw)
