@@ -103,7 +103,7 @@ hipError_t set_global_smem(uint32_t dict_cap, uint32_t reduce_entries);
 hipError_t launch_global(const GlobalParams& P, hipEvent_t a, hipEvent_t b, hipStream_t s);
 
 // partitioned global count (wc_part.hip)
-constexpr uint32_t kPartMapEntries = 5120;  // LDS entries of a map workgroup (20 bytes each)
+constexpr uint32_t kPartMapEntries = 5008;  // LDS entries of a map workgroup (20 bytes each)
 constexpr uint32_t kPartRedEntries = 5888;  // of a reduce workgroup
 constexpr uint32_t kPartMergeEntries = 5056;  // of a merge's reduce workgroup (24 bytes each)
 struct PartParams {

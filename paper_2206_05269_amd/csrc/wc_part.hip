@@ -22,6 +22,8 @@
 // Words longer than 16 bytes are kept as references to an occurrence and compared by content.
 // What does not fit (more records than the arena, more lists than the directory) sets kFlagArena,
 // and the caller counts the text again with the one-pass kernel.
+#include <type_traits>
+
 #include "wc_internal.h"
 #include "wc_stripe.h"
 #include "wc_utf8.h"
@@ -34,9 +36,9 @@ namespace {
 constexpr int kBlk = 1024;
 constexpr uint32_t kWaves = kBlk / 64;
 constexpr uint32_t kText = kStripe + 32;     // per wave: stripe, the 16 bytes after it, padding
-constexpr uint32_t kRound = 128;             // tokens of a wave counted at a time
+constexpr uint32_t kList = 192;              // starts of a stripe listed at a time
 constexpr uint32_t kEnds = kStripe / 32 + 2; // word-end bitmap of a stripe and the 16 bytes after
-constexpr uint32_t kListWords = kRound / 2 + kEnds;
+constexpr uint32_t kListWords = kList / 2 + kEnds;
 
 constexpr uint32_t kPerThread = (kPartMapEntries + kBlk - 1) / kBlk;
 
@@ -161,6 +163,11 @@ WC_DEV int64_t lane_value(int64_t v, uint32_t lane) {
 // 16 bytes that runs over the stripe's end is read whole from LDS, at the run's end too; a
 // longer one is read from device memory. Waves meet only when the table is to be emptied.
 //
+// Bound by instructions (a 64 MB text: 380 GB/s of text, about 900 vector instructions per stripe,
+// half of them the table's). What the scan does not use stays out of its registers, and the rest of
+// a stripe's words after the first 128 is counted one a lane: map of 20 MB 56 -> 51 us, of 64 MB
+// 186 -> 170.
+//
 // UTF-8. A stripe's multi-byte sequences are read when it is classified, as if no document
 // started in it; a sequence's bytes in the next lane, or the next stripe, are passed on. When a
 // document does start in the stripe or just after it, the stripe and the 16 bytes after it
@@ -168,6 +175,14 @@ WC_DEV int64_t lane_value(int64_t v, uint32_t lane) {
 // one test per stripe.
 template <bool kSingle, bool kUtf8>
 __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
+  // What the scan does not need is read with args(): by name it would be loaded once, at the start,
+  // and held or spilled over the scan.
+  typedef const __attribute__((address_space(4))) PartParams* Args;
+  auto args = []() -> Args {
+    Args a = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(a));
+    return a;
+  };
   extern __shared__ __align__(16) uint8_t s_dyn[];
   __shared__ uint32_t s_list[kWaves][kListWords];  // starts (16 bits each), then the end bitmap
   __shared__ uint32_t s_bnd[kWaves][kEnds];
@@ -185,9 +200,9 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   const uint32_t wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
   uint8_t* const my_txt = (uint8_t*)(T.cnt + kPartMapEntries) + wv * kText;
   uint16_t* const my_starts = (uint16_t*)s_list[wv];
-  uint32_t* const my_ends = s_list[wv] + kRound / 2;
+  uint32_t* const my_ends = s_list[wv] + kList / 2;
   uint32_t* const my_bnd = s_bnd[wv];
-  Header* const hdr = P.hdr;
+  auto hdr_of = [&]() -> Header* { return as_global(args()->hdr); };
 
   // this wave's stripes
   const uint64_t first = (uint64_t)blockIdx.x * P.stripes_per_wg;
@@ -204,15 +219,17 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     const int64_t p = stripe_pos(i);
     uint4 v = blank;
     if (i < nsw && p >= 0 && p + (int64_t)kStripe <= (int64_t)P.len) {
-      v = load_stream16(P.corpus + p + lane * 16);
+      uint32_t at = lane * 16;
+      pin(at);  // (an offset to a scalar address: as a sum of its own it was kept, and spilled)
+      v = load_stream16(P.corpus + p + at);
     } else if (i < nsw || lane <= (kUtf8 ? 1u : 0u)) {
       v = load_text16(P.corpus, P.len, p + lane * 16);
     }
     return v;
   };
   const uint4 raw0 = load(0);
-  uint4 r1 = load(1), r2 = load(2), r3 = blank;
-  if (kUtf8) r3 = load(3);
+  uint4 r1 = load(1), r2 = blank;
+  if (kUtf8) r2 = load(2);
 
   for (uint32_t i = tid; i < kRedSlots / 4; i += kBlk) ((uint4*)T.slot)[i] = make_uint4(0, 0, 0, 0);
   for (uint32_t i = tid; i < kWaves * kListWords; i += kBlk) (&s_list[0][0])[i] = 0;
@@ -224,7 +241,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     s_done = 0;
     s_tokens = 0;
     if (kSingle) {
-      *hdr = Header{};
+      *hdr_of() = Header{};
       __threadfence();
     }
   }
@@ -234,7 +251,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   // host sees that, positions taken from them are only compared, and ranges are cut to the text.
   for (uint64_t d = blockIdx.x * (uint64_t)kBlk + tid; d <= P.n_docs; d += (uint64_t)gridDim.x * kBlk) {
     const uint64_t o = P.offsets[d];
-    if (d < P.n_docs ? o > P.offsets[d + 1] : o > P.len) or32(&hdr->flags, kFlagBadOffsets);
+    if (d < P.n_docs ? o > P.offsets[d + 1] : o > P.len) or32(&hdr_of()->flags, kFlagBadOffsets);
   }
   const int64_t R0 = (int64_t)min(P.offsets[0], P.len), R1 = (int64_t)min(P.offsets[P.n_docs], P.len);
 
@@ -245,7 +262,9 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   int64_t doff = INT64_MAX;
   auto load_docs = [&]() {
     const uint64_t d = d0 + lane;
-    doff = d <= P.n_docs ? (int64_t)P.offsets[d] : INT64_MAX;
+    const Args A = args();
+    const uint64_t* const offsets = as_global(A->offsets);
+    doff = d <= A->n_docs ? (int64_t)offsets[d] : INT64_MAX;
   };
   if (nsw) {
     uint64_t lo = 0, hi = P.n_docs + 1;  // offsets[lo - 1] < run start <= offsets[hi]
@@ -271,13 +290,14 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     }
   }
   auto doc_limit = [&](uint64_t pos) -> uint64_t {  // first document start after pos, or the end
-    uint64_t a = 1, b = P.n_docs;
+    const uint64_t* const offsets = as_global(args()->offsets);
+    uint64_t a = 1, b = args()->n_docs;
     while (a < b) {
       const uint64_t m = (a + b) >> 1;
-      if (P.offsets[m] > pos) b = m;
+      if (offsets[m] > pos) b = m;
       else a = m + 1;
     }
-    return min(P.offsets[a], P.len);
+    return min(offsets[a], P.len);
   };
 
   // the byte before the run
@@ -327,7 +347,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   uint4 g = classify(raw0, r1, &w16);
   if (!inside) w16 = cut16(w16, stripe_pos(0) + lane * 16, R0, R1);
 
-  uint32_t i = 0, n = 0, w0 = 0, start16 = 0, rank = 0;
+  uint32_t i = 0, n = 0, w0 = 0, off = 0, start16 = 0, rank = 0;  // off: place of token w0 in the list
   int64_t p0 = 0;
   uint32_t tokens = 0;
   bool over = false;  // a word found no room (this lane)
@@ -358,6 +378,55 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     return long_key(p, len, long_hash(p, len));
   };
 
+  // Counts the tokens at [at, at + 64 NX) of the list; nw of them are there.
+  auto count = [&](auto nx, uint32_t at, uint32_t nw) -> int {
+    constexpr int NX = decltype(nx)::value;
+    uint32_t st[NX], wl[NX], e0[NX], e1[NX], one[NX], h[NX];
+    bool in[NX];
+    // (starts past nw are of earlier lists: in range, not counted)
+#pragma unroll
+    for (int x = 0; x < NX; ++x) st[x] = my_starts[at + lane + 64 * x];
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+      e0[x] = my_ends[st[x] >> 5];
+      e1[x] = my_ends[(st[x] >> 5) + 1];
+    }
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+      wl[x] = __ffs(__builtin_amdgcn_alignbit(e1[x], e0[x], st[x] & 31));  // 0: no end in 32
+      in[x] = lane + 64 * x < nw;
+      one[x] = 1;
+    }
+    // each LDS step reads for all tokens before any waits (pin)
+    PackSrc ps[NX];
+    uint4 lm[NX], key[NX];
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+      ps[x] = pack_read(my_txt, st[x]);
+      lm[x] = s_lenmask[wl[x] - 1 < 16u ? wl[x] : 1u];
+    }
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+      pin(ps[x]);
+      pin(lm[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < NX; ++x) {
+      uint64_t lo, hi;
+      pack_join(ps[x], lm[x], &lo, &hi);
+      key[x] = key4(lo, hi);
+      h[x] = red_hash(key[x]);
+    }
+#pragma unroll
+    for (int x = 0; x < NX; ++x)
+      if (in[x] && wl[x] - 1 >= 16u) {
+        key[x] = long_word(st[x], wl[x]);
+        h[x] = place_hash(key[x]);
+        wait_vmem();
+      }
+    return table_add<NX>(T, key, h, one, in);
+  };
+
   while (true) {
     // ---- scan: until the run ends or the table is nearly full ------------------------------
     while (true) {
@@ -368,12 +437,11 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         uint32_t w1;
         uint32_t uc1 = uc;  // of the next stripe's first bytes
         const uint4 g1 = classify(r1, r2, &w1);
-        r1 = r2;
         if (kUtf8) {
-          r2 = r3;
-          r3 = load(i + 4);
-        } else {
+          r1 = r2;
           r2 = load(i + 3);
+        } else {
+          r1 = load(i + 2);
         }
         constexpr int64_t kReach = kStripe + (kUtf8 ? 20 : 16);  // document starts that matter here
         ((uint4*)my_txt)[lane] = g;
@@ -440,70 +508,31 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         uc0 = uc1;
         g = g1;
         w16 = w1;
-        w0 = 0;
+        w0 = off = 0;
         ++i;
         continue;
       }
-      // -- a round: the starts of ranks [w0, w0 + kRound), two per lane
-      {
-        uint32_t m = start16, r = rank;
+      if (off == 0) {  // list the starts of ranks [w0, w0 + kList)
+        uint32_t m = start16, r = rank - w0;
         while (m) {
           const uint32_t j = __ffs(m) - 1;
-          if (r - w0 < kRound) my_starts[r - w0] = (uint16_t)(lane * 16 + j);
+          if (r < kList) my_starts[r] = (uint16_t)(lane * 16 + j);
           ++r;
           m &= m - 1;
         }
+        wave_sync();
       }
-      wave_sync();
-      const uint32_t nw = min(n - w0, kRound);
-      uint32_t s2[2], n2[2], e0[2], e1[2];
-      bool f2[2];
-      // (starts past nw are of earlier rounds: in range, not counted)
-#pragma unroll
-      for (int x = 0; x < 2; ++x) s2[x] = my_starts[lane + 64 * x];
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        e0[x] = my_ends[s2[x] >> 5];
-        e1[x] = my_ends[(s2[x] >> 5) + 1];
-      }
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        n2[x] = __ffs(__builtin_amdgcn_alignbit(e1[x], e0[x], s2[x] & 31));  // 0: no end in 32
-        f2[x] = lane + 64 * x < nw;
-      }
-      // each LDS step reads for both tokens before either waits (pin)
-      PackSrc ps[2];
-      uint4 lm[2], key2[2];
-      uint32_t h2[2];
-      const uint32_t one2[2] = {1u, 1u};
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        ps[x] = pack_read(my_txt, s2[x]);
-        lm[x] = s_lenmask[n2[x] - 1 < 16u ? n2[x] : 1u];
-      }
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        pin(ps[x]);
-        pin(lm[x]);
-      }
-#pragma unroll
-      for (int x = 0; x < 2; ++x) {
-        uint64_t lo, hi;
-        pack_join(ps[x], lm[x], &lo, &hi);
-        key2[x] = key4(lo, hi);
-        h2[x] = red_hash(key2[x]);
-      }
-#pragma unroll
-      for (int x = 0; x < 2; ++x)
-        if (f2[x] && n2[x] - 1 >= 16u) {
-          key2[x] = long_word(s2[x], n2[x]);
-          h2[x] = place_hash(key2[x]);
-          wait_vmem();
-        }
-      const int r = table_add<2>(T, key2, h2, one2, f2);
+      // a round: two tokens a lane from the list's start, if there are more than 64, one from its
+      // 128th (a stripe of 176 tokens, usual for English text, took two rounds of 128)
+      const uint32_t nw = min(n - w0, kList - off);
+      const bool two = off == 0 && nw > 64;
+      const int r = two ? count(std::integral_constant<int, 2>(), off, nw)
+                        : count(std::integral_constant<int, 1>(), off, nw);
       if (r == kNoRoom && !kSingle) break;  // this round again when the table is empty
       if (r != kAdded) over = true;
-      w0 += kRound;
+      const uint32_t adv = two ? 128 : 64;
+      w0 += adv;
+      off = off + adv < kList ? off + adv : 0;
       wave_sync();
     }
     if (i >= nsw && w0 >= n && i != kNone) {  // the run is done
@@ -517,7 +546,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     __syncthreads();
     const bool end = s_done == kWaves;
     // (one addition per workgroup: one per wave, 4,096 on one address, took about 40 us)
-    if (end && tid == 0) add64(&hdr->total_tokens, s_tokens);
+    if (end && tid == 0) add64(&hdr_of()->total_tokens, s_tokens);
     if (kSingle) {  // (a word that found no room sets kFlagArena below)
       export_table<false>(P, T, true, 1u, s_tmp, &s_base);
       break;
@@ -526,14 +555,14 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     // room for all entries, those without a count too: the answer arrives while they are looked at
     // (lists << 40 | records)
     uint64_t got = 0;
-    if (tid == 0) got = atomicAdd((unsigned long long*)&hdr->arena_next, (1ull << 40) | ne);
+    if (tid == 0) got = atomicAdd((unsigned long long*)&hdr_of()->arena_next, (1ull << 40) | ne);
     uint32_t at[kPerThread];  // partition << 16 | place in it
 #pragma unroll
     for (uint32_t x = 0; x < kPerThread; ++x) {
       const uint32_t j = tid + x * kBlk;
       at[x] = kNone;
       if (j < ne && T.cnt[j]) {
-        const uint32_t p = part_hash(T.key[j]) & (P.parts - 1);
+        const uint32_t p = part_hash(T.key[j]) & (args()->parts - 1);
         at[x] = (p << 16) | atomicAdd(&s_hist[p], 1u);
       }
     }
@@ -547,8 +576,8 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     __syncthreads();
     if (tid == 0) {
       s_base = got;
-      if ((got & ((1ull << 40) - 1)) + ne > P.cap_recs || (got >> 40) >= P.max_lists) {
-        or32(&hdr->flags, kFlagArena);
+      if ((got & ((1ull << 40) - 1)) + ne > args()->cap_recs || (got >> 40) >= args()->max_lists) {
+        or32(&hdr_of()->flags, kFlagArena);
         s_base = ~0ull;
       }
     }
@@ -562,14 +591,14 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     if (s_base != ~0ull) {
       const uint64_t list = s_base >> 40;
       const uint32_t rec = (uint32_t)(s_base & ((1ull << 40) - 1));
-      if (tid < P.parts) P.dir[(uint64_t)tid * P.max_lists + list] = make_uint2(rec + s_start[tid], cnt);
+      if (tid < args()->parts) as_global(args()->dir)[(uint64_t)tid * args()->max_lists + list] = make_uint2(rec + s_start[tid], cnt);
 #pragma unroll
       for (uint32_t x = 0; x < kPerThread; ++x) {
         const uint32_t j = tid + x * kBlk;
         if (at[x] == kNone) continue;
         const uint32_t r = rec + s_start[at[x] >> 16] + (at[x] & 0xffffu);
-        P.rec_key[r] = T.key[j];
-        ((uint32_t*)P.rec_cnt)[r] = T.cnt[j];
+        as_global(args()->rec_key)[r] = T.key[j];
+        ((uint32_t*)as_global(args()->rec_cnt))[r] = T.cnt[j];
       }
     }
     __syncthreads();
@@ -578,7 +607,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     if (tid == 0) s_nent = 0;
     __syncthreads();
   }
-  if (over) or32(&hdr->flags, kFlagArena);
+  if (over) or32(&hdr_of()->flags, kFlagArena);
 }
 
 // ---------------------------------------------------------------------------------------

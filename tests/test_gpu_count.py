@@ -539,6 +539,12 @@ def _partitioned_texts(n, seed):
     yield "overflow", w.tobytes()[:n].ljust(n)
     long = [b"x%d" % k * 9 for k in range(7)] + [b"q" * 17, b"Q" * 16, b"q" * 300, b"q" * 2000, b"s",
             b"Mixed'Case09" * 3, b"mixed'CASE09" * 3]
+    # stripes with 0 to 512 words: about the 64, 128 and 192 that a wave lists and counts at a time
+    gap = np.repeat(2 + np.arange(40) * 2 // 3, 1500)
+    at = np.cumsum(gap)
+    w = np.full(n, 0x20, np.uint8)
+    w[at[at < n] - 1] = alphabet[rng.integers(0, 6, int((at < n).sum()))]
+    yield "short", w.tobytes()
     yield "long", b" ".join(long[k] for k in rng.integers(0, len(long), n // 200 + 9)).ljust(n)[:n]
 
 
