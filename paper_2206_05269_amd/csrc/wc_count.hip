@@ -228,8 +228,7 @@ __global__ __launch_bounds__(BLOCK) void count_kernel(CountParams P) {
     uint32_t f0, f1, f2, f3;
     uint32_t g0 = fold_classify4(cur.x, &f0), g1 = fold_classify4(cur.y, &f1);
     uint32_t g2 = fold_classify4(cur.z, &f2), g3 = fold_classify4(cur.w, &f3);
-    uint32_t w16 = movemask4(f0) | (movemask4(f1) << 4) | (movemask4(f2) << 8) |
-                   (movemask4(f3) << 12);
+    uint32_t w16 = movemask16(f0, f1, f2, f3);
     const int64_t p = ls + tid * 16;
     if (!kUtf8 && (p < R0 || p + 16 > R1)) {
       int64_t lo_cut = R0 - p, hi_cut = R1 - p;

@@ -159,12 +159,12 @@ WC_DEV uint32_t fold_classify4(uint32_t x, uint32_t* wflag) {
   return x | (letter >> 2);                   // set bit 5 of letters: fold A-Z
 }
 
-// 0x80-per-byte flags of 4 bytes -> 4-bit mask.
-WC_DEV uint32_t movemask4(uint32_t f) {
-  uint32_t s = (f >> 7) & 0x01010101u;
-  s |= s >> 7;
-  s |= s >> 14;
-  return s & 0xfu;
+// 0x80-per-byte flags of 16 bytes -> 16-bit mask, by byte dot products: each flag times its
+// bit's weight, eight bytes to a sum (6 instructions; shifts and masks of 4 bytes at a time took 25).
+WC_DEV uint32_t movemask16(uint32_t f0, uint32_t f1, uint32_t f2, uint32_t f3) {
+  const uint32_t a = __builtin_amdgcn_udot4(f1, 0x80402010u, __builtin_amdgcn_udot4(f0, 0x08040201u, 0u, false), false);
+  const uint32_t b = __builtin_amdgcn_udot4(f3, 0x80402010u, __builtin_amdgcn_udot4(f2, 0x08040201u, 0u, false), false);
+  return (a >> 7) | (b << 1);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -20,6 +20,8 @@
 // Counts are exact whatever the dictionary holds: it only decides where a word is summed.
 // Words longer than 16 bytes, and anything a bounded structure cannot take (an exhausted arena
 // region, a full pass-2 table), go to the global table directly.
+#include <type_traits>
+
 #include "wc_internal.h"
 #include "wc_stripe.h"
 
@@ -583,7 +585,7 @@ size_t global_map_dyn(uint32_t dict_cap) {
   return (size_t)kMapWaves * kStripeText +
          (size_t)kDispBuckets * 4 + (size_t)kDictSlots * 2 + (size_t)(dict_cap + 1) * 16 +
          (size_t)dict_cap * 4 +
-         (size_t)kMapWaves * kWaveStarts * 4;
+         (size_t)kMapWaves * kWaveList * 4;
 }
 
 // One workgroup of BLOCK threads scans a contiguous range of STAGE-byte stages; wave v takes
@@ -593,6 +595,10 @@ size_t global_map_dyn(uint32_t dict_cap) {
 // the word ends beside it), and up to two tokens per lane per round: counted in the
 // dictionary, or written as a record to its partition, or (longer than 16 bytes) counted in the
 // global table.
+//
+// Bound by vector instructions (8 GiB, 106 words a KiB: about 320 a stripe, the units busy for more
+// than 85 % of 5.58 ms, 1.54 TB/s of text; 6.11 ms with 361, when word flags were gathered with
+// shifts, 19 instructions a stripe, and parameters were spilled over the scan).
 //
 // Records. Each partition's records of this workgroup go to the workgroup's own blocks of that
 // partition, in the order of a per-partition ticket taken with one LDS atomic: ticket t is
@@ -612,7 +618,15 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
   static_assert(STAGE == (int)kGlobalStage && NW * (int)kStripe == STAGE,
                 "a stage is one stripe per wave");
   static_assert(NW == kMapWaves && BLOCK >= (int)kParts, "one thread per partition at the end");
-  static_assert(kWaveStarts == 128, "a round takes two tokens per lane");
+  static_assert(kWaveStarts == 192, "a round of two tokens per lane and one of one");
+  // what the scan does not need is read with args(): by name it would be loaded once, at the start,
+  // and held or spilled over the scan
+  typedef const __attribute__((address_space(4))) GlobalParams* Args;
+  auto args = []() -> Args {
+    Args a = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    __asm__ volatile("" : "+s"(a));
+    return a;
+  };
   extern __shared__ __align__(16) uint8_t s_dyn[];
   __shared__ uint32_t s_tick[kParts];  // records of each partition so far
   __shared__ uint4 s_lenmask[17];       // byte masks of word lengths 0..16
@@ -629,12 +643,12 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
   uint16_t* s_dslot = (uint16_t*)(s_disp + kDispBuckets);       // [kDictSlots]
   uint4* s_keys = (uint4*)(s_dslot + kDictSlots);               // [D + 1]
   uint32_t* s_cnt = (uint32_t*)(s_keys + D + 1);                // [D]
-  uint32_t* s_pairs = s_cnt + D;                                // [NW][kWaveStarts]
+  uint32_t* s_pairs = s_cnt + D;                                // [NW][kWaveList]
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
-  Header* hdr = P.hdr;
-  if (ld_relaxed32(&hdr->flags) & kFlagBadOffsets) return;
+  auto hdr_of = [&]() -> Header* { return as_global(args()->hdr); };
+  if (ld_relaxed32(&hdr_of()->flags) & kFlagBadOffsets) return;
   const uint64_t st0 = (uint64_t)blockIdx.x * P.stages_per_wg;
   const uint64_t st1 = min(st0 + P.stages_per_wg, P.n_stages);
   const uint64_t n_stages = P.n_stages;
@@ -652,7 +666,7 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
   for (uint32_t p = tid; p < kParts; p += BLOCK) s_tick[p] = 0;
   init_len_masks(s_lenmask, tid, BLOCK);
   for (uint32_t i = tid; i < NW * kBndWords; i += BLOCK) (&s_bnd[0][0])[i] = 0;
-  for (uint32_t i = tid; i < NW * kWaveStarts; i += BLOCK) s_pairs[i] = 0;
+  for (uint32_t i = tid; i < NW * kWaveList; i += BLOCK) s_pairs[i] = 0;
   if (tid < 4) s_stat[tid] = 0;
   if (tid == 0) s_tokens = 0;
   __syncthreads();
@@ -663,25 +677,26 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
   uint8_t* const my_txt = s_txt + wv * kStripeText;
   uint32_t* const my_bnd = s_bnd[wv];
   // per wave: kWaveStarts 16-bit starts, then the word-end bitmap
-  uint16_t* const my_starts = (uint16_t*)(s_pairs + wv * kWaveStarts);
-  uint32_t* const my_ends = s_pairs + wv * kWaveStarts + kWaveStarts / 2;
-  static_assert(kWaveStarts / 2 + kEndWords <= kWaveStarts, "starts and ends fit a wave's list");
+  uint16_t* const my_starts = (uint16_t*)(s_pairs + wv * kWaveList);
+  uint32_t* const my_ends = s_pairs + wv * kWaveList + kWaveStarts / 2;
 
   auto insert_record = [&](const uint4 r) {
     const uint64_t lo = (uint64_t)r.x | ((uint64_t)r.y << 32);
     const uint64_t hi = (uint64_t)r.z | ((uint64_t)r.w << 32);
-    table_insert<false>(P.table, P.mask, short_key_g<false>(lo, hi, P.key_mask),
-                        short_id(lo, hi, 0), 1, hdr, P.occ_limit);
+    const Args A = args();
+    table_insert<false>(as_global(A->table), A->mask, short_key_g<false>(lo, hi, A->key_mask),
+                        short_id(lo, hi, 0), 1, as_global(A->hdr), A->occ_limit);
   };
   // first document start after pos (offsets[n_docs], the end of the range, is one)
   auto doc_limit = [&](uint64_t pos) -> uint64_t {
-    uint64_t a = 1, b = P.n_docs;
+    const uint64_t* const offsets = as_global(args()->offsets);
+    uint64_t a = 1, b = args()->n_docs;
     while (a < b) {
       const uint64_t m = (a + b) >> 1;
-      if (P.offsets[m] > pos) b = m;
+      if (offsets[m] > pos) b = m;
       else a = m + 1;
     }
-    return P.offsets[a];
+    return offsets[a];
   };
 
   uint32_t spilled = 0, direct = 0;
@@ -693,106 +708,110 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
     const uint64_t limit = e == kLongEnd ? doc_limit(start) : start + (e - s + 1);
     uint64_t lo, hi, h64;
     const uint64_t n = scan_word(P.corpus, start, limit, &lo, &hi, &h64);
+    const Args A = args();
     if (n > 16) {
-      table_insert<false>(P.table, P.mask, finish_key(h64, P.key_mask),
-                          long_id(P.corpus + start, n, 0), 1, hdr, P.occ_limit);
+      table_insert<false>(as_global(A->table), A->mask, finish_key(h64, A->key_mask),
+                          long_id(P.corpus + start, n, 0), 1, as_global(A->hdr), A->occ_limit);
     } else {
-      table_insert<false>(P.table, P.mask, short_key_g<false>(lo, hi, P.key_mask),
-                          short_id(lo, hi, 0), 1, hdr, P.occ_limit);
+      table_insert<false>(as_global(A->table), A->mask, short_key_g<false>(lo, hi, A->key_mask),
+                          short_id(lo, hi, 0), 1, as_global(A->hdr), A->occ_limit);
     }
   };
 
-  // One round: starts t and t + 64 of this wave's list (t = lane), for those below nw. A word's
-  // end is the first set bit of the end bitmap at or after its start. Both tokens go through
-  // each step together, so their LDS reads overlap. A token that misses the dictionary becomes
+  // One round: NX starts per lane of this wave's list from place `from` on (lane l: from + l, and
+  // 64 after it), for the nw that are there. A word's end is the first set bit of the end bitmap
+  // at or after its start. A lane's tokens go through each step together, so their LDS reads
+  // overlap. A token that misses the dictionary becomes
   // a record of its partition.
-  auto token_round = [&](uint32_t nw, int64_t p0) {
-    uint32_t s2[2], n2[2], e0[2], e1[2];
-    bool f2[2];
+  auto token_round = [&](auto nx, uint32_t from, uint32_t nw, int64_t p0) {
+    constexpr int NX = decltype(nx)::value;
+    uint32_t s2[NX], n2[NX], e0[NX], e1[NX];
+    bool f2[NX];
     // (list entries past nw are stale starts of earlier rounds: in range, not counted)
 #pragma unroll
-    for (int x = 0; x < 2; ++x) s2[x] = my_starts[lane + 64 * x];
+    for (int x = 0; x < NX; ++x) s2[x] = my_starts[from + lane + 64 * x];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       e0[x] = my_ends[s2[x] >> 5];
       e1[x] = my_ends[(s2[x] >> 5) + 1];
     }
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       n2[x] = __ffs(__builtin_amdgcn_alignbit(e1[x], e0[x], s2[x] & 31));  // 0: no end in 32
       f2[x] = lane + 64 * x < nw && n2[x] - 1 < 16u;
     }
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < NX; ++x)
       if (lane + 64 * x < nw && !f2[x]) {
         long_token(p0, s2[x], n2[x] ? s2[x] + n2[x] - 1 : kLongEnd);
         wait_vmem();
       }
-    // each LDS step reads for both tokens before either waits (pin)
-    PackSrc ps[2];
-    uint4 lm[2];
+    // each LDS step reads for all tokens before either waits (pin)
+    PackSrc ps[NX];
+    uint4 lm[NX];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       ps[x] = pack_read(my_txt, s2[x]);
       lm[x] = s_lenmask[f2[x] ? n2[x] : 1u];
     }
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       pin(ps[x]);
       pin(lm[x]);
     }
-    uint64_t lo2[2], hi2[2];
-    uint32_t h2[2];
+    uint64_t lo2[NX], hi2[NX];
+    uint32_t h2[NX];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       pack_join(ps[x], lm[x], &lo2[x], &hi2[x]);
       h2[x] = word_hash32(lo2[x], hi2[x]);
     }
     // the perfect hash's slot (dict_slot) from the unpacked displacement
-    uint32_t d2[2], i2[2];
-    uint4 k2[2];
+    uint32_t d2[NX], i2[NX];
+    uint4 k2[NX];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) d2[x] = s_disp[dict_group(h2[x])];
+    for (int x = 0; x < NX; ++x) d2[x] = s_disp[dict_group(h2[x])];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) pin(d2[x]);
+    for (int x = 0; x < NX; ++x) pin(d2[x]);
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       const uint32_t f = (h2[x] >> ((d2[x] >> 8) & 31u)) ^ d2[x];
       i2[x] = *(const uint16_t*)((const uint8_t*)s_dslot + (d2[x] >> 16) + ((f & 0xffu) << 1));
     }
 #pragma unroll
-    for (int x = 0; x < 2; ++x) pin(i2[x]);
+    for (int x = 0; x < NX; ++x) pin(i2[x]);
 #pragma unroll
-    for (int x = 0; x < 2; ++x) k2[x] = s_keys[i2[x]];
+    for (int x = 0; x < NX; ++x) k2[x] = s_keys[i2[x]];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) pin(k2[x]);
-    bool m2[2];
+    for (int x = 0; x < NX; ++x) pin(k2[x]);
+    bool m2[NX];
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       const bool hit = key_eq(k2[x], key4(lo2[x], hi2[x]));
       if (f2[x] && hit) atomicAdd(&s_cnt[i2[x]], 1u);
       m2[x] = f2[x] && !hit;
     }
-    uint32_t t2[2] = {0u, 0u};
+    uint32_t t2[NX] = {};
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < NX; ++x)
       if (m2[x]) t2[x] = atomicAdd(&s_tick[part_of(h2[x])], 1u);
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+    for (int x = 0; x < NX; ++x) {
       if (m2[x]) {
         const uint32_t p = part_of(h2[x]), j = t2[x] / kBlockRec, at = t2[x] % kBlockRec;
         const uint4 rec = key4(lo2[x], hi2[x]);
         if (j < J) {
           const uint64_t k = (uint64_t)w * J + j;
           P.arena[(k * kParts + p) * kBlockRec + at] = rec;
-          if (at == kBlockRec - 1) P.fill[(uint64_t)p * P.S + k] = (uint16_t)kBlockRec;
+          if (at == kBlockRec - 1) as_global(args()->fill)[(uint64_t)p * args()->S + k] = (uint16_t)kBlockRec;
         } else {
           ++direct;  // the partition's share of blocks is used up
           insert_record(rec);
         }
       }
     }
-    spilled += (m2[0] ? 1u : 0u) + (m2[1] ? 1u : 0u);
+#pragma unroll
+    for (int x = 0; x < NX; ++x) spilled += m2[x] ? 1u : 0u;
   };
 
   // Wave wv scans its own contiguous run of nsw stripes of the workgroup's range. The word
@@ -808,7 +827,9 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
   // a stripe inside the text (the wave-uniform common case) is loaded without per-lane checks
   auto load_main = [&](uint64_t i) -> uint4 {
     const int64_t p = stripe_pos(i);
-    if (p >= 0 && p + (int64_t)kStripe <= (int64_t)P.len) return load_stream16(P.corpus + p + lane * 16);
+    uint32_t at = lane * 16;
+    pin(at);
+    if (p >= 0 && p + (int64_t)kStripe <= (int64_t)P.len) return load_stream16(P.corpus + p + at);
     return load_text16(P.corpus, P.len, p + lane * 16);
   };
 
@@ -843,8 +864,9 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
     bool plain = run_plain;
     if (!run_plain) {
       const uint64_t stage = (sw0 + i) / NW;
-      c0 = P.stage_doc[stage];
-      c2 = P.stage_doc[min(stage + 1, n_stages)];
+      const uint64_t* const stage_doc = as_global(args()->stage_doc);
+      c0 = stage_doc[stage];
+      c2 = stage_doc[min(stage + 1, n_stages)];
       plain = c2 == c0 && p0 >= R0 && p0 + (int64_t)kStripe <= R1;
     }
 
@@ -860,15 +882,16 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
     uint32_t bnd16 = 0, bnext = 0;
     if (!plain) {
       if (c2 > c0) {
+        const uint64_t* const offsets = as_global(args()->offsets);
         uint64_t j0 = c0, j1 = c2;
         while (j1 - j0 > 64) {  // first document starting at or after p0
           const uint64_t m = (j0 + j1) >> 1;
-          if ((int64_t)P.offsets[m] < p0) j0 = m + 1;
+          if ((int64_t)offsets[m] < p0) j0 = m + 1;
           else j1 = m;
         }
         for (uint64_t jb = j0; jb < c2; jb += 64) {
           const uint64_t j = jb + lane;
-          const int64_t o = j < c2 ? (int64_t)P.offsets[j] : INT64_MAX;
+          const int64_t o = j < c2 ? (int64_t)offsets[j] : INT64_MAX;
           if (o >= p0 && o < p0 + (int64_t)kStripe) {
             const uint32_t rel = (uint32_t)(o - p0);
             atomicOr(&my_bnd[rel >> 5], 1u << (rel & 31));
@@ -921,7 +944,14 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
       if (extra && w0 == 0) my_starts[0] = (uint16_t)def_s;
       write_starts16(start16, incl - c + extra, w0, my_starts);
       wave_sync();
-      token_round(min(n - w0, kWaveStarts), p0 - 16);
+      // (a stripe of 170 words, usual for English text, took two rounds of 128)
+      const uint32_t nw = min(n - w0, kWaveStarts);
+      uint32_t from = 0;
+      if (nw > 64) {
+        token_round(std::integral_constant<int, 2>(), 0, nw, p0 - 16);
+        from = 128;
+      }
+      if (from < nw) token_round(std::integral_constant<int, 1>(), from, nw - from, p0 - 16);
       wave_sync();
     }
     // the stripe's last 16 bytes become the next stripe's prefix
@@ -941,17 +971,17 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
   __syncthreads();
   if (tid < (int)kParts) {
     const uint32_t t = s_tick[tid], j = t / kBlockRec, at = t % kBlockRec;
-    if (at && j < J) P.fill[(uint64_t)tid * P.S + (uint64_t)w * J + j] = (uint16_t)at;
+    if (at && j < J) as_global(args()->fill)[(uint64_t)tid * args()->S + (uint64_t)w * J + j] = (uint16_t)at;
   }
-  for (uint32_t i = tid; i < nd; i += BLOCK) P.dict_part[(uint64_t)blockIdx.x * D + i] = s_cnt[i];
+  for (uint32_t i = tid; i < nd; i += BLOCK) as_global(args()->dict_part)[(uint64_t)blockIdx.x * D + i] = s_cnt[i];
   if (spilled) atomicAdd(&s_stat[0], spilled);
   if (direct) atomicAdd(&s_stat[1], direct);
   if (lane == 0 && tokens) atomicAdd(&s_tokens, (unsigned long long)tokens);
   __syncthreads();
   if (tid == 0) {
-    add64(&hdr->total_tokens, s_tokens);
-    if (s_stat[0]) add64(&hdr->stat[0], s_stat[0]);
-    if (s_stat[1]) add64(&hdr->stat[1], s_stat[1]);
+    add64(&hdr_of()->total_tokens, s_tokens);
+    if (s_stat[0]) add64(&hdr_of()->stat[0], s_stat[0]);
+    if (s_stat[1]) add64(&hdr_of()->stat[1], s_stat[1]);
   }
 }
 

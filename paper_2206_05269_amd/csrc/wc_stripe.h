@@ -38,7 +38,7 @@ WC_DEV uint4 classify16(uint4 v, uint32_t* w16) {
   g.y = fold_classify4(v.y, &f1);
   g.z = fold_classify4(v.z, &f2);
   g.w = fold_classify4(v.w, &f3);
-  *w16 = movemask4(f0) | (movemask4(f1) << 4) | (movemask4(f2) << 8) | (movemask4(f3) << 12);
+  *w16 = movemask16(f0, f1, f2, f3);
   return g;
 }
 
@@ -192,6 +192,7 @@ WC_DEV void write_starts16(uint32_t m, uint32_t rank, uint32_t w0, uint16_t* sta
 // Word-end bitmap of a wave's staged text: bit p set when byte p of the staged text (16-byte
 // prefix, the stripe) is the last byte of a word; kEndWords words, the tail always zero.
 constexpr uint32_t kEndWords = (kStripeText + 31) / 32 + 1;
+constexpr uint32_t kWaveList = (kWaveStarts / 2 + kEndWords + 3) & ~3u;  // words of starts and ends
 
 // ---------------------------------------------------------------------------------------
 // LDS table of 16-byte keys: kRedSlots slots of (19-bit tag << 13 | entry) probed in groups of

@@ -85,8 +85,8 @@ WC_DEV bool doc_starts_at(const uint64_t* offsets, uint64_t n_docs, int64_t q) {
 // iteration per lead byte of the lane with the most; lanes without one cost nothing.
 WC_DEV uint32_t utf8_mask(const uint4 g, uint32_t next, uint32_t starts) {
   const uint32_t H = 0x80808080u;  // leads have the two top bits set
-  uint32_t leads = movemask4(g.x & (g.x << 1) & H) | (movemask4(g.y & (g.y << 1) & H) << 4) |
-                   (movemask4(g.z & (g.z << 1) & H) << 8) | (movemask4(g.w & (g.w << 1) & H) << 12);
+  uint32_t leads = movemask16(g.x & (g.x << 1) & H, g.y & (g.y << 1) & H, g.z & (g.z << 1) & H,
+                              g.w & (g.w << 1) & H);
   uint32_t res = 0;
   while (leads) {
     const uint32_t j = __ffs(leads) - 1, k = j >> 2;

@@ -574,6 +574,14 @@ def test_partitioned_count(n):
             assert (np.diff(wo) > 0).all() and wo[-1] == got.res.word_bytes
 
 
+@pytest.mark.parametrize("n", [1025, 300_007])
+def test_two_pass_words_per_stripe(n):
+    """Pass 1 lists 192 words of a stripe and counts two a lane, then one: 0 to 512 a stripe."""
+    for name, text in _partitioned_texts(n, n + 1):
+        if name in ("short", "bytes", "hot"):
+            check(text, np.array([0, n // 3, n // 3 + 1, n]), debug_flags=wc.WC_DEBUG_SPILL)
+
+
 @pytest.mark.parametrize("path", ["direct", "spill"])
 def test_plain_1mb_int32(path):
     c = synth.generate("plain-1MB")
