@@ -429,15 +429,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
         else if (res == kNoSlot && lane == 0) or32(&hdr_of()->flags, kFlagStall);
       };
       for (uint32_t w0 = 0; w0 < n; w0 += kList) {
-        {
-          uint32_t m = start16, r = incl - c;
-          while (m) {
-            const uint32_t j = __ffs(m) - 1;
-            if (r - w0 < kList) my_starts[r - w0] = (uint16_t)(lane * 16 + j);
-            ++r;
-            m &= m - 1;
-          }
-        }
+        list_starts(start16, lane * 16, incl - c - w0, n <= kList, kList, my_starts);
         wave_sync();
         // two tokens a lane while more than 64 are left, then one
         const uint32_t nl = min(n - w0, kList);
@@ -787,7 +779,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   __syncthreads();
   if (tid == 0) {
     if (s_tokens) add64(&hdr_of()->total_tokens, s_tokens);
-    __threadfence();
+    // (the cursor, which the last workgroup reads, has answered all of this one's additions)
     const uint64_t done = __hip_atomic_fetch_add(&hdr_of()->occupied, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (done + 1 == gridDim.x) {  // the last workgroup closes the output
       const uint64_t c = ld_relaxed(&hdr_of()->out_cursor);

@@ -942,7 +942,7 @@ __global__ __launch_bounds__(BLOCK) void global_map_kernel(GlobalParams P) {
     tokens += n;
     for (uint32_t w0 = 0; w0 < n; w0 += kWaveStarts) {
       if (extra && w0 == 0) my_starts[0] = (uint16_t)def_s;
-      write_starts16(start16, incl - c + extra, w0, my_starts);
+      list_starts(start16, 16 + lane * 16, incl - c + extra - w0, n <= kWaveStarts, kWaveStarts, my_starts);
       wave_sync();
       // (a stripe of 170 words, usual for English text, took two rounds of 128)
       const uint32_t nw = min(n - w0, kWaveStarts);

@@ -137,7 +137,8 @@ WC_DEV void export_table(const PartParams& P, const PartTable<C>& T, bool last, 
   }
   __syncthreads();
   if (kWide && last && tid == 0) {
-    __threadfence();
+    // (what the last one reads, the cursor, has answered this workgroup's addition: no fence, which
+    // writes the XCD's L2 back, before this one: reduce of 2,000 tables 26 -> 23 us)
     const uint64_t done = __hip_atomic_fetch_add(&P.hdr->work_next, 1ull, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
     if (done + 1 == parts) {
@@ -513,13 +514,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         continue;
       }
       if (off == 0) {  // list the starts of ranks [w0, w0 + kList)
-        uint32_t m = start16, r = rank - w0;
-        while (m) {
-          const uint32_t j = __ffs(m) - 1;
-          if (r < kList) my_starts[r] = (uint16_t)(lane * 16 + j);
-          ++r;
-          m &= m - 1;
-        }
+        list_starts(start16, lane * 16, rank - w0, n <= kList, kList, my_starts);
         wave_sync();
       }
       // a round: two tokens a lane from the list's start, if there are more than 64, one from its

@@ -177,15 +177,22 @@ WC_DEV uint32_t load_text4(const uint8_t* corpus, uint64_t len, int64_t p) {
   return w;
 }
 
-// Positions of the word starts in this lane's 16 bytes (after the 16-byte prefix), in text
-// order, for the ranks in [w0, w0 + kWaveStarts).
-WC_DEV void write_starts16(uint32_t m, uint32_t rank, uint32_t w0, uint16_t* starts) {
-  const uint32_t pos0 = 16 + (threadIdx.x & 63) * 16;
-  while (m) {
-    const uint32_t j = __ffs(m) - 1;
-    if (rank - w0 < kWaveStarts) starts[rank - w0] = (uint16_t)(pos0 + j);
-    ++rank;
-    m &= m - 1;
+// Lists the set bits of each lane's 16-bit mask m, as positions pos0 + bit (pos0 a multiple of 16),
+// in order from `rank` of the wave's list on, where that is below cap; fits (the same in all
+// lanes): it is for all bits of all lanes. (An iteration is then 8 instructions instead of 17.)
+WC_DEV void list_starts(uint32_t m, uint32_t pos0, uint32_t rank, bool fits, uint32_t cap, uint16_t* starts) {
+  if (fits) {
+    uint16_t* at = starts + rank;
+    while (m) {
+      *at++ = (uint16_t)(pos0 | (uint32_t)__builtin_ctz(m));
+      m &= m - 1;
+    }
+  } else {
+    while (m) {
+      if (rank < cap) starts[rank] = (uint16_t)(pos0 | (uint32_t)__builtin_ctz(m));
+      ++rank;
+      m &= m - 1;
+    }
   }
 }
 
