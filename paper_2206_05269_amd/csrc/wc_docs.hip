@@ -39,7 +39,7 @@
 // workgroups per CU with half the table each were slower (more and smaller groups, more spills).
 // 100,000 documents (lognormal, median 16 KiB, 2.7 GB, 119 million entries), before as two passes
 // with tables of 4,096 entries in LDS and in device memory: 12.7 -> 6.6 ms; 2,000 documents of 2 to
-// 20 KiB: 181 -> 96 us.
+// 20 KiB: 181 -> 81 us.
 //
 // Every size the kernels need is read from a device-side task description, so a whole call
 // can be captured once in a HIP graph and replayed for other corpora.
@@ -823,14 +823,16 @@ __global__ __launch_bounds__(1024) void doc_order_kernel(DocParams P) {
   }
 }
 
-// Bytes per work item where the caller has not said: two items per workgroup, in steps of 16 KiB.
-// Fewer and larger ones have less to wait for between them (the output's place, the first text;
-// about 5 us an item), until many do not fit the table: kernel time of 100,000 documents (2.7 GB)
-// with 16 / 24 / 32 / 48 / 64 KiB 8.4 / 8.3 / 7.5 / 7.1 / 7.6 ms, of 2,000 (18 MB, 256 workgroups)
-// 122 / 105 / 100 / 133 / 195 us.
+// Bytes per work item where the caller has not said: the fewest items that are the same number for
+// every workgroup and at most kMaxWin bytes. Fewer and larger ones have less to wait for between
+// them (the output's place, the first text; about 5 us an item), until many do not fit the table:
+// kernel time of 100,000 documents (2.7 GB) with 16 / 24 / 32 / 48 / 64 KiB 8.4 / 8.3 / 7.5 / 7.1 /
+// 7.6 ms. With few to a workgroup some would take one more than others: 2,000 documents (17.6 MB,
+// 256 workgroups) took 94 us with 32 KiB, 2.1 items each, and 81 with 34, two each.
 WC_DEV uint64_t window_bytes(uint64_t len, uint32_t grid) {
-  const uint64_t w = len / (2 * (uint64_t)grid) & ~(kMinWin - 1);
-  return min(max(w, kMinWin), kMaxWin);
+  const uint64_t k = (len + grid * kMaxWin - 1) / (grid * kMaxWin);  // items per workgroup
+  const uint64_t w = (len + grid * max(k, (uint64_t)1) - 1) / (grid * max(k, (uint64_t)1));
+  return min(max((w + 1023) & ~1023ull, kMinWin), kMaxWin);
 }
 
 // Checks the offsets and lists the work: documents longer than a window and the size limit in
