@@ -95,9 +95,10 @@ typedef struct wc_tuning {
   uint32_t chunk_bytes;   /* per-document mode: bytes per work item, power of two in
                              16 KiB..1 MiB (0 = by the size of the text, 16 to 48 KiB) */
   uint32_t direct_kib;    /* per-document mode, document-centric kernel: documents longer
-                             than chunk_bytes and than this many KiB are counted before all
-                             others, largest first (0 = 9/4 of chunk_bytes, 72 KiB without
-                             it; WC_DIRECT_NEVER = none) */
+                             than chunk_bytes and than this many KiB are reported in
+                             stats[3] (0 = 9/4 of chunk_bytes, 72 KiB without it;
+                             WC_DIRECT_NEVER = none). Work is taken largest first whatever
+                             it says */
 } wc_tuning;
 
 #define WC_DIRECT_NEVER 0xffffffffu

@@ -256,8 +256,7 @@ struct DocLayout {
   uint64_t* doc_ptr;
   uint64_t* doc_len;
   Slot* arena;
-  uint64_t* over_docs;
-  uint64_t* over_sorted;
+  uint64_t class_at[kDocClasses + 1];
   uint64_t total;
 };
 
@@ -278,9 +277,13 @@ void layout_docs(uint64_t len, uint64_t n_docs, const wc_opts* o, void* ws, DocL
   L->arena_slots = o->table_slots ? o->table_slots
                                   : std::max<uint64_t>(1ull << 16, len / 16 + 64 * 4096);
   Bump B(ws);
-  L->hdr = B.take<Header>(sizeof(Header));
+  L->hdr = B.take<Header>(kDocHeadBytes);
   L->task = B.take<DocTask>(sizeof(DocTask));
-  L->items = B.take<uint64_t>(std::max<uint64_t>(n_docs, 1) * 8);
+  // items of a class: each has a document, and together at most the text
+  L->class_at[0] = 0;
+  for (uint32_t k = 0; k < kDocClasses; ++k)
+    L->class_at[k + 1] = L->class_at[k] + std::min(n_docs, k ? (len >> (13 + k)) + 1 : n_docs);
+  L->items = B.take<uint64_t>(std::max<uint64_t>(L->class_at[kDocClasses], 1) * 8);
   L->woff = B.take<uint64_t>((L->cap_e + 1) * 8);
   L->words = B.take<uint8_t>(L->cap_b);
   L->counts = B.take<uint8_t>(L->cap_e * o->count_bytes);
@@ -288,8 +291,6 @@ void layout_docs(uint64_t len, uint64_t n_docs, const wc_opts* o, void* ws, DocL
   L->doc_ptr = B.take<uint64_t>(std::max<uint64_t>(n_docs, 1) * 8);
   L->doc_len = B.take<uint64_t>(std::max<uint64_t>(n_docs, 1) * 8);
   L->arena = B.take<Slot>(L->arena_slots * sizeof(Slot));
-  L->over_docs = B.take<uint64_t>(std::max<uint64_t>(n_docs, 1) * 8);
-  L->over_sorted = B.take<uint64_t>(std::max<uint64_t>(n_docs, 1) * 8);
   L->total = B.off;
 }
 
@@ -314,8 +315,8 @@ DocParams doc_params(const DocLayout& L, const wc_opts* o, uint32_t lds, uint32_
   P.cap_e = L.cap_e;
   P.cap_b = L.cap_b;
   P.arena = L.arena;
-  P.over_docs = L.over_docs;
-  P.over_sorted = L.over_sorted;
+  memcpy(P.class_at, L.class_at, sizeof(P.class_at));
+  P.class_n = (uint32_t*)(L.hdr + 1);
   P.arena_slots = L.arena_slots;
   P.count_bias = o->debug_count_bias;
   return P;
@@ -569,8 +570,7 @@ wc_status wc_count(const uint8_t* d_corpus, uint64_t corpus_len, const uint64_t*
     HIPCHK(tm.init(opts->debug_flags & WC_DEBUG_TIME));
     if (tm.on) HIPCHK(hipEventRecord(tm.c, s));
     DocTask task{d_corpus, corpus_len, d_offsets, n_docs};
-    HIPCHK(hipMemcpyAsync(D.task, &task, sizeof(task), hipMemcpyHostToDevice, s));
-    HIPCHK(launch_fill_zero(D.hdr, sizeof(Header), s));
+    HIPCHK(launch_doc_begin(D.hdr, D.task, task, s));
     uint32_t grid = tu.grid ? tu.grid : (uint32_t)device_cus();
     DocParams P = doc_params(D, opts, lds, tu.pct, tu.chunk, tu.direct_kib, grid);
     if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
@@ -1321,7 +1321,7 @@ wc_status wc_batch_run(wc_batch* b, const uint8_t* d_corpus, uint64_t corpus_len
     DocParams P = doc_params(b->D, &b->opts, b->lds, tu.pct, tu.chunk, tu.direct_kib, b->grid);
     hipError_t e = hipMemcpyAsync(b->D.task, b->h_task, sizeof(DocTask), hipMemcpyHostToDevice,
                                   b->bs);
-    if (e == hipSuccess) e = launch_fill_zero(b->D.hdr, sizeof(Header), b->bs);
+    if (e == hipSuccess) e = launch_fill_zero(b->D.hdr, kDocHeadBytes, b->bs);
     if (e == hipSuccess) e = launch_docs(P, b->bs);
     if (e == hipSuccess)
       e = hipMemcpyAsync(b->h_hdr, b->D.hdr, sizeof(Header), hipMemcpyDeviceToHost, b->bs);

@@ -60,14 +60,14 @@ struct Header {
   uint64_t max_count;
   uint64_t work_next;     // work-queue cursor (persistent launches)
   uint64_t out_cursor;    // per-document output: (entries << 32) | word bytes reserved
-  uint64_t arena_next;    // per-document output: private-table slots taken; partitioned count:
+  uint64_t arena_next;    // per-document output: arena slots taken; partitioned count:
                           // (lists << 40) | records
   // two-pass global count statistics: records written to the partitions, records pass 1
   // counted straight in the global table, dictionary words, (unused), records pass 2 could
   // not sum in LDS
   uint64_t stat[5];
-  uint64_t over_n;        // per-document output: documents queued for the second pass
-  uint64_t over_next;     // per-document output: second-pass queue cursor
+  uint64_t over_n;        // per-document output: documents above the size limit
+  uint64_t pad1;
 };
 static_assert(sizeof(Header) == 128, "header layout");
 

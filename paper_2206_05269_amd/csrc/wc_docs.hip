@@ -2,10 +2,10 @@
 // Section 3.1, before the grouping of Section 3.3).
 //
 // Work. The corpus is cut into windows; a window owns the documents whose first byte lies in it. A
-// document longer than the window is always its last one; such documents are counted alone, and
-// those longer than the size limit (direct_kib) too, largest first and before all others. The rest
-// of a window is counted up to kDocW documents at a time ("group"). doc_plan_kernel lists the
-// groups; persistent workgroups (1024 threads, one per CU) take them from a queue.
+// document longer than the window is always its last one; such documents are counted alone, the
+// rest of a window up to kDocW documents at a time ("group"). doc_plan_kernel lists the groups by
+// size class; persistent workgroups (1024 threads, one per CU) take them from a queue, the
+// largest class first.
 //
 // Counting. A group's text is scanned by the workgroup's waves, each on a contiguous run of 1 KiB
 // stripes and on its own (no workgroup barrier inside the scan). A token's document is its index r
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   __shared__ uint4 s_lenmask[17];
   __shared__ uint64_t s_doff[3][kDocW + 1];        // document offsets of the group and the next two
   __shared__ unsigned long long s_dcur[kDocW];     // places taken: (entries << 32 | bytes)
-  __shared__ uint32_t s_sum[4];
+  __shared__ uint32_t s_sum[4], s_class[kDocClasses + 1];
   __shared__ uint64_t s_out;
   __shared__ unsigned long long s_tokens;
   __shared__ uint32_t s_nent, s_spill, s_next, s_done;
@@ -136,8 +136,6 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   const uint64_t len = uniform64(as_global(args()->task)->len);
   auto offset_at = [&](uint32_t d) -> uint64_t { return as_global(as_global(args()->task)->offsets)[d]; };
   const int64_t base_off = -(int64_t)((uintptr_t)corpus & 15);
-  const uint32_t n_big = (uint32_t)uniform64(hdr_of()->over_n);
-  const uint32_t n_items = n_big + (uint32_t)uniform64(hdr_of()->over_next);
   if (ld_relaxed32(&hdr_of()->flags) & kFlagBadOffsets) return;
 
   PartTable<uint32_t, kDocSlots> T;
@@ -636,10 +634,24 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   };
 
   // ---- the queue ------------------------------------------------------------------------------
-  // An item is a run of documents: (documents << 32 | first one), 0 when there is none left.
+  // An item is a run of documents: (documents << 32 | first one), 0 when there is none left. The
+  // queue takes them by size class, the largest first (a workgroup that took a large document
+  // late would otherwise finish alone).
+  if (tid == 0) {
+    uint32_t n = 0;
+    for (int k = kDocClasses - 1; k >= 0; --k) {
+      s_class[kDocClasses - 1 - k] = n;
+      n += as_global(args()->class_n)[k];
+    }
+    s_class[kDocClasses] = n;
+  }
+  __syncthreads();
   auto item_at = [&](uint32_t q) -> uint64_t {
-    if (q >= n_items) return 0;
-    return uniform64(q < n_big ? (1ull << 32) | as_global(args()->over_sorted)[q] : as_global(args()->items)[q - n_big]);
+    if (q >= s_class[kDocClasses]) return 0;
+    const uint32_t at = s_class[min(lane, kDocClasses - 1)];
+    const uint32_t c = 31 - (uint32_t)__clz((int)(uint32_t)(__ballot(at <= q) & ((1u << kDocClasses) - 1)));
+    const uint32_t i = q - (uint32_t)__builtin_amdgcn_readlane((int)at, (int)c);
+    return uniform64(as_global(args()->items)[args()->class_at[kDocClasses - 1 - c] + i]);
   };
   auto next_pos = [&]() -> uint32_t {  // (one lane's)
     return gridDim.x + (uint32_t)atomicAdd((unsigned long long*)&hdr_of()->work_next, 1ull);
@@ -790,39 +802,6 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   }
 }
 
-// The queued documents, largest first: a counting sort over power-of-two size classes by one
-// workgroup (each thread keeps the same entries in both passes). A workgroup that took a large
-// document late would otherwise finish alone.
-__global__ __launch_bounds__(1024) void doc_order_kernel(DocParams P) {
-  constexpr uint32_t kClasses = 48;  // floor(log2(bytes)), largest first
-  __shared__ uint32_t s_cnt[kClasses], s_at[kClasses];
-  const uint64_t n = P.hdr->over_n;
-  const uint64_t* offsets = as_global(P.task->offsets);
-  if (threadIdx.x < kClasses) s_cnt[threadIdx.x] = 0;
-  __syncthreads();
-  for (uint64_t q = threadIdx.x; q < n; q += blockDim.x) {
-    const uint64_t d = P.over_docs[q];
-    const uint64_t b = offsets[d + 1] - offsets[d];
-    const uint32_t c = b ? 63u - (uint32_t)__clzll((long long)b) : 0u;
-    const uint32_t k = kClasses - 1 - min(c, kClasses - 1);
-    P.over_docs[q] = d | ((uint64_t)k << 56);
-    atomicAdd(&s_cnt[k], 1u);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    uint32_t a = 0;
-    for (uint32_t k = 0; k < kClasses; ++k) {
-      s_at[k] = a;
-      a += s_cnt[k];
-    }
-  }
-  __syncthreads();
-  for (uint64_t q = threadIdx.x; q < n; q += blockDim.x) {
-    const uint64_t e = P.over_docs[q];
-    P.over_sorted[atomicAdd(&s_at[(uint32_t)(e >> 56)], 1u)] = e & kDocIdMask;
-  }
-}
-
 // Bytes per work item where the caller has not said: the fewest items that are the same number for
 // every workgroup and at most kMaxWin bytes. Fewer and larger ones have less to wait for between
 // them (the output's place, the first text; about 5 us an item), until many do not fit the table:
@@ -835,22 +814,35 @@ WC_DEV uint64_t window_bytes(uint64_t len, uint32_t grid) {
   return min(max((w + 1023) & ~1023ull, kMinWin), kMaxWin);
 }
 
-// Checks the offsets and lists the work: documents longer than a window and the size limit in
-// the queue, other documents longer than a window as an item each, and the rest of each window's
-// documents, the window's first document's lane by kDocW at a time.
-__global__ __launch_bounds__(256) void doc_plan_kernel(DocParams P) {
+__global__ void doc_begin_kernel(Header* hdr, DocTask* task, DocTask value) {
+  if (threadIdx.x < kDocHeadBytes / 4) ((uint32_t*)hdr)[threadIdx.x] = 0;
+  if (threadIdx.x == 0) *task = value;
+}
+
+// Checks the offsets and lists the work items in their size classes: documents longer than a window
+// by themselves, and the rest of each window's documents, by the thread of the first of them. (More
+// than kDocW documents: several items, in class 0.) Items are ranked in LDS, and a workgroup takes
+// its places with an atomic per class: one per wave and class, on few addresses, took 98 us for
+// 100,000 documents instead of 25.
+__global__ __launch_bounds__(kBlk) void doc_plan_kernel(DocParams P) {
+  __shared__ uint32_t s_n[kDocClasses], s_at[kDocClasses];
   const uint64_t len = P.task->len, n_docs = P.task->n_docs;
   const uint64_t* offsets = as_global(P.task->offsets);
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t step = (uint64_t)gridDim.x * blockDim.x;
-  const uint64_t win = P.win_bytes ? P.win_bytes : window_bytes(len, P.grid), limit = P.direct_kib ? max(win, (uint64_t)P.direct_kib << 10) : ~0ull;
-  for (uint64_t i0 = blockIdx.x * (uint64_t)blockDim.x + (threadIdx.x & ~63u); i0 <= n_docs; i0 += step) {
-    const uint64_t i = i0 + lane;
+  const uint64_t win = P.win_bytes ? P.win_bytes : window_bytes(len, P.grid);
+  const uint64_t limit = P.direct_kib ? max(win, (uint64_t)P.direct_kib << 10) : ~0ull;
+  for (uint64_t i0 = blockIdx.x * (uint64_t)blockDim.x; i0 <= n_docs; i0 += step) {
+    const uint64_t i = i0 + threadIdx.x;
+    if (threadIdx.x < kDocClasses) s_n[threadIdx.x] = 0;
+    __syncthreads();
     const uint64_t a = i <= n_docs ? offsets[i] : 0, b = i < n_docs ? offsets[i + 1] : a;
     const bool bad = i <= n_docs && (a > b || (i == n_docs && a > len));
     if (bad) or32(&P.hdr->flags, kFlagBadOffsets);
     const bool doc = i < n_docs && !bad;
-    const bool queued = doc && b - a > limit, alone = doc && !queued && b - a > win;
+    const bool alone = doc && b - a > win;
+    const uint64_t over = __ballot(doc && b - a > limit);
+    if (over && lane == 0) add64(&P.hdr->over_n, (uint64_t)__popcll(over));
     uint64_t end = i;  // documents [i, end) of this lane's window
     if (doc && b - a <= win && (i == 0 || offsets[i - 1] / win != a / win)) {
       const uint64_t x = (a / win + 1) * win;
@@ -868,19 +860,26 @@ __global__ __launch_bounds__(256) void doc_plan_kernel(DocParams P) {
       const uint64_t z = offsets[end] - offsets[end - 1];
       if (end - 1 > i && z > win && z <= len) --end;  // the window's last, listed by its own lane
     }
-    const uint32_t n = alone ? 1u : (uint32_t)((end - i + kDocW - 1) / kDocW);
-    const uint32_t ni = wave_incl_scan(n), nq = wave_incl_scan(queued ? 1u : 0u);
-    uint64_t at = 0, aq = 0;
-    if (lane == 63) {
-      if (ni) at = atomicAdd((unsigned long long*)&P.hdr->over_next, (unsigned long long)ni);
-      if (nq) aq = atomicAdd((unsigned long long*)&P.hdr->over_n, (unsigned long long)nq);
+    if (alone) end = i + 1;
+    const uint32_t n = (uint32_t)((end - i + kDocW - 1) / kDocW);
+    uint32_t cls = 0;
+    if (n == 1) {
+      const uint64_t bytes = offsets[end] - a;
+      cls = bytes < (16u << 10) ? 0u : min(63u - (uint32_t)__clzll((long long)(bytes >> 13)), kDocClasses - 1);
     }
-    at = __shfl(at, 63, 64) + ni - n;
-    aq = __shfl(aq, 63, 64) + nq - 1;
-    if (queued) P.over_docs[aq] = i;
-    // (runs of offsets in order are apart, so that there are at most n_docs)
-    for (uint64_t d = i; d < (alone ? i + 1 : end) && at < n_docs; d += kDocW)
-      P.items[at++] = ((alone ? 1ull : min((uint64_t)kDocW, end - d)) << 32) | d;
+    uint32_t at = n ? atomicAdd(&s_n[cls], n) : 0u;
+    __syncthreads();
+    if (threadIdx.x < kDocClasses && s_n[threadIdx.x])
+      s_at[threadIdx.x] = atomicAdd(&P.class_n[threadIdx.x], s_n[threadIdx.x]);
+    __syncthreads();
+    if (n) {
+      at += s_at[cls];
+      // (runs of offsets in order fit their class; others fail the call)
+      const uint64_t lo = P.class_at[cls], hi = P.class_at[cls + 1];
+      for (uint64_t d = i; d < end; d += kDocW, ++at)
+        if (lo + at < hi) P.items[lo + at] = (min((uint64_t)kDocW, end - d) << 32) | d;
+    }
+    __syncthreads();
   }
 }
 
@@ -888,9 +887,13 @@ hipError_t set_doc_smem() {
   return hipFuncSetAttribute((const void*)doc_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDyn);
 }
 
+hipError_t launch_doc_begin(Header* hdr, DocTask* task, const DocTask& value, hipStream_t s) {
+  hipLaunchKernelGGL(doc_begin_kernel, dim3(1), dim3(64), 0, s, hdr, task, value);
+  return hipGetLastError();
+}
+
 hipError_t launch_docs(const DocParams& P, hipStream_t s) {
-  hipLaunchKernelGGL(doc_plan_kernel, dim3(256), dim3(256), 0, s, P);
-  if (P.direct_kib) hipLaunchKernelGGL(doc_order_kernel, dim3(1), dim3(1024), 0, s, P);
+  hipLaunchKernelGGL(doc_plan_kernel, dim3(256), dim3(kBlk), 0, s, P);
   hipLaunchKernelGGL(doc_kernel, dim3(P.grid), dim3(kBlk), kDyn, s, P);
   return hipGetLastError();
 }

@@ -138,6 +138,8 @@ hipError_t launch_part_single(const PartParams& P, hipStream_t s);
 // per-document count (wc_docs.hip)
 constexpr uint64_t kMinWin = 16 * 1024, kMaxWin = 48 * 1024;  // bytes per work item
 constexpr uint32_t kDirectKib = 72;
+// Work items by their bytes: class 0 below 16 KiB, class k from 8 KiB << k on.
+constexpr uint32_t kDocClasses = 16;
 constexpr uint32_t kDocW = 256;        // documents per sub-window
 constexpr uint32_t kDocLds = 4528;     // LDS table entries (20 bytes each, beside 8192 slots)
 
@@ -151,28 +153,29 @@ struct DocTask {           // device-resident: every size the per-document kerne
 struct DocParams {
   const DocTask* task;
   Header* hdr;
-  uint64_t* items;         // [n_docs] runs of documents (documents << 32 | the first)
+  uint64_t* items;         // runs of documents (documents << 32 | the first), by size class
+  uint64_t class_at[kDocClasses + 1];  // a class's first item, and where the last one's end at most
+  uint32_t* class_n;       // [kDocClasses] items of each class (zero before)
   uint64_t* word_offsets;  // [cap_e + 1]
   uint8_t* words;          // [cap_b]
   void* counts;
   uint32_t count_bytes;
   uint32_t grid;           // workgroups
   uint32_t lds_cap;        // entries used before keys are spilled
-  uint32_t direct_kib;     // documents above this many KiB, and a window, are queued first (0: none)
+  uint32_t direct_kib;     // documents above this many KiB, and a window, are reported (0: none)
   uint64_t win_bytes;      // work item window; 0: by the size of the text
   uint64_t* docs;          // [cap_e]
   uint64_t* doc_ptr;       // [n_docs]
   uint64_t* doc_len;       // [n_docs]
   uint64_t cap_e, cap_b;
   Slot* arena;             // spilled keys and tables set aside
-  uint64_t* over_docs;     // [n_docs] documents counted from the queue, as found
-  uint64_t* over_sorted;   // [n_docs] the same, largest first
   uint64_t arena_slots;
   uint64_t count_bias;     // added to every exported count (debug; 0 normally)
 };
-// queue entries: document index (bits 0-55), size class while the queue is sorted (bits 56-62)
-constexpr uint64_t kDocIdMask = (1ull << 56) - 1;
 hipError_t set_doc_smem();
+constexpr size_t kDocHeadBytes = sizeof(Header) + kDocClasses * 4;  // the header and class_n
+// clears them and sets the task
+hipError_t launch_doc_begin(Header* hdr, DocTask* task, const DocTask& value, hipStream_t s);
 hipError_t launch_docs(const DocParams& P, hipStream_t s);
 
 hipError_t launch_count(const CountParams& P, bool per_doc, uint32_t grid, uint32_t block,
