@@ -7,9 +7,10 @@
 // size class; persistent workgroups (1024 threads, one per CU) take them from a queue, the
 // largest class first.
 //
-// Counting. A group's text is scanned by the workgroup's waves, each on a contiguous run of 1 KiB
-// stripes and on its own (no workgroup barrier inside the scan). A token's document is its index r
-// in the group, found from the document starts of its stripe; (word, r) is one 16-byte key in the
+// Counting. A group's text is cut into tiles of 992 bytes, staged with the 16 bytes before and after;
+// a wave that has counted one takes the next that is left (no workgroup barrier inside the scan; with
+// equal runs of whole stripes for the waves 19 % of the time went by with the last of them alone).
+// A token's document is its index r in the group, found from the tile's document starts; (word, r) is one 16-byte key in the
 // LDS table of wc_words.h: r sits in bit 7 of the bytes of a packed word's second half, bits that
 // no word byte uses, or above the 48 address bits of a long word. Most groups fit the table. A
 // token whose key finds no entry left is spilled: its key goes to a chunk of records in device
@@ -33,13 +34,13 @@
 // the first wave that ends its scan, its offsets are read while this group's entries find their
 // places, and the next group's first text is loaded before this group's entries are written.
 //
-// Bound by instructions: of 16.3 million cycles per CU for the text below vector units are busy for
-// 58 %; a third is the table (and what spills), a fifth taking the words apart, a tenth writing the
-// output, a sixth finding words, and the rest the waits between groups, about 5 us each. Two
+// Bound by instructions: vector units are busy for 65 % of the time; a third of it is the table (and
+// what spills), a fifth taking the words apart, a tenth writing the output, a sixth finding words,
+// and the rest the waits inside a group and between them. Two
 // workgroups per CU with half the table each were slower (more and smaller groups, more spills).
 // 100,000 documents (lognormal, median 16 KiB, 2.7 GB, 119 million entries), before as two passes
-// with tables of 4,096 entries in LDS and in device memory: 12.7 -> 6.6 ms; 2,000 documents of 2 to
-// 20 KiB: 181 -> 81 us.
+// with tables of 4,096 entries in LDS and in device memory: 12.7 -> 5.5 ms; 2,000 documents of 2 to
+// 20 KiB: 181 -> 74 us.
 //
 // Every size the kernels need is read from a device-side task description, so a whole call
 // can be captured once in a HIP graph and replayed for other corpora.
@@ -56,9 +57,10 @@ namespace {
 constexpr int kBlk = 1024;
 constexpr uint32_t kDocSlots = 8192;
 constexpr uint32_t kWaves = kBlk / 64;
-constexpr uint32_t kText = kStripe + 32;      // per wave: stripe, the 16 bytes after it, padding
-constexpr uint32_t kList = 256;               // starts of a stripe listed at a time
-constexpr uint32_t kEnds = kStripe / 32 + 2;  // word-end bitmap of a stripe and the 16 bytes after
+constexpr uint32_t kTile = kStripe - 32;      // bytes whose words a wave counts at a time
+constexpr uint32_t kText = kStripe + 32;      // per wave: a tile with 16 bytes on each side, padding
+constexpr uint32_t kList = 256;               // starts of a tile listed at a time
+constexpr uint32_t kEnds = kStripe / 32 + 2;  // word-end bitmap of the staged text, two words of zeros
 constexpr uint32_t kListWords = kList / 2 + kEnds;
 constexpr uint32_t kPerThread = (kDocLds + kBlk - 1) / kBlk;
 // spilled keys: a chunk is a link to the wave's chunk before it and kChunkRecs keys
@@ -105,7 +107,7 @@ WC_DEV uint4 without_doc(uint4 k) {
 constexpr size_t kDyn = (size_t)kDocSlots * 4 + (size_t)kDocLds * 20 + (size_t)kWaves * kText;
 
 // (the parameters are read with args(): as an argument by name they would be loaded once, at the
-// start, and held or spilled over the scan: 50 of its instructions per stripe read such values back)
+// start, and held or spilled over the scan: 50 of its instructions per KiB read such values back)
 __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   typedef const __attribute__((address_space(4))) DocParams* Args;
   auto args = []() -> Args {
@@ -116,14 +118,14 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
 
   extern __shared__ __align__(16) uint8_t s_dyn[];
   __shared__ uint32_t s_list[kWaves][kListWords];  // starts (16 bits each), then the end bitmap
-  __shared__ uint32_t s_bnd[kWaves][kEnds];        // document starts of a stripe
+  __shared__ uint32_t s_bnd[kWaves][kEnds];        // document starts of a tile
   __shared__ uint4 s_lenmask[17];
   __shared__ uint64_t s_doff[3][kDocW + 1];        // document offsets of the group and the next two
   __shared__ unsigned long long s_dcur[kDocW];     // places taken: (entries << 32 | bytes)
   __shared__ uint32_t s_sum[4], s_class[kDocClasses + 1];
   __shared__ uint64_t s_out;
   __shared__ unsigned long long s_tokens;
-  __shared__ uint32_t s_nent, s_spill, s_next, s_done;
+  __shared__ uint32_t s_nent, s_spill, s_next, s_done, s_tile;
   __shared__ uint32_t s_region[16 * kClassesMax];  // first unit + 1 (0: not taken yet)
   __shared__ uint32_t s_part[kDocParts];
   __shared__ uint32_t s_used, s_lost, s_at;         // virtual slots used; some region was refused
@@ -241,105 +243,75 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
 
   // ---- the scan of documents [0, nd) of the group at doff ----------------------------------
   uint32_t tokens = 0;
-  // this wave's stripes of the text [A, B) (equal parts in bytes, with a part of a stripe at the end
-  // of each, were no faster: the waves with a stripe less leave their issue slots to the others)
-  struct Run {
-    int64_t first;  // position of the first
-    uint32_t n;
-  };
-  auto run_of = [&](int64_t A, int64_t B) -> Run {
-    const int64_t k0 = (A - base_off) / (int64_t)kStripe;
-    const int64_t k1 = B > A ? (B - base_off + (int64_t)kStripe - 1) / (int64_t)kStripe : k0;
-    const int64_t per = (k1 - k0 + kWaves - 1) / kWaves;
-    const int64_t ka = min(k0 + (int64_t)wv * per, k1);
-    return Run{base_off + ka * (int64_t)kStripe, (uint32_t)(min(ka + per, k1) - ka)};
-  };
-  // stripe i of a run; of the one after it only the first 16 bytes
-  auto load = [&](const Run& R, uint32_t i) -> uint4 {
+  // The text [A, B) in tiles of kTile bytes, staged with the 16 bytes before and after them: a lane
+  // reads 16 bytes, the first and the last lane for what the others' words touch. Tile k, from the
+  // first 16-byte block on; bytes outside the text may be anything.
+  auto tile_at = [&](int64_t A, uint32_t k) -> int64_t { return A - ((A - base_off) & 15) + (int64_t)k * kTile; };
+  auto load = [&](int64_t A, int64_t B, uint32_t k) -> uint4 {
+    const int64_t p = tile_at(A, k) - 16;
     uint4 v = make_uint4(0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u);
-    if (i > R.n || R.n == 0) return v;
-    const int64_t p = R.first + i * (int64_t)kStripe;
+    if (p + 16 >= B) return v;
     uint32_t at = lane * 16;
     pin(at);  // (an offset to a scalar address: as a sum of its own it was kept, and spilled)
-    if (i < R.n && p >= 0 && p + (int64_t)kStripe <= (int64_t)len) v = load_stream16(corpus + p + at);
-    else if (i < R.n || lane == 0) v = load_text16(corpus, len, p + at);
+    if (p >= 0 && p + (int64_t)kStripe <= (int64_t)len) v = load_stream16(corpus + p + at);
+    else v = load_text16(corpus, len, p + at);
     return v;
   };
-  // the next group's first stripes, loaded before the current group's entries are written
-  uint4 t0 = make_uint4(0, 0, 0, 0), t1 = t0;
-  uint32_t t_before = 0;
-  auto load_first = [&](const Run& R) {
-    t0 = load(R, 0);
-    t1 = load(R, 1);
-    t_before = R.n ? load_text4(corpus, len, R.first - 4) : 0u;
-  };
+  uint4 t0 = make_uint4(0, 0, 0, 0);  // the wave's first tile of the next group, loaded a group ahead
   auto scan = [&](const uint64_t* doff, uint32_t nd) {
     const int64_t A = (int64_t)uniform64(doff[0]), B = (int64_t)uniform64(doff[nd]);
-    const Run R = run_of(A, B);
-    const uint32_t nsw = R.n;
-    if (nsw == 0) return;
-    auto stripe_pos = [&](uint32_t i) -> int64_t { return R.first + i * (int64_t)kStripe; };
-    uint4 r1 = t1;
-    // rb: the last document that starts before the stripe (-1: none), upcoming: the next start
-    int32_t rb = -1;
-    for (uint32_t j = 0; j < nd; j += 64)
-      rb += (int32_t)__popcll(__ballot(j + lane < nd && (int64_t)doff[min(j + lane, nd)] < stripe_pos(0)));
-    int64_t upcoming = (int64_t)uniform64(doff[rb + 1]);
-    uint32_t carry;
-    {
-      const int64_t q = stripe_pos(0) - 1;
-      uint32_t f;
-      fold_classify4(t_before, &f);
-      carry = (q >= A && q < B) ? f >> 31 : 0u;
-    }
-    const bool inside = stripe_pos(0) >= A && stripe_pos(nsw) + 16 <= B;
-    uint32_t w16;
-    uint4 g = classify16(t0, &w16);
-    if (!inside) w16 = cut16(w16, stripe_pos(0) + lane * 16, A, B);
-
-    for (uint32_t i = 0; i < nsw; ++i) {
-      const int64_t p0 = stripe_pos(i);
-      uint32_t w1;
-      const uint4 g1 = classify16(r1, &w1);
-      if (!inside) w1 = cut16(w1, p0 + (int64_t)kStripe + lane * 16, A, B);
-      r1 = load(R, i + 2);
+    // (the group's first 64 document starts in the lanes)
+    const int64_t o0 = lane < nd ? (int64_t)doff[min(lane, nd)] : INT64_MAX;
+    uint4 raw = t0;
+    uint32_t spare[2] = {kNone, kNone};
+    for (uint32_t k = wv; tile_at(A, k) < B;) {
+      // the next tile is whichever no wave has taken
+      uint32_t kn = 0;
+      if (lane == 0) kn = atomicAdd(&s_tile, 1u);
+      const int64_t pk = tile_at(A, k), p0 = pk - 16;
+      uint32_t w16;
+      const uint4 g = classify16(raw, &w16);
+      if (p0 < A || p0 + (int64_t)kStripe > B) w16 = cut16(w16, p0 + lane * 16, A, B);
       ((uint4*)my_txt)[lane] = g;
-      if (lane == 0) ((uint4*)my_txt)[64] = g1;
-      // document starts in the stripe and the 16 bytes after it
-      uint32_t bnd16 = 0, bnext = 0, bsfx = 0, nb = 0;
-      if (upcoming < p0 + (int64_t)kStripe + 16) {
-        for (int32_t j0 = rb + 1; j0 < (int32_t)nd; j0 += 64) {
-          const int32_t j = j0 + (int32_t)lane;
-          const int64_t o = j < (int32_t)nd ? (int64_t)doff[j] : INT64_MAX;
-          if (o < p0 + (int64_t)kStripe + 16)
+      kn = (uint32_t)__builtin_amdgcn_readfirstlane((int)kn);
+      raw = load(A, B, kn);
+      // rb: the last document that starts before the tile (-1: none), nb: starts in it; a bit for
+      // each start in it and the 16 bytes after it
+      int32_t rb = -1;
+      uint32_t bnd16 = 0, bnext = 0, nb = 0;
+      bool some = false;
+      for (uint32_t j = 0; j < nd; j += 64) {
+        const int64_t o = j == 0 ? o0 : j + lane < nd ? (int64_t)doff[j + lane] : INT64_MAX;
+        const uint64_t before = __ballot(o < pk), reach = __ballot(o < pk + kTile + 16);
+        rb += (int32_t)__popcll(before);
+        if (reach != before) {
+          some = true;
+          nb += (uint32_t)__popcll(__ballot(o < pk + kTile) & ~before);
+          if (o >= pk && o < pk + kTile + 16)
             atomicOr(&my_bnd[(uint32_t)(o - p0) >> 5], 1u << ((uint32_t)(o - p0) & 31));
-          const uint64_t m = __ballot(o < p0 + (int64_t)kStripe);
-          nb += (uint32_t)__popcll(m);
-          if (m != ~0ull) break;
         }
+        if (reach != ~0ull) break;
+      }
+      if (some) {
         wave_sync();
         bnd16 = (my_bnd[lane >> 1] >> ((lane & 1) * 16)) & 0xffffu;
-        bnext = (my_bnd[(lane + 1) >> 1] >> (((lane + 1) & 1) * 16)) & 1u;
-        bsfx = my_bnd[kStripe / 32] & 0xffffu;
+        bnext = (my_bnd[(lane + 1) >> 1] >> (((lane + 1) & 1) * 16)) & 1u;  // lane 63: 0
         wave_sync();
         if (lane < kEnds) my_bnd[lane] = 0;
       }
-      const uint32_t sfx = (uint32_t)__builtin_amdgcn_readlane((int)w1, 0);
-      const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)carry, (int)(w16 >> 15), 0x138, 0xf, 0xf, false);
-      const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)(sfx & 1u), (int)(w16 & 1u), 0x130, 0xf, 0xf, false);
-      const uint32_t start16 = w16 & (~((w16 << 1) | prev) | bnd16) & 0xffffu;
+      const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(w16 >> 15), 0x138, 0xf, 0xf, false);
+      // (lane 63: a word that reaches the last byte started 16 bytes before it, and goes on for all
+      // that is known: longer than 16 bytes)
+      const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(1, (int)(w16 & 1u), 0x130, 0xf, 0xf, false);
+      uint32_t start16 = w16 & (~((w16 << 1) | prev) | bnd16) & 0xffffu;
+      if (lane - 1 >= kTile / 16) start16 = 0;  // another tile's
       const uint32_t last16 = w16 & (~((w16 >> 1) | (next << 15)) | (bnd16 >> 1) | (bnext << 15)) & 0xffffu;
       ((uint16_t*)my_ends)[lane] = (uint16_t)last16;
-      // (a word of the stripe that reaches the last of these 16 bytes is longer than 16 bytes)
-      if (lane == 0) ((uint16_t*)my_ends)[64] = (uint16_t)(sfx & (~(sfx >> 1) | (bsfx >> 1)) & 0x7fffu);
       const uint32_t c = __popc(start16), incl = wave_incl_scan(c);
       const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-      carry = (uint32_t)__builtin_amdgcn_readlane((int)(w16 >> 15), 63);
       tokens += n;
-      g = g1;
-      w16 = w1;
       // document of the token at staged byte s: the last one that starts at or before it (empty
-      // documents share their start with the next one); only the nb starts of the stripe follow rb
+      // documents share their start with the next one); only the nb starts of the tile follow rb
       auto doc_at = [&](uint32_t s) -> uint32_t {
         int32_t a = rb, b = rb + 1 + (int32_t)nb;  // doff[a] <= p0 + s < doff[b]
         while (b - a > 1) {
@@ -422,7 +394,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
             h[x] = place_hash(key[x]);
             wait_vmem();
           }
-        const int res = table_add<NX, true>(T, key, h, one, in, left);
+        const int res = table_add<NX, true>(T, key, h, one, in, left, spare);
         if (res == kNoRoom) spill(key, left, nx);
         else if (res == kNoSlot && lane == 0) or32(&hdr_of()->flags, kFlagStall);
       };
@@ -436,8 +408,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
         if (at < nl) count(std::integral_constant<int, 1>(), at, nl - at);
         wave_sync();
       }
-      rb += (int32_t)nb;
-      if (nb) upcoming = (int64_t)uniform64(doff[rb + 1]);
+      k = kn;
     }
   };
 
@@ -660,6 +631,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   if (tid == 0) {
     s_tokens = 0;
     s_nent = s_spill = s_used = s_done = 0;
+    s_tile = kWaves;
     s_next = next_pos();
   }
   uint64_t it = item_at(blockIdx.x);
@@ -669,7 +641,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   uint64_t ahead = item_at(s_next);
   if (ahead && tid <= (uint32_t)(ahead >> 32)) s_doff[1][tid] = offset_at((uint32_t)ahead + tid);
   __syncthreads();
-  if (it) load_first(run_of((int64_t)uniform64(s_doff[0][0]), (int64_t)uniform64(s_doff[0][it >> 32])));
+  if (it) t0 = load((int64_t)uniform64(s_doff[0][0]), (int64_t)uniform64(s_doff[0][it >> 32]), wv);
   while (it) {
     const uint32_t nd = (uint32_t)(it >> 32);
     const uint64_t d0 = (uint32_t)it;
@@ -685,7 +657,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
     __syncthreads();
     const uint64_t after = ahead ? item_at(s_next) : 0;
     const uint32_t nxt = cur == 2 ? 0 : cur + 1, nxt2 = cur == 0 ? 2 : cur - 1;
-    if (ahead) load_first(run_of((int64_t)uniform64(s_doff[nxt][0]), (int64_t)uniform64(s_doff[nxt][ahead >> 32])));
+    if (ahead) t0 = load((int64_t)uniform64(s_doff[nxt][0]), (int64_t)uniform64(s_doff[nxt][ahead >> 32]), wv);
     if (s_spill) {
       if (tid == 0) add64(&hdr_of()->stat[3], nd);
       for (uint32_t level = 0; s_spill && !s_lost; ++level) count_spilled(level);
@@ -742,6 +714,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
       if (lane == 63) {
         s_out = first;  // the end of the group's output
         s_nent = s_spill = s_used = s_done = 0;
+        s_tile = kWaves;
         if ((first >> 32) > args()->cap_e || (first & 0xffffffffull) > args()->cap_b) or32(&hdr_of()->flags, kFlagWordCap);
       }
     }
@@ -749,8 +722,6 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
     // waited for in their order)
     if (after && tid <= (uint32_t)(after >> 32)) s_doff[nxt2][tid] = off;
     pin(t0);
-    pin(t1);
-    pin(t_before);
     __syncthreads();
     const bool room = (s_out >> 32) <= args()->cap_e && (s_out & 0xffffffffull) <= args()->cap_b;
     if (room) {
