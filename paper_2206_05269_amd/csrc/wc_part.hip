@@ -35,9 +35,9 @@ namespace {
 
 constexpr int kBlk = 1024;
 constexpr uint32_t kWaves = kBlk / 64;
-constexpr uint32_t kText = kStripe + 32;     // per wave: stripe, the 16 bytes after it, padding
-constexpr uint32_t kList = 192;              // starts of a stripe listed at a time
-constexpr uint32_t kEnds = kStripe / 32 + 2; // word-end bitmap of a stripe and the 16 bytes after
+constexpr uint32_t kText = kStripe + 32;     // per wave: a tile with the bytes around it, padding
+constexpr uint32_t kList = 192;              // starts of a tile listed at a time
+constexpr uint32_t kEnds = kStripe / 32 + 2; // word-end bitmap of the staged text, two words of zeros
 constexpr uint32_t kListWords = kList / 2 + kEnds;
 
 constexpr uint32_t kPerThread = (kPartMapEntries + kBlk - 1) / kBlk;
@@ -159,21 +159,20 @@ WC_DEV int64_t lane_value(int64_t v, uint32_t lane) {
 // ---------------------------------------------------------------------------------------
 // map
 // ---------------------------------------------------------------------------------------
-// Each wave scans its own contiguous run of the workgroup's 1 KiB stripes. The 16 bytes after a
-// stripe are staged with it (the next stripe is classified one step early), so a word of at most
-// 16 bytes that runs over the stripe's end is read whole from LDS, at the run's end too; a
-// longer one is read from device memory. Waves meet only when the table is to be emptied.
+// The workgroup's range is cut into tiles of 992 bytes, staged with the 16 bytes before and after
+// them, so a word of at most 16 bytes is read whole from LDS; a longer one from device memory. A wave
+// that has counted a tile takes the next one that is left; waves meet only when the table is to be
+// emptied. (With equal runs of 1 KiB stripes, their next one classified a
+// step early, the last waves were alone at the end: map of 20 MB 50 -> 43 us, of 64 MB 166 -> 141.)
 //
-// Bound by instructions (a 64 MB text: 380 GB/s of text, about 900 vector instructions per stripe,
+// Bound by instructions (a 64 MB text: 475 GB/s of text, about 900 vector instructions per KiB,
 // half of them the table's). What the scan does not use stays out of its registers, and the rest of
-// a stripe's words after the first 128 is counted one a lane: map of 20 MB 56 -> 51 us, of 64 MB
+// a tile's words after the first 128 is counted one a lane: map of 20 MB 56 -> 51 us, of 64 MB
 // 186 -> 170.
 //
-// UTF-8. A stripe's multi-byte sequences are read when it is classified, as if no document
-// started in it; a sequence's bytes in the next lane, or the next stripe, are passed on. When a
-// document does start in the stripe or just after it, the stripe and the 16 bytes after it
-// are read again with the starts in hand. ASCII text takes the same steps as without UTF-8, and
-// one test per stripe.
+// UTF-8. A tile is staged with 32 bytes after it, so that the sequences are whole in all 16 bytes
+// that a short word can reach. ASCII text takes the same steps as without UTF-8, and one test per
+// tile.
 template <bool kSingle, bool kUtf8>
 __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   // What the scan does not need is read with args(): by name it would be loaded once, at the start,
@@ -189,7 +188,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   __shared__ uint32_t s_bnd[kWaves][kEnds];
   __shared__ uint4 s_lenmask[17];
   __shared__ uint32_t s_hist[kParts], s_start[kParts];
-  __shared__ uint32_t s_nent, s_done, s_tokens, s_scan[4];
+  __shared__ uint32_t s_nent, s_done, s_tokens, s_tile, s_scan[4];
   __shared__ uint64_t s_tmp[kWaves], s_base;
   PartTable<uint32_t> T;
   T.slot = (uint32_t*)s_dyn;
@@ -205,32 +204,25 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   uint32_t* const my_bnd = s_bnd[wv];
   auto hdr_of = [&]() -> Header* { return as_global(args()->hdr); };
 
-  // this wave's stripes
+  // The workgroup's text [G0, G1) in tiles of kTile bytes, staged with the 16 bytes before them and
+  // the 16 (UTF-8: 32) after: a lane reads 16 bytes. Bytes outside the text may be anything.
+  constexpr uint32_t kTile = kStripe - (kUtf8 ? 48 : 32);
   const uint64_t first = (uint64_t)blockIdx.x * P.stripes_per_wg;
-  const uint64_t last = min(first + P.stripes_per_wg, P.n_stripes);
-  const uint64_t n_wg = last > first ? last - first : 0;
-  const uint64_t per = (n_wg + kWaves - 1) / kWaves;
-  const uint64_t sa = first + min(wv * per, n_wg);
-  const uint32_t nsw = (uint32_t)(min(first + (wv + 1) * per, first + n_wg) - sa);
-  auto stripe_pos = [&](uint64_t i) -> int64_t { return P.base_off + (int64_t)((sa + i) * kStripe); };
-  // stripe i of the run; of the stripe after it, the first 16 bytes (lane 0; UTF-8: 32)
-  const uint4 blank = make_uint4(0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u);
-  auto load = [&](uint32_t i) -> uint4 {
-    if (i > nsw || nsw == 0) return blank;
-    const int64_t p = stripe_pos(i);
-    uint4 v = blank;
-    if (i < nsw && p >= 0 && p + (int64_t)kStripe <= (int64_t)P.len) {
-      uint32_t at = lane * 16;
-      pin(at);  // (an offset to a scalar address: as a sum of its own it was kept, and spilled)
-      v = load_stream16(P.corpus + p + at);
-    } else if (i < nsw || lane <= (kUtf8 ? 1u : 0u)) {
-      v = load_text16(P.corpus, P.len, p + lane * 16);
-    }
+  const int64_t G0 = P.base_off + (int64_t)(first * kStripe);
+  const int64_t G1 = P.base_off + (int64_t)(min(first + P.stripes_per_wg, P.n_stripes) * kStripe);
+  auto tile_at = [&](uint32_t k) -> int64_t { return G0 + (int64_t)((uint64_t)k * kTile); };
+  auto load = [&](uint32_t k) -> uint4 {
+    const int64_t p = tile_at(k) - 16;
+    uint4 v = make_uint4(0x20202020u, 0x20202020u, 0x20202020u, 0x20202020u);
+    if (p + 16 >= G1) return v;
+    uint32_t at = lane * 16;
+    pin(at);  // (an offset to a scalar address: as a sum of its own it was kept, and spilled)
+    if (p >= 0 && p + (int64_t)kStripe <= (int64_t)P.len) v = load_stream16(P.corpus + p + at);
+    else v = load_text16(P.corpus, P.len, p + at);
     return v;
   };
-  const uint4 raw0 = load(0);
-  uint4 r1 = load(1), r2 = blank;
-  if (kUtf8) r2 = load(2);
+  uint32_t kn = wv;  // the wave's next tile, its bytes in raw
+  uint4 raw = load(kn);
 
   for (uint32_t i = tid; i < kRedSlots / 4; i += kBlk) ((uint4*)T.slot)[i] = make_uint4(0, 0, 0, 0);
   for (uint32_t i = tid; i < kWaves * kListWords; i += kBlk) (&s_list[0][0])[i] = 0;
@@ -241,6 +233,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     s_nent = 0;
     s_done = 0;
     s_tokens = 0;
+    s_tile = kWaves;
     if (kSingle) {
       *hdr_of() = Header{};
       __threadfence();
@@ -256,23 +249,18 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   }
   const int64_t R0 = (int64_t)min(P.offsets[0], P.len), R1 = (int64_t)min(P.offsets[P.n_docs], P.len);
 
-  // Document starts from the run's first byte on, 64 at a time in the lanes (lane l: document
-  // d0 + l); those before dn lie before the current stripe. The first one: 64 probes at a time.
+  // Document starts, 64 at a time in the lanes (lane l: document d0 + l): all documents before d0
+  // start before the tile at hand.
   uint64_t d0 = 0;
-  uint32_t dn = 0;
-  int64_t doff = INT64_MAX;
-  auto load_docs = [&]() {
-    const uint64_t d = d0 + lane;
-    const Args A = args();
-    const uint64_t* const offsets = as_global(A->offsets);
-    doff = d <= A->n_docs ? (int64_t)offsets[d] : INT64_MAX;
+  int64_t doff;
+  auto start_of = [&](uint64_t d) -> int64_t {
+    return d <= P.n_docs ? (int64_t)P.offsets[d] : INT64_MAX;
   };
-  if (nsw) {
-    uint64_t lo = 0, hi = P.n_docs + 1;  // offsets[lo - 1] < run start <= offsets[hi]
-    const int64_t p0 = stripe_pos(0);
-    while (hi - lo > 64) {
+  auto seek = [&](int64_t p, uint64_t lo) {  // 64 probes at a time
+    uint64_t hi = P.n_docs + 1;  // offsets[lo - 1] < p <= offsets[hi]
+    while (hi > lo && hi - lo > 64) {
       const uint64_t step = (hi - lo + 63) / 64, d = lo + lane * step;
-      const uint64_t m = __ballot(d < hi && (int64_t)P.offsets[d] < p0);
+      const uint64_t m = __ballot(d < hi && start_of(d) < p);
       const uint64_t k = (uint64_t)__popcll(m);
       if (k == 0) {
         hi = lo;
@@ -282,14 +270,9 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
       }
     }
     d0 = lo;
-    load_docs();
-    dn = (uint32_t)__popcll(__ballot(doff < p0));  // of these at most 64, the ones before the run
-    if (dn >= 64) {
-      d0 += 64;
-      dn = 0;
-      load_docs();
-    }
-  }
+    doff = start_of(d0 + lane);
+  };
+  seek(tile_at(kn) - 16, 0);
   auto doc_limit = [&](uint64_t pos) -> uint64_t {  // first document start after pos, or the end
     const uint64_t* const offsets = as_global(args()->offsets);
     uint64_t a = 1, b = args()->n_docs;
@@ -301,54 +284,8 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     return min(offsets[a], P.len);
   };
 
-  // the byte before the run
-  uint32_t carry = 0;
-  // UTF-8: bytes of the next stripe to classify that end a sequence of the one before (its first
-  // three bytes at most), and of the stripe at hand, corrected for document starts
-  uint32_t uc = 0, uc0 = 0;
-  if (nsw) {
-    const int64_t q = stripe_pos(0) - 1;
-    if (kUtf8) {
-      // lane l: the word flag of byte q + l, for l < 4 (for all but the first, if it is not ASCII)
-      uint32_t f = 0;
-      if (lane < 4) {
-        auto byte_at = [&](int64_t x) -> uint32_t { return P.corpus[x]; };
-        auto starts_at = [&](int64_t x) -> bool { return doc_starts_at(P.offsets, P.n_docs, x); };
-        const int64_t x = q + lane;
-        if (x >= R0 && x < R1 && (lane == 0 || (P.corpus[x] & 0xc0u) == 0x80u))
-          f = utf8_word_byte(x, R0, R1, byte_at, starts_at);
-      }
-      const uint32_t m = (uint32_t)__ballot(f != 0);
-      carry = m & 1u;
-      uc = (m >> 1) & 7u;
-    } else {
-      uint32_t f;
-      fold_classify4(load_text4(P.corpus, P.len, q - 3), &f);
-      carry = (q >= R0 && q < R1) ? f >> 31 : 0u;
-    }
-  }
-  const bool inside = nsw && stripe_pos(0) >= R0 && stripe_pos(nsw) + 16 <= R1;
-  // Folded bytes and word bytes of a stripe; after: the stripe after it.
-  auto classify = [&](const uint4 v, const uint4 after, uint32_t* w) -> uint4 {
-    const uint4 c = classify16(v, w);
-    if (kUtf8 && __any(((c.x | c.y | c.z | c.w) & 0x80808080u) != 0)) {
-      const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)after.x, 0);
-      const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)c.x, 0x130, 0xf, 0xf, false);
-      const uint32_t res = utf8_mask(c, next, 0u);
-      *w |= (res & 0xffffu) |
-            (uint32_t)__builtin_amdgcn_update_dpp((int)uc, (int)(res >> 16), 0x138, 0xf, 0xf, false);
-      uc = (uint32_t)__builtin_amdgcn_readlane((int)(res >> 16), 63);
-    } else {
-      uc = 0;
-    }
-    return c;
-  };
-  uint32_t w16;
-  uc0 = uc;
-  uint4 g = classify(raw0, r1, &w16);
-  if (!inside) w16 = cut16(w16, stripe_pos(0) + lane * 16, R0, R1);
-
-  uint32_t i = 0, n = 0, w0 = 0, off = 0, start16 = 0, rank = 0;  // off: place of token w0 in the list
+  bool done = false, counted = false;  // no tiles are left
+  uint32_t n = 0, w0 = 0, off = 0, start16 = 0, rank = 0;  // off: place of token w0 in the list
   int64_t p0 = 0;
   uint32_t tokens = 0;
   bool over = false;  // a word found no room (this lane)
@@ -432,85 +369,66 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
     // ---- scan: until the run ends or the table is nearly full ------------------------------
     while (true) {
       if (w0 >= n) {
-        if (i >= nsw) break;
-        // -- next stripe: (g, w16) classified; the next one's bytes are in r1
-        p0 = stripe_pos(i);
-        uint32_t w1;
-        uint32_t uc1 = uc;  // of the next stripe's first bytes
-        const uint4 g1 = classify(r1, r2, &w1);
-        if (kUtf8) {
-          r1 = r2;
-          r2 = load(i + 3);
-        } else {
-          r1 = load(i + 2);
+        // -- the next tile; after it the wave takes whichever no wave has taken
+        if (tile_at(kn) >= G1) {
+          done = true;
+          break;
         }
-        constexpr int64_t kReach = kStripe + (kUtf8 ? 20 : 16);  // document starts that matter here
+        p0 = tile_at(kn) - 16;
+        uint32_t after = 0;
+        if (lane == 0) after = atomicAdd(&s_tile, 1u);
+        uint32_t w16;
+        const uint4 g = classify16(raw, &w16);
         ((uint4*)my_txt)[lane] = g;
-        if (lane == 0) ((uint4*)my_txt)[64] = g1;
-        uint32_t bnd16 = 0, bnext = 0, bsfx = 0, wsfx = w1;
-        if (lane_value(doff, dn) < p0 + kReach) {
-          while (true) {
-            const bool mine = lane >= dn && doff >= p0 && doff < p0 + kReach;
-            if (mine) {
-              const uint32_t rel = (uint32_t)(doff - p0);
-              atomicOr(&my_bnd[rel >> 5], 1u << (rel & 31));
-            }
-            dn += (uint32_t)__popcll(__ballot(lane >= dn && doff < p0 + (int64_t)kStripe));
-            if (dn < 64) break;
-            d0 += 64;
-            dn = 0;
-            load_docs();
+        kn = (uint32_t)__builtin_amdgcn_readfirstlane((int)after);
+        raw = load(kn);
+        // a bit for each document start in the staged bytes
+        uint32_t bnd16 = 0, bnext = 0;
+        if (__all(doff < p0)) {
+          d0 += 64;
+          doff = start_of(d0 + lane);
+          if (__all(doff < p0)) seek(p0, d0 + 64);
+        }
+        const bool here = doff > p0 && doff < p0 + (int64_t)kStripe;
+        if (__any(here) || __all(doff < p0 + (int64_t)kStripe)) {
+          int64_t o = doff;
+          for (uint64_t d = d0;;) {
+            if (o > p0 && o < p0 + (int64_t)kStripe)
+              atomicOr(&my_bnd[(uint32_t)(o - p0) >> 5], 1u << ((uint32_t)(o - p0) & 31));
+            if (!__all(o < p0 + (int64_t)kStripe)) break;
+            d += 64;
+            o = start_of(d + lane);
           }
           wave_sync();
           bnd16 = (my_bnd[lane >> 1] >> ((lane & 1) * 16)) & 0xffffu;
-          bnext = (my_bnd[(lane + 1) >> 1] >> (((lane + 1) & 1) * 16)) & 1u;
-          bsfx = my_bnd[kStripe / 32] & 0xffffu;
-          if (kUtf8) {
-            const uint32_t b0 = bnd16 | (((my_bnd[(lane + 1) >> 1] >> (((lane + 1) & 1) * 16)) & 0xffffu) << 16);
-            uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)g1.x, 0);
-            uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)g.x, 0x130, 0xf, 0xf, false);
-            uint32_t res = utf8_mask(g, next, b0);
-            classify16(g, &w16);
-            w16 |= (res & 0xffffu) |
-                   (uint32_t)__builtin_amdgcn_update_dpp((int)uc0, (int)(res >> 16), 0x138, 0xf, 0xf, false);
-            const uint32_t now = (uint32_t)__builtin_amdgcn_readlane((int)(res >> 16), 63);
-            if (lane == 0) w1 = (w1 & ~uc1) | now;
-            uc1 = now;
-            // the first 16 bytes of the next stripe (lane 0), for the words that run into them
-            next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)g1.x, 0x130, 0xf, 0xf, false);
-            res = utf8_mask(g1, next, my_bnd[kStripe / 32]);
-            classify16(g1, &wsfx);
-            wsfx |= (res & 0xffffu) | now;
-          }
+          bnext = (my_bnd[(lane + 1) >> 1] >> (((lane + 1) & 1) * 16)) & 0xffffu;  // lane 63: 0
           wave_sync();
           if (lane < kEnds) my_bnd[lane] = 0;
         }
-        if (!inside) {
-          if (kUtf8) w16 = cut16(w16, p0 + lane * 16, R0, R1);
-          w1 = cut16(w1, p0 + (int64_t)kStripe + lane * 16, R0, R1);
-          wsfx = cut16(wsfx, p0 + (int64_t)kStripe + lane * 16, R0, R1);
+        if (kUtf8 && __any(((g.x | g.y | g.z | g.w) & 0x80808080u) != 0)) {
+          const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)g.x, 0x130, 0xf, 0xf, false);
+          const uint32_t res = utf8_mask(g, next, bnd16 | (bnext << 16));
+          w16 |= (res & 0xffffu) |
+                 (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(res >> 16), 0x138, 0xf, 0xf, false);
         }
-        uint32_t sfx = (uint32_t)__builtin_amdgcn_readlane((int)wsfx, 0);
-        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp((int)carry, (int)(w16 >> 15), 0x138,
-                                                                    0xf, 0xf, false);
-        const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp((int)(sfx & 1u), (int)(w16 & 1u),
-                                                                    0x130, 0xf, 0xf, false);
+        if (p0 < R0 || p0 + (int64_t)kStripe > R1) w16 = cut16(w16, p0 + lane * 16, R0, R1);
+        const uint32_t prev = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(w16 >> 15), 0x138, 0xf, 0xf, false);
+        // (lane 63: a word that reaches the last byte goes on for all that is known, and is longer
+        // than 16 bytes)
+        const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(1, (int)(w16 & 1u), 0x130, 0xf, 0xf, false);
         start16 = w16 & (~((w16 << 1) | prev) | bnd16) & 0xffffu;
-        const uint32_t last16 =
-            w16 & (~((w16 >> 1) | (next << 15)) | (bnd16 >> 1) | (bnext << 15)) & 0xffffu;
+        // the words of other tiles, and of the next workgroup
+        if (lane - 1 >= kTile / 16 || p0 + (int64_t)(lane * 16) >= G1) start16 = 0;
+        uint32_t last16 = w16 & (~((w16 >> 1) | (next << 15)) | (bnd16 >> 1) | ((bnext & 1u) << 15)) & 0xffffu;
+        // (UTF-8: a sequence that runs over the staged text is not known to be one; only words longer
+        // than 16 bytes reach the last lane)
+        if (kUtf8 && lane == 63) last16 = 0;
         ((uint16_t*)my_ends)[lane] = (uint16_t)last16;
-        // (a word of the stripe that reaches the last of these 16 bytes is longer than 16 bytes)
-        if (lane == 0) ((uint16_t*)my_ends)[64] = (uint16_t)(sfx & (~(sfx >> 1) | (bsfx >> 1)) & 0x7fffu);
         const uint32_t c = __popc(start16), incl = wave_incl_scan(c);
         rank = incl - c;
         n = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-        carry = (uint32_t)__builtin_amdgcn_readlane((int)(w16 >> 15), 63);
         tokens += n;
-        uc0 = uc1;
-        g = g1;
-        w16 = w1;
         w0 = off = 0;
-        ++i;
         continue;
       }
       if (off == 0) {  // list the starts of ranks [w0, w0 + kList)
@@ -518,7 +436,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         wave_sync();
       }
       // a round: two tokens a lane from the list's start, if there are more than 64, one from its
-      // 128th (a stripe of 176 tokens, usual for English text, took two rounds of 128)
+      // 128th (a tile of 176 tokens, usual for English text, took two rounds of 128)
       const uint32_t nw = min(n - w0, kList - off);
       const bool two = off == 0 && nw > 64;
       const int r = two ? count(std::integral_constant<int, 2>(), off, nw)
@@ -530,8 +448,8 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
       off = off + adv < kList ? off + adv : 0;
       wave_sync();
     }
-    if (i >= nsw && w0 >= n && i != kNone) {  // the run is done
-      i = kNone;
+    if (done && !counted) {
+      counted = true;
       if (lane == 0) {
         atomicAdd(&s_done, 1u);
         atomicAdd(&s_tokens, (uint32_t)tokens);

@@ -574,6 +574,30 @@ def test_partitioned_count(n):
             assert (np.diff(wo) > 0).all() and wo[-1] == got.res.word_bytes
 
 
+@pytest.mark.parametrize("step", [1, 2, 3])
+def test_partitioned_tiny_documents(step):
+    """64 document starts at a time against tiles: every alignment of the one to the other."""
+    n = 400_003
+    text = (b"ab c'D 7 e" * (n // 10 + 1))[:n]
+    off = np.append(np.arange(0, n, step), n)
+    assert gpu_count(text, off).total_tokens == oracle.count(text, off).total
+    check(text, off)
+
+
+@pytest.mark.parametrize("utf8", [False, True])
+def test_partitioned_document_starts_at_tile_edge(utf8):
+    """The 128th document start is the first byte staged for the 17th tile (16 waves begin with
+    the tiles before it, and no document does): the next ones are in the tile."""
+    n, tile = 20_000, 976 if utf8 else 992
+    edge = 16 * tile - 16
+    off = np.array([*range(edge - 640, edge - 640 + 127 * 4, 4), edge,
+                    *range(edge + 20, edge + tile, 7), n])
+    assert len(off) > 200 and off[127] == edge
+    text = b"a" * n
+    got = gpu_count(text, off, utf8=utf8)
+    assert got.total_tokens == oracle.count(text, off, utf8=utf8).total == len(off) - 1
+
+
 @pytest.mark.parametrize("n", [1025, 300_007])
 def test_two_pass_words_per_stripe(n):
     """Pass 1 lists 192 words of a stripe and counts two a lane, then one: 0 to 512 a stripe."""
