@@ -108,9 +108,10 @@ namespace {
 // ---- copies of many pieces by one launch ----------------------------------------------------
 // A table's entries [0, n) on the way to a resident block: offsets rebased to the first word,
 // counts, word bytes; or (off null) just bytes. Pieces are kernel arguments, kKeep at a time; a
-// piece has a workgroup per kKeepSpan bytes.
+// piece has a workgroup per kKeepSpan bytes: two copies of 8 bytes a thread, one after the other (32 KiB
+// were sixteen: a table of 100 KiB took 7 us, now 3.6; 96 requests 1.58 -> 1.53 ms).
 constexpr uint32_t kKeep = 32;
-constexpr uint64_t kKeepSpan = 32768;
+constexpr uint64_t kKeepSpan = 4096;
 struct KeepItem {
   const uint64_t* off;
   const uint8_t* counts;
