@@ -148,12 +148,6 @@ WC_DEV void export_table(const PartParams& P, const PartTable<C>& T, bool last, 
   }
 }
 
-WC_DEV int64_t lane_value(int64_t v, uint32_t lane) {
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, (int)lane);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), (int)lane);
-  return (int64_t)((uint64_t)lo | ((uint64_t)hi << 32));
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------------------

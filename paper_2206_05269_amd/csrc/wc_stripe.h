@@ -251,50 +251,6 @@ WC_DEV uint32_t red_pick8(const uint4 a, const uint4 b, uint32_t tag) {
   return m;
 }
 
-// The common case: the word has an entry, found by the first tag match of its home group.
-// Counts it and returns true; false sends the word to red_add.
-WC_DEV bool red_hit(const RedTable& T, const uint4 want, uint32_t h) {
-  const uint32_t tag = red_tag(h);
-  const uint4 s4 = ((const uint4*)T.slot)[red_group(h)];
-  const uint32_t e = (s4.x >> 13) == tag   ? s4.x
-                     : (s4.y >> 13) == tag ? s4.y
-                     : (s4.z >> 13) == tag ? s4.z
-                     : (s4.w >> 13) == tag ? s4.w
-                                           : 0u;
-  if (e == 0) return false;
-  const uint32_t idx = e & 0x1fffu;
-  const uint4 k = T.key[idx];
-  if (k.x != want.x || k.y != want.y || k.z != want.z || k.w != want.w) return false;
-  atomicAdd(&T.cnt[idx], 1u);
-  return true;
-}
-
-// Entry index of a key, or -1, in a table nobody is changing: the probe of red_add without
-// its claims (a group with an empty slot ends it: claimed slots of a group form a prefix).
-WC_DEV int red_find(const RedTable& T, const uint4 want, uint32_t h) {
-  constexpr uint32_t kGroups = kRedSlots / 4;
-  const uint32_t tag = red_tag(h);
-  uint32_t g = red_group(h);
-  for (int probe = 0; probe < 16; ++probe) {
-    const uint4 s4 = ((const uint4*)T.slot)[g];
-    const uint32_t e[4] = {s4.x, s4.y, s4.z, s4.w};
-    bool empty = false;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      if ((e[j] >> 13) == tag) {
-        const uint32_t idx = e[j] & 0x1fffu;
-        const uint4 k = T.key[idx];
-        if (k.x == want.x && k.y == want.y && k.z == want.z && k.w == want.w) return (int)idx;
-      } else if (e[j] == 0) {
-        empty = true;
-      }
-    }
-    if (empty) return -1;
-    g = (g + 1) & (kGroups - 1);
-  }
-  return -1;
-}
-
 // Add one occurrence. Returns false when the word has no entry and none can be made (entries
 // exhausted or 16 groups probed): the caller counts it elsewhere. New entries are handed out
 // with one atomic per wave on the entry count.
