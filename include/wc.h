@@ -60,8 +60,10 @@ typedef int32_t wc_status;
 
 /* debug flags (wc_opts.debug_flags) */
 #define WC_DEBUG_TIME   1u  /* time the count kernel with HIP events (wc_result.kernel_ms) */
-#define WC_DEBUG_NO_LDS 2u  /* skip the LDS table: every token goes to the global table */
-#define WC_DEBUG_DIRECT 4u  /* global mode: one-pass kernel (LDS table + global atomics);
+#define WC_DEBUG_NO_LDS 2u  /* one-pass kernel without its LDS table: every token goes to the
+                               global table */
+#define WC_DEBUG_DIRECT 4u  /* global mode: one-pass kernel (LDS table + global atomics)
+                               instead of the partitioned kernels that run below 256 MiB;
                                per-document mode: the same kernel over one (document, word)
                                table, sorted into the CSR afterwards */
 #define WC_DEBUG_SPILL  8u  /* global mode: two-pass kernels (LDS table + partitioned spill)
@@ -78,20 +80,25 @@ typedef int32_t wc_status;
                                  Table 3-7) inside its document whose code point is a word
                                  character: ASCII word bytes, or any code point from U+0080
                                  except U+0080..U+00BF, U+00D7, U+00F7, U+2000..U+206F,
-                                 U+3000..U+303F and U+FEFF; folding stays ASCII-only. Counted
-                                 by the one-pass kernel (global, and per-document through one
-                                 (document, word) table); wc_batch_* take ASCII only */
+                                 U+3000..U+303F and U+FEFF; folding stays ASCII-only. Global
+                                 counts run the partitioned kernels, from 256 MiB and in
+                                 per-document mode (one (document, word) table) the one-pass
+                                 kernel; wc_batch_* take ASCII only */
 
-/* Launch tuning; a zero field takes the library default. */
+/* Launch tuning; a zero field takes the library default. (A global count below 256 MiB that
+ * names a stage size, LDS entries, a flush policy, a grid or a load runs the one-pass kernel,
+ * which they tune.) */
 typedef struct wc_tuning {
   uint32_t stage_bytes;   /* bytes one workgroup scans per step: 4096 or 8192 (= 16 B/thread) */
-  uint32_t lds_entries;   /* LDS table entries per workgroup, power of two, 256..4096 */
+  uint32_t lds_entries;   /* LDS table entries per workgroup, power of two, 256..4096 (0 = 2048
+                             for the one-pass kernel, all that fit for the others) */
   uint32_t flush_policy;  /* WC_FLUSH_ALL or WC_FLUSH_BYPASS */
-  uint32_t grid_blocks;   /* workgroups in the count launch (0 = 2 per CU) */
-  uint32_t lds_load_pct;  /* LDS table load at which it is flushed (one-pass kernel) or at
-                             which further words are spilled to device memory (document-
-                             centric kernel); 0 = default (50 % for the one-pass kernel, all
-                             of it for the document-centric) */
+  uint32_t grid_blocks;   /* workgroups in the count launch (0 = 2 per CU, document-centric
+                             kernel 1 per CU) */
+  uint32_t lds_load_pct;  /* LDS table load at which it is flushed (one-pass kernel: of its
+                             entries; 0 = 50 %) or at which further words are spilled to
+                             device memory (document-centric kernel: of its 8192 slots, where
+                             that is below its entries; 0 = 100 %) */
   uint32_t chunk_bytes;   /* per-document mode: bytes per work item, power of two in
                              16 KiB..1 MiB (0 = by the size of the text, 16 to 48 KiB) */
   uint32_t direct_kib;    /* per-document mode, document-centric kernel: documents longer
@@ -156,9 +163,9 @@ typedef struct wc_result {
    * [4] records pass 2 could not sum in its LDS table (added to the global table).
    * Document-centric per-document count (the batch API, and wc_count in per-document mode for
    * small documents):
-   * [3] documents counted in the kernel's second pass, with a private table in device
-   *     memory: those whose words did not fit the LDS table, and those that skipped the
-   *     first pass by size (wc_tuning.direct_kib). */
+   * [3] documents longer than the size limit (wc_tuning.direct_kib), plus the documents of
+   *     every group whose words did not fit the LDS table and were spilled to device memory
+   *     (a document of both kinds counts twice). */
   uint64_t stats[5];
 } wc_result;
 
@@ -193,8 +200,10 @@ wc_status wc_count(const uint8_t* d_corpus, uint64_t corpus_len, const uint64_t*
  * 4.1 names the host-to-device copy as the main cost of the GPU reduce): the text is cut into
  * pieces of about piece_bytes (at least 1 MiB), each cut made right after an ASCII delimiter
  * byte or at a document start so that no token spans two pieces; piece p+1 is copied on a
- * second stream of the library while piece p is counted on `stream`, all into one global
- * table exported once at the end. Same result as wc_count of the whole corpus.
+ * second stream of the library while piece p is counted on `stream`. Pieces below 256 MiB are
+ * counted into lists that are reduced once at the end (towards the end a piece is half of what
+ * is left, down to 4 MiB, so that little is left to count when the last copy ends); larger
+ * ones into one global table exported at the end. Same result as wc_count of the whole corpus.
  *   h_corpus   host uint8[corpus_len] (pinned memory lets the copies run asynchronously);
  *              read, never written; must stay valid until the call returns.
  *   h_offsets  host uint64[n_docs + 1] document offsets.
@@ -293,7 +302,8 @@ wc_status wc_topk_ratio(const wc_result* const* corpora, uint32_t n_corpora, uin
 
 /* Batched per-document counting (Section 3.1 counts every document in its own dictionary):
  * all documents of a corpus are counted into per-document tables by one persistent launch
- * that takes 32 KiB windows of documents from a device-side queue. The first wc_batch_run
+ * that takes groups of documents (16 to 48 KiB, larger documents by themselves) from a
+ * device-side queue. The first wc_batch_run
  * captures the whole call (task upload, clears, kernels, size readback) into a HIP graph; later
  * runs only update a pinned host task description and replay the graph, so a run makes no
  * allocation and one graph launch. Device memory is the caller's workspace of
@@ -311,8 +321,8 @@ wc_status wc_batch_create(const wc_opts* opts, uint64_t max_docs, uint64_t max_b
 
 /* Count one corpus (device pointers, as wc_count). The caller's stream is ordered before the
  * graph launch and the call returns after the results are complete. Errors: WC_EINVAL
- * (larger than the plan, invalid offsets), WC_ENOMEM (outputs or private tables short: plan
- * with larger word_bytes_cap / table_slots), WC_ETABLEFULL, WC_EOVERFLOW, WC_EDEVICE. */
+ * (larger than the plan, invalid offsets), WC_ENOMEM (outputs, or the room for words that
+ * do not fit LDS, short: plan with larger word_bytes_cap / table_slots), WC_ETABLEFULL, WC_EOVERFLOW, WC_EDEVICE. */
 wc_status wc_batch_run(wc_batch* b, const uint8_t* d_corpus, uint64_t corpus_len,
                        const uint64_t* d_offsets, uint64_t n_docs, wc_result* out, void* stream);
 
@@ -324,10 +334,11 @@ wc_status wc_batch_destroy(wc_batch* b);
  * workspace) is taken from its low end and resident tables from its high end. A request
  * waits for admission until the memory its count needs is free, as long as some running
  * request holds count memory (it will return it); requests larger than the budget fail with
- * WC_ENOMEM at submission, and a request fails with WC_ENOMEM when nothing runs and resident
- * tables leave no block large enough (only wc_server_release can free them). A finished count
- * waits for its resident block while another running request can still return memory, and
- * fails with WC_ENOMEM otherwise. max_streams worker threads (1..16)
+ * WC_ENOMEM at submission, and a request fails with WC_ENOMEM when nothing runs, resident
+ * tables leave no block large enough (only wc_server_release can free them) and no request has
+ * been finished nor a table released for 100 ms. A finished count waits for its resident block
+ * while another running request can still return memory, or as long, and fails with WC_ENOMEM
+ * otherwise. Requests are admitted in order. max_streams worker threads (1..16)
  * each drive one HIP stream, so admitted requests overlap on the device; small
  * single-document requests queued together are counted in one per-document launch and split
  * into one table per request. Results are global word tables in the server's memory, valid

@@ -84,6 +84,9 @@ struct wc_server {
   wc::Admission adm;
   std::mutex mu;
   std::condition_variable cv_work, cv_done, cv_mem;
+  std::chrono::steady_clock::time_point last_progress;  // a request finished or a table released
+  std::deque<uint64_t> count_queue;                     // requests waiting for count memory, in order
+  uint64_t count_ticket = 0;
   std::deque<std::shared_ptr<Request>> queue;
   std::unordered_map<uint64_t, std::shared_ptr<Request>> reqs;
   std::vector<std::thread> workers;
@@ -203,6 +206,22 @@ __global__ __launch_bounds__(256) void doc_span_kernel(wc_result t, uint64_t* ou
   }
 }
 
+// Waits for memory that was not granted; false: there is none to wait for. Where only the client's
+// release can return any, the client is taken to be at it until nothing has been finished or
+// released for kReleaseGrace (a server that counts 20,000 requests a second is ahead of the thread
+// that releases them).
+constexpr std::chrono::milliseconds kReleaseGrace(100);
+bool wait_memory(wc_server* S, std::unique_lock<std::mutex>& lk, wc::Admit a) {
+  if (a == wc::Admit::kWait) {
+    S->cv_mem.wait(lk);
+    return true;
+  }
+  const auto until = S->last_progress + kReleaseGrace;
+  if (std::chrono::steady_clock::now() >= until) return false;
+  S->cv_mem.wait_until(lk, until);
+  return true;
+}
+
 // A resident block for entries [e_begin, e_begin + n) of table t with nb word bytes: R's result
 // points into it, and *item is the copy that fills it.
 wc_status take_resident(wc_server* S, const wc_result& t, uint64_t e_begin, uint64_t n, uint64_t nb,
@@ -216,10 +235,11 @@ wc_status take_resident(wc_server* S, const wc_result& t, uint64_t e_begin, uint
     std::unique_lock<std::mutex> lk(S->mu);
     uint64_t off = 0;
     wc::Admit a;
-    while ((a = S->adm.try_resident(bytes, &off)) == wc::Admit::kWait && !S->stop) {
+    while ((a = S->adm.try_resident(bytes, &off)) != wc::Admit::kGranted && !S->stop) {
       ++S->adm.resident_waiters;
-      S->cv_mem.wait(lk);
+      const bool again = wait_memory(S, lk, a);
       --S->adm.resident_waiters;
+      if (!again) break;
     }
     if (a != wc::Admit::kGranted) return WC_ENOMEM;
     mem = S->pool_mem + off;
@@ -271,8 +291,21 @@ wc_status keep_table(wc_server* S, hipStream_t s, const wc_result& t, Request* R
 uint8_t* pool_alloc_wait(wc_server* S, uint64_t bytes) {
   std::unique_lock<std::mutex> lk(S->mu);
   uint64_t off = 0;
-  wc::Admit a;
-  while ((a = S->adm.try_count(bytes, &off)) == wc::Admit::kWait && !S->stop) S->cv_mem.wait(lk);
+  wc::Admit a = wc::Admit::kFail;
+  // in the order of arrival: a large request that later ones were granted memory before would wait
+  // until their tables are released, which a client that releases in order does after its own
+  const uint64_t me = ++S->count_ticket;
+  S->count_queue.push_back(me);
+  while (!S->stop) {
+    if (S->count_queue.front() != me) {
+      S->cv_mem.wait(lk);
+      continue;
+    }
+    a = S->adm.try_count(bytes, &off);
+    if (a == wc::Admit::kGranted || !wait_memory(S, lk, a)) break;
+  }
+  S->count_queue.erase(std::find(S->count_queue.begin(), S->count_queue.end(), me));
+  S->cv_mem.notify_all();
   return a == wc::Admit::kGranted ? S->pool_mem + off : nullptr;
 }
 
@@ -286,6 +319,7 @@ void pool_free(wc_server* S, uint8_t* p) {
 void free_resident_locked(wc_server* S, Request* R) {
   if (R->resident) S->adm.free_resident((uint64_t)(R->resident - S->pool_mem));
   R->resident = nullptr;
+  S->last_progress = std::chrono::steady_clock::now();
   S->cv_mem.notify_all();
 }
 
@@ -301,6 +335,7 @@ void finish(wc_server* S, Request* R, wc_status st) {
   std::lock_guard<std::mutex> lk(S->mu);
   R->status = st;
   R->state = 2;
+  if (st == WC_OK) S->last_progress = std::chrono::steady_clock::now();
   R->t_done = now_s();
   R->text.clear();
   R->text.shrink_to_fit();

@@ -11,6 +11,7 @@ import itertools
 import json
 import os
 import sys
+import time
 
 import numpy as np
 import pytest
@@ -1064,6 +1065,21 @@ def test_server_budget_errors():
     assert e.value.status == wc.WC_ENOMEM
     i = srv.submit(b"a b c a")
     assert wc.result_to_dict(srv.wait(i)) == {b"a": 2, b"b": 1, b"c": 1}
+    srv.close()
+
+
+def test_server_waits_for_a_slow_release():
+    """Resident tables of 40 requests need four times the budget: requests wait for the client,
+    which releases one table every few milliseconds, instead of failing."""
+    rng = np.random.default_rng(41)
+    texts = [b" ".join(b"%05x" % v for v in rng.integers(0, 1 << 17, 150_000)) for _ in range(8)]
+    want = [oracle.count(t).total for t in texts]
+    srv = wc.Server(mem_budget=32 << 20, max_streams=4)
+    ids = [srv.submit(texts[i % 8]) for i in range(40)]
+    for k, i in enumerate(ids):
+        assert srv.wait(i).total_tokens == want[k % 8], k
+        time.sleep(0.004)
+        srv.release(i)
     srv.close()
 
 
