@@ -297,8 +297,9 @@ void layout_docs(uint64_t len, uint64_t n_docs, const wc_opts* o, void* ws, DocL
 DocParams doc_params(const DocLayout& L, const wc_opts* o, uint32_t lds, uint32_t pct,
                      uint32_t chunk, uint32_t direct_kib, uint32_t grid) {
   DocParams P;
-  // (a round's keys at least: an empty table takes them whatever was asked for)
-  P.lds_cap = std::max<uint32_t>((uint32_t)((uint64_t)lds * (pct ? pct : 100) / 100), 128);
+  // entries, as long as the slots are filled to the load (a round's keys at least: an empty table
+  // takes them whatever was asked for)
+  P.lds_cap = std::max<uint32_t>(std::min<uint32_t>(lds, kDocSlots * (pct ? pct : 100) / 100), 128);
   P.direct_kib = direct_kib;
   P.win_bytes = chunk;
   P.grid = grid;
@@ -1380,12 +1381,9 @@ namespace {
 std::vector<wc_tuning> tune_grid(const wc_opts* o) {
   std::vector<wc_tuning> g;
   if (o->mode == WC_PER_DOC) {
-    // One point: 32 KiB work items, the full LDS table at the highest load. On a calibration
-    // sample of a few thousand documents the second pass lasts as long as its largest
-    // document, whatever else it counts, so the sample favours points that send more
-    // documents there: it chose a smaller table and load (batched-100k 21.7 ms, nearly every
-    // document counted twice instead of 8,400) or 16 KiB items (15.1 ms, 24,600) over this
-    // point (13.1 ms); 64 KiB items overflow the default private-table arena.
+    // One point: a table and a work item that fit most text. A calibration sample of a few
+    // thousand documents cannot rank others: it lasts as long as its largest document.
+    // (100,000 documents: 5.83 ms; 5.56 with the default work items, which no power of two names.)
     g.push_back(wc_tuning{0, 4096, 0, 0, 85, 32u << 10, 0});
   } else {
     // one-pass kernel: LDS entries x flush load x flush policy (the two-pass kernels, from
@@ -1426,10 +1424,7 @@ wc_status wc_autotune(const uint8_t* d_sample, uint64_t len, const uint64_t* d_o
   float best_t = 3.4e38f;
   bool found = false;
   // times one point (two calls after a warm-up); false when it needs more room than planned.
-  // (direct_kib keeps its default: on a calibration sample of a few thousand documents the
-  // second pass's time is that of its largest document, whatever the size limit, and the
-  // sample favoured sending every long document straight to it, which was slower on the
-  // whole corpus.)
+  // (direct_kib keeps its default: it only decides what is reported.)
   auto try_point = [&](const wc_tuning& t, wc_status* err) -> bool {
     wc_opts o = *opts;
     o.tuning = &t;

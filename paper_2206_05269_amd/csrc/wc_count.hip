@@ -1,5 +1,7 @@
-// Count kernel: the map (tokenise, hash) and the first level of the reduce (merge counts),
-// fused. Section 3.1 counts each document's words in its own dictionary on CPU threads and
+// One-pass count kernel: the map (tokenise, hash) and the first level of the reduce (merge counts),
+// fused. It counts what the partitioned and two-pass kernels do not take: calls without a
+// workspace, (document, word) tables of large documents, UTF-8 from 256 MiB, text with hardly a
+// repeated word, and calls that tune it. Section 3.1 counts each document's words in its own dictionary on CPU threads and
 // Section 3.3 sums the grouped counts on the GPU; here one kernel scans the raw bytes, keeps
 // a per-workgroup dictionary in LDS and merges it into one table in device memory, which is
 // the GPU-resident dictionary that Section 5.2 proposes.

@@ -55,7 +55,6 @@ namespace wc {
 namespace {
 
 constexpr int kBlk = 1024;
-constexpr uint32_t kDocSlots = 8192;
 constexpr uint32_t kWaves = kBlk / 64;
 constexpr uint32_t kTile = kStripe - 32;      // bytes whose words a wave counts at a time
 constexpr uint32_t kText = kStripe + 32;      // per wave: a tile with 16 bytes on each side, padding
