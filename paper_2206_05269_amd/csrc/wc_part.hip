@@ -531,7 +531,7 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
   constexpr bool kWide = sizeof(C) == 8;
   constexpr uint32_t kRows = 1024;
   constexpr uint32_t kMaxBits = 16;
-  constexpr int kRecs = 4;  // records of a thread read and added together
+  constexpr int kRecs = 2;  // records of a thread read and added together
   extern __shared__ __align__(16) uint8_t s_dyn[];
   __shared__ uint32_t s_pre[kRows + 1], s_rec[kRows];
   __shared__ uint32_t s_nent, s_full;
@@ -567,11 +567,13 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
       if (tid == 0) s_pre[kRows] = (uint32_t)tot;
       __syncthreads();
       const uint32_t m = (uint32_t)tot;
-      for (uint32_t f0 = 0; f0 < m; f0 += kRecs * kBlk) {
-        uint4 k[kRecs];
-        uint32_t h[kRecs], lo[kRecs];
-        C c[kRecs];
-        bool use[kRecs];
+      // A round's records are read while those of the round before are added: two a thread, for the
+      // registers (four without reading ahead: reduce of 1 / 20 / 64 MB 12.2 / 17.7 / 69.8 us, of
+      // 2,000 tables 23.7; now 10.0 / 16.2 / 67.3 and 20.9).
+      uint4 k[kRecs], kn[kRecs];
+      C c[kRecs], cn[kRecs];
+      auto read = [&](uint32_t f0) {
+        uint32_t lo[kRecs];
 #pragma unroll
         for (int x = 0; x < kRecs; ++x) lo[x] = 0;
 #pragma unroll
@@ -582,11 +584,22 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
 #pragma unroll
         for (int x = 0; x < kRecs; ++x) {
           const uint32_t f = f0 + x * kBlk + tid;
-          use[x] = f < m;
-          const uint32_t r = use[x] ? s_rec[lo[x]] + (f - s_pre[lo[x]]) : 0u;
-          k[x] = P.rec_key[r];
-          c[x] = ((const C*)P.rec_cnt)[r];
+          const uint32_t r = f < m ? s_rec[lo[x]] + (f - s_pre[lo[x]]) : 0u;
+          kn[x] = P.rec_key[r];
+          cn[x] = ((const C*)P.rec_cnt)[r];
         }
+      };
+      if (m) read(0);
+      for (uint32_t f0 = 0; f0 < m; f0 += kRecs * kBlk) {
+        uint32_t h[kRecs];
+        bool use[kRecs];
+#pragma unroll
+        for (int x = 0; x < kRecs; ++x) {
+          k[x] = kn[x];
+          c[x] = cn[x];
+          use[x] = f0 + x * kBlk + tid < m;
+        }
+        if (f0 + kRecs * kBlk < m) read(f0 + kRecs * kBlk);
 #pragma unroll
         for (int x = 0; x < kRecs; ++x) {
           h[x] = place_hash(k[x]);
