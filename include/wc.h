@@ -117,7 +117,8 @@ typedef struct wc_opts {
   const wc_tuning* tuning;   /* NULL = defaults */
   uint32_t debug_flags;      /* WC_DEBUG_* */
   uint32_t debug_hash_bits;  /* 0 = full 64-bit keys; 1..63 keep only the low bits of every
-                                key, forcing key collisions so the byte compare decides */
+                                key, forcing key collisions so the byte compare decides (the
+                                document-centric kernel compares whole words only) */
   uint64_t word_bytes_cap;   /* capacity reserved for exported word bytes; 0 = auto */
   uint64_t debug_count_bias; /* 0 normally; otherwise added to every exported count, so that
                                 the count-width check (WC_EOVERFLOW) and wide counts can be

@@ -70,6 +70,11 @@ constexpr uint32_t kDocParts = 256;
 constexpr uint32_t kUnit = 1024, kClassesMax = 20;
 constexpr uint32_t kTaking = 0xfffffffeu, kNoRegion = 0xffffffffu;
 
+// A work item: documents << kItemShift | the first one.
+constexpr uint32_t kItemShift = 48;
+WC_DEV uint32_t item_docs(uint64_t it) { return (uint32_t)(it >> kItemShift); }
+WC_DEV uint64_t item_first(uint64_t it) { return it & ((1ull << kItemShift) - 1); }
+
 // bits 0..3 of n -> bits 7, 15, 23, 31 (the top bits of four bytes)
 WC_DEV uint32_t spread4(uint32_t n) {
   return (__umul24(n & 7u, 0x204080u) & 0x808080u) | ((n & 8u) << 28);
@@ -135,7 +140,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
 
   const uint8_t* const corpus = as_global(as_global(args()->task)->corpus);
   const uint64_t len = uniform64(as_global(args()->task)->len);
-  auto offset_at = [&](uint32_t d) -> uint64_t { return as_global(as_global(args()->task)->offsets)[d]; };
+  auto offset_at = [&](uint64_t d) -> uint64_t { return as_global(as_global(args()->task)->offsets)[d]; };
   const int64_t base_off = -(int64_t)((uintptr_t)corpus & 15);
   if (ld_relaxed32(&hdr_of()->flags) & kFlagBadOffsets) return;
 
@@ -604,7 +609,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   };
 
   // ---- the queue ------------------------------------------------------------------------------
-  // An item is a run of documents: (documents << 32 | first one), 0 when there is none left. The
+  // An item is a run of documents, 0 when there is none left. The
   // queue takes them by size class, the largest first (a workgroup that took a large document
   // late would otherwise finish alone).
   if (tid == 0) {
@@ -635,15 +640,15 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
   }
   uint64_t it = item_at(blockIdx.x);
   uint32_t cur = 0;  // s_doff buffer of the group
-  if (it && tid <= (uint32_t)(it >> 32)) s_doff[0][tid] = offset_at((uint32_t)it + tid);
+  if (it && tid <= item_docs(it)) s_doff[0][tid] = offset_at(item_first(it) + tid);
   __syncthreads();
   uint64_t ahead = item_at(s_next);
-  if (ahead && tid <= (uint32_t)(ahead >> 32)) s_doff[1][tid] = offset_at((uint32_t)ahead + tid);
+  if (ahead && tid <= item_docs(ahead)) s_doff[1][tid] = offset_at(item_first(ahead) + tid);
   __syncthreads();
-  if (it) t0 = load((int64_t)uniform64(s_doff[0][0]), (int64_t)uniform64(s_doff[0][it >> 32]), wv);
+  if (it) t0 = load((int64_t)uniform64(s_doff[0][0]), (int64_t)uniform64(s_doff[0][item_docs(it)]), wv);
   while (it) {
-    const uint32_t nd = (uint32_t)(it >> 32);
-    const uint64_t d0 = (uint32_t)it;
+    const uint32_t nd = item_docs(it);
+    const uint64_t d0 = item_first(it);
     const uint64_t* const doff = s_doff[cur];
     chunk = 0;
     chunk_n = 0;
@@ -656,7 +661,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
     __syncthreads();
     const uint64_t after = ahead ? item_at(s_next) : 0;
     const uint32_t nxt = cur == 2 ? 0 : cur + 1, nxt2 = cur == 0 ? 2 : cur - 1;
-    if (ahead) t0 = load((int64_t)uniform64(s_doff[nxt][0]), (int64_t)uniform64(s_doff[nxt][ahead >> 32]), wv);
+    if (ahead) t0 = load((int64_t)uniform64(s_doff[nxt][0]), (int64_t)uniform64(s_doff[nxt][item_docs(ahead)]), wv);
     if (s_spill) {
       if (tid == 0) add64(&hdr_of()->stat[3], nd);
       for (uint32_t level = 0; s_spill && !s_lost; ++level) count_spilled(level);
@@ -680,7 +685,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
       }
     }
     uint64_t off = 0;
-    if (after && tid <= (uint32_t)(after >> 32)) off = offset_at((uint32_t)after + tid);
+    if (after && tid <= item_docs(after)) off = offset_at(item_first(after) + tid);
     __syncthreads();
     // documents' places in the group, and its place in the output, by wave 0; the other waves
     // go on to their text of the next group
@@ -719,7 +724,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
     }
     // what was asked for before the entries' stores is taken before them (loads and stores are
     // waited for in their order)
-    if (after && tid <= (uint32_t)(after >> 32)) s_doff[nxt2][tid] = off;
+    if (after && tid <= item_docs(after)) s_doff[nxt2][tid] = off;
     pin(t0);
     __syncthreads();
     const bool room = (s_out >> 32) <= args()->cap_e && (s_out & 0xffffffffull) <= args()->cap_b;
@@ -847,7 +852,7 @@ __global__ __launch_bounds__(kBlk) void doc_plan_kernel(DocParams P) {
       // (runs of offsets in order fit their class; others fail the call)
       const uint64_t lo = P.class_at[cls], hi = P.class_at[cls + 1];
       for (uint64_t d = i; d < end; d += kDocW, ++at)
-        if (lo + at < hi) P.items[lo + at] = (min((uint64_t)kDocW, end - d) << 32) | d;
+        if (lo + at < hi) P.items[lo + at] = (min((uint64_t)kDocW, end - d) << kItemShift) | d;
     }
     __syncthreads();
   }

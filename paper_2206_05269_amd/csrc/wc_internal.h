@@ -154,7 +154,7 @@ struct DocTask {           // device-resident: every size the per-document kerne
 struct DocParams {
   const DocTask* task;
   Header* hdr;
-  uint64_t* items;         // runs of documents (documents << 32 | the first), by size class
+  uint64_t* items;         // runs of documents, by size class
   uint64_t class_at[kDocClasses + 1];  // a class's first item, and where the last one's end at most
   uint32_t* class_n;       // [kDocClasses] items of each class (zero before)
   uint64_t* word_offsets;  // [cap_e + 1]
