@@ -142,7 +142,7 @@ constexpr uint32_t kDirectKib = 72;
 constexpr uint32_t kDocClasses = 16;
 constexpr uint32_t kDocW = 256;        // documents per sub-window
 constexpr uint32_t kDocSlots = 8192;   // LDS table slots
-constexpr uint32_t kDocLds = 4528;     // LDS table entries (20 bytes each, beside 8192 slots)
+constexpr uint32_t kDocLds = 4628;     // LDS table entries (20 bytes each, beside 8192 slots)
 
 struct DocTask {           // device-resident: every size the per-document kernels read
   const uint8_t* corpus;
