@@ -162,6 +162,9 @@ typedef struct wc_result {
    *     their partition's arena blocks was used up,
    * [2] dictionary words,
    * [4] records pass 2 could not sum in its LDS table (added to the global table).
+   * Partitioned global count, and wc_merge:
+   * [1] 1 when the partitioned kernels had too little room (records, or a partition's table) and
+   *     the text or the entries were counted again into one table.
    * Document-centric per-document count (the batch API, and wc_count in per-document mode for
    * small documents):
    * [3] documents longer than the size limit (wc_tuning.direct_kib), plus the documents of

@@ -689,10 +689,12 @@ wc_status count_table(const uint8_t* d_corpus, uint64_t corpus_len, const uint64
     HostBox box;
     HIPCHK(box.read(L.hdr, s));
     const Header& h = *box.as<Header>();
-    if ((h.flags & kFlagArena) && !(h.flags & kFlagBadOffsets)) {
+    if ((h.flags & kFlagAgain) && !(h.flags & kFlagBadOffsets)) {
       CountLayout again = L;
       again.part = false;
-      return count_table(d_corpus, corpus_len, d_offsets, n_docs, opts, tu, again, out, s, phases);
+      const wc_status st = count_table(d_corpus, corpus_len, d_offsets, n_docs, opts, tu, again, out, s, phases);
+      if (st != WC_EINVAL && st != WC_ETABLEFULL && st != WC_EDEVICE) out->stats[1] = 1;
+      return st;
     }
     const wc_status st = part_result(h, n_docs, opts, L, out);
     if (tm.on && !(h.flags & (kFlagBadOffsets | kFlagTableFull))) {
@@ -985,7 +987,7 @@ wc_status wc_merge(const wc_result* const* tables, uint32_t k, const wc_opts* op
   const std::vector<MergeInput> ins = merge_inputs(tables, k);
   HostBox box;
   Header h;
-  h.flags = kFlagArena;
+  h.flags = kFlagAgain;
   if (L.part) {
     PartParams P;
     memset(&P, 0, sizeof(P));
@@ -1011,7 +1013,8 @@ wc_status wc_merge(const wc_result* const* tables, uint32_t k, const wc_opts* op
     HIPCHK(box.read(L.hdr, s));
     h = *box.as<Header>();
   }
-  if (h.flags & kFlagArena) {
+  const bool again = (h.flags & kFlagAgain) != 0;
+  if (again) {
     HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));
     HIPCHK(launch_fill_zero(L.table, L.S * sizeof(Slot), s));
     if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
@@ -1046,6 +1049,7 @@ wc_status wc_merge(const wc_result* const* tables, uint32_t k, const wc_opts* op
   out->d_counts = L.counts;
   for (uint32_t i = 0; i < k; ++i) total += tables[i]->total_tokens;
   out->total_tokens = total;
+  out->stats[1] = L.part && again;
   if (tm.on) {
     HIPCHK(hipEventRecord(tm.d, s));
     HIPCHK(hipEventSynchronize(tm.d));
@@ -1822,8 +1826,8 @@ wc_status wc_count_host(const uint8_t* h_corpus, uint64_t corpus_len, const uint
       e = box.read(L.hdr, s);
       if (e == hipSuccess) h = *box.as<Header>();
     }
-    if (st == WC_OK && e == hipSuccess && !(h.flags & kFlagArena)) st = part_result(h, n_docs, &q, L, out);
-    if (h.flags & kFlagArena) q.debug_flags |= kNoPart;  // the pieces again, into one table
+    if (st == WC_OK && e == hipSuccess && !(h.flags & kFlagAgain)) st = part_result(h, n_docs, &q, L, out);
+    if (h.flags & kFlagAgain) q.debug_flags |= kNoPart;  // the pieces again, into one table
   }
   if (st == WC_OK && e == hipSuccess && (q.debug_flags & kNoPart)) {
     CountLayout L;
@@ -1863,7 +1867,10 @@ wc_status wc_count_host(const uint8_t* h_corpus, uint64_t corpus_len, const uint
     g_last_hip = (int32_t)e;
     return WC_EDEVICE;
   }
-  if (st == WC_OK) out->n_docs = n_docs;
+  if (st == WC_OK) {
+    out->n_docs = n_docs;
+    out->stats[1] = part && (q.debug_flags & kNoPart);
+  }
   return st;
 }
 

@@ -39,6 +39,11 @@ constexpr uint32_t kFlagBadOffsets = 2u;
 constexpr uint32_t kFlagWordCap = 4u;
 constexpr uint32_t kFlagCountOverflow = 8u;
 constexpr uint32_t kFlagArena = 32u;  // the partitioned count ran out of room: count again one-pass
+// The partitioned reduce found more words with one hash than its table holds: count again one-pass.
+// (Not kFlagArena, which its workgroups look at before they begin: one that begins while another
+// sets the flag could have some of its waves leave and the others go on without them.)
+constexpr uint32_t kFlagSplit = 64u;
+constexpr uint32_t kFlagAgain = kFlagArena | kFlagSplit;
 constexpr uint32_t kFlagStall = 16u;  // a bounded wait inside a kernel gave up (internal error)
 
 struct Slot {

@@ -21,7 +21,8 @@
 //
 // Words longer than 16 bytes are kept as references to an occurrence and compared by content.
 // What does not fit (more records than the arena, more lists than the directory) sets kFlagArena,
-// and the caller counts the text again with the one-pass kernel.
+// more long words alike in length and hash than a table holds set kFlagSplit, and the caller counts
+// the text again with the one-pass kernel.
 #include <type_traits>
 
 #include "wc_internal.h"
@@ -523,7 +524,8 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
 // One workgroup per partition. The directory rows of kRows lists at a time give the flat order
 // of their records; a thread finds its record's list by a binary search in LDS. A partition
 // whose words do not fit the LDS table is summed in classes of its hash (two, four, ... classes,
-// each reading the records again), so that any number of distinct words is counted in LDS.
+// each reading the records again), so that any number of distinct words is counted in LDS (but for
+// long words alike in length and the 24 hash bits of their key, which no split tells apart).
 template <class C>
 constexpr uint32_t kRedEntries = sizeof(C) == 4 ? kPartRedEntries : kPartMergeEntries;
 template <class C>
@@ -537,6 +539,7 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
   __shared__ uint32_t s_nent, s_full;
   __shared__ uint64_t s_tmp[kWaves], s_base;
   Header* const hdr = P.hdr;
+  // (flags of the launches before: nothing in this one sets them, so all threads see the same)
   if (ld_relaxed32(&hdr->flags) & (kFlagBadOffsets | kFlagArena)) return;
   PartTable<C> T;
   T.slot = (uint32_t*)s_dyn;
@@ -612,7 +615,7 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
     __syncthreads();
     if (s_full) {
       if (bits == kMaxBits) {
-        if (tid == 0) or32(&hdr->flags, kFlagArena);
+        if (tid == 0) or32(&hdr->flags, kFlagSplit);
         return;
       }
       ++bits;  // this class in two: first the half whose new bit is 0

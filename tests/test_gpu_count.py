@@ -816,6 +816,49 @@ def test_merge_partitions():
     assert (w == np.array(text.split(), dtype="S7")).all()
 
 
+def _words_of_one_long_hash(n):
+    """n words of 20 bytes that share the 24 hash bits a long word's key holds (wc_words.h:
+    h = (h ^ d) * M, h ^= h >> 15 for each four bytes d, from the length on): random first 16 bytes,
+    and the last four solved for, kept where they are letters or digits."""
+    M, m32 = 0x9E3779B1, np.uint64(0xFFFFFFFF)
+    inv = np.uint64(pow(M, -1, 1 << 32))
+    chars = np.frombuffer(b"abcdefghijklmnopqrstuvwxyz0123456789", np.uint8)
+    rng = np.random.default_rng(24)
+    first = chars[rng.integers(0, 36, (16 * n, 16))]
+    h = np.full(len(first), 20, np.uint64)
+    for j in range(4):
+        h = ((h ^ np.ascontiguousarray(first[:, 4 * j:4 * j + 4]).view("<u4")[:, 0]) * np.uint64(M)) & m32
+        h ^= h >> np.uint64(15)
+    words = []
+    for top in range(256):  # (h ^ (h >> 24)) & 0xffffff is the same for these 256 values of h
+        t = (top << 24) | (0x5A5A5A ^ top)
+        x = np.uint64(t ^ (t >> 15) ^ (t >> 30))
+        d = (((x * inv) & m32) ^ h).astype("<u4").view(np.uint8).reshape(-1, 4)
+        ok = np.isin(d, chars).all(axis=1)
+        words += [a.tobytes() + b.tobytes() for a, b in zip(first[ok], d[ok])]
+        if len(words) >= n:
+            return words[:n]
+    raise AssertionError("too few words")
+
+
+def test_partitioned_words_of_one_long_hash():
+    """More long words alike in length and hash than a partition's table holds, which no split of
+    the partition tells apart (6,000 for 5,888 entries, a merge's 5,300 for 5,056): the reduce gives
+    up as a whole and the call counts again. A few of them less, and it does not."""
+    words = _words_of_one_long_hash(6000)
+    assert len(set(words)) == 6000
+    for n, again in ((6000, 1), (1500, 0)):
+        t = check(b" ".join(words[:n] + words[:n // 2]) + b" x")
+        assert int(t.res.stats[1]) == again
+    t = gpu_count(b" ".join(words[:5300]))
+    assert int(t.res.stats[1]) == 0
+    got = wc.merge([t])
+    assert int(got.res.stats[1]) == 1 and got.as_dict() == dict.fromkeys(words[:5300], 1)
+    t = gpu_count(b" ".join(words[:1500]))
+    got = wc.merge([t, t])
+    assert int(got.res.stats[1]) == 0 and got.as_dict() == dict.fromkeys(words[:1500], 2)
+
+
 def test_merge_long_words_and_collisions():
     w = b"Q" * 40
     t1 = gpu_count(b" ".join([w, w.lower(), b"a" * 17, b"b"]))
