@@ -355,6 +355,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
       if (in[x] && wl[x] - 1 >= 16u) {
         key[x] = long_word(st[x], wl[x]);
         h[x] = place_hash(key[x]);
+        key[x] = known_key(T, key[x], h[x]);
         wait_vmem();
       }
     return table_add<NX>(T, key, h, one, in);
@@ -607,6 +608,7 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
         for (int x = 0; x < kRecs; ++x) {
           h[x] = place_hash(k[x]);
           if (bits) use[x] &= ((part_hash(k[x]) >> 8) & ((1u << bits) - 1)) == value;
+          if (use[x] && is_long_key(k[x])) k[x] = known_key(T, k[x], h[x]);
         }
         if (f0 + (tid & ~63u) < m && table_add<kRecs>(T, k, h, c, use) != kAdded) s_full = 1;
       }

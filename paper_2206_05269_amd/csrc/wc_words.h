@@ -214,6 +214,36 @@ WC_DEV uint32_t pick4(const uint4 g, uint32_t tag) {  // the first slot with the
   return m;
 }
 
+// Entry of a key, or -1 (claimed slots of a group are a prefix). While others add to the table, a key
+// that they have only just added may not be found.
+template <class Table>
+WC_DEV int table_find(const Table& T, const uint4 want, uint32_t h) {
+  constexpr uint32_t kGroups = Table::kGroups;
+  const uint32_t tag = red_tag(h);
+  uint32_t g = Table::group(h);
+  for (uint32_t probe = 0; probe < kGroups; ++probe) {
+    const uint4 s4 = ((const uint4*)T.slot)[g];
+    const uint32_t e[4] = {s4.x, s4.y, s4.z, s4.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if ((e[j] >> 13) == tag && same_key(T.key[e[j] & 0x1fffu], want)) return (int)(e[j] & 0x1fffu);
+    if (s4.w == 0) return -1;
+    g = (g + 1) & (kGroups - 1);
+  }
+  return -1;
+}
+
+// The key of a word of more than 16 bytes, as the table has it if it does: under the address of the
+// occurrence that took the entry. table_add compares keys, and a word under another address
+// would take an entry that part_add, which finds the word by its content, leaves unused: the
+// occurrences of one word filled a partition's table. (Looked for in table_add itself, by a test of
+// every key, it cost 1.5 to 3.5 % of a count.)
+template <class Table>
+WC_DEV uint4 known_key(const Table& T, const uint4 key, uint32_t h) {
+  const int i = table_find(T, key, h);
+  return i >= 0 ? T.key[i] : key;
+}
+
 // Adds n[x] occurrences of key[x] (hash h[x]) for the lanes and x with f[x]; called by whole
 // waves. kNoRoom: the entries ran out, and nothing was counted, or, with kPartial, the keys
 // that have an entry were and `left` says which were not; kNoSlot: some key found no slot.
@@ -395,24 +425,6 @@ WC_DEV int table_add(const Table& T, const uint4 (&key)[N], const uint32_t (&h)[
     }
   }
   return __all(ok) ? kAdded : kNoSlot;
-}
-
-// Entry of a key in a table that nobody is changing, or -1 (claimed slots of a group are a prefix).
-template <class Table>
-WC_DEV int table_find(const Table& T, const uint4 want, uint32_t h) {
-  constexpr uint32_t kGroups = Table::kGroups;
-  const uint32_t tag = red_tag(h);
-  uint32_t g = Table::group(h);
-  for (uint32_t probe = 0; probe < kGroups; ++probe) {
-    const uint4 s4 = ((const uint4*)T.slot)[g];
-    const uint32_t e[4] = {s4.x, s4.y, s4.z, s4.w};
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      if ((e[j] >> 13) == tag && same_key(T.key[e[j] & 0x1fffu], want)) return (int)(e[j] & 0x1fffu);
-    if (s4.w == 0) return -1;
-    g = (g + 1) & (kGroups - 1);
-  }
-  return -1;
 }
 
 // The bytes of a packed word of 1..16 bytes to any address: at most two stores of each width, the

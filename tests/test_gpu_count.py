@@ -859,6 +859,21 @@ def test_partitioned_words_of_one_long_hash():
     assert int(got.res.stats[1]) == 0 and got.as_dict() == dict.fromkeys(words[:1500], 2)
 
 
+@pytest.mark.parametrize("docs", [5100, 40_000])
+def test_merge_long_word_of_many_documents(docs):
+    """Words of more than 16 bytes in every document of a per-document table: each of a word's
+    entries has its own address, and there are more of them than a partition's table holds
+    (5,056). The partitions count them without giving up."""
+    long = [b"Https'Example'Org'%d" % i * 2 for i in range(7)]
+    text, off = join_docs([b"w%d %s %s\n" % (i % 50, long[0].upper() if i & 1 else long[0], long[1 + i % 6])
+                           for i in range(docs)])
+    per = gpu_count(text, off, per_doc=True)
+    got = wc.merge([per])
+    assert int(got.res.stats[1]) == 0
+    want = collections.Counter(text.lower().split())
+    assert got.as_dict() == dict(want) and want[long[0].lower()] == docs
+
+
 def test_merge_long_words_and_collisions():
     w = b"Q" * 40
     t1 = gpu_count(b" ".join([w, w.lower(), b"a" * 17, b"b"]))
