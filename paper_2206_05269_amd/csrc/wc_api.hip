@@ -363,18 +363,23 @@ bool layout_count(uint64_t len, uint64_t n_docs, const wc_opts* o, const Tune& t
   uint64_t region = S * sizeof(Slot);
   if (L->part) {
     // One workgroup per CU, each with at least a stripe per wave; about 16 KiB of text per
-    // partition, as long as there are CUs (64 KiB: reduce of 1 MB 14.2 us instead of 12.4). Records: natural text makes
-    // one per 14 to 25 bytes; with twice that, only text with hardly a repeated word runs out
-    // (and is then counted by the one-pass kernel). The arena shares its memory with the one-pass
-    // kernel's table: only one of them is in use.
+    // partition, as long as there are CUs (64 KiB: reduce of 1 MB 14.2 us instead of 12.4).
+    // Records: natural text makes one per 26 bytes (1 MB, 5,000 words), 24 (20 MB, 50,000), 19
+    // (64 MB, 500,000 and long ones) or 14 (64 to 250 MB, four million words, Zipf 1.0). There is
+    // room for one per 8, per 10 above 16 MiB, and for as many as the one-pass kernel's table,
+    // which shares its memory, leaves: only text with hardly a repeated word runs out, and is then
+    // counted by the one-pass kernel.
     const uint64_t ns = (len + 15 + kStripe - 1) / kStripe;
     uint64_t grid = std::min<uint64_t>((uint64_t)device_cus(), (ns + 15) / 16);
     L->stripes_per_wg = (ns + grid - 1) / grid;
     L->part_grid = (uint32_t)((ns + L->stripes_per_wg - 1) / L->stripes_per_wg);
     L->parts = 16;
     while (L->parts < kParts && (uint64_t)L->parts << 14 < len) L->parts *= 2;
-    L->cap_recs = (len <= (16ull << 20) ? len / 8 : std::max<uint64_t>(2ull << 20, len / 12)) + 8192;
-    L->max_lists = (uint32_t)(pieces * L->part_grid + L->cap_recs / 1024 + 64);
+    const uint64_t few = pieces * L->part_grid + 65;  // lists that may hold few records
+    L->cap_recs = (len <= (16ull << 20) ? len / 8 : std::max<uint64_t>(2ull << 20, len / 10)) + 8192;
+    const uint64_t fixed = few * L->parts * 8 + 3 * kAlign, each = 20 + (L->parts * 8 + 1023) / 1024;
+    if (region > fixed) L->cap_recs = std::max(L->cap_recs, std::min((region - fixed) / each, len / 2 + 8192));
+    L->max_lists = (uint32_t)(few + L->cap_recs / 1024);
     Bump A(nullptr);
     A.take<uint4>(L->cap_recs * 16);
     A.take<uint32_t>(L->cap_recs * 4);

@@ -575,6 +575,29 @@ def test_partitioned_count(n):
             assert (np.diff(wo) > 0).all() and wo[-1] == got.res.word_bytes
 
 
+def test_partitioned_record_room():
+    """Records are reserved for words with a count alone (not for the entries that lost claims of the
+    same new word leave), and there is room for as many as the table's memory holds: neither text is
+    counted again. One that does run out of room is, with the same result."""
+    rng = np.random.default_rng(6)
+    vocab = [bytes(rng.integers(97, 123, rng.integers(1, 9), dtype=np.uint8)) for _ in range(5000)]
+    p = np.arange(1, 5001) ** -0.9
+    text = b" ".join(vocab[i] for i in rng.choice(5000, 220_000, p=p / p.sum()))[:1_000_000]
+    for n in (1_000_000, 300_000):
+        assert int(check(text[:n]).res.stats[1]) == 0
+    # all words different; and 2^17 words over and over, each list with 5,000 others
+    for n, width, words, slots, again in ((3_300_000, 9, 3_300_000, 1 << 23, 0),
+                                          (800_000, 5, 1 << 17, 1 << 18, 1)):
+        i = np.arange(n) % words
+        w = np.full((n, width), 0x20, np.uint8)
+        for j in range(width - 1):
+            w[:, j] = np.frombuffer(b"abcdefghijklmnopqrstuvwxyz012345", np.uint8)[(i >> (5 * j)) & 31]
+        t = gpu_count(w.reshape(-1), table_slots=slots)
+        assert int(t.res.stats[1]) == again and t.total_tokens == n
+        assert t.n_entries == words and int(t.counts().sum()) == n
+        assert t.res.word_bytes == (width - 1) * words
+
+
 @pytest.mark.parametrize("step", [1, 2, 3])
 def test_partitioned_tiny_documents(step):
     """64 document starts at a time against tiles: every alignment of the one to the other."""
