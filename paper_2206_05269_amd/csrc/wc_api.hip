@@ -684,15 +684,19 @@ wc_status count_table(const uint8_t* d_corpus, uint64_t corpus_len, const uint64
   const uint64_t occ_limit = L.S - L.S / 8;
   if (L.part && phases == kPhaseAll) {
     PartParams P = part_params(d_corpus, corpus_len, d_offsets, n_docs, opts, L);
-    const bool single = corpus_len <= kSingleBytes;
-    if (single) P.stripes_per_wg = P.n_stripes;
-    else HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));
-    if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
-    HIPCHK(single ? launch_part_single(P, s) : launch_part_map(P, L.part_grid, s));
-    if (tm.on) HIPCHK(hipEventRecord(tm.b, s));
-    if (!single) HIPCHK(launch_part_reduce(P, s));
     HostBox box;
-    HIPCHK(box.read(L.hdr, s));
+    bool single = corpus_len <= kSingleBytes;
+    while (true) {
+      P.stripes_per_wg = single ? P.n_stripes : L.stripes_per_wg;
+      if (!single) HIPCHK(launch_fill_zero(L.hdr, sizeof(Header), s));
+      if (tm.on) HIPCHK(hipEventRecord(tm.a, s));
+      HIPCHK(single ? launch_part_single(P, s) : launch_part_map(P, L.part_grid, s));
+      if (tm.on) HIPCHK(hipEventRecord(tm.b, s));
+      if (!single) HIPCHK(launch_part_reduce(P, s));
+      HIPCHK(box.read(L.hdr, s));
+      if (!single || !(box.as<Header>()->flags & kFlagArena)) break;
+      single = false;  // more words than one table holds
+    }
     const Header& h = *box.as<Header>();
     if ((h.flags & kFlagAgain) && !(h.flags & kFlagBadOffsets)) {
       CountLayout again = L;

@@ -598,6 +598,15 @@ def test_partitioned_record_room():
         assert t.res.word_bytes == (width - 1) * words
 
 
+@pytest.mark.parametrize("n", [5008, 5009, 6800])
+def test_partitioned_one_workgroup_full(n):
+    """A text of at most 48 KiB with as many different words as the one workgroup's table holds, and
+    with more: the partitions count it then, not the one-pass kernel."""
+    text = b" ".join(b"%06x" % (i * 2467) for i in range(n))
+    assert len(text) <= 48 << 10
+    assert int(check(text, table_slots=1 << 14).res.stats[1]) == 0
+
+
 @pytest.mark.parametrize("step", [1, 2, 3])
 def test_partitioned_tiny_documents(step):
     """64 document starts at a time against tiles: every alignment of the one to the other."""
