@@ -365,10 +365,14 @@ bool layout_count(uint64_t len, uint64_t n_docs, const wc_opts* o, const Tune& t
     // One workgroup per CU, each with at least a stripe per wave; about 16 KiB of text per
     // partition, as long as there are CUs (64 KiB: reduce of 1 MB 14.2 us instead of 12.4).
     // Records: natural text makes one per 26 bytes (1 MB, 5,000 words), 24 (20 MB, 50,000), 19
-    // (64 MB, 500,000 and long ones) or 14 (64 to 250 MB, four million words, Zipf 1.0). There is
-    // room for one per 8, per 10 above 16 MiB, and for as many as the one-pass kernel's table,
-    // which shares its memory, leaves: only text with hardly a repeated word runs out, and is then
-    // counted by the one-pass kernel.
+    // (64 MB, 500,000 and long ones) or 14 (64 to 250 MB, four million words, Zipf 1.0), and some
+    // are reserved for entries that a lost claim leaves without a word: 2,000 in a workgroup's
+    // first list, whose words are new to all of its waves, 450 in others. There is room for one per
+    // 8 bytes, per 10 above 16 MiB, beside the entries of the first rounds of all waves, and for as
+    // many as the one-pass kernel's table, which shares the memory, holds: 43 to 76 % of the room
+    // is used by these texts. Only text with hardly a repeated word runs out, and is then counted
+    // by the one-pass kernel. (Counting the words before they are reserved leaves no such entries,
+    // and cost 0.8 us of a 20 MB text's 83.)
     const uint64_t ns = (len + 15 + kStripe - 1) / kStripe;
     uint64_t grid = std::min<uint64_t>((uint64_t)device_cus(), (ns + 15) / 16);
     L->stripes_per_wg = (ns + grid - 1) / grid;
@@ -376,9 +380,10 @@ bool layout_count(uint64_t len, uint64_t n_docs, const wc_opts* o, const Tune& t
     L->parts = 16;
     while (L->parts < kParts && (uint64_t)L->parts << 14 < len) L->parts *= 2;
     const uint64_t few = pieces * L->part_grid + 65;  // lists that may hold few records
-    L->cap_recs = (len <= (16ull << 20) ? len / 8 : std::max<uint64_t>(2ull << 20, len / 10)) + 8192;
+    L->cap_recs = (len <= (16ull << 20) ? len / 8 : std::max<uint64_t>(2ull << 20, len / 10)) + 8192 +
+                  (uint64_t)L->part_grid * 2048;
     const uint64_t fixed = few * L->parts * 8 + 3 * kAlign, each = 20 + (L->parts * 8 + 1023) / 1024;
-    if (region > fixed) L->cap_recs = std::max(L->cap_recs, std::min((region - fixed) / each, len / 2 + 8192));
+    if (region > fixed) L->cap_recs = std::max(L->cap_recs, std::min((region - fixed) / each, len));
     L->max_lists = (uint32_t)(few + L->cap_recs / 1024);
     Bump A(nullptr);
     A.take<uint4>(L->cap_recs * 16);

@@ -397,7 +397,6 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
           if (in[x] && wl[x] - 1 >= 16u) {
             key[x] = with_doc(long_word(st[x], wl[x], doc[x]), doc[x]);
             h[x] = place_hash(key[x]);
-            key[x] = known_key(T, key[x], h[x]);
             wait_vmem();
           }
         const int res = table_add<NX, true>(T, key, h, one, in, left, spare);
@@ -504,7 +503,6 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
         use[x] = j < n;
         k[x] = use[x] ? *rec(j) : make_uint4(0, 0, 0, 0);
         h[x] = place_hash(k[x]);
-        if (use[x] && is_long_key(k[x])) k[x] = known_key(T, k[x], h[x]);
       }
       const int res = table_add<2, true>(T, k, h, one, use, left);
       if (res == kNoRoom) spill(k, left, std::integral_constant<int, 2>());

@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   __shared__ uint32_t s_bnd[kWaves][kEnds];
   __shared__ uint4 s_lenmask[17];
   __shared__ uint32_t s_hist[kParts], s_start[kParts];
-  __shared__ uint32_t s_nent, s_live, s_done, s_tokens, s_tile, s_scan[4];
+  __shared__ uint32_t s_nent, s_done, s_tokens, s_tile, s_scan[4];
   __shared__ uint64_t s_tmp[kWaves], s_base;
   PartTable<uint32_t> T;
   T.slot = (uint32_t*)s_dyn;
@@ -226,7 +226,6 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   init_len_masks(s_lenmask, tid, kBlk);
   if (tid == 0) {
     s_nent = 0;
-    s_live = 0;
     s_done = 0;
     s_tokens = 0;
     s_tile = kWaves;
@@ -356,7 +355,6 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
       if (in[x] && wl[x] - 1 >= 16u) {
         key[x] = long_word(st[x], wl[x]);
         h[x] = place_hash(key[x]);
-        key[x] = known_key(T, key[x], h[x]);
         wait_vmem();
       }
     return table_add<NX>(T, key, h, one, in);
@@ -462,31 +460,21 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
       break;
     }
     const uint32_t ne = min(s_nent, T.cap);
+    // room for all entries, those without a count too: the answer arrives while they are looked at
+    // (lists << 40 | records)
+    uint64_t got = 0;
+    if (tid == 0) got = atomicAdd((unsigned long long*)&hdr_of()->arena_next, (1ull << 40) | ne);
     uint32_t at[kPerThread];  // partition << 16 | place in it
-    uint32_t live = 0;        // words with a count (entries of lost claims have none)
 #pragma unroll
     for (uint32_t x = 0; x < kPerThread; ++x) {
       const uint32_t j = tid + x * kBlk;
       at[x] = kNone;
-      const bool in = j < ne && T.cnt[j];
-      live += (uint32_t)__popcll(__ballot(in));
-      if (in) {
+      if (j < ne && T.cnt[j]) {
         const uint32_t p = part_hash(T.key[j]) & (args()->parts - 1);
         at[x] = (p << 16) | atomicAdd(&s_hist[p], 1u);
       }
     }
-    if (lane == 0) atomicAdd(&s_live, live);
     __syncthreads();
-    // room for them (lists << 40 | records), while the first waves add up the partitions
-    if (tid == kParts) {
-      const uint64_t got = atomicAdd((unsigned long long*)&hdr_of()->arena_next, (1ull << 40) | s_live);
-      s_base = got;
-      if ((got & ((1ull << 40) - 1)) + s_live > args()->cap_recs || (got >> 40) >= args()->max_lists) {
-        or32(&hdr_of()->flags, kFlagArena);
-        s_base = ~0ull;
-      }
-      s_live = 0;
-    }
     uint32_t cnt = 0, incl = 0;
     if (tid < kParts) {
       cnt = s_hist[tid];
@@ -494,7 +482,13 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
       if (lane == 63) s_scan[wv] = incl;
     }
     __syncthreads();
-    if (s_base == ~0ull) return;  // the call counts again: nothing more is of use
+    if (tid == 0) {
+      s_base = got;
+      if ((got & ((1ull << 40) - 1)) + ne > args()->cap_recs || (got >> 40) >= args()->max_lists) {
+        or32(&hdr_of()->flags, kFlagArena);
+        s_base = ~0ull;
+      }
+    }
     if (tid < kParts) {
       uint32_t b = incl - cnt;
       for (uint32_t w = 0; w < 4; ++w) b += w < wv ? s_scan[w] : 0u;
@@ -502,6 +496,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
       s_hist[tid] = 0;
     }
     __syncthreads();
+    if (s_base == ~0ull) return;  // the call counts again: nothing more is of use
     const uint64_t list = s_base >> 40;
     const uint32_t rec = (uint32_t)(s_base & ((1ull << 40) - 1));
     if (tid < args()->parts) as_global(args()->dir)[(uint64_t)tid * args()->max_lists + list] = make_uint2(rec + s_start[tid], cnt);

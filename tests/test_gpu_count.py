@@ -576,18 +576,19 @@ def test_partitioned_count(n):
 
 
 def test_partitioned_record_room():
-    """Records are reserved for words with a count alone (not for the entries that lost claims of the
-    same new word leave), and there is room for as many as the table's memory holds: neither text is
-    counted again. One that does run out of room is, with the same result."""
+    """There is room for the entries that lost claims of the same new word leave without a count (two
+    thirds of a small text's lists), and for as many records as the table's memory holds: neither
+    text is counted again. One that does run out of room is, with the same result."""
     rng = np.random.default_rng(6)
     vocab = [bytes(rng.integers(97, 123, rng.integers(1, 9), dtype=np.uint8)) for _ in range(5000)]
     p = np.arange(1, 5001) ** -0.9
     text = b" ".join(vocab[i] for i in rng.choice(5000, 220_000, p=p / p.sum()))[:1_000_000]
     for n in (1_000_000, 300_000):
         assert int(check(text[:n]).res.stats[1]) == 0
-    # all words different; and 2^17 words over and over, each list with 5,000 others
+    # all words different; and 2^17 words over and over, each list with 5,000 others: 4 million
+    # records, where there is room for 2.6 million
     for n, width, words, slots, again in ((3_300_000, 9, 3_300_000, 1 << 23, 0),
-                                          (800_000, 5, 1 << 17, 1 << 18, 1)):
+                                          (4_000_000, 5, 1 << 17, 1 << 18, 1)):
         i = np.arange(n) % words
         w = np.full((n, width), 0x20, np.uint8)
         for j in range(width - 1):
