@@ -82,6 +82,12 @@ WC_DEV uint64_t uniform64(uint64_t v) {
          (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);
 }
 
+// lane 63's value
+WC_DEV uint64_t last_lane64(uint64_t v) {
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+}
+
 // A pointer into device memory that was itself read from memory. Without the cast its accesses
 // are flat ones, which count as LDS accesses too: every wait for an LDS read then also waits for
 // the text loads in flight.

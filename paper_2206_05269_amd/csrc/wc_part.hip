@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
   auto start_of = [&](uint64_t d) -> int64_t {
     return d <= P.n_docs ? (int64_t)P.offsets[d] : INT64_MAX;
   };
-  auto seek = [&](int64_t p, uint64_t lo) {  // 64 probes at a time
+  auto first_from = [&](int64_t p, uint64_t lo) -> uint64_t {  // 64 probes at a time
     uint64_t hi = P.n_docs + 1;  // offsets[lo - 1] < p <= offsets[hi]
     while (hi > lo && hi - lo > 64) {
       const uint64_t step = (hi - lo + 63) / 64, d = lo + lane * step;
@@ -264,7 +264,10 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
         lo += (k - 1) * step + 1;
       }
     }
-    d0 = lo;
+    return lo;
+  };
+  auto seek = [&](int64_t p, uint64_t lo) {
+    d0 = first_from(p, lo);
     doff = start_of(d0 + lane);
   };
   seek(tile_at(kn) - 16, 0);
@@ -391,7 +394,11 @@ __global__ __launch_bounds__(kBlk) void part_map_kernel(PartParams P) {
             if (o > p0 && o < p0 + (int64_t)kStripe)
               atomicOr(&my_bnd[(uint32_t)(o - p0) >> 5], 1u << ((uint32_t)(o - p0) & 31));
             if (!__all(o < p0 + (int64_t)kStripe)) break;
+            // (a run of empty documents, which all start here, is passed in a few steps: a million of
+            // them in one place, read 64 at a time, took 4.7 ms)
+            const int64_t o63 = (int64_t)last_lane64((uint64_t)o);
             d += 64;
+            if (__builtin_expect(__all(o == o63), 0)) d = first_from(o63 + 1, d);
             o = start_of(d + lane);
           }
           wave_sync();

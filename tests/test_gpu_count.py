@@ -632,6 +632,34 @@ def test_partitioned_document_starts_at_tile_edge(utf8):
     assert got.total_tokens == oracle.count(text, off, utf8=utf8).total == len(off) - 1
 
 
+@pytest.mark.parametrize("utf8", [False, True])
+def test_partitioned_runs_of_empty_documents(utf8):
+    """Runs of empty documents (shorter and longer than the 64 starts that a wave looks at) that
+    start inside words, at tile edges and in the same tile; and a million in one place, which cost
+    a few steps, not one per 64."""
+    tile = 976 if utf8 else 992
+    text = (b"abc de'F ghijklmnopqrstuv 12 " * 2000)[:50_000]
+    at = [0, 1, 5, tile - 17, tile - 16, tile - 15, tile, 3 * tile + 1, 3 * tile + 2, 3 * tile + 40, 20_000, 50_000]
+    for run in (1, 2, 62, 63, 64, 65, 127, 128, 129, 1000):
+        off = np.sort(np.concatenate([[0, 50_000], np.repeat(at, run), np.arange(30_000, 30_200)]))
+        want = oracle.count(text, off, utf8=utf8)
+        got = gpu_count(text, off, utf8=utf8)
+        assert got.total_tokens == want.total and got.as_dict() == want.as_dict(), run
+    text = text * 20
+    best = []
+    for run in (0, 1_000_000):
+        t, o = to_dev(text, np.concatenate([[0], np.full(run, 500_003), [len(text)]]))
+        times = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            a = time.perf_counter()
+            wc.count(t, o, utf8=utf8)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - a)
+        best.append(min(times))
+    assert best[1] < 10 * best[0], best
+
+
 @pytest.mark.parametrize("n", [1025, 300_007])
 def test_two_pass_words_per_stripe(n):
     """Pass 1 lists 192 words of a stripe and counts two a lane, then one: 0 to 512 a stripe."""
