@@ -1404,6 +1404,9 @@ std::vector<wc_tuning> tune_grid(const wc_opts* o) {
     // (100,000 documents: 5.83 ms; 5.56 with the default work items, which no power of two names.)
     g.push_back(wc_tuning{0, 4096, 0, 0, 85, 32u << 10, 0});
   } else {
+    // the default: below 256 MiB the partitioned kernels, which any of the other points rules out
+    // (20 MB: 79 us, the best of the others about 480)
+    g.push_back(wc_tuning{});
     // one-pass kernel: LDS entries x flush load x flush policy (the two-pass kernels, from
     // 256 MiB, take lds_entries as the dictionary size and ignore the rest)
     for (uint32_t lds : {2048u, 4096u})

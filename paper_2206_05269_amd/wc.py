@@ -806,7 +806,7 @@ def autotune(corpus: torch.Tensor, offsets: torch.Tensor, *, per_doc: bool = Tru
     props = torch.cuda.get_device_properties(corpus.device)
     size_class = int(corpus.numel()).bit_length()
     key = (f"{props.name}|{props.multi_processor_count}|{'doc' if per_doc else 'global'}|"
-           f"{size_class}|direct")
+           f"{size_class}|default")  # choices of grids without the default had other keys
     path = _cache_file(cache_path)
     cache = {}
     if use_cache and os.path.exists(path):

@@ -1248,6 +1248,23 @@ def test_autotune_choice_is_exact_and_cached(tmp_path):
     check(c.text.numpy(), c.offsets.numpy(), tuning=g, debug_flags=wc.WC_DEBUG_SPILL)
 
 
+def test_autotune_global_includes_the_default(tmp_path):
+    """Below 256 MiB the default is the partitioned count, several times faster than every tuned
+    point (which names the one-pass kernel), also where a cache holds an older choice."""
+    n = 8_000_000
+    rng = np.random.default_rng(8)
+    vocab = [b"%x" % (i * i * 7919) for i in range(20_000)]
+    text = b" ".join(vocab[i] for i in rng.zipf(1.3, n // 4) % 20_000)[:n].ljust(n)
+    t, o = to_dev(text)
+    p = torch.cuda.get_device_properties(t.device)
+    cache = tmp_path / "tune.json"
+    cache.write_text(json.dumps({f"{p.name}|{p.multi_processor_count}|global|{n.bit_length()}|direct":
+                                 {"tuning": [0, 4096, 0, 0, 75, 0, 0], "ms": 1.0}}))
+    tu = wc.autotune(t, o, per_doc=False, cache_path=str(cache))
+    assert not any(getattr(tu, f) for f, _ in wc.Tuning._fields_)
+    assert wc.count(t, o, tuning=tu).as_dict() == oracle.count(text).as_dict()
+
+
 @pytest.mark.parametrize("direct_kib", [1, 32, wc.WC_DIRECT_NEVER])
 def test_per_doc_direct_second_pass(direct_kib):
     """Documents longer than a 16 KiB work item and than direct_kib KiB skip the first count:
