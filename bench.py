@@ -570,8 +570,8 @@ def batched_docs_per_s(steps: int, warmup: int, plain_docs: int):
     tu = wc.autotune(cal_text, c.offsets[:cal + 1].contiguous(), per_doc=True, count_bytes=4,
                      use_cache=False)
     t_tune = time.perf_counter() - t0
-    log(f"autotune: chunk {tu.chunk_bytes} lds {tu.lds_entries} load {tu.lds_load_pct}% "
-        f"direct {tu.direct_kib} KiB in {t_tune:.1f} s")
+    log(f"autotune (0: the library's default): chunk {tu.chunk_bytes} lds {tu.lds_entries} "
+        f"load {tu.lds_load_pct}% direct {tu.direct_kib} KiB in {t_tune:.1f} s")
     b = wc.Batch(max_docs=n_docs, max_bytes=B, count_bytes=4, tuning=tu,
                  **wc.output_sizes(c.text, c.offsets, count_bytes=4))
     for _ in range(warmup):

@@ -392,11 +392,10 @@ uint64_t wc_server_launches(wc_server* s);
 wc_status wc_server_destroy(wc_server* s);
 
 /* Autotuner: time wc_count on a calibration sample (device-resident, as wc_count) for each
- * point of a small grid of launch tunings (per-document mode: one point, 32 KiB work items
- * with 4096 LDS entries at an 85 % load, which a calibration sample of a few thousand
- * documents cannot rank against others; global mode: the default, all zero, and LDS entries x
- * flush load x flush policy) with HIP events on `stream`, and return the fastest in *best (its
- * time per call in *best_ms). The workspace must hold
+ * point of a small grid of launch tunings (per-document mode: the default, all zero, alone, which a
+ * calibration sample of a few thousand documents cannot rank against others; global mode: the
+ * default and LDS entries x flush load x flush policy) with HIP events on `stream`, and return
+ * the fastest in *best (its time per call in *best_ms). The workspace must hold
  * wc_autotune_plan() bytes. The sample's counts are not returned. Output and private-table
  * sizes come from opts (word_bytes_cap, table_slots) as in wc_count; a grid point that runs
  * out of that room is skipped, and WC_ENOMEM is returned when no point fits. */

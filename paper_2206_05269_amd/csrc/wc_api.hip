@@ -1399,10 +1399,10 @@ namespace {
 std::vector<wc_tuning> tune_grid(const wc_opts* o) {
   std::vector<wc_tuning> g;
   if (o->mode == WC_PER_DOC) {
-    // One point: a table and a work item that fit most text. A calibration sample of a few
-    // thousand documents cannot rank others: it lasts as long as its largest document.
-    // (100,000 documents: 5.83 ms; 5.56 with the default work items, which no power of two names.)
-    g.push_back(wc_tuning{0, 4096, 0, 0, 85, 32u << 10, 0});
+    // One point, the default: a calibration sample of a few thousand documents cannot rank others, it
+    // lasts as long as its largest document. (100,000 documents: 5.5 ms; with 32 KiB work items and
+    // 4,096 LDS entries 5.8: no power of two names the default's items.)
+    g.push_back(wc_tuning{});
   } else {
     // the default: below 256 MiB the partitioned kernels, which any of the other points rules out
     // (20 MB: 79 us, the best of the others about 480)
