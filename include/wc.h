@@ -345,7 +345,7 @@ wc_status wc_batch_destroy(wc_batch* b);
  * otherwise. Requests are admitted in order. max_streams worker threads (1..16)
  * each drive one HIP stream, so admitted requests overlap on the device; small
  * single-document requests queued together are counted in one per-document launch and split
- * into one table per request. Results are global word tables in the server's memory, valid
+ * into one table per request (one by one where memory for the group is short). Results are global word tables in the server's memory, valid
  * until wc_server_release(id). Thread-safe: submit/poll/wait/merge/release may be called from
  * any host thread. */
 typedef struct wc_server wc_server;

@@ -209,13 +209,15 @@ __global__ __launch_bounds__(256) void doc_span_kernel(wc_result t, uint64_t* ou
 // Waits for memory that was not granted; false: there is none to wait for. Where only the client's
 // release can return any, the client is taken to be at it until nothing has been finished or
 // released for kReleaseGrace (a server that counts 20,000 requests a second is ahead of the thread
-// that releases them).
+// that releases them). A group does not wait for that (`grace`): its requests can still be counted
+// one by one.
 constexpr std::chrono::milliseconds kReleaseGrace(100);
-bool wait_memory(wc_server* S, std::unique_lock<std::mutex>& lk, wc::Admit a) {
+bool wait_memory(wc_server* S, std::unique_lock<std::mutex>& lk, wc::Admit a, bool grace) {
   if (a == wc::Admit::kWait) {
     S->cv_mem.wait(lk);
     return true;
   }
+  if (!grace) return false;
   const auto until = S->last_progress + kReleaseGrace;
   if (std::chrono::steady_clock::now() >= until) return false;
   S->cv_mem.wait_until(lk, until);
@@ -225,7 +227,7 @@ bool wait_memory(wc_server* S, std::unique_lock<std::mutex>& lk, wc::Admit a) {
 // A resident block for entries [e_begin, e_begin + n) of table t with nb word bytes: R's result
 // points into it, and *item is the copy that fills it.
 wc_status take_resident(wc_server* S, const wc_result& t, uint64_t e_begin, uint64_t n, uint64_t nb,
-                        uint64_t tokens, Request* R, KeepItem* item) {
+                        uint64_t tokens, Request* R, KeepItem* item, bool grace) {
   const uint32_t cb = t.count_bytes;
   const uint64_t bytes = (n + 1) * 8 + n * cb + nb + 64;
   uint8_t* mem = nullptr;
@@ -237,7 +239,7 @@ wc_status take_resident(wc_server* S, const wc_result& t, uint64_t e_begin, uint
     wc::Admit a;
     while ((a = S->adm.try_resident(bytes, &off)) != wc::Admit::kGranted && !S->stop) {
       ++S->adm.resident_waiters;
-      const bool again = wait_memory(S, lk, a);
+      const bool again = wait_memory(S, lk, a, grace);
       --S->adm.resident_waiters;
       if (!again) break;
     }
@@ -281,14 +283,14 @@ wc_status fill_residents(wc_server* S, const std::vector<KeepItem>& items, const
 // The whole table t into a resident block of R.
 wc_status keep_table(wc_server* S, hipStream_t s, const wc_result& t, Request* R) {
   std::vector<KeepItem> item(1);
-  const wc_status st = take_resident(S, t, 0, t.n_entries, t.word_bytes, t.total_tokens, R, &item[0]);
+  const wc_status st = take_resident(S, t, 0, t.n_entries, t.word_bytes, t.total_tokens, R, &item[0], true);
   return st == WC_OK ? fill_residents(S, item, {R}, s) : st;
 }
 
 // Take count memory for a request (wc::Admission::try_count): wait while other requests
 // hold count memory (they will return it); when none does, the memory is held by resident
 // tables, which only the client can release, so the request fails with WC_ENOMEM.
-uint8_t* pool_alloc_wait(wc_server* S, uint64_t bytes) {
+uint8_t* pool_alloc_wait(wc_server* S, uint64_t bytes, bool grace) {
   std::unique_lock<std::mutex> lk(S->mu);
   uint64_t off = 0;
   wc::Admit a = wc::Admit::kFail;
@@ -302,7 +304,7 @@ uint8_t* pool_alloc_wait(wc_server* S, uint64_t bytes) {
       continue;
     }
     a = S->adm.try_count(bytes, &off);
-    if (a == wc::Admit::kGranted || !wait_memory(S, lk, a)) break;
+    if (a == wc::Admit::kGranted || !wait_memory(S, lk, a, grace)) break;
   }
   S->count_queue.erase(std::find(S->count_queue.begin(), S->count_queue.end(), me));
   S->cv_mem.notify_all();
@@ -366,7 +368,8 @@ hipError_t upload(wc_server::Staging& W, uint8_t* dst, const uint8_t* src, uint6
 void run_group(wc_server* S, int idx, std::vector<std::shared_ptr<Request>>& G) {
   hipStream_t s = S->streams[idx];
   const double t0 = now_s();
-  for (auto& r : G) r->t_start = t0;
+  for (auto& r : G)
+    if (!r->t_start) r->t_start = t0;
   if (G.size() == 1 && G[0]->merge) {
     Request* R = G[0].get();
     // The inputs were pinned when the merge was submitted (a release defers freeing their
@@ -389,7 +392,7 @@ void run_group(wc_server* S, int idx, std::vector<std::shared_ptr<Request>>& G) 
     wc_plan p;
     if (st == WC_OK) st = wc_merge_plan(ins.data(), (uint32_t)ins.size(), &o, &p);
     uint8_t* ws = nullptr;
-    if (st == WC_OK && !(ws = pool_alloc_wait(S, p.workspace_bytes))) st = WC_ENOMEM;
+    if (st == WC_OK && !(ws = pool_alloc_wait(S, p.workspace_bytes, true))) st = WC_ENOMEM;
     if (st == WC_OK) {
       wc_result t;
       st = wc_merge(ins.data(), (uint32_t)ins.size(), &o, ws, p.workspace_bytes, &t, s);
@@ -433,7 +436,7 @@ void run_group(wc_server* S, int idx, std::vector<std::shared_ptr<Request>>& G) 
       st = WC_ENOMEM;
       break;
     }
-    uint8_t* mem = pool_alloc_wait(S, need);
+    uint8_t* mem = pool_alloc_wait(S, need, !packed);
     if (!mem) {
       st = WC_ENOMEM;
       break;
@@ -515,18 +518,32 @@ void run_group(wc_server* S, int idx, std::vector<std::shared_ptr<Request>>& G) 
         for (size_t i = 0; st == WC_OK && i < G.size(); ++i) {
           const uint64_t* v = W.small + 4 * i;
           KeepItem item;
-          st = take_resident(S, t, v[0], v[1], v[2], v[3], G[i].get(), &item);
+          st = take_resident(S, t, v[0], v[1], v[2], v[3], G[i].get(), &item, false);
           if (st == WC_OK) {
             items.push_back(item);
             taken.push_back(G[i].get());
           }
         }
         const wc_status filled = fill_residents(S, items, taken, s);
-        if (st == WC_OK) st = filled;
+        if (filled != WC_OK) st = filled;
       }
     }
     pool_free(S, mem);
     break;
+  }
+  if (packed && st == WC_ENOMEM) {
+    // Too little memory for the group, which each of its requests may have enough of: those without
+    // a table yet are counted one by one. (The group's count takes at least 8 MiB, for words that do
+    // not fit LDS; a request of 32 KiB alone less than 1.)
+    for (auto& r : G) {
+      if (r->resident) {
+        finish(S, r.get(), WC_OK);
+      } else {
+        std::vector<std::shared_ptr<Request>> one{r};
+        run_group(S, idx, one);
+      }
+    }
+    return;
   }
   for (auto& r : G) finish(S, r.get(), st);
 }

@@ -1187,6 +1187,26 @@ def test_server_budget_errors():
     srv.close()
 
 
+def test_server_group_under_a_tight_budget():
+    """Small requests queued together where memory for a group's count is short (it needs 8 MiB),
+    in the whole budget or beside resident tables: they are counted one by one, none fails."""
+    rng = np.random.default_rng(4)
+    words = [b"%x" % v for v in rng.integers(0, 1 << 28, 20_000)]
+    small = [b" ".join(words[i] for i in rng.integers(0, 20_000, 3000))[:24 << 10] for _ in range(40)]
+    first = b"abc def " * 25_000
+    for budget, resident in ((4 << 20, 0), (13 << 20, 9)):
+        srv = wc.Server(mem_budget=budget, max_streams=1)
+        for k in range(resident):
+            t = b" ".join(b"%08x" % (i * 9973 + k) for i in range(22_000))
+            assert srv.wait(srv.submit(t)).n_entries == 22_000
+        ids = [srv.submit(t) for t in [first] + small]  # the worker is busy when the small ones queue
+        for t, i in zip([first] + small, ids):
+            want = oracle.count(t)
+            r = srv.wait(i)
+            assert wc.result_to_dict(r) == want.as_dict() and r.total_tokens == want.total
+        srv.close()
+
+
 def test_server_waits_for_a_slow_release():
     """Resident tables of 40 requests need four times the budget: requests wait for the client,
     which releases one table every few milliseconds, instead of failing."""
