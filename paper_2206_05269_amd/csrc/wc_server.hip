@@ -3,7 +3,7 @@
 // across requests).
 //
 // Admission. The server owns one device pool of `mem_budget` bytes; the policy (count memory
-// from the low end, resident tables from the high end, when to wait and when to fail) is the
+// from the low end, resident tables from the high end, in order, when to wait and when to fail) is the
 // host-only wc::Admission of wc_admission.h. A request is admitted when the memory its count
 // needs (text, offsets, workspace) is free; until then it waits in arrival order. Results are
 // compacted into an exact-size resident block, and the count memory is returned at once.
@@ -84,9 +84,6 @@ struct wc_server {
   wc::Admission adm;
   std::mutex mu;
   std::condition_variable cv_work, cv_done, cv_mem;
-  std::chrono::steady_clock::time_point last_progress;  // a request finished or a table released
-  std::deque<uint64_t> count_queue;                     // requests waiting for count memory, in order
-  uint64_t count_ticket = 0;
   std::deque<std::shared_ptr<Request>> queue;
   std::unordered_map<uint64_t, std::shared_ptr<Request>> reqs;
   std::vector<std::thread> workers;
@@ -206,21 +203,16 @@ __global__ __launch_bounds__(256) void doc_span_kernel(wc_result t, uint64_t* ou
   }
 }
 
-// Waits for memory that was not granted; false: there is none to wait for. Where only the client's
-// release can return any, the client is taken to be at it until nothing has been finished or
-// released for kReleaseGrace (a server that counts 20,000 requests a second is ahead of the thread
-// that releases them). A group does not wait for that (`grace`): its requests can still be counted
-// one by one.
-constexpr std::chrono::milliseconds kReleaseGrace(100);
-bool wait_memory(wc_server* S, std::unique_lock<std::mutex>& lk, wc::Admit a, bool grace) {
-  if (a == wc::Admit::kWait) {
-    S->cv_mem.wait(lk);
-    return true;
-  }
-  if (!grace) return false;
-  const auto until = S->last_progress + kReleaseGrace;
-  if (std::chrono::steady_clock::now() >= until) return false;
-  S->cv_mem.wait_until(lk, until);
+uint64_t now_ns() {
+  return (uint64_t)std::chrono::duration_cast<std::chrono::nanoseconds>(Clock::now().time_since_epoch()).count();
+}
+
+// Waits as the policy's answer says; false: the answer is final.
+bool wait_memory(wc_server* S, std::unique_lock<std::mutex>& lk, wc::Admit a) {
+  if (a == wc::Admit::kWait) S->cv_mem.wait(lk);
+  else if (a == wc::Admit::kWaitRelease)
+    S->cv_mem.wait_until(lk, Clock::time_point(std::chrono::nanoseconds(S->adm.deadline())));
+  else return false;
   return true;
 }
 
@@ -232,14 +224,14 @@ wc_status take_resident(wc_server* S, const wc_result& t, uint64_t e_begin, uint
   const uint64_t bytes = (n + 1) * 8 + n * cb + nb + 64;
   uint8_t* mem = nullptr;
   {
-    // This worker holds count memory; the policy (wc::Admission::try_resident) lets it wait
-    // only while another holder that is not itself waiting here can still return memory.
+    // This worker holds count memory; the policy (wc::Admission) lets it wait only while another
+    // holder that is not itself waiting here, or the client, can still return memory.
     std::unique_lock<std::mutex> lk(S->mu);
     uint64_t off = 0;
     wc::Admit a;
-    while ((a = S->adm.try_resident(bytes, &off)) != wc::Admit::kGranted && !S->stop) {
+    while ((a = S->adm.ask_resident(bytes, now_ns(), grace, &off)) != wc::Admit::kGranted && !S->stop) {
       ++S->adm.resident_waiters;
-      const bool again = wait_memory(S, lk, a, grace);
+      const bool again = wait_memory(S, lk, a);
       --S->adm.resident_waiters;
       if (!again) break;
     }
@@ -287,26 +279,18 @@ wc_status keep_table(wc_server* S, hipStream_t s, const wc_result& t, Request* R
   return st == WC_OK ? fill_residents(S, item, {R}, s) : st;
 }
 
-// Take count memory for a request (wc::Admission::try_count): wait while other requests
-// hold count memory (they will return it); when none does, the memory is held by resident
-// tables, which only the client can release, so the request fails with WC_ENOMEM.
+// Count memory for a request or a group (wc::Admission: in order, waiting while other requests, or
+// with `grace` the client, can return memory); null when there is none.
 uint8_t* pool_alloc_wait(wc_server* S, uint64_t bytes, bool grace) {
   std::unique_lock<std::mutex> lk(S->mu);
   uint64_t off = 0;
   wc::Admit a = wc::Admit::kFail;
-  // in the order of arrival: a large request that later ones were granted memory before would wait
-  // until their tables are released, which a client that releases in order does after its own
-  const uint64_t me = ++S->count_ticket;
-  S->count_queue.push_back(me);
+  const uint64_t me = S->adm.arrive();
   while (!S->stop) {
-    if (S->count_queue.front() != me) {
-      S->cv_mem.wait(lk);
-      continue;
-    }
-    a = S->adm.try_count(bytes, &off);
-    if (a == wc::Admit::kGranted || !wait_memory(S, lk, a, grace)) break;
+    a = S->adm.ask_count(me, bytes, now_ns(), grace, &off);
+    if (!wait_memory(S, lk, a)) break;
   }
-  S->count_queue.erase(std::find(S->count_queue.begin(), S->count_queue.end(), me));
+  S->adm.leave(me);
   S->cv_mem.notify_all();
   return a == wc::Admit::kGranted ? S->pool_mem + off : nullptr;
 }
@@ -321,7 +305,7 @@ void pool_free(wc_server* S, uint8_t* p) {
 void free_resident_locked(wc_server* S, Request* R) {
   if (R->resident) S->adm.free_resident((uint64_t)(R->resident - S->pool_mem));
   R->resident = nullptr;
-  S->last_progress = std::chrono::steady_clock::now();
+  S->adm.progress(now_ns());
   S->cv_mem.notify_all();
 }
 
@@ -337,7 +321,7 @@ void finish(wc_server* S, Request* R, wc_status st) {
   std::lock_guard<std::mutex> lk(S->mu);
   R->status = st;
   R->state = 2;
-  if (st == WC_OK) S->last_progress = std::chrono::steady_clock::now();
+  if (st == WC_OK) S->adm.progress(now_ns());
   R->t_done = now_s();
   R->text.clear();
   R->text.shrink_to_fit();

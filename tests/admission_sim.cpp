@@ -147,7 +147,11 @@ struct Worker {
   Req* r = nullptr;
   uint64_t count_off = 0;
   double until = 0;
+  uint64_t ticket = 0;  // (ordered) its place among those that wait for count memory
+  bool release = false; // (ordered) its answer was kWaitRelease
 };
+
+static uint64_t fake_ns(double t) { return 1000000000ull + (uint64_t)(t * 1e9 + 0.5); }
 
 struct Trace {
   std::vector<std::string> lines;
@@ -158,8 +162,10 @@ struct Trace {
   }
 };
 
+// ordered: with the server's order and grace (ask_count, ask_resident), else the rules alone.
 static Trace simulate(std::vector<Req>& reqs, uint64_t budget, int n_workers, int* fails,
-                      bool check_rules) {
+                      bool check_rules, bool ordered = false) {
+  uint64_t last_out = 0;  // ticket that was last granted memory or failed
   Admission a;
   a.init(budget);
   std::vector<Worker> W(n_workers);
@@ -185,6 +191,7 @@ static Trace simulate(std::vector<Req>& reqs, uint64_t budget, int n_workers, in
       for (size_t i = 0; i < releases.size();) {
         if (releases[i].t <= now) {
           a.free_resident(releases[i].r->res_off);
+          a.progress(fake_ns(now));
           tr.add(now, "release", releases[i].r->id);
           releases.erase(releases.begin() + i);
           changed = true;
@@ -197,12 +204,21 @@ static Trace simulate(std::vector<Req>& reqs, uint64_t budget, int n_workers, in
           w.r = queue.front();
           queue.pop_front();
           w.state = 1;
+          if (ordered) w.ticket = a.arrive();
           changed = true;
         }
+        w.release = false;
         if (w.state == 1) {
           const uint64_t largest = a.pool.largest_free();
           const uint32_t holders = a.holders;
-          Admit d = a.try_count(w.r->count_bytes, &w.count_off);
+          Admit d = ordered ? a.ask_count(w.ticket, w.r->count_bytes, fake_ns(now), true, &w.count_off)
+                            : a.try_count(w.r->count_bytes, &w.count_off);
+          w.release = d == Admit::kWaitRelease;
+          if (ordered && (d == Admit::kGranted || d == Admit::kFail)) {
+            CHECK(w.ticket == last_out + 1);  // nobody overtakes
+            last_out = w.ticket;
+            a.leave(w.ticket);
+          }
           if (d == Admit::kGranted) {
             w.state = 2;
             w.until = now + w.r->duration;
@@ -211,6 +227,7 @@ static Trace simulate(std::vector<Req>& reqs, uint64_t budget, int n_workers, in
           } else if (d == Admit::kFail) {
             // the rule: fail only when nothing holds count memory and no block fits
             if (check_rules) CHECK(holders == 0 && largest < TwoEndedRound(w.r->count_bytes));
+            if (ordered) CHECK(fake_ns(now) >= a.deadline());
             w.r->status = -2;
             ++*fails;
             tr.add(now, "enomem", w.r->id);
@@ -225,9 +242,12 @@ static Trace simulate(std::vector<Req>& reqs, uint64_t budget, int n_workers, in
         if (w.state == 3) {
           const bool was_waiting = w.until < 0;
           if (was_waiting) --a.resident_waiters;
-          Admit d = a.try_resident(w.r->resident_bytes, &w.r->res_off);
+          Admit d = ordered ? a.ask_resident(w.r->resident_bytes, fake_ns(now), true, &w.r->res_off)
+                            : a.try_resident(w.r->resident_bytes, &w.r->res_off);
+          w.release = d == Admit::kWaitRelease;
           if (d == Admit::kGranted) {
             a.free_count(w.count_off);
+            a.progress(fake_ns(now));
             w.r->status = 1;
             w.r->done = now;
             tr.add(now, "done", w.r->id);
@@ -236,6 +256,7 @@ static Trace simulate(std::vector<Req>& reqs, uint64_t budget, int n_workers, in
             changed = true;
           } else if (d == Admit::kFail) {
             if (check_rules) CHECK(a.holders <= a.resident_waiters + 1);
+            if (ordered) CHECK(fake_ns(now) >= a.deadline());
             a.free_count(w.count_off);
             w.r->status = -2;
             ++*fails;
@@ -255,6 +276,7 @@ static Trace simulate(std::vector<Req>& reqs, uint64_t budget, int n_workers, in
     for (auto& r : releases) t = std::min(t, r.t);
     for (auto& w : W)
       if (w.state == 2) t = std::min(t, w.until);
+      else if (w.release) t = std::min(t, std::max(now, ((double)a.deadline() - 1e9) / 1e9) + 1e-9);
     if (t == 1e300) break;
     now = t;
   }
@@ -328,12 +350,105 @@ static void scenario_executor() {
          total_fails);
 }
 
+// A large request at the head is not overtaken by a small one that would fit; when it leaves, the
+// next is asked.
+static void scenario_order() {
+  Admission a;
+  a.init(16 * MiB);
+  uint64_t r0, x, y;
+  const uint64_t now = 5000000000ull;
+  a.progress(now);
+  const uint64_t first = a.arrive();
+  CHECK(a.ask_count(first, 10 * MiB, now, true, &r0) == Admit::kGranted);
+  a.leave(first);
+  const uint64_t large = a.arrive(), small = a.arrive();
+  CHECK(a.ask_count(small, 1 * MiB, now, true, &y) == Admit::kWait);  // would fit
+  CHECK(a.ask_count(large, 12 * MiB, now, true, &x) == Admit::kWait);
+  a.free_count(r0);
+  CHECK(a.ask_count(small, 1 * MiB, now, true, &y) == Admit::kWait);
+  CHECK(a.ask_count(large, 12 * MiB, now, true, &x) == Admit::kGranted);
+  a.leave(large);
+  CHECK(a.ask_count(small, 1 * MiB, now, true, &y) == Admit::kGranted);
+  a.leave(small);
+  CHECK(a.order.empty());
+  a.free_count(x);
+  a.free_count(y);
+  // one that gives up in the middle of the queue
+  const uint64_t p = a.arrive(), q = a.arrive(), r = a.arrive();
+  a.leave(q);
+  CHECK(a.ask_count(r, 1 * MiB, now, true, &y) == Admit::kWait);
+  a.leave(p);
+  CHECK(a.ask_count(r, 1 * MiB, now, true, &y) == Admit::kGranted);
+  printf("ok order\n");
+}
+
+// Only the client can return memory: the request waits for it until nothing has been finished or
+// released for the grace; a group does not wait.
+static void scenario_grace() {
+  Admission a;
+  a.init(16 * MiB);
+  uint64_t r[2], x, now = 7000000000ull;
+  uint64_t c;
+  CHECK(a.try_count(1 * MiB, &c) == Admit::kGranted);
+  CHECK(a.try_resident(7 * MiB, &r[0]) == Admit::kGranted);
+  CHECK(a.try_resident(7 * MiB, &r[1]) == Admit::kGranted);
+  a.free_count(c);
+  a.progress(now);
+  const uint64_t me = a.arrive();
+  CHECK(a.ask_count(me, 4 * MiB, now, true, &x) == Admit::kWaitRelease);
+  CHECK(a.deadline() == now + wc::kReleaseGraceNs);
+  CHECK(a.ask_count(me, 4 * MiB, now, false, &x) == Admit::kFail);  // a group
+  CHECK(a.ask_count(me, 4 * MiB, a.deadline() - 1, true, &x) == Admit::kWaitRelease);
+  a.progress(now + 1000);  // something finished: the grace begins anew
+  CHECK(a.ask_count(me, 4 * MiB, now + wc::kReleaseGraceNs, true, &x) == Admit::kWaitRelease);
+  CHECK(a.ask_count(me, 4 * MiB, a.deadline(), true, &x) == Admit::kFail);
+  a.free_resident(r[1]);
+  CHECK(a.ask_count(me, 4 * MiB, a.deadline(), true, &x) == Admit::kGranted);
+  a.leave(me);
+  // the same for resident memory, asked for by the one holder
+  CHECK(a.ask_resident(8 * MiB, a.deadline() - 1, true, &c) == Admit::kWaitRelease);
+  CHECK(a.ask_resident(8 * MiB, a.deadline() - 1, false, &c) == Admit::kFail);
+  CHECK(a.ask_resident(8 * MiB, a.deadline(), true, &c) == Admit::kFail);
+  printf("ok grace\n");
+}
+
+// The executor with order and grace: grants and failures come in ticket order, a failure only when
+// the grace has passed, and requests whose tables are released within it never fail.
+static void scenario_executor_ordered() {
+  const uint64_t budget = 64 * MiB;
+  int total_fails = 0;
+  for (uint64_t seed = 1; seed <= 6; ++seed) {
+    for (int workers : {1, 4, 8}) {
+      auto r1 = workload(seed, 400, budget);
+      auto r2 = workload(seed, 400, budget);
+      int f1, f2;
+      Trace t1 = simulate(r1, budget, workers, &f1, true, true);
+      Trace t2 = simulate(r2, budget, workers, &f2, true, true);
+      CHECK(t1.lines == t2.lines);
+      total_fails += f1;
+      auto r3 = workload(seed, 400, budget);  // the client is slow, but within the grace
+      for (auto& q : r3) {
+        q.release_after = 0.05;
+        q.resident_bytes = std::min<uint64_t>(q.resident_bytes * 4, budget / 8);
+      }
+      int f3;
+      simulate(r3, budget, workers, &f3, true, true);
+      CHECK(f3 == 0);
+    }
+  }
+  CHECK(total_fails > 0);
+  printf("ok executor_ordered: %d requests failed where unreleased tables fill the pool\n", total_fails);
+}
+
 int main() {
   scenario_fragmentation();
   scenario_resident_full();
   scenario_resident_waiters();
   scenario_merge_pins();
   scenario_executor();
+  scenario_order();
+  scenario_grace();
+  scenario_executor_ordered();
   if (failures) {
     printf("%d checks failed\n", failures);
     return 1;
