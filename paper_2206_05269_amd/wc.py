@@ -283,6 +283,20 @@ def count_plan(corpus_len: int, n_docs: int, *, count_bytes=8, per_doc=False, ta
     return p
 
 
+def _per_doc_room(n: int, n_docs: int, debug_flags: int, utf8: bool) -> int:
+    """Word bytes to reserve for the tables of n_docs documents of n bytes together; 0: the
+    library's default, a quarter of the text, or all of it where one (document, word) table is
+    counted (documents above 64 KiB on average, UTF-8).
+
+    The quarter holds the words of documents of some 30 KiB and more; smaller ones repeat their words
+    less, and running out costs a second count (2,000 documents of 10 KB: 516 us, 260 us when the
+    first count fits), so the first call takes room for any text up to 64 MiB, half the text above."""
+    mean = n / max(n_docs, 1)
+    if utf8 or debug_flags & WC_DEBUG_DIRECT or (mean > 65536 and not debug_flags & WC_DEBUG_DOCS):
+        return 0
+    return max(min(n, 64 << 20), n // 2)
+
+
 def count(corpus: torch.Tensor, offsets: Optional[torch.Tensor] = None, *, count_bytes: int = 8,
           per_doc: bool = False, table_slots: int = 0, tuning: Optional[Tuning] = None,
           debug_flags: int = 0, debug_hash_bits: int = 0, word_bytes_cap: int = 0,
@@ -305,14 +319,9 @@ def count(corpus: torch.Tensor, offsets: Optional[torch.Tensor] = None, *, count
     n_docs = offsets.numel() - 1
     if n_docs < 0:
         raise ValueError("offsets must hold at least one value")
-    # Per-document output: the library's default room (a quarter of the text) holds the words of
-    # documents of some 30 KiB and more; smaller ones repeat their words less, and running out
-    # costs a second count (2,000 documents of 10 KB: 516 us, 260 us when the first count fits).
-    # Memory that is only reserved costs nothing, so the first call takes room for any text up to
-    # 64 MiB, half the text above (the default where the caller's workspace or the GPU has no more).
     roomy = per_doc and not word_bytes_cap and workspace is None and regrow
     if roomy:
-        word_bytes_cap = max(min(n, 64 << 20), n // 2)
+        word_bytes_cap = _per_doc_room(n, n_docs, debug_flags, utf8)
     while True:
         o = _opts(count_bytes, per_doc, table_slots, tuning, debug_flags, debug_hash_bits,
                   word_bytes_cap, debug_count_bias, utf8)

@@ -1344,6 +1344,35 @@ def test_per_doc_groups_and_spilled_words(kind, tuning):
         check(text, off, per_doc=True, debug_flags=wc.WC_DEBUG_DOCS, table_slots=1 << 12, **kw)
 
 
+class _CountedLib:
+    """The library with its wc_count calls counted."""
+
+    def __init__(self, lib):
+        self._lib, self.calls = lib, 0
+
+    def __getattr__(self, name):
+        return getattr(self._lib, name)
+
+    def wc_count(self, *args):
+        self.calls += 1
+        return self._lib.wc_count(*args)
+
+
+def test_per_doc_utf8_room(monkeypatch):
+    """The (document, word) table of UTF-8 text keeps the library's default room (all of the text):
+    documents of different words, which fill five sixths of it, are counted once."""
+    docs = 1_400_000
+    i = np.arange(docs * 10)
+    w = np.full((docs * 10, 6), 0x20, np.uint8)
+    for j in range(5):
+        w[:, j] = np.frombuffer(b"abcdefghijklmnopqrstuvwxyz012345", np.uint8)[(i >> (5 * j)) & 31]
+    lib = _CountedLib(wc.lib())
+    monkeypatch.setattr(wc, "_lib", lib)
+    got = gpu_count(w.reshape(-1), np.arange(docs + 1) * 60, per_doc=True, count_bytes=4, utf8=True)
+    assert lib.calls == 1 and got.n_entries == got.total_tokens == docs * 10
+    assert got.res.word_bytes == docs * 50 and (got.counts() == 1).all()
+
+
 @pytest.mark.parametrize("chunk", [16 << 10, 32 << 10, 256 << 10, 1 << 20])
 def test_per_doc_chunk_sizes(chunk):
     c = synth.generate("batched-100k", scale=0.002)
