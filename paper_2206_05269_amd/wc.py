@@ -288,13 +288,17 @@ def _per_doc_room(n: int, n_docs: int, debug_flags: int, utf8: bool) -> int:
     library's default, a quarter of the text, or all of it where one (document, word) table is
     counted (documents above 64 KiB on average, UTF-8).
 
-    The quarter holds the words of documents of some 30 KiB and more; smaller ones repeat their words
-    less, and running out costs a second count (2,000 documents of 10 KB: 516 us, 260 us when the
-    first count fits), so the first call takes room for any text up to 64 MiB, half the text above."""
+    Running out costs a second count (2,000 documents of 10 KB: 516 us, 260 us when the first
+    fits), and the quarter holds the words of documents of some 60 KiB: of 32,000 / 16,000 / 8,000 /
+    4,000 / 2,000 / 500 bytes on average (lognormal, one million words, Zipf 1.0) they take 0.48 /
+    0.52 / 0.56 / 0.60 / 0.65 / 0.73 of the text, of fifty thousand words 0.31 to 0.63. A tenth more
+    than the former is reserved up to 64 MiB, half the text at most above. The workspace is kept
+    with the result: it is about eight times the word bytes reserved, and twice the text."""
     mean = n / max(n_docs, 1)
     if utf8 or debug_flags & WC_DEBUG_DIRECT or (mean > 65536 and not debug_flags & WC_DEBUG_DOCS):
         return 0
-    return max(min(n, 64 << 20), n // 2)
+    share = 14 if mean < 1000 else 12 if mean < 4000 else 11 if mean < 12_000 else 10 if mean < 24_000 else 9
+    return max(n * min(share, 8) // 16, min(n, 64 << 20) * share // 16, 4096)
 
 
 def count(corpus: torch.Tensor, offsets: Optional[torch.Tensor] = None, *, count_bytes: int = 8,

@@ -1358,6 +1358,24 @@ class _CountedLib:
         return self._lib.wc_count(*args)
 
 
+@pytest.mark.parametrize("mean", [500, 3000, 8000, 20_000, 50_000])
+def test_per_doc_room(mean, monkeypatch):
+    """Per-document tables are counted once, and what their result keeps is bounded: eight times
+    the word bytes reserved (as documents of this size fill it, and a tenth), twice the text."""
+    n, rng = 6_000_000, np.random.default_rng(mean)
+    vocab = [bytes(rng.integers(97, 123, rng.integers(1, 13), dtype=np.uint8)) for _ in range(50_000)]
+    p = np.arange(1, 50_001) ** -1.05
+    text = b" ".join(vocab[i] for i in rng.choice(50_000, n // 4, p=p / p.sum()))[:n]
+    off = np.append(np.arange(0, n, mean), n)
+    lib = _CountedLib(wc.lib())
+    monkeypatch.setattr(wc, "_lib", lib)
+    got = gpu_count(text, off, per_doc=True, count_bytes=4)
+    assert lib.calls == 1 and got.total_tokens == len(text.split()) + int(
+        sum(text[o - 1:o] != b" " and text[o:o + 1] != b" " for o in off[1:-1]))
+    most = {500: 14, 3000: 12, 8000: 11, 20_000: 10, 50_000: 9}[mean] / 16
+    assert got.workspace.numel() < (8 * most + 2.1) * n + (10 << 20) + 40 * len(off)
+
+
 def test_per_doc_utf8_room(monkeypatch):
     """The (document, word) table of UTF-8 text keeps the library's default room (all of the text):
     documents of different words, which fill five sixths of it, are counted once."""
