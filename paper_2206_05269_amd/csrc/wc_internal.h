@@ -246,6 +246,8 @@ struct MergeBatch {
   uint32_t n;
 };
 // launch(batch, workgroups) for the inputs, kMergeInputs at a time, `span` entries per workgroup
+// (of at most 1,024 threads; a launch has fewer than 2^32 threads, so many large inputs take several)
+constexpr uint64_t kMergeBlocks = 0xffffffffull / 1024;
 template <class Launch>
 hipError_t for_merge_batches(const MergeInput* in, uint32_t k, uint32_t span, Launch launch) {
   for (uint32_t i = 0; i < k;) {
@@ -254,7 +256,7 @@ hipError_t for_merge_batches(const MergeInput* in, uint32_t k, uint32_t span, La
     for (M.n = 0; i < k && M.n < kMergeInputs; ++i) {
       const uint64_t nb = (in[i].n + span - 1) / span;
       if (nb == 0) continue;
-      if (blocks + nb > 0x7fffffffull && M.n) break;
+      if (blocks + nb > kMergeBlocks && M.n) break;
       M.in[M.n] = in[i];
       M.first_block[M.n++] = (uint32_t)blocks;
       blocks += nb;
