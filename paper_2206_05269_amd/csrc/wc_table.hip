@@ -553,13 +553,14 @@ __global__ __launch_bounds__(1024) void topk_sort_kernel(TopkParams P, const uin
 
 // For k above half of kRankSpan: pairs of sorted runs merged, each id to the place that its own
 // position and the number of better ids of the other run give (a binary search); the best k stay.
+// (Pairs in x: the other dimensions of a grid end at 65,535.)
 __global__ __launch_bounds__(256) void topk_merge_kernel(TopkParams P, const uint32_t* in,
                                                          const uint32_t* in_len, uint32_t in_runs,
                                                          uint32_t run, uint32_t* out,
                                                          uint32_t* out_len, uint32_t out_run) {
-  const uint32_t c = blockIdx.z, pair = blockIdx.y, out_runs = gridDim.y;
+  const uint32_t c = blockIdx.z, pair = blockIdx.x, out_runs = gridDim.x;
   if (P.hdr->flags) return;
-  const uint32_t at = blockIdx.x * 256 + threadIdx.x;  // position among both runs
+  const uint32_t at = blockIdx.y * 256 + threadIdx.x;  // position among both runs
   const uint32_t side = at / run, i = at - side * run;
   if (side > 1) return;
   const uint64_t base = (uint64_t)c * in_runs;
@@ -672,7 +673,7 @@ hipError_t launch_topk(const TopkParams& P, uint64_t n, hipStream_t s) {
     } else {
       const uint32_t next = (runs + 1) / 2;
       const uint32_t longer = 2 * run < P.k ? 2 * run : P.k;
-      hipLaunchKernelGGL(topk_merge_kernel, dim3((2 * run + 255) / 256, next, P.C), dim3(256), 0,
+      hipLaunchKernelGGL(topk_merge_kernel, dim3(next, (2 * run + 255) / 256, P.C), dim3(256), 0,
                          s, P, P.lists[src], P.list_len[src], runs, run, P.lists[dst],
                          P.list_len[dst], longer);
       runs = next;
