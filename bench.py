@@ -586,7 +586,7 @@ def batched_docs_per_s(steps: int, warmup: int, plain_docs: int):
     torch.cuda.synchronize()
     dt_b = (time.perf_counter() - t0) / steps
     entries = r.n_entries
-    recounted = r.stats["docs_recounted"]
+    spilled = r.stats["docs_spilled"]
     b.close()
     # plain: one launch (wc_count, global table of that document) per document
     off = c.offsets.cpu().numpy()
@@ -604,7 +604,7 @@ def batched_docs_per_s(steps: int, warmup: int, plain_docs: int):
     torch.cuda.synchronize()
     dt_p = (time.perf_counter() - t0) / m
     res = {"workload": name, "docs": n_docs, "bytes": B, "tokens": c.n_tokens,
-           "doc_word_pairs": entries, "docs_recounted": recounted,
+           "doc_word_pairs": entries, "docs_spilled": spilled,
            "batched_docs_per_s": round(n_docs / dt_b, 1), "batched_ms": round(dt_b * 1e3, 3),
            "batched_GBps": round(B / dt_b / 1e9, 2),
            "plain_docs_per_s": round(1.0 / dt_p, 1), "plain_sample_docs": m,

@@ -396,8 +396,8 @@ wc_status wc_server_destroy(wc_server* s);
  * calibration sample of a few thousand documents cannot rank against others; global mode: the
  * default and LDS entries x flush load x flush policy) with HIP events on `stream`, and return
  * the fastest in *best (its time per call in *best_ms). The workspace must hold
- * wc_autotune_plan() bytes. The sample's counts are not returned. Output and private-table
- * sizes come from opts (word_bytes_cap, table_slots) as in wc_count; a grid point that runs
+ * wc_autotune_plan() bytes. The sample's counts are not returned. The sizes of the output and of
+ * the room for words that do not fit LDS come from opts (word_bytes_cap, table_slots) as in wc_count; a grid point that runs
  * out of that room is skipped, and WC_ENOMEM is returned when no point fits. */
 wc_status wc_autotune_plan(uint64_t len, uint64_t n_docs, const wc_opts* opts,
                            uint64_t* workspace_bytes);

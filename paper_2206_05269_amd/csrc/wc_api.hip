@@ -243,7 +243,7 @@ int64_t base_offset(const uint8_t* corpus) {
   return -(int64_t)((uintptr_t)corpus & 15);
 }
 
-// Per-document count (document-centric kernel): outputs and private tables of large documents.
+// Per-document count (document-centric kernel): outputs, work items and the room for spilled words.
 struct DocLayout {
   uint64_t cap_e, cap_b, arena_slots;
   Header* hdr;

@@ -22,7 +22,7 @@ WC_OK, WC_EINVAL, WC_ENOMEM, WC_ETABLEFULL, WC_EOVERFLOW, WC_EDEVICE, WC_EAGAIN 
     0, -1, -2, -3, -4, -5, -6
 WC_GLOBAL, WC_PER_DOC = 0, 1
 WC_FLUSH_ALL, WC_FLUSH_BYPASS = 0, 1
-WC_DIRECT_NEVER = 0xFFFFFFFF  # wc_tuning.direct_kib: no document skips the first count
+WC_DIRECT_NEVER = 0xFFFFFFFF  # wc_tuning.direct_kib: no size limit
 WC_DEBUG_TIME, WC_DEBUG_NO_LDS, WC_DEBUG_DIRECT, WC_DEBUG_SPILL, WC_DEBUG_DOCS = 1, 2, 4, 8, 16
 WC_FOLD_SQRT, WC_FOLD_ALT_HARMONIC = 0, 1
 WC_TOKENIZE_ASCII, WC_TOKENIZE_UTF8 = 0, 1
@@ -201,13 +201,15 @@ class Table:
 
     @property
     def stats(self) -> dict:
-        """Per-call statistics: the two-pass global count's spilled records, records sent
-        straight to the global table, dictionary words and pass-2 overflow; the
-        document-centric kernel's documents counted by its second pass (overflowed, or over the
-        size limit; zero where a path has none)."""
+        """Per-call statistics, zero where a path has none. Two-pass global count: spilled records,
+        records sent straight to the global table, dictionary words and pass-2 overflow.
+        Partitioned count and merge: arena_direct is 1 when their room ran out and the text or the
+        entries were counted again into one table. Document-centric kernel: docs_spilled, the
+        documents over the size limit and those of groups whose words did not fit LDS
+        (docs_recounted is its former name: no document is counted twice any more)."""
         s = self.res.stats
         return {"spilled": int(s[0]), "arena_direct": int(s[1]), "dict_words": int(s[2]),
-                "docs_recounted": int(s[3]), "reduce_overflow": int(s[4])}
+                "docs_spilled": int(s[3]), "docs_recounted": int(s[3]), "reduce_overflow": int(s[4])}
 
     def word_offsets(self) -> torch.Tensor:
         return self._view(self.res.d_word_offsets, 8 * (self.n_entries + 1), torch.int64)
@@ -352,7 +354,7 @@ def count(corpus: torch.Tensor, offsets: Optional[torch.Tensor] = None, *, count
             table_slots = 2 * int(p.table_slots)
             continue
         if st == WC_ENOMEM and regrow and per_doc:
-            # per-document outputs or private tables ran out: grow what was short
+            # per-document outputs, or the room for spilled words, ran out: grow what was short
             need_b = max(int(res.word_bytes), 3 * int(res.n_entries))
             grew = False
             if need_b > p.word_bytes_cap or int(res.n_entries) > p.max_entries:
@@ -638,8 +640,8 @@ def output_sizes(corpus: torch.Tensor, offsets: torch.Tensor, *, per_doc: bool =
                  count_bytes: int = 4, stream=None) -> dict:
     """Output sizes (word_bytes_cap, table_slots) for fixed-capacity calls (Batch, autotune)
     on corpora like this one, from one count of it: the output words do not depend on the
-    launch tuning and get a quarter of headroom; the private-table arena does, and gets twice
-    what this count used (rounded up to a power of two)."""
+    launch tuning and get a quarter of headroom; the room for words that do not fit LDS does, and
+    gets twice what this count had or used (rounded up to a power of two)."""
     t = count(corpus, offsets, count_bytes=count_bytes, per_doc=per_doc, stream=stream)
     wb = int(t.res.word_bytes)
     slots = 1 << (2 * int(t.res.table_slots) - 1).bit_length() if per_doc else 0
@@ -650,7 +652,7 @@ class Batch:
     """Per-document counting of whole corpora with one captured HIP graph (see wc_batch_*).
 
     Output capacity is fixed at creation: word_bytes_cap and table_slots (0 = defaults sized
-    for natural text) bound the words and private tables of every run; a run beyond them
+    for natural text) bound the words of every run, and those that do not fit LDS; a run beyond them
     raises WcError(WC_ENOMEM). output_sizes() derives both from a representative corpus."""
 
     def __init__(self, max_docs: int, max_bytes: int, *, count_bytes: int = 4,

@@ -7,6 +7,7 @@ every tuning point, and the synthetic workloads (full size where the oracle's an
 from the generator's rank histogram).
 """
 import collections
+import ctypes
 import itertools
 import json
 import os
@@ -389,6 +390,9 @@ def test_per_doc_relief_and_private_tables(lds):
 
 
 def test_per_doc_long_words_and_collisions():
+    """(debug_hash_bits concerns the keys of tables in device memory, which the document-centric
+    kernel has none of: it counts the same with it. For words that collide in its table see
+    test_words_of_one_place_hash.)"""
     w = b"Z" * 40
     docs = [w + b" " + w.lower(), b"a" * 17 + b" x", b"", w + b" y " * 3000]
     text, off = join_docs(docs)
@@ -399,11 +403,9 @@ def test_per_doc_long_words_and_collisions():
 
 @pytest.mark.parametrize("bits,direct", [(0, wc.WC_DIRECT_NEVER), (3, wc.WC_DIRECT_NEVER), (3, 0)])
 def test_per_doc_private_table_collisions(bits, direct):
-    """A document with more distinct words (9,000) than the second pass's LDS table holds: the
-    rest go to its private table in device memory, claimed with a compare-and-swap first; with
-    debug_hash_bits=3 every private key is one of eight values, so inserts probe far and tell
-    words apart by their bytes. The document reaches the second pass by overflowing the first
-    (WC_DIRECT_NEVER) or by its size (default limit)."""
+    """A document with more distinct words (9,000) than the LDS table holds: the rest are spilled to
+    device memory and counted in further tables. It is reported as spilled, and with the default
+    limit as a large document too; debug_hash_bits changes nothing in this kernel."""
     words = [b"w%05d" % i for i in range(9000)]
     rng = np.random.default_rng(5)
     doc = b" ".join(words + [words[i] for i in rng.integers(0, 9000, 6000)])
@@ -414,6 +416,50 @@ def test_per_doc_private_table_collisions(bits, direct):
     got = wc.count(t, o, per_doc=True, count_bytes=4, debug_hash_bits=bits,
                    debug_flags=wc.WC_DEBUG_DOCS, tuning=tu)
     assert got.stats["docs_recounted"] >= 1
+
+
+def _words_of_one_place_hash(n):
+    """n words of 16 bytes with the same 32-bit hash in the LDS tables (wc_stripe.h: red_hash folds the
+    packed dwords a, b, c, d to (a ^ rotr(b, 11)) + (c ^ rotr(d, 23))): random b, c, d, and a
+    solved for, kept where it is letters and digits."""
+    chars = np.frombuffer(b"abcdefghijklmnopqrstuvwxyz0123456789", np.uint8)
+    rng = np.random.default_rng(16)
+    words, m32 = [], np.uint64(0xFFFFFFFF)
+    while len(words) < n:
+        tail = chars[rng.integers(0, 36, (1 << 20, 12))]
+        b, c, d = (np.ascontiguousarray(tail[:, 4 * j:4 * j + 4]).view("<u4")[:, 0].astype(np.uint64)
+                   for j in range(3))
+
+        def rotr(v, k):
+            return ((v >> np.uint64(k)) | (v << np.uint64(32 - k))) & m32
+
+        a = ((np.uint64(0x9ABCDEF0) - (c ^ rotr(d, 23))) & m32) ^ rotr(b, 11)
+        a = a.astype("<u4").view(np.uint8).reshape(-1, 4)
+        ok = np.isin(a, chars).all(axis=1)
+        words += [x.tobytes() + y.tobytes() for x, y in zip(a[ok], tail[ok])]
+    return words[:n]
+
+
+@pytest.mark.parametrize("n", [5, 600, 6000])
+def test_words_of_one_place_hash(n):
+    """Words that share their whole hash in the LDS tables (home group and tag): only the keys tell
+    them apart, and 6,000 are more than any table holds, also after a split by hash. Through the
+    one workgroup, the map and the reduce, the per-document kernel (alone and among others) and
+    the merge."""
+    words = _words_of_one_place_hash(n)
+    assert len(set(words)) == n
+    rng = np.random.default_rng(n)
+    text = b" ".join(words + [words[i] for i in rng.integers(0, n, n)])
+    check(text)
+    tab = check(text + b" a b c" * 9000)
+    docs = [text, b"x y", text[:5000], b"", text[17:]]
+    t, off = join_docs(docs)
+    per = check(t, off, per_doc=True, debug_flags=wc.WC_DEBUG_DOCS)
+    assert wc.merge([per]).as_dict() == oracle.count(t, off).as_dict()
+    two = collections.Counter(text.split())
+    two.update(text.split())
+    two.update({b"a": 9000, b"b": 9000, b"c": 9000})
+    assert wc.merge([tab, gpu_count(text)]).as_dict() == dict(two)
 
 
 def test_per_doc_kernel_choice():
@@ -1177,6 +1223,27 @@ def test_server_packed_group_edges(where):
     srv.close()
 
 
+def test_server_utf8_requests():
+    """Small UTF-8 requests among ASCII ones: a group holds requests of one tokeniser, and each
+    request's table is the oracle's under its own."""
+    word = "Grüße naïve 日本語 Привет ascii x\u2019y 5×3 ".encode()
+    texts = [word * (1 + 7 * i % 90) + b"w%d " % i + word[:i % 23] for i in range(60)] + [word * 2000]
+    srv = wc.Server(mem_budget=256 << 20, max_streams=1)
+    reqs = []
+    for i, t in enumerate([b"busy " * 200_000] + texts):
+        utf8 = i % 5 != 0
+        o = wc._opts(8, False, 0, None, 0, 0, 0, utf8=utf8)
+        rid, buf, off = ctypes.c_uint64(), np.frombuffer(t, np.uint8), np.array([0, len(t)], np.uint64)
+        assert wc.lib().wc_server_submit(srv._h, buf.ctypes.data_as(ctypes.c_void_p), len(t),
+                                         off.ctypes.data_as(ctypes.c_void_p), 1, 0, ctypes.byref(o),
+                                         ctypes.byref(rid)) == wc.WC_OK
+        reqs.append((rid.value, t, utf8))
+    for rid, t, utf8 in reqs:
+        r, want = srv.wait(rid), oracle.count(t, utf8=utf8)
+        assert wc.result_to_dict(r) == want.as_dict() and r.total_tokens == want.total, (t[:40], utf8)
+    srv.close()
+
+
 def test_server_budget_errors():
     srv = wc.Server(mem_budget=4 << 20, max_streams=1)
     with pytest.raises(wc.WcError) as e:
@@ -1287,8 +1354,8 @@ def test_autotune_global_includes_the_default(tmp_path):
 
 @pytest.mark.parametrize("direct_kib", [1, 32, wc.WC_DIRECT_NEVER])
 def test_per_doc_direct_second_pass(direct_kib):
-    """Documents longer than a 16 KiB work item and than direct_kib KiB skip the first count:
-    counted once by the second pass (tokens included), the tables must not change."""
+    """Documents longer than a 16 KiB work item and than direct_kib KiB are reported (there is no
+    second pass any more, all documents are counted the same way): the tables must not change."""
     c = synth.generate("batched-100k", scale=0.002)
     text, offs = c.text.numpy(), c.offsets.numpy()
     tu = wc.make_tuning(chunk_bytes=16 << 10, lds_entries=4096, lds_load_pct=85,
