@@ -601,8 +601,7 @@ __global__ __launch_bounds__(kBlk) void doc_kernel(DocParams) {
     }
     o.docs[e] = d;
     if (is_long_key(k)) {
-      const uint8_t* src = long_ptr(k);
-      for (uint32_t q = 0; q < k.z; ++q) o.words[b + q] = (uint8_t)fold_byte(src[q]);
+      store_long(o.words + b, long_ptr(k), k.z);
     } else {
       store_word(o.words + b, (uint64_t)k.x | ((uint64_t)k.y << 32), (uint64_t)k.z | ((uint64_t)k.w << 32),
                  (uint32_t)key_len(k));

@@ -126,8 +126,7 @@ WC_DEV void export_table(const PartParams& P, const PartTable<C>& T, bool last, 
     }
     if (b + len <= P.word_cap) {
       if (is_long_key(k)) {
-        const uint8_t* src = long_ptr(k);
-        for (uint64_t q = 0; q < len; ++q) P.words[b + q] = (uint8_t)fold_byte(src[q]);
+        store_long(P.words + b, long_ptr(k), len);
       } else {
         store_word(P.words + b, (uint64_t)k.x | ((uint64_t)k.y << 32),
                    (uint64_t)k.z | ((uint64_t)k.w << 32), (uint32_t)len);

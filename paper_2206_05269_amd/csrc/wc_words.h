@@ -449,6 +449,20 @@ WC_DEV void store_word(uint8_t* dst, uint64_t lo, uint64_t hi, uint32_t n) {
   }
 }
 
+// The folded bytes of a word of n >= 16 bytes, 16 at a time, the last 16 overlapping those before.
+// (Byte by byte, a read at a time in flight, a partition's 2,900 words of 38 bytes took 100 us.)
+WC_DEV void store_long(uint8_t* dst, const uint8_t* src, uint64_t n) {
+  for (uint64_t i = 0;;) {
+    uint32_t d[4], f;
+    __builtin_memcpy(d, src + i, 16);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) d[j] = fold_classify4(d[j], &f);
+    __builtin_memcpy(dst + i, d, 16);
+    if (i + 16 == n) return;
+    i = min(i + 16, n - 16);
+  }
+}
+
 WC_DEV uint64_t key_len(const uint4 k) {
   if (is_long_key(k)) return k.z;
   return packed_len((uint64_t)k.x | ((uint64_t)k.y << 32), (uint64_t)k.z | ((uint64_t)k.w << 32));

@@ -418,6 +418,23 @@ def test_per_doc_private_table_collisions(bits, direct):
     assert got.stats["docs_recounted"] >= 1
 
 
+@pytest.mark.parametrize("shift", [0, 1, 7])
+def test_long_word_bytes_written(shift):
+    """Words of 17 to 130 bytes, folded and written 16 bytes at a time with the last 16 overlapping:
+    every length and remainder, from and to any alignment, none of a neighbour's bytes touched."""
+    rng = np.random.default_rng(shift)
+    chars = np.frombuffer(b"abcxyzABCXYZ0189'", np.uint8)
+    words = [chars[rng.integers(0, len(chars), n)].tobytes() for n in range(17, 131) for _ in range(6)]
+    words += [b"%d" % i + b"k" * (i % 3) for i in range(400)]
+    order = rng.permutation(np.repeat(np.arange(len(words)), 2))
+    text = b"q" * shift + b" " + b" ".join(words[i] for i in order)
+    check(text[:40_000])
+    check(text + b" z" * 20_000)
+    off = [0, len(text) // 3, len(text) // 2, len(text)]
+    per = check(text, off, per_doc=True)
+    assert wc.merge([per]).as_dict() == oracle.count(text, off).as_dict()
+
+
 def _words_of_one_place_hash(n):
     """n words of 16 bytes with the same 32-bit hash in the LDS tables (wc_stripe.h: red_hash folds the
     packed dwords a, b, c, d to (a ^ rotr(b, 11)) + (c ^ rotr(d, 23))): random b, c, d, and a
