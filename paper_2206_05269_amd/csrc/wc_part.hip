@@ -159,8 +159,8 @@ WC_DEV void export_table(const PartParams& P, const PartTable<C>& T, bool last, 
 // emptied. (With equal runs of 1 KiB stripes, their next one classified a
 // step early, the last waves were alone at the end: map of 20 MB 50 -> 43 us, of 64 MB 166 -> 141.)
 //
-// Bound by instructions (a 64 MB text: 475 GB/s of text, about 900 vector instructions per KiB,
-// half of them the table's). What the scan does not use stays out of its registers, and the rest of
+// Bound by instructions (a 64 MB text: 473 GB/s of text, 724 vector and 490 scalar instructions per
+// KiB, the vector units busy for 61 % of the time). What the scan does not use stays out of its registers, and the rest of
 // a tile's words after the first 128 is counted one a lane: map of 20 MB 56 -> 51 us, of 64 MB
 // 186 -> 170.
 //
@@ -577,7 +577,8 @@ __global__ __launch_bounds__(kBlk) void part_reduce_kernel(PartParams P) {
       const uint32_t m = (uint32_t)tot;
       // A round's records are read while those of the round before are added: two a thread, for the
       // registers (four without reading ahead: reduce of 1 / 20 / 64 MB 12.2 / 17.7 / 69.8 us, of
-      // 2,000 tables 23.7; now 10.0 / 16.2 / 67.3 and 20.9).
+      // 2,000 tables 23.7; now 10.4 / 16.3 / 58.0, 67.3 before long words were written 16 bytes at a
+      // time, and 20.8).
       uint4 k[kRecs], kn[kRecs];
       C c[kRecs], cn[kRecs];
       auto read = [&](uint32_t f0) {
